@@ -1,17 +1,24 @@
-"""ctypes binding of include/tw.h and include/tw_measure.h. Argument marshalling only.
+"""Binding of include/tw.h and include/tw_measure.h. Argument marshalling only.
 
 Tensors are torch tensors on the GPU (bfloat16, contiguous); the binding passes
-their data_ptr() and sizes. Streams are torch.cuda.Stream objects (or None for
+their data pointers and sizes. Streams are torch.cuda.Stream objects (or None for
 the current stream). Every function raises TwError on a non-zero status.
+
+The entry points a serving loop calls go through the module built from
+csrc/tw_python.cpp, which checks the tensors and calls the library in one step;
+the measurement aids and start-up calls go through ctypes, with structs filled by
+the same module.
 """
 import ctypes
+import importlib
 import os
 import threading
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libtw.so")
-_lock = threading.Lock()
+_lock = threading.RLock()
 _lib = None
+_native = None
 
 STATUS = {0: "TW_OK", 1: "TW_ERR_NULL", 2: "TW_ERR_SHAPE", 3: "TW_ERR_ALIGN", 4: "TW_ERR_ALIAS",
           5: "TW_ERR_UNSUPPORTED", 6: "TW_ERR_SPLIT", 7: "TW_ERR_HIP"}
@@ -65,8 +72,8 @@ def lib():
         if _lib is not None:
             return _lib
         if not os.path.exists(_LIB_PATH):
-            from .build import build_libtw
-            build_libtw()
+            from .build import build_all
+            build_all()
         # libtw must share ONE HIP runtime with PyTorch (streams and device
         # pointers cross the boundary). PyTorch ships its own libamdhip64 with
         # the same soname as the system one: importing torch first puts that
@@ -183,41 +190,38 @@ def fused_grid(N, H, P, cu_budget=0):
 
 # ---- marshalling helpers -------------------------------------------------
 
+def native():
+    """The module built from csrc/tw_python.cpp (built first if it is not there)."""
+    global _native
+    if _native is not None:
+        return _native
+    with _lock:
+        lib()     # libtw.so, which the module is linked to, and torch's libraries
+        try:
+            from . import _twpy
+        except ModuleNotFoundError:
+            from .build import finish_pymodule, start_pymodule
+            finish_pymodule(start_pymodule())
+            importlib.invalidate_caches()
+            from . import _twpy
+        _twpy.set_error(TwError)
+        _native = _twpy
+        return _native
+
+
 def _stream_handle(stream):
     """hipStream_t of a torch stream; None means torch's current stream."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return _vp(stream.cuda_stream)
+    return _vp(native().stream_handle(stream))
 
 
-def _bf16_ptr(t, name, shape=None):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
-        raise TypeError("%s must be a GPU tensor" % name)
-    if t.dtype != torch.bfloat16:
-        raise TypeError("%s must be bfloat16, got %s" % (name, t.dtype))
-    if not t.is_contiguous():
-        raise ValueError("%s must be contiguous" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
-        raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
-    return _vp(t.data_ptr())
+def _bf16_ptr(t, name, shape):
+    return _vp(native().bf16_ptr(t, name, *shape))
 
 
 def _fused_pack(partials, residual, weight, eps, cu_budget, out, residual_out):
-    import torch
-    if residual.dim() != 2:
-        raise ValueError("residual must be [N, H]")
-    N, H = residual.shape
-    P = len(partials)
-    if out is None:
-        out = torch.empty_like(residual)
-    if residual_out is None:
-        residual_out = torch.empty_like(residual)
-    arr = (_vp * max(P, 1))(*[_bf16_ptr(p, "partials[%d]" % i, (N, H)) for i, p in enumerate(partials)])
-    args = FusedArgs(ctypes.cast(arr, ctypes.POINTER(_vp)), _bf16_ptr(residual, "residual"),
-                     _bf16_ptr(weight, "weight", (H,)), float(eps), N, H, P, int(cu_budget),
-                     _bf16_ptr(out, "out", (N, H)), _bf16_ptr(residual_out, "residual_out", (N, H)))
+    arr = (_vp * max(len(partials), 1))()
+    args = FusedArgs()
+    out, residual_out = native().fill_fused(args, arr, partials, residual, weight, eps, cu_budget, out, residual_out)
     return args, arr, out, residual_out
 
 
@@ -226,11 +230,7 @@ def _fused_pack(partials, residual, weight, eps, cu_budget, out, residual_out):
 def reduce_add_rmsnorm(partials, residual, weight, eps, cu_budget=0, out=None, residual_out=None,
                        stream=None):
     """tw_reduce_add_rmsnorm. Returns (out, residual_out)."""
-    a, keep, out, residual_out = _fused_pack(partials, residual, weight, eps, cu_budget, out, residual_out)
-    _check(lib().tw_reduce_add_rmsnorm(a.partials, a.residual, a.weight, a.eps, a.N, a.H, a.P,
-                                       a.cu_budget, a.out, a.residual_out, _stream_handle(stream)),
-           "tw_reduce_add_rmsnorm")
-    return out, residual_out
+    return (_native or native()).reduce_add_rmsnorm(partials, residual, weight, eps, cu_budget, out, residual_out, stream)
 
 
 def prepare_reduce_add_rmsnorm(partials, residual, weight, eps, cu_budget=0, out=None, residual_out=None,
@@ -292,64 +292,20 @@ def reduce_add_rmsnorm_unfused_static(partials, residual, weight, eps, out, resi
 def split_launch(partials, residual, weight, eps, split_row, stream_a, stream_b, cu_budget=0,
                  out=None, residual_out=None, parent=None, use_parent=True, join=True):
     """tw_split_launch. parent=None with use_parent=True means torch's current stream."""
-    a, keep, out, residual_out = _fused_pack(partials, residual, weight, eps, cu_budget, out, residual_out)
-    _check(lib().tw_split_launch(ctypes.byref(a), int(split_row), _stream_handle(stream_a),
-                                 _stream_handle(stream_b),
-                                 _stream_handle(parent) if use_parent else _vp(None),
-                                 1 if use_parent else 0, 1 if join else 0),
-           "tw_split_launch")
-    return out, residual_out
-
-
-def _gemm_pack(A, B, C, b_layout, cu_budget):
-    import torch
-    if A.dim() != 2 or B.dim() != 2:
-        raise ValueError("A and B must be matrices")
-    M, K = A.shape
-    if b_layout == B_NK:
-        N = B.shape[0]
-        _bf16_ptr(B, "B", (N, K))
-    elif b_layout == B_KN:
-        N = B.shape[1]
-        _bf16_ptr(B, "B", (K, N))
-    else:
-        raise ValueError("b_layout must be B_NK or B_KN")
-    if C is None:
-        C = torch.empty((M, N), dtype=torch.bfloat16, device=A.device)
-    g = GemmArgs(_bf16_ptr(A, "A"), _bf16_ptr(B, "B"), _bf16_ptr(C, "C", (M, N)), M, N, K,
-                 int(b_layout), int(cu_budget))
-    return g, C
+    return (_native or native()).split_launch(partials, residual, weight, eps, split_row, stream_a, stream_b, cu_budget,
+                                              out, residual_out, parent, use_parent, join)
 
 
 def gemm_bf16(A, B, C=None, b_layout=B_NK, cu_budget=0, stream=None):
     """tw_gemm_bf16. Returns C."""
-    g, C = _gemm_pack(A, B, C, b_layout, cu_budget)
-    _check(lib().tw_gemm_bf16(g.A, g.B, g.C, g.M, g.N, g.K, g.b_layout, g.cu_budget,
-                              _stream_handle(stream)), "tw_gemm_bf16")
-    return C
+    return (_native or native()).gemm_bf16(A, B, C, b_layout, cu_budget, stream)
 
 
 def overlap_launch(fused, gemm, stream_comm, stream_compute, parent=None, use_parent=True, join=True):
     """tw_overlap_launch. `fused` is a dict(partials, residual, weight, eps, cu_budget, out,
     residual_out) or None; `gemm` a dict(A, B, C, b_layout, cu_budget) or None.
     Returns (out, residual_out, C) with None for the side left out."""
-    fa = ga = None
-    out = residual_out = C = None
-    keep = None
-    if fused is not None:
-        fa, keep, out, residual_out = _fused_pack(fused["partials"], fused["residual"], fused["weight"],
-                                                  fused["eps"], fused.get("cu_budget", 0),
-                                                  fused.get("out"), fused.get("residual_out"))
-    if gemm is not None:
-        ga, C = _gemm_pack(gemm["A"], gemm["B"], gemm.get("C"), gemm.get("b_layout", B_NK),
-                           gemm.get("cu_budget", 0))
-    _check(lib().tw_overlap_launch(ctypes.byref(fa) if fa is not None else None,
-                                   ctypes.byref(ga) if ga is not None else None,
-                                   _stream_handle(stream_comm), _stream_handle(stream_compute),
-                                   _stream_handle(parent) if use_parent else _vp(None),
-                                   1 if use_parent else 0, 1 if join else 0),
-           "tw_overlap_launch")
-    return out, residual_out, C
+    return (_native or native()).overlap_launch(fused, gemm, stream_comm, stream_compute, parent, use_parent, join)
 
 
 def hbm_probe(src, dst, nbytes, mode, cu_budget=0, stream=None):
@@ -414,85 +370,35 @@ def weave_layer(X1, W1, partials, residual, weight, eps, W2, split_row, stream_c
                 fused_cu_budget=32, gemm_cu_budget=0, out=None, residual_out=None, Y=None, parent=None,
                 use_parent=True, join=True, schedule=WEAVE_AUTO):
     """tw_weave_layer. partials[0] is overwritten with X1 @ W1.T. Returns (out, residual_out, Y)."""
-    import torch
-    a, keep, out, residual_out = _fused_pack(partials, residual, weight, eps, fused_cu_budget, out, residual_out)
-    T, H = residual.shape
-    K1 = X1.shape[1]
-    N2 = W2.shape[0]
-    if Y is None:
-        Y = torch.empty((T, N2), dtype=torch.bfloat16, device=residual.device)
-    la = LayerArgs(_bf16_ptr(X1, "X1", (T, K1)), _bf16_ptr(W1, "W1", (H, K1)), K1, a,
-                   _bf16_ptr(W2, "W2", (N2, H)), N2, _bf16_ptr(Y, "Y", (T, N2)), int(gemm_cu_budget), int(schedule))
-    _check(lib().tw_weave_layer(ctypes.byref(la), int(split_row), _stream_handle(stream_compute),
-                                _stream_handle(stream_comm),
-                                _stream_handle(parent) if use_parent else _vp(None),
-                                1 if use_parent else 0, 1 if join else 0), "tw_weave_layer")
-    return out, residual_out, Y
+    return (_native or native()).weave_layer(X1, W1, partials, residual, weight, eps, W2, stream_compute, stream_comm,
+                                             fused_cu_budget, gemm_cu_budget, out, residual_out, Y, parent, use_parent,
+                                             join, schedule, split_row)
 
 
 def weave_layer_cuts(X1, W1, partials, residual, weight, eps, W2, cuts, stream_compute, stream_comm,
                      fused_cu_budget=CU_SHARED, gemm_cu_budget=0, out=None, residual_out=None, Y=None, parent=None,
                      use_parent=True, join=True, schedule=WEAVE_AUTO):
     """tw_weave_layer_cuts: the boundary over len(cuts) + 1 splits. Returns (out, residual_out, Y)."""
-    import torch
-    a, keep, out, residual_out = _fused_pack(partials, residual, weight, eps, fused_cu_budget, out, residual_out)
-    T, H = residual.shape
-    K1 = X1.shape[1]
-    N2 = W2.shape[0]
-    if Y is None:
-        Y = torch.empty((T, N2), dtype=torch.bfloat16, device=residual.device)
-    la = LayerArgs(_bf16_ptr(X1, "X1", (T, K1)), _bf16_ptr(W1, "W1", (H, K1)), K1, a,
-                   _bf16_ptr(W2, "W2", (N2, H)), N2, _bf16_ptr(Y, "Y", (T, N2)), int(gemm_cu_budget), int(schedule))
-    cuts = [int(c) for c in cuts]
-    arr = (_i64 * max(len(cuts), 1))(*cuts)
-    _check(lib().tw_weave_layer_cuts(ctypes.byref(la), arr, len(cuts), _stream_handle(stream_compute),
-                                     _stream_handle(stream_comm),
-                                     _stream_handle(parent) if use_parent else _vp(None),
-                                     1 if use_parent else 0, 1 if join else 0), "tw_weave_layer_cuts")
-    return out, residual_out, Y
+    return (_native or native()).weave_layer_cuts(X1, W1, partials, residual, weight, eps, W2, stream_compute, stream_comm,
+                                                  fused_cu_budget, gemm_cu_budget, out, residual_out, Y, parent,
+                                                  use_parent, join, schedule, cuts)
 
 
 def weave_train(boundaries, split_row, stream_compute, stream_comm, parent=None, use_parent=True, join=True,
                 fused_cu_budget=CU_SHARED, gemm_cu_budget=0, schedule=WEAVE_AUTO):
     """tw_weave_train. `boundaries` is a list of dicts(X1, W1, partials, residual, weight, eps, W2, out,
     residual_out, Y), all with the same number of rows; every tensor must be given. Returns None."""
-    n = len(boundaries)
-    arr = (LayerArgs * max(n, 1))()
-    keep = []
-    for i, b in enumerate(boundaries):
-        a, k, out, residual_out = _fused_pack(b["partials"], b["residual"], b["weight"], b["eps"], fused_cu_budget,
-                                              b["out"], b["residual_out"])
-        T, H = b["residual"].shape
-        K1, N2 = b["X1"].shape[1], b["W2"].shape[0]
-        arr[i] = LayerArgs(_bf16_ptr(b["X1"], "X1", (T, K1)), _bf16_ptr(b["W1"], "W1", (H, K1)), K1, a,
-                           _bf16_ptr(b["W2"], "W2", (N2, H)), N2, _bf16_ptr(b["Y"], "Y", (T, N2)), int(gemm_cu_budget),
-                           int(schedule))
-        keep.append(k)
-    _check(lib().tw_weave_train(arr, n, int(split_row), _stream_handle(stream_compute), _stream_handle(stream_comm),
-                                _stream_handle(parent) if use_parent else _vp(None),
-                                1 if use_parent else 0, 1 if join else 0), "tw_weave_train")
+    return (_native or native()).weave_train(boundaries, split_row, stream_compute, stream_comm, parent, use_parent, join,
+                                             fused_cu_budget, gemm_cu_budget, schedule)
 
 
 def weave_layer_auto(X1, W1, partials, residual, weight, eps, W2, stream_compute, stream_comm, threshold=0,
                      multiple=0, fused_cu_budget=CU_SHARED, gemm_cu_budget=0, out=None, residual_out=None, Y=None,
                      parent=None, use_parent=True, join=True, schedule=WEAVE_AUTO):
     """tw_weave_layer_auto. Returns (out, residual_out, Y, split_row_taken)."""
-    import torch
-    a, keep, out, residual_out = _fused_pack(partials, residual, weight, eps, fused_cu_budget, out, residual_out)
-    T, H = residual.shape
-    K1 = X1.shape[1]
-    N2 = W2.shape[0]
-    if Y is None:
-        Y = torch.empty((T, N2), dtype=torch.bfloat16, device=residual.device)
-    la = LayerArgs(_bf16_ptr(X1, "X1", (T, K1)), _bf16_ptr(W1, "W1", (H, K1)), K1, a,
-                   _bf16_ptr(W2, "W2", (N2, H)), N2, _bf16_ptr(Y, "Y", (T, N2)), int(gemm_cu_budget), int(schedule))
-    taken = _i64(-1)
-    _check(lib().tw_weave_layer_auto(ctypes.byref(la), int(threshold), int(multiple), _stream_handle(stream_compute),
-                                     _stream_handle(stream_comm),
-                                     _stream_handle(parent) if use_parent else _vp(None),
-                                     1 if use_parent else 0, 1 if join else 0, ctypes.byref(taken)),
-           "tw_weave_layer_auto")
-    return out, residual_out, Y, int(taken.value)
+    return (_native or native()).weave_layer_auto(X1, W1, partials, residual, weight, eps, W2, stream_compute, stream_comm,
+                                                  fused_cu_budget, gemm_cu_budget, out, residual_out, Y, parent,
+                                                  use_parent, join, schedule, threshold, multiple)
 
 
 GEMM_PHASES = 8
@@ -523,21 +429,16 @@ def weave_tune(X1, W1, partials, residual, weight, eps, W2, stream_compute, stre
                schedule=WEAVE_AUTO):
     """tw_weave_tune. Returns (best_row, us): us[0] the unsplit chain, us[1] the smart row, us[2 + i] offsets[i];
     negative where a candidate was not run. Waits for the device."""
-    import torch
-    a, keep, out, residual_out = _fused_pack(partials, residual, weight, eps, fused_cu_budget, out, residual_out)
-    T, H = residual.shape
-    K1 = X1.shape[1]
-    N2 = W2.shape[0]
-    if Y is None:
-        Y = torch.empty((T, N2), dtype=torch.bfloat16, device=residual.device)
-    la = LayerArgs(_bf16_ptr(X1, "X1", (T, K1)), _bf16_ptr(W1, "W1", (H, K1)), K1, a,
-                   _bf16_ptr(W2, "W2", (N2, H)), N2, _bf16_ptr(Y, "Y", (T, N2)), int(gemm_cu_budget), int(schedule))
+    la, keep = LayerArgs(), (_vp * max(len(partials), 1))()
+    outputs = native().fill_layer(la, keep, X1, W1, partials, residual, weight, eps, W2, fused_cu_budget, gemm_cu_budget,
+                                  out, residual_out, Y, schedule)   # kept alive until the call has finished
     offs = (_i64 * max(1, len(offsets)))(*[int(o) for o in offsets])
     us = (ctypes.c_float * (2 + len(offsets)))()
     best = _i64(-1)
     _check(lib().tw_weave_tune(ctypes.byref(la), int(multiple), offs, len(offsets), int(reps),
                                _stream_handle(stream_compute), _stream_handle(stream_comm), ctypes.byref(best), us),
            "tw_weave_tune")
+    del outputs
     return int(best.value), [float(x) for x in us]
 
 

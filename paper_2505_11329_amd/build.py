@@ -1,12 +1,14 @@
-"""Builds libtw.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libtw.so (HIP, gfx950 only) with hipcc and the Python module over it with g++, both in-tree."""
 import os
 import shutil
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtw.so")
+PYMODULE = os.path.join(HERE, "_twpy" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["tw_host.hip", "tw_fused.hip", "tw_unfused.hip", "tw_gemm.hip", "tw_probe.hip"]
 
 # Packed fp32 VALU instructions are switched off for every kernel (the compiler
@@ -55,5 +57,47 @@ def build_libtw(verbose=False):
     return LIB
 
 
+def start_pymodule():
+    """Starts compiling tw_python.cpp; finish_pymodule() links it against libtw.so."""
+    import torch
+    base = os.path.join(os.path.dirname(torch.__file__), "include")
+    objdir = os.path.join(HERE, "_build")
+    os.makedirs(objdir, exist_ok=True)
+    obj = os.path.join(objdir, "tw_python.o")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", os.path.join(ROOT, "include"), "-isystem", base,
+           "-isystem", os.path.join(base, "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+           "-c", os.path.join(CSRC, "tw_python.cpp"), "-o", obj]
+    return obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+
+
+def finish_pymodule(started):
+    import torch
+    obj, proc = started
+    out, _ = proc.communicate()
+    if proc.returncode != 0:
+        raise RuntimeError("g++ failed on tw_python.cpp:\n%s" % out)
+    tmp = PYMODULE + ".tmp.%d" % os.getpid()
+    # libtw.so is found next to the module; torch's libraries are in the process already
+    cmd = ["g++", "-shared", "-o", tmp, obj, "-L", HERE, "-ltw", "-L", os.path.join(os.path.dirname(torch.__file__), "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,--disable-new-dtags,-rpath,$ORIGIN",
+           "-Wl,--allow-shlib-undefined"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link of the Python module failed:\n%s" % r.stdout)
+    os.replace(tmp, PYMODULE)
+    return PYMODULE
+
+
+def build_all(verbose=False):
+    """libtw.so and the Python module. Returns libtw.so's path."""
+    started = start_pymodule()
+    path = build_libtw(verbose)
+    finish_pymodule(started)
+    return path
+
+
 if __name__ == "__main__":
-    print(build_libtw(verbose=True))
+    print(build_all(verbose=True))
