@@ -232,7 +232,8 @@ int64_t tw_split_point(int64_t N, int64_t multiple);
  * nor on the tile shape the launch picks (256 x 128 outputs per workgroup; 256 x
  * 64 when the wider tiles would fill at most half of the compute units; 256 x
  * 256 for a large product launched on its own, when such tiles fill the compute
- * units about as well). Every output element is the sum of its K / 32 partial
+ * units about as well; from 16 x 16 to 192 x 128 where those leave compute units
+ * idle, as for a few rows or a few hundred). Every output element is the sum of its K / 32 partial
  * dot products of depth 32, accumulated in fp32 in the order of increasing k.
  */
 #define TW_B_NK 0

@@ -61,16 +61,13 @@
 //     MFMA operand (8 consecutive k of one column n) is gathered with the
 //     transposing LDS read ds_read_b64_tr_b16.
 #include <atomic>
-#include <type_traits>
-#include <utility>
 
-#include "tw_device.h"
 #include "tw_internal.h"
+#include "tw_mfma.h"
 
 namespace tw {
 
 static constexpr int BM = kGemmTileM;
-static constexpr int kXcds = 8;
 // what the tracing variant counts per wave, in shader clocks (tw_measure.h lists them in this order)
 enum { kPhaseSub0, kPhaseLanded, kPhaseBarrier, kPhaseSub1, kPhaseFill, kPhaseStores, kPhaseTiles, kPhaseTotal };
 static constexpr int kGemmPhases = TW_GEMM_PHASES;
@@ -83,8 +80,6 @@ static_assert(kPhaseTotal + 1 == kGemmPhases, "phase list");
 // eight waves of 64 x 32, tile 256 x 64, 3 x 40 KiB; and for large products
 // <8, 8, 2, 64>: four waves of 128 x 128, tile 256 x 256, two K steps of 64 in a
 // ring of five 32 KiB slots (STAGES = 2 stands for that ring, see the K loop).
-static constexpr int kBlk = 16;    // rows and columns of one MFMA result block
-static constexpr int kSubK = 32;   // K depth of one MFMA
 template <int WM, int WN, int STAGES, int BK_>
 struct TileCfg {
     static constexpr int kWaves = 2 * BM / (kBlk * WM);
@@ -100,10 +95,6 @@ struct TileCfg {
     static constexpr int kLdsBytes = kRing ? kRingSlots * kStageABytes : STAGES * kStageBytes;
     static_assert(!kRing || kStageABytes == kStageBBytes, "ring slots hold either operand");
 };
-
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct GemmParams {
     const char *A;
@@ -141,30 +132,6 @@ __device__ __forceinline__ uint32_t lds_piece(int r, int c)
     } else {
         return r * 64 + ((c ^ ((r >> 1) & 3)) << 4);
     }
-}
-
-typedef __attribute__((address_space(3))) void *lds_ptr_t;
-typedef __attribute__((address_space(3))) char *lds_char_ptr_t;
-
-template <int OFF>
-__device__ __forceinline__ bf16x8 lds_read16(uint32_t addr)
-{
-    bf16x8 v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
-    return v;
-}
-// gfx950's transposing LDS read. Within each group of 16 lanes, lane 4a+b
-// receives, for j = 0..3, the b-th 16-bit element of the 8-byte chunk that lane
-// a + 4j points at (lane mapping established with a probe kernel). With lane
-// a + 4j pointing at row k0+j, columns 4a..4a+3 of a [k][n] tile, lane d = 4a+b
-// ends up with column d of rows k0..k0+3: four consecutive k of one n, which is
-// what an MFMA operand register pair holds.
-template <int OFF>
-__device__ __forceinline__ u32x2 lds_read_tr8(uint32_t addr)
-{
-    u32x2 v;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
-    return v;
 }
 
 // Operand fragments of one K sub-step (one MFMA deep, k = 32) for a wave that
@@ -206,18 +173,6 @@ struct Frags {
                       "the wait must name every register an LDS fragment read writes");                   \
         asm volatile("s_waitcnt lgkmcnt(%[cnt])" : A_LIST(f), B_LIST(f) : [cnt] "n"(N) : "memory");       \
     } while (0)
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), unrolled
-template <int... I, typename Fn>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, Fn &&f)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename Fn>
-__device__ __forceinline__ void static_for(Fn &&f)
-{
-    static_for_impl(std::make_integer_sequence<int, N>{}, f);
-}
 
 template <int N, bool B_KN, int WM, int WN>
 __device__ __forceinline__ void wait_lgkm(Frags<B_KN, WM, WN> &f)
@@ -344,13 +299,8 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         const int slot_w = w / kXcds;
         const int lin = (w % kXcds) * prm.tiles_per_xcd + slot_w;
         if (lin >= total_tiles) continue;
-        const int per_group = prm.group_m * prm.tiles_n;
-        const int grp = lin / per_group;
-        const int first_tm = grp * prm.group_m;
-        const int gsz = min(prm.group_m, prm.tiles_m - first_tm);
-        const int in_grp = lin - grp * per_group;
-        const int tm = first_tm + in_grp % gsz;
-        const int tn = in_grp / gsz;
+        const TileAt at = tile_at(lin, prm.tiles_m, prm.tiles_n, prm.group_m);
+        const int tm = at.m, tn = at.n;
 
         unsigned long long t_tile = 0;
         if constexpr (TRACE) t_tile = now();
@@ -750,6 +700,29 @@ tw_status validate_gemm(const tw_gemm_args &g)
     return TW_OK;
 }
 
+// Block shape of the tile ordering: the tiles an XCD works on at one time (one per
+// compute unit it contributes to the launch) should touch as few distinct rows of A
+// and columns of B as possible, i.e. form a block as square as the tile shape lets
+// them: what they fetch at one K step they fetch once into that XCD's L2. (Sizing the
+// block by the XCD's whole share of the tile list instead made the blocks twice as
+// tall as wide for large products: 6 % slower on a 16K-token layer boundary.)
+int tile_group_m(int64_t tiles_m, int tile_rows, int tile_cols, int budget)
+{
+    const int64_t at_once = (int64_t(budget) + kXcds - 1) / kXcds;
+    int best_gm = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int gm = 1; gm <= 8; gm *= 2) {
+        if (gm > tiles_m && gm != 1) break;
+        const int64_t gn = (at_once + gm - 1) / gm;
+        const int64_t cost = int64_t(gm) * tile_rows + gn * tile_cols;
+        if (cost < best_cost) {
+            best_cost = cost;
+            best_gm = gm;
+        }
+    }
+    return best_gm;
+}
+
 template <bool B_KN, int WM, int WN, int STAGES, int BK, bool TRACE = false>
 static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t stream,
                             unsigned long long *phase_cycles = nullptr, int64_t phase_len = 0)
@@ -770,25 +743,7 @@ static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t strea
     prm.tiles_n = static_cast<int>(tiles_n);
     const int64_t total = tiles_m * tiles_n;
     prm.tiles_per_xcd = static_cast<int>((total + kXcds - 1) / kXcds);
-    // Block shape of the tile ordering: the tiles an XCD works on at one time (one per
-    // compute unit it contributes to the launch) should touch as few distinct rows of A
-    // and columns of B as possible, i.e. form a block as square as the tile shape lets
-    // them: what they fetch at one K step they fetch once into that XCD's L2. (Sizing the
-    // block by the XCD's whole share of the tile list instead made the blocks twice as
-    // tall as wide for large products: 6 % slower on a 16K-token layer boundary.)
-    const int64_t at_once = (int64_t(budget) + kXcds - 1) / kXcds;
-    int best_gm = 1;
-    int64_t best_cost = INT64_MAX;
-    for (int gm = 1; gm <= 8; gm *= 2) {
-        if (gm > tiles_m && gm != 1) break;
-        const int64_t gn = (at_once + gm - 1) / gm;
-        const int64_t cost = int64_t(gm) * BM + gn * BN;
-        if (cost < best_cost) {
-            best_cost = cost;
-            best_gm = gm;
-        }
-    }
-    prm.group_m = best_gm;
+    prm.group_m = tile_group_m(tiles_m, BM, BN, budget);
 
     const int64_t slots = int64_t(prm.tiles_per_xcd) * kXcds;
     const unsigned grid = static_cast<unsigned>(slots < budget ? slots : budget);
@@ -820,10 +775,10 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_oth
     // The part runs this kernel at its power limit (1.2-1.9 GHz on N(0, 0.02^2)
     // operands against 2.4 GHz idle), so what a tile shape is worth is decided by
     // the energy it spends per flop, not by its share of busy matrix-core cycles.
-    if (g.b_layout == TW_B_KN) return launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
+    enum { kWide, kNarrow, kBig } take = kWide;
     const int64_t tiles_m = (g.M + BM - 1) / BM;
     const int64_t wide_tiles = tiles_m * ((g.N + kGemmTileN - 1) / kGemmTileN);
-    if (!beside_other_kernels) {
+    if (g.b_layout == TW_B_NK && !beside_other_kernels) {
         // A product whose 256 x 128 tiles fill at most half of the compute units it may
         // use is cut into 256 x 64 tiles instead (eight waves of 64 x 32, 3 x 40 KiB of
         // LDS): twice the workgroups, each with half the work. A tile of that shape
@@ -831,7 +786,6 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_oth
         // time, so it only pays while it brings idle compute units in: 14-23 % faster
         // on 40 ... 128 wide tiles, 25-40 % slower once the wide tiles already fill
         // more than half.
-        if (2 * wide_tiles <= budget) return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);
         // A large product takes 256 x 256 tiles: four waves of 128 x 128 (all 512
         // registers of a lane: 256 accumulators and two fragment sets), K steps of
         // 64 over two LDS stages of 64 KiB. Two thirds of the operand bytes fetched
@@ -840,15 +794,37 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_oth
         // 128-byte line of A and B in two halves a K step apart, by which time the
         // line has left the L1: twice the L2 requests, and 27 % more cycles.)
         const int64_t big_tiles = tiles_m * ((g.N + 255) / 256);
-        if (wave_fill(big_tiles, budget) >= wave_fill(wide_tiles, budget) - 0.05)
-            return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream);
+        if (2 * wide_tiles <= budget) take = kNarrow;
+        else if (wave_fill(big_tiles, budget) >= wave_fill(wide_tiles, budget) - 0.05) take = kBig;
     }
     // Next to other kernels (tw_overlap_launch, the split schedules of
     // tw_weave_layer) the 256 x 128 tiles are kept: the compute units are not idle
     // there, the narrow tiles' extra operand traffic competes for the same L1
     // request slots (a woven layer measured level to 3 % slower with them), and
     // the 256 x 256 tiles leave no registers for a co-resident workgroup.
-    return launch_cfg<false, 4, 4, 3, 64>(g, budget, stream);
+
+    // Where 256-row tiles leave compute units idle or half their rows empty, a smaller
+    // shape takes the product: whichever grid of tiles the estimates put ahead (us per
+    // 64-deep K step of a tile, measured; for the smaller shapes see tw_gemm_tile.hip).
+    // The 256 x 64 and 256 x 256 tiles run at the power limit when every compute unit has
+    // one, and up to a quarter faster when few do.
+    const double fill = take == kBig      ? wave_fill(tiles_m * ((g.N + 255) / 256), budget)
+                        : take == kNarrow ? wave_fill(tiles_m * ((g.N + 63) / 64), budget)
+                                          : 1.0;
+    const double cool = 0.75 + 0.25 * fill;
+    const double us = take == kBig      ? tile_grid_us(g.M, g.N, g.K, BM, 256, 64, 1.38 * cool, budget)
+                      : take == kNarrow ? tile_grid_us(g.M, g.N, g.K, BM, 64, 64, 0.60 * cool, budget)
+                                        : tile_grid_us(g.M, g.N, g.K, BM, kGemmTileN, 64,
+                                                       g.b_layout == TW_B_KN ? 0.83 : 0.735, budget);
+    double small_us = 0.0;
+    const int small = best_small_tile(g, budget, &small_us);
+    if (small >= 0 && small_us < 0.97 * us) return launch_small_tile(g, small, budget, cus, stream);
+    if (g.b_layout == TW_B_KN) return launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
+    switch (take) {
+    case kNarrow: return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);
+    case kBig: return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream);
+    default: return launch_cfg<false, 4, 4, 3, 64>(g, budget, stream);
+    }
 }
 
 }  // namespace tw

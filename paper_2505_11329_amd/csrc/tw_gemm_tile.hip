@@ -1,0 +1,438 @@
+// bf16 GEMM on small output tiles, for products that the 256-row tiles of
+// tw_gemm.hip cannot spread over the device: decode steps (a few rows: the weights
+// are read once and that is all the work) and batches of up to a thousand rows or
+// so. Same product, same bits: every output is the chain of its K / 32 partial dot
+// products (v_mfma_f32_16x16x32_bf16) in the order of increasing k, so K is never
+// split, and parallelism comes from the tile shape alone.
+//
+// What bounds it: what a compute unit can pull into its LDS. Whatever the tile, and
+// whether its operands come from HBM or from the L2, a compute unit takes in 60 to
+// 85 GB/s (about 19 KB of requests in flight, 0.25 to 0.33 us a round trip), so a
+// tile of BM x BN outputs costs (BM + BN) * K * 2 bytes of that, and the best shape
+// is the smallest that still gives every compute unit at most one tile. A kernel
+// with the LDS reads and matrix instructions taken out ran within 4 to 13 % of the
+// whole. Tried and not kept: fetching lines into the L2 ahead of time, each
+// workgroup a share of the panels its XCD reads (3 to 20 % slower); rotating the
+// order in which the workgroups of an XCD ask for a shared panel's rows (nothing at
+// these sizes).
+//
+// Measured on MI355X, weights from HBM, us (the 256-row tiles before / now / the
+// vendor library): [16 x 8192] x [8192 x 3584] 64 / 13.1 / 20 (59 MB of weights: 4.5
+// TB/s), [16 x 8192] x [8192 x 1280] 46 / 11.5 / 20, [64 x 8192] x [8192 x 3584] 64 /
+// 20.6 / 24, [333 x 8192] x [8192 x 3584] 65 / 37 / 45, [512 x 8192] x [8192 x 1280]
+// 73 / 33 / 32.
+//
+// Shape of a workgroup: WVM x WVN waves own WM x WN blocks of 16 x 16 each; tiles of
+// one or two blocks still get four waves, which share the loading. S stages of BK deep
+// K steps sit in LDS, filled by 16-byte global-to-LDS loads. Step s: the fragments of
+// stage s are in registers; once every wave has them and stage s + 1 has landed (one
+// vmcnt wait and one barrier), the stage's LDS takes the loads of step s + S, and the
+// reads of stage s + 1's fragments go out between the matrix instructions of stage s
+// (a single wave's chain of dependent matrix instructions leaves 22 clocks between two
+// of them, room for two reads: 15.2 -> 13.7 us at 16 rows against reads first).
+// Rows are laid out as in tw_gemm.hip: 16-byte pieces xor-swizzled so that a fragment
+// read touches every bank once.
+#include <atomic>
+
+#include "tw_internal.h"
+#include "tw_mfma.h"
+
+namespace tw {
+
+struct TileParams {
+    const char *A;
+    const char *B;
+    char *C;
+    long long M, N, K;
+    int tiles_m, tiles_n;
+    int group_m;
+    int tiles_per_xcd;
+};
+
+template <int WM, int WN, int WVM, int WVN, int BK, int S>
+struct SmallTile {
+    static constexpr int kCompute = WVM * WVN;                 // waves that own outputs
+    static constexpr int kWaves = kCompute < 4 ? 4 : kCompute;  // waves that load
+    static constexpr int BM = kBlk * WM * WVM, BN = kBlk * WN * WVN;
+    static constexpr int kABytes = BM * BK * 2, kBBytes = BN * BK * 2, kStageBytes = kABytes + kBBytes;
+    static constexpr int kLdsBytes = S * kStageBytes;
+    static constexpr int kALoads = kABytes / 1024 / kWaves, kBLoads = kBBytes / 1024 / kWaves;
+    static constexpr int kLoads = kALoads + kBLoads;  // per wave and stage, 1 KiB each
+    static_assert(kABytes % (1024 * kWaves) == 0 && kBBytes % (1024 * kWaves) == 0, "whole load instructions");
+    static_assert((S - 1) * kLoads < 64, "vmcnt field");
+    static_assert(S >= 3 && kLdsBytes <= 160 * 1024, "LDS of one compute unit");
+    static_assert(BK == 64 || BK == 128 || BK == 256, "LDS layouts below");
+    static constexpr bool kStagedStores = WN == 2 || WN == 4;
+};
+
+// Position of the 16-byte piece c of row r, of the 2 BK bytes a row takes: two rows of
+// 128 bytes share a 256-byte line of all 64 banks (see lds_piece in tw_gemm.hip); rows of
+// 256 and 512 bytes are one and two lines, and the sixteen rows a read covers fall on the
+// line's sixteen pieces, whichever rows one of its passes takes together.
+template <int BK>
+__device__ __forceinline__ int swizzled(int r, int c)
+{
+    return BK == 64 ? (c ^ ((r >> 1) & 7)) : ((c & ~15) | ((c ^ r) & 15));
+}
+
+// B stored [K x N]: the stage holds BK rows (k) of BN columns. A transposing read takes,
+// per half wave, 32 bytes of eight rows: four consecutive ones of two groups eight rows
+// apart. R = 128 / BN rows share a 256-byte line; the other row bits that differ move the
+// 32 bytes within the row, so that the eight lie on different banks. (BN = 32: rows r and
+// r + 8.)
+template <int BN>
+__device__ __forceinline__ int kn_swizzle(int r)
+{
+    if constexpr (BN == 128) return (r & 3) | (((r >> 3) & 1) << 2);
+    else if constexpr (BN == 64) return ((r >> 1) & 1) | (((r >> 3) & 1) << 1);
+    else return (r >> 3) & 1;
+}
+
+template <bool B_KN, int WM, int WN, int SUBS>
+struct StageFrags {
+    bf16x8 a[SUBS][WM];
+    bf16x8 b[B_KN ? 1 : SUBS][B_KN ? 1 : WN];
+    u32x2 blo[B_KN ? SUBS : 1][B_KN ? WN : 1], bhi[B_KN ? SUBS : 1][B_KN ? WN : 1];
+};
+
+template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, bool STREAM_B>
+__global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_tile_kernel(const TileParams prm)
+{
+#if defined(__HIP_DEVICE_COMPILE__)  // as in tw_gemm.hip: the host pass needs the launch stub only
+    using T = SmallTile<WM, WN, WVM, WVN, BK, S>;
+    constexpr int SUBS = BK / kSubK, NW = T::kWaves, BM = T::BM, BN = T::BN, kRowBytes = BK * 2;
+    static_assert(!B_KN || BN == 32 || BN == 64 || BN == 128, "kn_swizzle");
+    // Weights that one row of tiles reads once are not worth keeping in the caches (16 rows,
+    // K = 8192, N = 3584: 13.7 -> 13.1 us; with three rows of tiles 40 % slower).
+    constexpr int kBPolicy = STREAM_B ? kStreamPolicy : 0;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l15 = lane & 15, lgrp = lane >> 4;
+    const bool computes = wave < T::kCompute;
+    const int wave_m = computes ? wave / WVN : 0, wave_n = computes ? wave % WVN : 0;
+    const long long row_bytes = prm.K * 2, bkn_row_bytes = prm.N * 2;
+    const int k_tiles = prm.K > 0 ? static_cast<int>((prm.K + BK - 1) / BK) : 1;
+    constexpr uint32_t kPastK = 0x80000000u;  // out of range whatever scalar offset (< 2^31) is added
+
+    // Load duty: instruction i of this wave fills the 64 pieces from (i * NW + wave) * 64 on.
+    constexpr int kRowPieces = kRowBytes / 16, kInstrRows = 64 / kRowPieces;
+    constexpr int kStepRows = NW * kInstrRows;                 // rows all waves' instruction i covers
+    constexpr int kRepeat = kStepRows % 16 == 0 || BK == 64 ? 1 : 16 / kStepRows;  // instructions after which the swizzle repeats
+    static_assert(BK == 64 ? kStepRows % 16 == 0 : 16 % kStepRows == 0 || kStepRows % 16 == 0, "swizzle period");
+    const int load_row = wave * kInstrRows + lane / kRowPieces;  // + i * kStepRows
+    int load_piece[kRepeat];
+#pragma unroll
+    for (int q = 0; q < kRepeat; ++q) load_piece[q] = swizzled<BK>(load_row + q * kStepRows, lane % kRowPieces);
+    // and of B stored [K x N]
+    constexpr int kKnPieces = BN / 8, kKnInstrRows = 64 / kKnPieces;
+    static_assert(!B_KN || (NW * kKnInstrRows) % 16 == 0, "the swizzle's row bits do not depend on the instruction");
+    const int kn_row = wave * kKnInstrRows + lane / kKnPieces;  // + i * NW * kKnInstrRows
+    const int kn_piece = (lane % kKnPieces) ^ (kn_swizzle<BN>(kn_row) << 1);
+
+    // fragment addresses inside a stage; block i lies 16 rows further on
+    uint32_t fa[SUBS], fb[SUBS], fbkn[B_KN ? WN : 1];
+#pragma unroll
+    for (int s = 0; s < SUBS; ++s) {
+        const int at = swizzled<BK>(l15, s * 4 + lgrp) * 16;
+        fa[s] = (wave_m * kBlk * WM + l15) * kRowBytes + at;
+        fb[s] = T::kABytes + (wave_n * kBlk * WN + l15) * kRowBytes + at;
+    }
+    if constexpr (B_KN) {
+        const int a4 = l15 & 3, row = lgrp * 8 + (l15 >> 2);  // see lds_read_tr8
+#pragma unroll
+        for (int i = 0; i < WN; ++i) {
+            const int col = wave_n * kBlk * WN + i * kBlk + 4 * a4;
+            fbkn[i] = T::kABytes + row * (BN * 2) + (((col >> 3) ^ (kn_swizzle<BN>(row) << 1)) << 4) + (col & 7) * 2;
+        }
+    }
+
+    for (int w = blockIdx.x; w < prm.tiles_per_xcd * kXcds; w += gridDim.x) {
+        const int lin = (w % kXcds) * prm.tiles_per_xcd + w / kXcds;
+        if (lin >= prm.tiles_m * prm.tiles_n) continue;
+        const TileAt at = tile_at(lin, prm.tiles_m, prm.tiles_n, prm.group_m);
+        const long long m0 = static_cast<long long>(at.m) * BM, n0 = static_cast<long long>(at.n) * BN;
+        const int rows_a = static_cast<int>(min(static_cast<long long>(BM), prm.M - m0));
+        const int rows_b = static_cast<int>(min(static_cast<long long>(BN), prm.N - n0));
+        const __amdgpu_buffer_rsrc_t ra = make_rsrc(prm.A + m0 * row_bytes, static_cast<uint32_t>(rows_a * row_bytes));
+        const __amdgpu_buffer_rsrc_t rb = make_rsrc(prm.B + n0 * row_bytes, static_cast<uint32_t>(rows_b * row_bytes));
+        const uint32_t load_row_off = static_cast<uint32_t>(load_row * row_bytes);
+        const uint32_t step_bytes = static_cast<uint32_t>(kStepRows * row_bytes);
+        const uint32_t kn_off = n0 + kn_piece * 8 < prm.N
+                                    ? static_cast<uint32_t>(kn_row * bkn_row_bytes + (n0 + kn_piece * 8) * 2)
+                                    : kPastK;
+        const uint32_t kn_step_bytes = static_cast<uint32_t>(NW * kKnInstrRows * bkn_row_bytes);
+
+        f32x4 acc[WM][WN];
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+        auto issue = [&](int kt, int slot) {
+            const lds_char_ptr_t base = (lds_char_ptr_t)(lds + slot * T::kStageBytes);
+            uint32_t off[kRepeat];
+#pragma unroll
+            for (int q = 0; q < kRepeat; ++q) {
+                const int k = kt * BK + load_piece[q] * 8;  // K <= 2^22, K steps run S past it at most
+                off[q] = k < static_cast<int>(prm.K) ? load_row_off + static_cast<uint32_t>(k) * 2 : kPastK;
+            }
+#pragma unroll
+            for (int i = 0; i < T::kALoads; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)(base + (i * NW + wave) * 1024), 16,
+                                                         off[i % kRepeat], step_bytes * i, 0, 0);
+            if constexpr (!B_KN) {
+#pragma unroll
+                for (int i = 0; i < T::kBLoads; ++i)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_ptr_t)(base + T::kABytes + (i * NW + wave) * 1024),
+                                                             16, off[i % kRepeat], step_bytes * i, 0, kBPolicy);
+            } else {
+                // rows k0 ... of B through a descriptor of their own: rows past K lie outside it
+                const long long k0 = static_cast<long long>(kt) * BK, left = prm.K - k0;
+                const int rows_k = static_cast<int>(left < 0 ? 0 : left > BK ? BK : left);
+                const __amdgpu_buffer_rsrc_t rbk =
+                    make_rsrc(prm.B + (left > 0 ? k0 : 0) * bkn_row_bytes, static_cast<uint32_t>(rows_k * bkn_row_bytes));
+#pragma unroll
+                for (int i = 0; i < T::kBLoads; ++i)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rbk, (lds_ptr_t)(base + T::kABytes + (i * NW + wave) * 1024),
+                                                             16, kn_off, kn_step_bytes * i, 0, kBPolicy);
+            }
+        };
+        using F = StageFrags<B_KN, WM, WN, SUBS>;
+        constexpr int kPerSub = WM + (B_KN ? 2 * WN : WN);
+        constexpr int kReads = SUBS * kPerSub, kMma = SUBS * WM * WN;
+        auto read_one = [&](F &f, uint32_t base, auto t_tag) {
+            constexpr int t = decltype(t_tag)::value, s = t / kPerSub, i = t % kPerSub;
+            if constexpr (i < WM) {
+                f.a[s][i] = lds_read16<i * kBlk * kRowBytes>(base + fa[s]);
+            } else if constexpr (!B_KN) {
+                f.b[s][i - WM] = lds_read16<(i - WM) * kBlk * kRowBytes>(base + fb[s]);
+            } else {
+                constexpr int j = (i - WM) >> 1, kOff = s * kSubK * BN * 2;
+                if constexpr (((i - WM) & 1) == 0) f.blo[s][j] = lds_read_tr8<kOff>(base + fbkn[j]);
+                else f.bhi[s][j] = lds_read_tr8<kOff + 4 * BN * 2>(base + fbkn[j]);
+            }
+        };
+        auto read_all = [&](F &f, int slot) {
+            const uint32_t base = slot * T::kStageBytes;
+            static_for<kReads>([&](auto t) { read_one(f, base, t); });
+        };
+        // Waits for this wave's LDS reads; the registers they fill pass through, so that no use moves above.
+        auto settle = [&](F &f) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int s = 0; s < SUBS; ++s) {
+#pragma unroll
+                for (int i = 0; i < WM; ++i) asm volatile("" : "+v"(f.a[s][i]));
+#pragma unroll
+                for (int j = 0; j < WN; ++j) {
+                    if constexpr (B_KN) asm volatile("" : "+v"(f.blo[s][j]), "+v"(f.bhi[s][j]));
+                    else asm volatile("" : "+v"(f.b[s][j]));
+                }
+            }
+        };
+        // the matrix instructions of one stage, and between them the reads of the next one's fragments
+        auto multiply = [&](F &cur, F &nxt, int nxt_slot) {
+            const uint32_t base = nxt_slot * T::kStageBytes;
+            static_for<kMma>([&](auto m_tag) {
+                constexpr int m = decltype(m_tag)::value, s = m / (WM * WN), j = m % (WM * WN) / WM, i = m % WM;
+                bf16x8 b;
+                if constexpr (B_KN) {
+                    const u32x4 t = {cur.blo[s][j].x, cur.blo[s][j].y, cur.bhi[s][j].x, cur.bhi[s][j].y};
+                    b = __builtin_bit_cast(bf16x8, t);
+                } else {
+                    b = cur.b[s][j];
+                }
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, cur.a[s][i], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                constexpr int kReadSlots = kMma >= 8 ? kMma * 3 / 4 : kMma;  // the last quarter lets them arrive
+                static_for<kReads>([&](auto t) {
+                    if constexpr (decltype(t)::value * kReadSlots / kReads == m) read_one(nxt, base, t);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+        auto wait_vm = [&](auto n_tag) {  // at most n of this wave's loads outstanding; then the same for all waves
+            constexpr int n = decltype(n_tag)::value;
+            __builtin_amdgcn_s_waitcnt(((n >> 4) << 14) | 0x0F70 | (n & 15));
+            __builtin_amdgcn_s_barrier();
+        };
+
+        // the previous tile's loads have landed and nobody reads LDS any more
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        static_for<S>([&](auto s) { issue(decltype(s)::value, decltype(s)::value); });
+        wait_vm(std::integral_constant<int, (S - 1) * T::kLoads>{});
+        F f0, f1;
+        if (computes) read_all(f0, 0);
+        int slot = 0;
+        auto step = [&](F &cur, F &nxt, int kt) {
+            if (computes) settle(cur);
+            wait_vm(std::integral_constant<int, (S - 2) * T::kLoads>{});  // stage kt + 1 has landed, stage kt is read
+            issue(kt + S, slot);  // (past the end: out of range, so the counts stay the same)
+            slot = slot + 1 == S ? 0 : slot + 1;
+            __builtin_amdgcn_sched_barrier(0);
+            if (computes) multiply(cur, nxt, slot);
+        };
+        for (int kt = 0; kt < k_tiles; kt += 2) {  // a step past an odd end works on zeros
+            step(f0, f1, kt);
+            step(f1, f0, kt + 1);
+        }
+        // the reads past the end are still in flight, and so are loads into LDS
+        if (computes) settle(f0);
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        // A lane holds row l15 and four consecutive columns of each block. Rows past M and
+        // columns past N are dropped by the range check.
+        const long long c_row_bytes = prm.N * 2;
+        const __amdgpu_buffer_rsrc_t rc = make_rsrc(prm.C + m0 * c_row_bytes, static_cast<uint32_t>(rows_a * c_row_bytes));
+        if constexpr (T::kStagedStores) {
+            // Through LDS, each wave in a region of its own, rows padded by 32 bytes, so that a
+            // store covers whole rows of the wave's outputs (as in tw_gemm.hip).
+            constexpr int kRowPitch = kBlk * WN * 2 + 32, kRegion = kBlk * WM * kRowPitch;
+            constexpr int kPieces = kBlk * WN * 2 / 16, kRowsPerStore = 64 / kPieces;
+            static_assert(NW == T::kCompute && NW * kRegion <= T::kLdsBytes, "the waves' regions");
+            static_assert(64 % kPieces == 0 && (kBlk * WM) % kRowsPerStore == 0, "whole store instructions");
+            __builtin_amdgcn_s_barrier();  // every wave's loads have landed and its fragments are read
+            const uint32_t region = static_cast<uint32_t>(wave * kRegion);
+            const uint32_t w_addr = region + l15 * kRowPitch + lgrp * 8;
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+#pragma unroll
+                for (int j = 0; j < WN; ++j) {
+                    u32x2 v;
+                    v.x = pack_bf16x2(acc[i][j][0], acc[i][j][1]);
+                    v.y = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
+                    *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(
+                        static_cast<uintptr_t>(w_addr + i * kBlk * kRowPitch + j * kBlk * 2)) = v;
+                }
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+            const int piece_c = lane % kPieces, row_c = lane / kPieces;
+            const long long n = n0 + wave_n * (kBlk * WN) + piece_c * 8;
+            const uint32_t g_off =
+                n < prm.N ? static_cast<uint32_t>((wave_m * (kBlk * WM) + row_c) * c_row_bytes + n * 2) : kPastK;
+            const uint32_t r_addr = region + row_c * kRowPitch + piece_c * 16;
+            const uint32_t store_rows_bytes = static_cast<uint32_t>(kRowsPerStore * c_row_bytes);
+#pragma unroll
+            for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
+                const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) u32x4 *>(
+                    static_cast<uintptr_t>(r_addr + i * kRowsPerStore * kRowPitch));
+                __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off, store_rows_bytes * i, 0);
+            }
+        } else if (computes) {
+#pragma unroll
+            for (int j = 0; j < WN; ++j) {
+                const long long n = n0 + (wave_n * WN + j) * kBlk + lgrp * 4;
+#pragma unroll
+                for (int i = 0; i < WM; ++i) {
+                    u32x2 v;
+                    v.x = pack_bf16x2(acc[i][j][0], acc[i][j][1]);
+                    v.y = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
+                    const uint32_t off =
+                        n < prm.N ? static_cast<uint32_t>(((wave_m * WM + i) * kBlk + l15) * c_row_bytes + n * 2) : kPastK;
+                    __builtin_amdgcn_raw_buffer_store_b64(v, rc, off, 0, 0);
+                }
+            }
+        }
+    }
+#else
+    (void)prm;
+#endif
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+
+template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, bool STREAM_B = false>
+static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, hipStream_t stream)
+{
+    using T = SmallTile<WM, WN, WVM, WVN, BK, S>;
+    const int64_t tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
+    if constexpr (STREAM_B)
+        if (tiles_m > 1) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, false>(g, budget, cus, stream);
+    if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
+    TileParams prm;
+    prm.A = static_cast<const char *>(g.A);
+    prm.B = static_cast<const char *>(g.B);
+    prm.C = static_cast<char *>(g.C);
+    prm.M = g.M;
+    prm.N = g.N;
+    prm.K = g.K;
+    prm.tiles_m = static_cast<int>(tiles_m);
+    prm.tiles_n = static_cast<int>(tiles_n);
+    prm.group_m = tile_group_m(tiles_m, T::BM, T::BN, budget);
+    prm.tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
+    const int64_t slots = int64_t(prm.tiles_per_xcd) * kXcds;
+    // The whole device: a workgroup per tile, as many to a compute unit as fit. Under a
+    // budget one to a compute unit: more than half of its LDS is asked for.
+    constexpr int kAloneBytes = T::kLdsBytes > 81 * 1024 ? T::kLdsBytes : 81 * 1024;
+    const bool whole = budget >= cus;
+    const unsigned grid = static_cast<unsigned>(whole || slots < budget ? slots : budget);
+    auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, S, STREAM_B>;
+    static std::atomic<int> allowed[kMaxDevices];
+    TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), kAloneBytes, allowed));
+    TW_HIP(launch_kernel(kern, dim3(grid), dim3(64 * T::kWaves),
+                         static_cast<unsigned>(whole ? T::kLdsBytes : kAloneBytes), stream, prm));
+    return TW_OK;
+}
+
+// The shapes, smallest first, and what one 64-deep K step of a tile takes when about
+// every compute unit has one (us, measured on MI355X at K = 3584 and 8192). Several
+// tiles to a compute unit take their times in turn, also where two fit at once. [K x N]
+// weights cost two LDS reads a fragment instead of one, and rows of less than 128 bytes
+// of them half a request's worth each (tiles of 64 columns and 16 or 32 rows, whole
+// lines but half as many workgroups, came out level to 7 % slower than 32 x 32 there).
+struct SmallTileShape {
+    int rows, cols, k_step;
+    float us_nk, us_kn;  // 0: not built for that layout
+    tw_status (*nk)(const tw_gemm_args &, int, int, hipStream_t);
+    tw_status (*kn)(const tw_gemm_args &, int, int, hipStream_t);
+};
+static const SmallTileShape kSmallTiles[] = {
+    {16, 16, 256, 0.075f, 0.0f, launch_tile_t<false, 1, 1, 1, 1, 256, 4, true>, nullptr},
+    {32, 16, 256, 0.097f, 0.0f, launch_tile_t<false, 1, 1, 2, 1, 256, 4, true>, nullptr},
+    {32, 32, 128, 0.132f, 0.150f, launch_tile_t<false, 1, 1, 2, 2, 128, 4, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4>},
+    {64, 32, 128, 0.180f, 0.200f, launch_tile_t<false, 2, 1, 2, 2, 128, 4>, launch_tile_t<true, 2, 1, 2, 2, 128, 4>},
+    {64, 64, 128, 0.200f, 0.230f, launch_tile_t<false, 2, 2, 2, 2, 128, 4>, launch_tile_t<true, 2, 2, 2, 2, 128, 4>},
+    {96, 64, 64, 0.255f, 0.280f, launch_tile_t<false, 3, 2, 2, 2, 64, 6>, launch_tile_t<true, 3, 2, 2, 2, 64, 6>},
+    {96, 96, 64, 0.338f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6>, nullptr},
+    {96, 128, 64, 0.405f, 0.430f, launch_tile_t<false, 3, 4, 2, 2, 64, 5>, launch_tile_t<true, 3, 4, 2, 2, 64, 5>},
+    {192, 64, 64, 0.430f, 0.450f, launch_tile_t<false, 3, 2, 4, 2, 64, 4>, launch_tile_t<true, 3, 2, 4, 2, 64, 4>},
+    {128, 128, 64, 0.530f, 0.550f, launch_tile_t<false, 2, 4, 4, 2, 64, 4>, launch_tile_t<true, 2, 4, 4, 2, 64, 4>},
+    {192, 128, 64, 0.710f, 0.740f, launch_tile_t<false, 3, 4, 4, 2, 64, 3>, launch_tile_t<true, 3, 4, 4, 2, 64, 3>},
+};
+
+// A grid's tiles are worked off in turns of one to a compute unit. The first turn's
+// pipeline fill and the last one's stores cost any grid about the same; each further
+// turn adds its own.
+double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_step, double us_per_step, int budget)
+{
+    const int64_t tiles = ((M + rows - 1) / rows) * ((N + cols - 1) / cols);
+    const int64_t turns = (tiles + budget - 1) / budget;
+    const int64_t k_steps = (K + k_step - 1) / k_step * (k_step / 64);
+    return double(turns) * double(k_steps) * us_per_step + double(turns - 1) * 2.7 + 4.0;
+}
+
+int best_small_tile(const tw_gemm_args &g, int budget, double *us)
+{
+    int best = -1;
+    for (int i = 0; i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i) {
+        const SmallTileShape &t = kSmallTiles[i];
+        const float per_step = g.b_layout == TW_B_KN ? t.us_kn : t.us_nk;
+        if (per_step == 0.0f) continue;
+        const double est = tile_grid_us(g.M, g.N, g.K, t.rows, t.cols, t.k_step, per_step, budget);
+        if (best < 0 || est < *us) {
+            best = i;
+            *us = est;
+        }
+    }
+    return best;
+}
+
+tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, hipStream_t stream)
+{
+    const SmallTileShape &t = kSmallTiles[shape];
+    return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, budget, cus, stream);
+}
+
+}  // namespace tw

@@ -88,6 +88,34 @@ def test_gemm_large_product_tiles_give_the_same_bits(tw, torch_cuda, M, N, K, bu
     gemm_check(oracle.bf16_to_f64(Cb[ms, ns]), ref, K, 0.05, "large-tile gemm %dx%dx%d" % (M, N, K))
 
 
+# Sizes at the edges of the small tile shapes (16 ... 192 rows, 16 ... 128 columns, K steps of 64, 128, 256),
+# with outputs enough for each of them to be the one that fills the compute units.
+SMALL_TILE_SHAPES = [(1, 4096, 256), (15, 3592, 264), (17, 4104, 520), (33, 8, 2056), (64, 8200, 136), (65, 4104, 72),
+                     (129, 1288, 328), (200, 3592, 264), (193, 8, 8), (333, 3600, 392), (335, 8200, 72), (500, 3608, 136),
+                     (513, 4104, 264), (700, 8200, 328), (1023, 3592, 136)]
+
+
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("M,N,K", SMALL_TILE_SHAPES)
+def test_gemm_of_few_rows_gives_the_bits_of_the_same_rows_of_a_large_product(tw, torch_cuda, M, N, K, layout):
+    torch = torch_cuda
+    rows = 4096          # enough for 256-row tiles
+    g = W.make_gemm_inputs(M, K, N, 0.5, seed=M + N + K, b_layout=layout)
+    code = tw.B_NK if layout == "nk" else tw.B_KN
+    A, B = to_gpu(g["A"]), to_gpu(g["B"])
+    big = torch.cat([A, torch.ones((rows - M, K), dtype=torch.bfloat16, device="cuda:0")])
+    want = to_bits(tw.gemm_bf16(big, B, b_layout=code)[:M])
+    for budget in (0, 5):
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        tw.gemm_bf16(A, B, C, b_layout=code, cu_budget=budget)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_bits(C), want), "M=%d N=%d K=%d %s budget %d" % (M, N, K, layout, budget)
+    rng = np.random.default_rng(M + N)
+    ms, ns = rng.integers(0, M, 64), rng.integers(0, N, 64)
+    ref = oracle.gemm_samples(g["A"], g["B"], layout, ms, ns)
+    gemm_check(oracle.bf16_to_f64(want)[ms, ns], ref, K, 0.5, "sampled")
+
+
 def test_gemm_k_zero_gives_zeros(tw, torch_cuda):
     torch = torch_cuda
     for (M, N, budget) in ((40, 24, 0), (512, 512, 4)):      # the second takes the 256 x 256 tiles
