@@ -169,35 +169,43 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
 #pragma unroll
             for (int j = 0; j < WN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-        auto issue = [&](int kt, int slot) {
-            const lds_char_ptr_t base = (lds_char_ptr_t)(lds + slot * T::kStageBytes);
+        // The loads of one K step into one stage: offsets first, then load by load.
+        struct Fetch {
             uint32_t off[kRepeat];
+            lds_char_ptr_t base;
+            __amdgpu_buffer_rsrc_t rbk;
+        };
+        auto fetch_ctx = [&](int kt, int slot) {
+            Fetch c;
+            c.base = (lds_char_ptr_t)(lds + slot * T::kStageBytes + wave * 1024);
 #pragma unroll
             for (int q = 0; q < kRepeat; ++q) {
                 const int k = kt * BK + load_piece[q] * 8;  // K <= 2^22, K steps run S past it at most
-                off[q] = k < static_cast<int>(prm.K) ? load_row_off + static_cast<uint32_t>(k) * 2 : kPastK;
+                c.off[q] = k < static_cast<int>(prm.K) ? load_row_off + static_cast<uint32_t>(k) * 2 : kPastK;
             }
-#pragma unroll
-            for (int i = 0; i < T::kALoads; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)(base + (i * NW + wave) * 1024), 16,
-                                                         off[i % kRepeat], step_bytes * i, 0, 0);
-            if constexpr (!B_KN) {
-#pragma unroll
-                for (int i = 0; i < T::kBLoads; ++i)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_ptr_t)(base + T::kABytes + (i * NW + wave) * 1024),
-                                                             16, off[i % kRepeat], step_bytes * i, 0, kBPolicy);
-            } else {
+            if constexpr (B_KN) {
                 // rows k0 ... of B through a descriptor of their own: rows past K lie outside it
                 const long long k0 = static_cast<long long>(kt) * BK, left = prm.K - k0;
                 const int rows_k = static_cast<int>(left < 0 ? 0 : left > BK ? BK : left);
-                const __amdgpu_buffer_rsrc_t rbk =
-                    make_rsrc(prm.B + (left > 0 ? k0 : 0) * bkn_row_bytes, static_cast<uint32_t>(rows_k * bkn_row_bytes));
-#pragma unroll
-                for (int i = 0; i < T::kBLoads; ++i)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rbk, (lds_ptr_t)(base + T::kABytes + (i * NW + wave) * 1024),
-                                                             16, kn_off, kn_step_bytes * i, 0, kBPolicy);
+                c.rbk = make_rsrc(prm.B + (left > 0 ? k0 : 0) * bkn_row_bytes, static_cast<uint32_t>(rows_k * bkn_row_bytes));
+            } else {
+                c.rbk = rb;
+            }
+            return c;
+        };
+        auto fetch_one = [&](const Fetch &c, auto i_tag) {
+            constexpr int i = decltype(i_tag)::value;
+            if constexpr (i < T::kALoads) {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)(c.base + i * NW * 1024), 16, c.off[i % kRepeat],
+                                                         step_bytes * i, 0, 0);
+            } else {
+                constexpr int j = i - T::kALoads;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(c.rbk, (lds_ptr_t)(c.base + T::kABytes + j * NW * 1024), 16,
+                                                         B_KN ? kn_off : c.off[j % kRepeat],
+                                                         (B_KN ? kn_step_bytes : step_bytes) * j, 0, kBPolicy);
             }
         };
+        auto fetch = [&](const Fetch &c) { static_for<T::kLoads>([&](auto i) { fetch_one(c, i); }); };
         using F = StageFrags<B_KN, WM, WN, SUBS>;
         constexpr int kPerSub = WM + (B_KN ? 2 * WN : WN);
         constexpr int kReads = SUBS * kPerSub, kMma = SUBS * WM * WN;
@@ -231,8 +239,9 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
                 }
             }
         };
-        // the matrix instructions of one stage, and between them the reads of the next one's fragments
-        auto multiply = [&](F &cur, F &nxt, int nxt_slot) {
+        // the matrix instructions of one stage, and between them the reads of the next one's fragments and the loads
+        // of a later stage
+        auto multiply = [&](F &cur, F &nxt, int nxt_slot, const Fetch &c) {
             const uint32_t base = nxt_slot * T::kStageBytes;
             static_for<kMma>([&](auto m_tag) {
                 constexpr int m = decltype(m_tag)::value, s = m / (WM * WN), j = m % (WM * WN) / WM, i = m % WM;
@@ -249,6 +258,9 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
                 static_for<kReads>([&](auto t) {
                     if constexpr (decltype(t)::value * kReadSlots / kReads == m) read_one(nxt, base, t);
                 });
+                static_for<T::kLoads>([&](auto t) {
+                    if constexpr (decltype(t)::value * kMma / T::kLoads == m) fetch_one(c, t);
+                });
                 __builtin_amdgcn_sched_barrier(0);
             });
         };
@@ -261,7 +273,7 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
         // the previous tile's loads have landed and nobody reads LDS any more
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
-        static_for<S>([&](auto s) { issue(decltype(s)::value, decltype(s)::value); });
+        static_for<S>([&](auto s) { fetch(fetch_ctx(decltype(s)::value, decltype(s)::value)); });
         wait_vm(std::integral_constant<int, (S - 1) * T::kLoads>{});
         F f0, f1;
         if (computes) read_all(f0, 0);
@@ -269,10 +281,11 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
         auto step = [&](F &cur, F &nxt, int kt) {
             if (computes) settle(cur);
             wait_vm(std::integral_constant<int, (S - 2) * T::kLoads>{});  // stage kt + 1 has landed, stage kt is read
-            issue(kt + S, slot);  // (past the end: out of range, so the counts stay the same)
+            const Fetch c = fetch_ctx(kt + S, slot);  // (past the end: out of range, so the counts stay the same)
             slot = slot + 1 == S ? 0 : slot + 1;
             __builtin_amdgcn_sched_barrier(0);
-            if (computes) multiply(cur, nxt, slot);
+            if (computes) multiply(cur, nxt, slot, c);
+            else fetch(c);
         };
         for (int kt = 0; kt < k_tiles; kt += 2) {  // a step past an odd end works on zeros
             step(f0, f1, kt);
