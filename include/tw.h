@@ -106,10 +106,10 @@ typedef enum tw_status {
  *                 to run NEXT TO a tw_gemm_bf16 workgroup on the same compute
  *                 unit rather than in place of one; for H > 8192 it falls back
  *                 to the whole device. Other negative values mean the whole
- *                 device. A small whole-device launch (P = 1, 2, 4 or 8; up to
- *                 4 to 16 rows per compute unit depending on P and H <= 8192) is
+ *                 device. A small whole-device launch (up to 4 to 32 rows per
+ *                 compute unit depending on P and H <= 8192) is
  *                 sent as those small workgroups too: same bits, lower latency;
- *                 and one of a few dozen rows (decode steps: inputs of at most
+ *                 and one of a few dozen rows (P <= 8; decode steps: inputs of at most
  *                 6 MiB) requests a whole row and the weights at once, one round
  *                 trip to memory instead of three.
  *   out           device bf16 [N x H]

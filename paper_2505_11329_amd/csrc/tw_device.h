@@ -18,16 +18,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, static_cast<int>(bytes), 0x00020000);
 }
 static constexpr uint32_t kOutOfRange = 0xFFFFFFF0u;
+// Out of range with a scalar offset of less than 2^31 on top, which the check counts too (a
+// launch's tensors take at most 2^31 bytes).
+static constexpr uint32_t kPastTensor = 0x80000000u;
 static constexpr int kStreamPolicy = 2;  // loads, "nt": streamed once, do not keep in cache
 // Stores, "sc1": measured against "nt" and the default on MI355X it is 5-9 %
 // faster for whole-device launches of 0.3-0.8 GB, 2-3 % faster when a GEMM reads
 // the output next, the same under a CU budget and 1-2 % slower beyond 1 GB.
 static constexpr int kStorePolicy = 16;
 
-__device__ __forceinline__ u32x4 ld(__amdgpu_buffer_rsrc_t r, uint32_t off)
+__device__ __forceinline__ u32x4 ld(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t scalar_off = 0)
 {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kStreamPolicy);
+    return __builtin_amdgcn_raw_buffer_load_b128(r, off, scalar_off, kStreamPolicy);
 }
+// 16-byte stores take their whole offset in the lane register, with no scalar offset: a
+// store of more than 8 bytes still reads its data registers in the cycle after it was issued,
+// and the compiler keeps the next instruction from overwriting them only where there is no
+// scalar offset. With one, the first word of a store came out as the next row piece's, in the
+// last four lanes of each sixteen, once in some ten thousand stores.
 // `streamed` (a constant in every kernel that stores: each is built both ways,
 // a choice at run time costs the small launches 2 %): the outputs of the call are
 // larger than the 256 MiB last-level cache; they are then stored "nt" like the
@@ -93,17 +101,33 @@ static constexpr int kDppXor2 = 0x4E;         // quad_perm [2,3,0,1]
 static constexpr int kDppHalfMirror = 0x141;  // lane i <-> 7-i in each group of 8
 static constexpr int kDppMirror = 0x140;      // lane i <-> 15-i in each group of 16
 
-// Sum over aligned groups of 2^log2n lanes (log2n <= 6); every lane of a group
-// ends with the same bits. After the first two steps each quad is uniform, so
-// the mirrors act as "xor 4" and "xor 8".
+// v + (v of the lane 16 or 32 further on, crosswise): gfx950's row swaps, in vector
+// registers (the permute through the LDS that a shuffle compiles to takes 130 clocks, and a row of
+// 8192 elements does eight of them).
+__device__ __forceinline__ float swap_add16(float v)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __builtin_bit_cast(float, static_cast<unsigned>(r[0])) + __builtin_bit_cast(float, static_cast<unsigned>(r[1]));
+}
+__device__ __forceinline__ float swap_add32(float v)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __builtin_bit_cast(float, static_cast<unsigned>(r[0])) + __builtin_bit_cast(float, static_cast<unsigned>(r[1]));
+}
+
+// Sum over aligned groups of 2^log2n lanes (log2n <= 6; a constant where it can be: the
+// branches fold); every lane of a group ends with the same bits. After the first two
+// steps each quad is uniform, so the mirrors act as "xor 4" and "xor 8".
 __device__ __forceinline__ float group_sum(float v, int log2n)
 {
     if (log2n >= 1) v = dpp_add<kDppXor1>(v);
     if (log2n >= 2) v = dpp_add<kDppXor2>(v);
     if (log2n >= 3) v = dpp_add<kDppHalfMirror>(v);
     if (log2n >= 4) v = dpp_add<kDppMirror>(v);
-    if (log2n >= 5) v += __shfl_xor(v, 16, 64);
-    if (log2n >= 6) v += __shfl_xor(v, 32, 64);
+    if (log2n >= 5) v = swap_add16(v);
+    if (log2n >= 6) v = swap_add32(v);
     return v;
 }
 

@@ -33,6 +33,8 @@
 //     wave one LDS slot per wave and one barrier; slots are double-buffered by
 //     row parity so one barrier per row suffices.
 #include <atomic>
+#include <type_traits>
+#include <utility>
 
 #include "tw_device.h"
 #include "tw_internal.h"
@@ -70,11 +72,18 @@ struct Chunk {
     u32x4 v[PT + 1];
 };
 
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
+template <int... I, typename F>
+__device__ __forceinline__ void each_chunk(std::integer_sequence<int, I...>, F &&f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
 // How many chunks are kept in flight per thread (register budget: 128 VGPRs).
 template <int PT, int VPT>
 constexpr int buffers_in_flight()
 {
-    return (PT == 0) ? 1 : (((PT + 1) * 8 + 12 * VPT <= 100) ? 2 : 1);
+    return (PT == 0) ? 1 : (((PT + 1) * 8 + 12 * VPT <= (VPT == 4 ? 92 : 100)) ? 2 : 1);
 }
 
 template <int PT, int VPT, bool TRACE, bool STREAMED>
@@ -224,7 +233,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
 
             // Row sum of squares: the row's lanes inside this wave, then (rows
             // wider than a wave) the row's waves through LDS.
-            ss = group_sum(ss, wpr ? 6 : tpr_log2);
+            ss = wpr ? group_sum(ss, 6) : group_sum(ss, tpr_log2);
             if (wpr) {
                 // the row's wave sums, padded with zeros to 16, through a 16-lane butterfly
                 if (lane == 0) s_wave_sum[parity][wave] = ss;
@@ -277,13 +286,22 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
 // step, and reads that are not interleaved with stores come in faster (a
 // 1024-row, H = 8192, P = 8 launch: 33.5 -> 32.2 us with both changes, 256 rows
 // 10.6 -> 9.7 us).
+//
+// What bounds it: HBM from a few thousand rows on; below that the chain of round
+// trips of one row. Three things lengthened the chain: each output vector's weights
+// were asked for on their own, behind the stores of the vector before, so that a row's
+// stores went out one round trip after the other; loads past the end, dropped but
+// issued; and row sums that went through the LDS, two permutes per vector. Without
+// them, us (back-to-back launches, P = 8, H = 8192): 16 rows 5.3 -> 4.5, 64 6.6 -> 5.7,
+// 512 17.7 -> 16.7, 1024 32.5 -> 31.7 (5.8 TB/s), 4096 119 -> 116; P = 2, H = 4096: 512 rows
+// 5.4 -> 4.4, 2048 15.7 -> 14.8. Every P has its own instance: P = 6, H = 5120, 1531 rows
+// 28.2 us with a run-time loop over P in the wide kernel, 25.4 (5.6 TB/s) here.
 // ---------------------------------------------------------------------------
 static constexpr int kThinThreads = 256;
 // The all-at-once form is taken by whole-device launches of at most one workgroup per compute
-// unit whose inputs come to at most this many bytes. Measured on MI355X, H = 8192, trains of
-// launches replayed from a graph: P = 8 up to 48 rows 4.4-4.7 us a launch against 5.0-5.2
-// (-11 %), at 256 rows 7.1 against 6.5 (+8 %): beyond a few MB the requests of a launch queue up
-// and two chunks at a time come in faster.
+// unit whose inputs come to at most this many bytes (and P <= kDeepMaxP: registers). Measured
+// on MI355X at 16 and 64 rows, H = 8192, 5120, 4096: level to 8 % faster than two chunks at a
+// time; at 256 rows of H = 8192 8 % slower: beyond a few MB the requests of a launch queue up.
 static constexpr int64_t kDeepInputBytes = 6 << 20;
 
 // DEEP: the form for batches so small that a launch is one round trip to memory
@@ -316,8 +334,8 @@ __device__ __forceinline__ void thin_body(const FusedParams &prm)
 
     // The weights are re-read for every row with ordinary (cached) loads: the
     // streamed tensors are loaded "nt" and do not displace them from the L1, and
-    // neither registers nor LDS are spent on them, which is what lets this
-    // workgroup fit beside a GEMM workgroup that uses 144 KiB of LDS.
+    // no LDS is spent on them, which is what lets this workgroup fit beside a GEMM
+    // workgroup that uses 144 KiB of it.
     const __amdgpu_buffer_rsrc_t r_w = make_rsrc(prm.weight, static_cast<uint32_t>(hv) * 16u);
 
     __amdgpu_buffer_rsrc_t r_part[PT > 0 ? PT : 1];
@@ -329,28 +347,32 @@ __device__ __forceinline__ void thin_body(const FusedParams &prm)
     const __amdgpu_buffer_rsrc_t r_out = make_rsrc(prm.out, prm.n_bytes);
     const __amdgpu_buffer_rsrc_t r_res_out = make_rsrc(prm.residual_out, prm.n_bytes);
 
-    uint32_t lane_off[Q];
-    bool cvalid[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int v = col0 + q * kThinThreads;
-        cvalid[q] = v < hv;
-        lane_off[q] = static_cast<uint32_t>(row_in_iter * hv + v) * 16u;
-    }
+    // Address of chunk q of a row group: a lane register (the same for every q but the last,
+    // which may reach past the row) and a scalar for group and q.
+    const int last_col = col0 + (Q - 1) * kThinThreads;
+    const uint32_t lane_off = static_cast<uint32_t>(row_in_iter * hv + col0) * 16u;
+    const uint32_t lane_off_last = last_col < hv ? lane_off : kPastTensor;
     const uint32_t group_bytes = prm.group_bytes;
-    auto chunk_off = [&](uint32_t group, int q) -> uint32_t {
-        return cvalid[q] ? lane_off[q] + group * group_bytes : kOutOfRange;
+    struct Off {
+        uint32_t lane, scalar;
     };
-    auto issue = [&](Chunk<PT> &c, uint32_t off) {
+    auto chunk_off = [&](uint32_t group, int q) -> Off {
+        return {q == Q - 1 ? lane_off_last : lane_off, group * group_bytes + q * (kThinThreads * 16u)};
+    };
+    auto load_w = [&](int q) {
+        return __builtin_amdgcn_raw_buffer_load_b128(r_w, q < Q - 1 || last_col < hv ? col0 * 16u : kPastTensor,
+                                                     q * (kThinThreads * 16u), 0);
+    };
+    auto issue = [&](Chunk<PT> &c, Off off) {
         if constexpr (PT > 0) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int p = 0; p < PT; ++p) c.v[p] = ld(r_part[p], off);
-            c.v[PT] = ld(r_res, off);
+            for (int p = 0; p < PT; ++p) c.v[p] = ld(r_part[p], off.lane, off.scalar);
+            c.v[PT] = ld(r_res, off.lane, off.scalar);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto reduce_chunk = [&](const Chunk<PT> &c, uint32_t off, float (&x)[8]) {
+    auto reduce_chunk = [&](const Chunk<PT> &c, Off off, float (&x)[8]) {
         if constexpr (PT > 0) {
             unpack8(c.v[0], x);
 #pragma unroll
@@ -361,13 +383,13 @@ __device__ __forceinline__ void thin_body(const FusedParams &prm)
             // thread here has four times the wide kernel's work per row and fewer
             // waves to hide a round trip behind (four at a time: 10-25 % slower)
             constexpr int kBatch = 8;
-            const u32x4 r = ld(r_res, off);
+            const u32x4 r = ld(r_res, off.lane, off.scalar);
             for (int p0 = 0; p0 < prm.P; p0 += kBatch) {
                 u32x4 t[kBatch];
 #pragma unroll
                 for (int i = 0; i < kBatch; ++i) {
                     const bool live = p0 + i < prm.P;
-                    t[i] = ld(make_rsrc(prm.partials[live ? p0 + i : 0], live ? prm.n_bytes : 0u), off);
+                    t[i] = ld(make_rsrc(prm.partials[live ? p0 + i : 0], live ? prm.n_bytes : 0u), off.lane, off.scalar);
                 }
                 if (p0 == 0) unpack8(t[0], x); else add8(t[0], x);
 #pragma unroll
@@ -387,41 +409,52 @@ __device__ __forceinline__ void thin_body(const FusedParams &prm)
     // Chunks in flight: NB. Chunk (group, q) sits in buffer q % NB and is refilled
     // with the chunk NB further on: the same row's, or the workgroup's next row's;
     // after its last row nothing is fetched.
-    constexpr int NB = DEEP ? Q : (Q % 2 == 0) ? 2 : 1;
+    constexpr int NB = DEEP ? Q : (Q % 2 == 0 && PT <= 8) ? 2 : 1;  // (registers: 128)
     static_assert(!DEEP || PT > 0, "the run-time loop over P keeps nothing in flight");
-    auto off_or_none = [&](uint32_t group, int q) -> uint32_t {
-        return group < last ? chunk_off(group, q) : kOutOfRange;
-    };
     Chunk<PT> buf[NB];
-    issue(buf[0], off_or_none(first, 0));
-    if constexpr (NB >= 2) issue(buf[1], off_or_none(first, 1));
-    if constexpr (NB >= 3) issue(buf[2], off_or_none(first, 2));
-    if constexpr (NB >= 4) issue(buf[3], off_or_none(first, 3));
+    issue(buf[0], chunk_off(first, 0));
+    if constexpr (NB >= 2) issue(buf[1], chunk_off(first, 1));
+    if constexpr (NB >= 3) issue(buf[2], chunk_off(first, 2));
+    if constexpr (NB >= 4) issue(buf[3], chunk_off(first, 3));
     static_assert(NB <= 4, "chunks issued above");
-    u32x4 w_ahead[DEEP ? Q : 1];
-    if constexpr (DEEP) {
+    u32x4 wv[Q];
+    auto load_weights = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < Q; ++q)
-            w_ahead[q] = __builtin_amdgcn_raw_buffer_load_b128(
-                r_w, cvalid[q] ? (col0 + q * kThinThreads) * 16u : kOutOfRange, 0, 0);
-    }
+        for (int q = 0; q < Q; ++q) wv[q] = load_w(q);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (DEEP) load_weights();
+    constexpr int kAheadOfStores = NB == 1 ? 1 : (PT + 1) * 8 + Q * 12 <= 112 ? 1 : 0;
     int parity = 0;
-    for (uint32_t group = first; group < last; group += gstride) {
+    // One row group. Loads come back in the order they were issued, and so do stores: the
+    // weights are asked for before the next row's chunks, or the output would wait for those,
+    // and all together, or each vector of the output would wait for the stores of the one
+    // before it. Of two chunks of the next row one goes out after the stores, or both, where
+    // the registers do not hold them beside the weights. MORE: the
+    // workgroup has another row group. (A compile-time choice: loads past the end would be
+    // dropped by the range check, but each still takes its turn in the L1's request queue.)
+    auto row_group = [&](uint32_t group, auto more_tag) {
+        constexpr bool MORE = decltype(more_tag)::value;
         float x[Q][8];
         float ss[Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
+        each_chunk(std::make_integer_sequence<int, Q>{}, [&](auto q_tag) {
+            constexpr int q = decltype(q_tag)::value;
             Chunk<PT> &b = buf[q % NB];
             reduce_chunk(b, chunk_off(group, q), x[q]);
-            if constexpr (!DEEP)
-                issue(b, (q + NB < Q) ? chunk_off(group, q + NB) : off_or_none(group + gstride, q + NB - Q));
+            if constexpr (!DEEP) {
+                if constexpr (q + NB < Q) issue(b, chunk_off(group, q + NB));
+                if constexpr (q == (Q >= 2 ? Q - 2 : 0)) load_weights();
+                if constexpr (MORE && q + NB >= Q && q - Q + NB < kAheadOfStores)
+                    issue(b, chunk_off(group + gstride, q + NB - Q));
+            }
             float acc = 0.0f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc = __builtin_fmaf(x[q][e], x[q][e], acc);
-            ss[q] = group_sum(acc, tpr_log2 < 6 ? tpr_log2 : 6);
-        }
+            ss[q] = Q > 1 ? group_sum(acc, 6) : group_sum(acc, tpr_log2 < 6 ? tpr_log2 : 6);
+        });
         float total = ss[0];
-        if (tpr_log2 > 6) {
+        if (Q > 1 || tpr_log2 > 6) {
             if (lane == 0) {
 #pragma unroll
                 for (int q = 0; q < Q; ++q) s_wave_sum[parity][wave + q * (kThinThreads / 64)] = ss[q];
@@ -438,15 +471,24 @@ __device__ __forceinline__ void thin_body(const FusedParams &prm)
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             float w[8], y[8];
-            const int v = col0 + q * kThinThreads;
-            if constexpr (DEEP) unpack8(w_ahead[q], w);
-            else unpack8(__builtin_amdgcn_raw_buffer_load_b128(r_w, cvalid[q] ? v * 16u : kOutOfRange, 0, 0), w);
+            unpack8(wv[q], w);
 #pragma unroll
             for (int e = 0; e < 8; ++e) y[e] = (x[q][e] * s) * w[e];
-            st(r_res_out, chunk_off(group, q), pack8(x[q]), streamed);
-            st(r_out, chunk_off(group, q), pack8(y), streamed);
+            const Off at = chunk_off(group, q);
+            const uint32_t off = at.lane + at.scalar;  // (see st())
+            st(r_res_out, off, pack8(x[q]), streamed);
+            st(r_out, off, pack8(y), streamed);
         }
-    }
+        if constexpr (MORE)
+            each_chunk(std::make_integer_sequence<int, NB - kAheadOfStores>{}, [&](auto i_tag) {
+                constexpr int c = kAheadOfStores + decltype(i_tag)::value;  // chunk c of the next row
+                issue(buf[c], chunk_off(group + gstride, c));
+            });
+    };
+    uint32_t group = first;
+    if constexpr (!DEEP)
+        for (; group + gstride < last; group += gstride) row_group(group, std::true_type{});
+    row_group(group, std::false_type{});
 }
 
 template <int PT, int Q, bool TRACE, bool STREAMED>
@@ -532,11 +574,19 @@ tw_status validate_fused(const tw_fused_args &a)
     return TW_OK;
 }
 
+// Partial counts that are traced with the kernel that runs them untraced; the others are
+// traced with the run-time loop over P (same grid, same bits).
+template <int PT>
+static constexpr bool kTracedP = PT == 1 || PT == 2 || PT == 4 || PT == 8;
+// Most partials the all-at-once form has registers for.
+static constexpr int kDeepMaxP = 8;
+
 template <int PT, int VPT>
 static tw_status launch_t(const FusedParams &prm, bool trace, bool streamed, int64_t grid, int block, hipStream_t stream)
 {
-    auto kern = trace ? fused_kernel<PT, VPT, true, false>
-                      : streamed ? fused_kernel<PT, VPT, false, true> : fused_kernel<PT, VPT, false, false>;
+    auto kern = streamed ? fused_kernel<PT, VPT, false, true> : fused_kernel<PT, VPT, false, false>;
+    if constexpr (PT == 0 || kTracedP<PT>)
+        if (trace) kern = fused_kernel<PT, VPT, true, false>;
     static std::atomic<int> allowed[2][kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kOccupancyPadBytes),
                              allowed[trace]));
@@ -549,8 +599,9 @@ template <int PT, int Q>
 static tw_status launch_thin_t(const FusedParams &prm, bool trace, bool streamed, int64_t grid,
                                hipStream_t stream)
 {
-    auto kern = trace ? fused_thin_kernel<PT, Q, true, false>
-                      : streamed ? fused_thin_kernel<PT, Q, false, true> : fused_thin_kernel<PT, Q, false, false>;
+    auto kern = streamed ? fused_thin_kernel<PT, Q, false, true> : fused_thin_kernel<PT, Q, false, false>;
+    if constexpr (PT == 0 || kTracedP<PT>)
+        if (trace) kern = fused_thin_kernel<PT, Q, true, false>;
     TW_HIP(launch_kernel(kern, dim3(static_cast<unsigned>(grid)), dim3(kThinThreads), 0u, stream, prm));
     return TW_OK;
 }
@@ -558,12 +609,26 @@ static tw_status launch_thin_t(const FusedParams &prm, bool trace, bool streamed
 template <int PT, int Q>
 static tw_status launch_deep_t(const FusedParams &prm, int64_t grid, hipStream_t stream)
 {
-    if constexpr (PT > 0) {
+    if constexpr (PT > 0 && PT <= kDeepMaxP) {
         TW_HIP(launch_kernel(fused_deep_kernel<PT, Q>, dim3(static_cast<unsigned>(grid)), dim3(kThinThreads), 0u,
                              stream, prm));
         return TW_OK;
     }
     return TW_ERR_UNSUPPORTED;
+}
+
+// Calls f(integral_constant<int, P>) for P in 1 ... TW_MAX_P.
+template <typename F, int... I>
+static tw_status with_partials(int P, F &&f, std::integer_sequence<int, I...>)
+{
+    tw_status s = TW_ERR_UNSUPPORTED;
+    (void)((P == I + 1 ? (s = f(std::integral_constant<int, I + 1>{}), true) : false) || ...);
+    return s;
+}
+template <typename F>
+static tw_status with_partials(int P, F &&f)
+{
+    return with_partials(P, static_cast<F &&>(f), std::make_integer_sequence<int, TW_MAX_P>{});
 }
 
 template <int PT>
@@ -611,45 +676,65 @@ static int64_t thin_grid(int64_t n_rows, const ThinGeometry &t, int cus)
     return (n_groups + gpw - 1) / gpw;
 }
 
+// Whether a row of VPT vectors per thread and one chunk of PT partials fit the 128 registers of
+// a 1024-thread workgroup; where they do not, the run-time loop over P (four loads at a time,
+// same order of additions) does.
+static constexpr bool wide_fits(int P, int vpt)
+{
+    return P == 0 || vpt == 1 || (vpt <= 4 ? P <= 8 : P == 1 || P == 2 || P == 4);
+}
+template <int PT, int VPT>
+static constexpr bool wide_fits()
+{
+    return wide_fits(PT, VPT);
+}
+
 template <int PT>
 static tw_status launch_vpt(const FusedParams &prm, const FusedGeometry &g, bool trace, bool streamed, int64_t grid,
                             hipStream_t s)
 {
     switch (g.vpt) {
     case 1: return launch_t<PT, 1>(prm, trace, streamed, grid, g.block, s);
-    case 2: return launch_t<PT, 2>(prm, trace, streamed, grid, g.block, s);
-    case 4: return launch_t<PT, 4>(prm, trace, streamed, grid, g.block, s);
+    case 2:
+        if constexpr (wide_fits<PT, 2>()) return launch_t<PT, 2>(prm, trace, streamed, grid, g.block, s);
+        break;
+    case 4:
+        if constexpr (wide_fits<PT, 4>()) return launch_t<PT, 4>(prm, trace, streamed, grid, g.block, s);
+        break;
     case 8:
-        if constexpr (PT != 8) return launch_t<PT, 8>(prm, trace, streamed, grid, g.block, s);  // P = 8 goes to the any-P kernel
+        if constexpr (wide_fits<PT, 8>()) return launch_t<PT, 8>(prm, trace, streamed, grid, g.block, s);
         break;
     }
     return TW_ERR_UNSUPPORTED;
 }
 
 // Which kernel a launch takes. Shared mode has a kernel for rows of up to 1024
-// vectors; wider rows run on the wide kernel over the whole device. A small
-// whole-device launch with P = 1, 2, 4 or 8 also takes the small workgroups: they
-// are placed faster and put every row in flight at once, where the wide kernel's
-// software pipeline has only a few rows per workgroup to run over. Measured on
-// MI355X, small workgroups against the wide kernel on 255 compute units, trains
-// of launches on rotating buffers. Rows of an even number of 256-vector pieces
-// (H = 4096, 8192: two chunks in flight per thread): P = 8 faster up to 8192 rows
-// (22 % at 512, 4 % at 4096, 1.5 % at 8192), P = 4 up to 2048 (level at 4096, 2 %
-// slower at 8192), P = 2 at H = 4096 up to 4096 (level at 8192, 5 % slower at
-// 16384), P = 1 up to 1024 (7 % slower at 4096). Other row widths (one chunk in
-// flight) keep narrower limits found the same way. For P without a specialised
-// kernel, whose loads go out eight at a time, the wide kernel is faster, by up
-// to 40 % on small batches. Both kernels give the same bits.
+// vectors; wider rows run on the wide kernel over the whole device. A
+// whole-device launch also takes the small workgroups up to a number of vectors
+// per compute unit: they are placed faster and put every row in flight at once,
+// where the wide kernel's software pipeline has only a few rows per workgroup to
+// run over; beyond it the wide kernel's fewer, longer streams are ahead. Measured
+// on MI355X, trains of launches on rotating buffers, small workgroups against the
+// wide kernel: faster by 15 to 20 % at 1024 rows whatever P and H; level at (rows per
+// compute unit, H = 8192 / 4096 / 5120 / 2048) 6 / 16 / 9 / 20 for P = 1, 16 / 24 / 10 / 32
+// for P = 2, 16 / 26 / 10 / 32 for P = 3 and 4, 32 / 32 / 14 / 32 for P = 5 to 8, 12 / 12 / 9 /
+// 18 from P = 9 on; past twice that 2 to 8 % slower. (Rows of an even number of
+// 256-vector pieces keep two chunks in flight per thread up to P = 8, hence their later
+// crossing.) Rows of 128 vectors and fewer share workgroups and cross at 12. Both
+// kernels give the same bits.
 static bool takes_thin_kernel(int cu_budget, int cus, const FusedGeometry &g, int64_t n_rows, int P)
 {
     if (g.vpt != 1) return false;
     if (cu_budget == TW_CU_SHARED) return true;
     if (resolve_budget(cu_budget, cus) != cus) return false;
-    const bool two_chunks = g.hv > kThinThreads && ((g.hv + kThinThreads - 1) / kThinThreads) % 2 == 0;
-    int64_t rows_per_cu;
-    if (two_chunks) rows_per_cu = P == 8 ? 16 : (P == 4 || P == 2) ? 8 : P == 1 ? 4 : 0;
-    else rows_per_cu = P == 8 ? 8 : (P == 4 || P == 2) ? 2 : 0;
-    return n_rows <= rows_per_cu * cus;
+    const int q = g.hv > kThinThreads ? (g.hv + kThinThreads - 1) / kThinThreads : 1;
+    int64_t vectors_per_cu;
+    if (g.hv <= 128) vectors_per_cu = int64_t(12) * g.hv;
+    else if (P == 1) vectors_per_cu = 5120;
+    else if (P > 8) vectors_per_cu = q % 2 == 0 ? 6144 : 4608;
+    else if (q % 2 == 0) vectors_per_cu = P > 4 ? 8192 * q : P > 2 && q == 4 ? 16384 : 12288;
+    else vectors_per_cu = q == 1 || P > 4 ? 8192 : 5120;
+    return n_rows * g.hv <= vectors_per_cu * cus;
 }
 
 tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_end, uint32_t *hw_ids,
@@ -685,7 +770,7 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
             // bytes: the launch is latency-bound, everything is requested at once. Not
             // in shared mode, whose workgroups must fit beside a GEMM's.
             const int64_t n_groups = (n_rows + rows_per_group - 1) / rows_per_group;
-            deep = !trace && a.cu_budget != TW_CU_SHARED && (a.P == 1 || a.P == 2 || a.P == 4 || a.P == 8) &&
+            deep = !trace && a.cu_budget != TW_CU_SHARED && a.P <= kDeepMaxP &&
                    grid == n_groups && n_groups <= cus && n_rows * row_bytes * (a.P + 1) <= kDeepInputBytes;
         } else {
             grid = fused_grid_size(n_rows, g, budget);
@@ -712,26 +797,21 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
         prm.eps = a.eps;
         prm.inv_h = 1.0f / static_cast<float>(a.H);
 
+        // the run-time loop over P: where no specialised kernel has the registers, or is built to be traced
+        const bool traced_p = a.P == 1 || a.P == 2 || a.P == 4 || a.P == 8;
+        const bool any_p = (trace && !traced_p) || (!thin && !wide_fits(a.P, g.vpt));
         if (thin) {
-            switch (a.P) {
-            case 1: TW_TRY((launch_thin<1>(prm, tg.q, trace, streamed, deep, grid, stream))); break;
-            case 2: TW_TRY((launch_thin<2>(prm, tg.q, trace, streamed, deep, grid, stream))); break;
-            case 4: TW_TRY((launch_thin<4>(prm, tg.q, trace, streamed, deep, grid, stream))); break;
-            case 8: TW_TRY((launch_thin<8>(prm, tg.q, trace, streamed, deep, grid, stream))); break;
-            default: TW_TRY((launch_thin<0>(prm, tg.q, trace, streamed, deep, grid, stream))); break;
-            }
-            continue;
-        }
-        // Rows of 8 vectors per thread with all 8 partials in flight would not fit
-        // the 128 registers; the any-P kernel (4 loads at a time, same order of
-        // additions) does.
-        const int p_case = (a.P == 8 && g.vpt == 8) ? 0 : a.P;
-        switch (p_case) {
-        case 1: TW_TRY((launch_vpt<1>(prm, g, trace, streamed, grid, stream))); break;
-        case 2: TW_TRY((launch_vpt<2>(prm, g, trace, streamed, grid, stream))); break;
-        case 4: TW_TRY((launch_vpt<4>(prm, g, trace, streamed, grid, stream))); break;
-        case 8: TW_TRY((launch_vpt<8>(prm, g, trace, streamed, grid, stream))); break;
-        default: TW_TRY((launch_vpt<0>(prm, g, trace, streamed, grid, stream))); break;
+            if (any_p) TW_TRY((launch_thin<0>(prm, tg.q, trace, streamed, false, grid, stream)));
+            else
+                TW_TRY(with_partials(a.P, [&](auto pt) {
+                    return launch_thin<decltype(pt)::value>(prm, tg.q, trace, streamed, deep, grid, stream);
+                }));
+        } else {
+            if (any_p) TW_TRY((launch_vpt<0>(prm, g, trace, streamed, grid, stream)));
+            else
+                TW_TRY(with_partials(a.P, [&](auto pt) {
+                    return launch_vpt<decltype(pt)::value>(prm, g, trace, streamed, grid, stream);
+                }));
         }
     }
     return TW_OK;

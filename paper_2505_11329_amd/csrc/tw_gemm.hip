@@ -662,7 +662,7 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
             const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) u32x4 *>(
                 static_cast<uintptr_t>(r_addr + i * kRowsPerStore * kRowPitch));
-            __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off, store_rows_bytes * i, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, 0);  // (no scalar offset: see st())
         }
         if constexpr (TRACE) phase[kPhaseStores] += now() - t_stores;
     }

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
             for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
                 const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) u32x4 *>(
                     static_cast<uintptr_t>(r_addr + i * kRowsPerStore * kRowPitch));
-                __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off, store_rows_bytes * i, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, 0);  // (no scalar offset: see st())
             }
         } else if (computes) {
 #pragma unroll

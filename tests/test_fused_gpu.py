@@ -141,6 +141,40 @@ def test_decode_sized_whole_device_launches_on_both_sides_of_the_all_at_once_lim
             assert np.array_equal(out, out2) and np.array_equal(res, res2), (N, budget)
 
 
+# Each P has kernels of its own, in small workgroups (1 to 4 vectors per thread, one chunk of loads in flight or
+# two) and in the wide geometry (1 to 8 vectors per thread): every launch mode against the confined one, which is
+# checked against the oracle, on one row and on row counts around the edges.
+@pytest.mark.parametrize("H", [504, 2056, 4096, 6136, 8192, 8200, 16392, 40000])
+@pytest.mark.parametrize("P", [3, 5, 6, 7, 9, 11, 13, 16])
+def test_kernels_of_every_partial_count(tw, torch_cuda, H, P):
+    torch = torch_cuda
+    for N in (1, 37):
+        d = small(N, H, P, seed=H + P + N)
+        g = upload(d)
+        want = run(tw, torch, g, cu_budget=3)
+        check_against_oracle(d, want[0], want[1], "N=%d H=%d P=%d" % (N, H, P))
+        for budget in (0, tw.CU_SHARED):
+            out, res = run(tw, torch, g, cu_budget=budget)
+            assert np.array_equal(out, want[0]) and np.array_equal(res, want[1]), (N, budget)
+
+
+@pytest.mark.parametrize("N,H,P", [(4100, 8192, 8), (4611, 4096, 2), (4099, 8192, 12), (6200, 5120, 5), (4097, 8184, 1),
+                                   (9000, 1032, 3)])
+def test_small_workgroups_with_several_rows_each(tw, torch_cuda, N, H, P):
+    """From 16 row groups per compute unit on, a small workgroup works through two and more of them, with loads of
+    the next row in flight while it stores."""
+    torch = torch_cuda
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(N)
+    def draw(*shape):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda:0").normal_(generator=gen)
+    parts, resid, w = [draw(N, H) for _ in range(P)], draw(N, H), draw(H)
+    want = [to_bits(x) for x in tw.reduce_add_rmsnorm(parts, resid, w, 1e-5, cu_budget=64)]
+    for _ in range(3):
+        out, res = tw.reduce_add_rmsnorm(parts, resid, w, 1e-5, cu_budget=tw.CU_SHARED)
+        assert np.array_equal(to_bits(out), want[0]) and np.array_equal(to_bits(res), want[1])
+
+
 def test_every_p_from_1_to_16(tw, torch_cuda):
     for P in range(1, 17):
         d = small(40, 2048, P, seed=P)
