@@ -39,7 +39,7 @@
 //     still has matrix work queued.
 //   - Large products launched on their own take 256 x 256 tiles instead: four
 //     waves of 128 x 128 (256 accumulator registers per lane), K steps of 64 whose
-//     operand areas rotate through a ring of five 32 KiB LDS slots, one operand's
+//     operand areas rotate through three LDS slots (A) and two (B), one operand's
 //     loads per sub-step (see the K loop). With one wave per SIMD every
 //     instruction between two MFMAs counts: a wave issues one instruction in
 //     four clocks and an MFMA lasts sixteen.
@@ -78,8 +78,9 @@ static_assert(kPhaseTotal + 1 == kGemmPhases, "phase list");
 // STAGES LDS stages. The library builds <4, 4, 3, 64>: eight waves of 64 x 64,
 // tile 256 x 128, 3 x 48 KiB of LDS; for products with few tiles <4, 2, 3, 64>:
 // eight waves of 64 x 32, tile 256 x 64, 3 x 40 KiB; and for large products
-// <8, 8, 2, 64>: four waves of 128 x 128, tile 256 x 256, two K steps of 64 in a
-// ring of five 32 KiB slots (STAGES = 2 stands for that ring, see the K loop).
+// <8, 8, 2, 64>: four waves of 128 x 128, tile 256 x 256, and <8, 6, 2, 64>: four of
+// 128 x 96, tile 256 x 192, with three LDS slots for A and two for B (STAGES = 2
+// stands for that, see the K loop).
 template <int WM, int WN, int STAGES, int BK_>
 struct TileCfg {
     static constexpr int kWaves = 2 * BM / (kBlk * WM);
@@ -88,12 +89,10 @@ struct TileCfg {
     static constexpr int kStageABytes = BM * BK_ * 2;
     static constexpr int kStageBBytes = kBN * BK_ * 2;
     static constexpr int kStageBytes = kStageABytes + kStageBBytes;
-    // Two stages of 2 x 32 KiB leave a fifth 32 KiB slot of the compute unit's LDS
-    // free: the operand areas then rotate through five slots.
+    // Two stages and a third slot for A: A's areas rotate through three, B's through two.
     static constexpr bool kRing = STAGES == 2;
-    static constexpr int kRingSlots = 5;
-    static constexpr int kLdsBytes = kRing ? kRingSlots * kStageABytes : STAGES * kStageBytes;
-    static_assert(!kRing || kStageABytes == kStageBBytes, "ring slots hold either operand");
+    static constexpr int kRingBOffset = 3 * kStageABytes;
+    static constexpr int kLdsBytes = kRing ? kRingBOffset + 2 * kStageBBytes : STAGES * kStageBytes;
 };
 
 struct GemmParams {
@@ -161,7 +160,9 @@ struct Frags {
 #define TW_FRAG_B2_LEN 2
 #define TW_FRAG_B4(f) TW_FRAG_B2(f), "+v"((f).b[2]), "+v"((f).b[3])
 #define TW_FRAG_B4_LEN 4
-#define TW_FRAG_B8(f) TW_FRAG_B4(f), "+v"((f).b[4]), "+v"((f).b[5]), "+v"((f).b[6]), "+v"((f).b[7])
+#define TW_FRAG_B6(f) TW_FRAG_B4(f), "+v"((f).b[4]), "+v"((f).b[5])
+#define TW_FRAG_B6_LEN 6
+#define TW_FRAG_B8(f) TW_FRAG_B6(f), "+v"((f).b[6]), "+v"((f).b[7])
 #define TW_FRAG_B8_LEN 8
 #define TW_FRAG_B_KN4(f)                                                                            \
     "+v"((f).blo[0]), "+v"((f).bhi[0]), "+v"((f).blo[1]), "+v"((f).bhi[1]), "+v"((f).blo[2]),       \
@@ -178,12 +179,13 @@ template <int N, bool B_KN, int WM, int WN>
 __device__ __forceinline__ void wait_lgkm(Frags<B_KN, WM, WN> &f)
 {
     static_assert(WM == 4 || WM == 8, "fragment operand lists below");
-    static_assert(B_KN ? (WM == 4 && WN == 4) : (WN == 2 || WN == 4 || WN == 8), "fragment operand lists below");
+    static_assert(B_KN ? (WM == 4 && WN == 4) : (WN == 2 || WN == 4 || WN == 6 || WN == 8), "fragment operand lists below");
     if constexpr (B_KN) TW_WAIT_LGKM(N, f, TW_FRAG_A4, TW_FRAG_B_KN4);
     if constexpr (!B_KN && WM == 4 && WN == 2) TW_WAIT_LGKM(N, f, TW_FRAG_A4, TW_FRAG_B2);
     if constexpr (!B_KN && WM == 4 && WN == 4) TW_WAIT_LGKM(N, f, TW_FRAG_A4, TW_FRAG_B4);
     if constexpr (!B_KN && WM == 4 && WN == 8) TW_WAIT_LGKM(N, f, TW_FRAG_A4, TW_FRAG_B8);
     if constexpr (!B_KN && WM == 8 && WN == 4) TW_WAIT_LGKM(N, f, TW_FRAG_A8, TW_FRAG_B4);
+    if constexpr (!B_KN && WM == 8 && WN == 6) TW_WAIT_LGKM(N, f, TW_FRAG_A8, TW_FRAG_B6);
     if constexpr (!B_KN && WM == 8 && WN == 8) TW_WAIT_LGKM(N, f, TW_FRAG_A8, TW_FRAG_B8);
 }
 
@@ -325,7 +327,7 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
                     // together before the stores costs a spilled accumulator, whose reload
                     // then waits for every store issued before it.
                     float z;
-                    if constexpr (WM * WN == 64) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(z));
+                    if constexpr (WM * WN >= 48) asm volatile("v_accvgpr_write_b32 %0, 0" : "=a"(z));
                     else asm volatile("v_mov_b32 %0, 0" : "=v"(z));
                     acc[i][j][e] = z;
                 }
@@ -477,30 +479,30 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         F f0, f1;
         int stage = 0;
         if constexpr (kRing) {
-            // Five slots of 32 KiB, each one operand's share of a K step. K step j keeps A
-            // in slot 2j mod 5 and B in the slot after it; while step j is worked on, step
-            // j + 1 sits in the next two slots (landed, or landing) and one slot is free:
+            // Three slots for A and two for B, each one operand's share of a K step: K step j
+            // keeps A in slot j mod 3 and B in slot j mod 2. While step j is worked on, step
+            // j + 1 sits in the next ones (landed, or landing) and the third slot of A is free:
             // it takes A of step j + 2 during the first sub-step. The barrier before the
             // second sub-step tells that every wave has fetched its last fragments of step
-            // j; the slot that held its A then takes B of step j + 2. So one operand's loads
+            // j; the slot that held its B then takes B of step j + 2. So one operand's loads
             // go out per sub-step, none in a burst (16 KiB-per-wave bursts after the barrier
             // of a two-stage rotation stalled the issuing waves for ~400 clocks a step).
-            constexpr int kSlotBytes = kStageABytes;
-            auto slot_off = [&](int sl) { return static_cast<uint32_t>(sl * kSlotBytes); };
+            auto slot_a = [&](int sl) { return static_cast<uint32_t>(sl * kStageABytes); };
+            auto slot_b = [&](int sl) { return static_cast<uint32_t>(Cfg::kRingBOffset + sl * Cfg::kStageBBytes); };
             static_for<2>([&](auto st) {
                 constexpr int j = decltype(st)::value;
-                const FetchCtx c = fetch_ctx(j, slot_off(2 * j), slot_off(2 * j + 1));
+                const FetchCtx c = fetch_ctx(j, slot_a(j), slot_b(j));
                 static_for<kLoads>([&](auto i) { fetch_one(c, decltype(i)::value); });
             });
             wait_vm(std::integral_constant<int, kLoads>{});  // K step 0 has landed
-            load_frags(f0, slot_off(0), slot_off(1), K0{});
+            load_frags(f0, slot_a(0), slot_b(0), K0{});
             if constexpr (TRACE) {
                 t_prev = now();
                 phase[kPhaseFill] += t_prev - t_tile;
             }
-            // byte offsets of the slots of this K step's A and B, of the next step's, and of the free one
-            uint32_t o_a = slot_off(0), o_b = slot_off(1), o_na = slot_off(2), o_nb = slot_off(3), o_free = slot_off(4);
-            FetchCtx fc = fetch_ctx(2, o_free, o_a);
+            // byte offsets of the slots of this K step's A and B, of the next step's, and of A's free one
+            uint32_t o_a = slot_a(0), o_b = slot_b(0), o_na = slot_a(1), o_nb = slot_b(1), o_free = slot_a(2);
+            FetchCtx fc = fetch_ctx(2, o_free, o_b);
             auto nothing = [] {};
             for (int kt = 0; kt < k_tiles; ++kt) {
                 wait_lgkm<0>(f0);
@@ -529,14 +531,14 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
                 sub_step(f1, f0, o_na, o_nb, K0{}, fc, std::integral_constant<int, A_LOADS>{},
                          std::integral_constant<int, B_LOADS>{}, HalfSlots{}, [&] {
                              // late in the sub-step, when its reads and loads are out: the slots
-                             // move on by two, and the next step's loads get their offsets
+                             // move on, and the next step's loads get their offsets
                              const uint32_t t_a = o_a, t_b = o_b;
                              o_a = o_na;
                              o_b = o_nb;
                              o_na = o_free;
-                             o_nb = t_a;
-                             o_free = t_b;
-                             fc = fetch_ctx(kt + 3, o_free, o_a);
+                             o_nb = t_b;
+                             o_free = t_a;
+                             fc = fetch_ctx(kt + 3, o_free, o_b);
                          });
             }
         } else if constexpr (kSubs > 1) {
@@ -630,9 +632,11 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         // wait for all of them.
         constexpr int kRowPitch = kBlk * WN * 2 + 32;
         constexpr int kRegion = kBlk * WM * kRowPitch;
-        constexpr int kPieces = kBlk * WN * 2 / 16;          // 16-byte pieces per row of the sub-tile
+        // A row of the sub-tile goes out as runs of kPieces 16-byte pieces (a row of 96 columns in three runs of 64 bytes).
+        constexpr int kRowPieces = kBlk * WN * 2 / 16, kPieces = 64 % kRowPieces == 0 ? kRowPieces : 4;
+        constexpr int kRuns = kRowPieces / kPieces;
         constexpr int kRowsPerStore = 64 / kPieces;          // rows one store instruction covers
-        static_assert(NW * kRegion <= Cfg::kLdsBytes && 64 % kPieces == 0 && (kBlk * WM) % kRowsPerStore == 0,
+        static_assert(NW * kRegion <= Cfg::kLdsBytes && kRowPieces % kPieces == 0 && (kBlk * WM) % kRowsPerStore == 0,
                       "the waves' staging regions");
         __builtin_amdgcn_s_barrier();  // every wave has fetched its last fragments: LDS is free
         const uint32_t region = static_cast<uint32_t>(wave * kRegion);
@@ -652,17 +656,19 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the region is this wave's own, no barrier
         // piece lane % kPieces of row lane / kPieces + kRowsPerStore * i
         const int piece_c = lane % kPieces, row_c = lane / kPieces;
-        const int n = static_cast<int>(n0) + wave_n * (kBlk * WN) + piece_c * 8;  // N < 2^23
-        const uint32_t g_off = n < static_cast<int>(prm.N)
-                                   ? static_cast<uint32_t>((wave_m * (kBlk * WM) + row_c) * c_row_bytes) + n * 2
-                                   : kPastK;
-        const uint32_t r_addr = region + row_c * kRowPitch + piece_c * 16;
+        const uint32_t row_off = static_cast<uint32_t>((wave_m * (kBlk * WM) + row_c) * c_row_bytes);
         const uint32_t store_rows_bytes = static_cast<uint32_t>(kRowsPerStore * c_row_bytes);
 #pragma unroll
-        for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
-            const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) u32x4 *>(
-                static_cast<uintptr_t>(r_addr + i * kRowsPerStore * kRowPitch));
-            __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, 0);  // (no scalar offset: see st())
+        for (int run = 0; run < kRuns; ++run) {
+            const int n = static_cast<int>(n0) + wave_n * (kBlk * WN) + (run * kPieces + piece_c) * 8;  // N < 2^23
+            const uint32_t g_off = n < static_cast<int>(prm.N) ? row_off + n * 2 : kPastK;
+            const uint32_t r_addr = region + row_c * kRowPitch + (run * kPieces + piece_c) * 16;
+#pragma unroll
+            for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
+                const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) u32x4 *>(
+                    static_cast<uintptr_t>(r_addr + i * kRowsPerStore * kRowPitch));
+                __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, 0);  // (no scalar offset: see st())
+            }
         }
         if constexpr (TRACE) phase[kPhaseStores] += now() - t_stores;
     }
@@ -749,11 +755,10 @@ static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t strea
     const unsigned grid = static_cast<unsigned>(slots < budget ? slots : budget);
 
     if (TRACE && phase_len < int64_t(grid) * Cfg::kWaves * kGemmPhases) return TW_ERR_SHAPE;
+    auto kern = gemm_bf16_kernel<B_KN, WM, WN, STAGES, BK, TRACE>;
     static std::atomic<int> allowed[kMaxDevices];
-    TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(gemm_bf16_kernel<B_KN, WM, WN, STAGES, BK, TRACE>),
-                             Cfg::kLdsBytes, allowed));
-    TW_HIP(launch_kernel(gemm_bf16_kernel<B_KN, WM, WN, STAGES, BK, TRACE>, dim3(grid), dim3(Cfg::kThreads),
-                         Cfg::kLdsBytes, stream, prm));
+    TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), Cfg::kLdsBytes, allowed));
+    TW_HIP(launch_kernel(kern, dim3(grid), dim3(Cfg::kThreads), Cfg::kLdsBytes, stream, prm));
     return TW_OK;
 }
 
@@ -775,54 +780,52 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_oth
     // The part runs this kernel at its power limit (1.2-1.9 GHz on N(0, 0.02^2)
     // operands against 2.4 GHz idle), so what a tile shape is worth is decided by
     // the energy it spends per flop, not by its share of busy matrix-core cycles.
-    enum { kWide, kNarrow, kBig } take = kWide;
-    const int64_t tiles_m = (g.M + BM - 1) / BM;
-    const int64_t wide_tiles = tiles_m * ((g.N + kGemmTileN - 1) / kGemmTileN);
-    if (g.b_layout == TW_B_NK && !beside_other_kernels) {
-        // A product whose 256 x 128 tiles fill at most half of the compute units it may
-        // use is cut into 256 x 64 tiles instead (eight waves of 64 x 32, 3 x 40 KiB of
-        // LDS): twice the workgroups, each with half the work. A tile of that shape
-        // fetches 5/3 of the operand bytes per flop and takes ~0.77 of the wide tile's
-        // time, so it only pays while it brings idle compute units in: 14-23 % faster
-        // on 40 ... 128 wide tiles, 25-40 % slower once the wide tiles already fill
-        // more than half.
-        // A large product takes 256 x 256 tiles: four waves of 128 x 128 (all 512
-        // registers of a lane: 256 accumulators and two fragment sets), K steps of
-        // 64 over two LDS stages of 64 KiB. Two thirds of the operand bytes fetched
-        // per flop and half the LDS reads. (K steps of 32 over four stages of 32 KiB
-        // fit the same LDS and give the loads twice as long to land, but fetch every
-        // 128-byte line of A and B in two halves a K step apart, by which time the
-        // line has left the L1: twice the L2 requests, and 27 % more cycles.)
-        const int64_t big_tiles = tiles_m * ((g.N + 255) / 256);
-        if (2 * wide_tiles <= budget) take = kNarrow;
-        else if (wave_fill(big_tiles, budget) >= wave_fill(wide_tiles, budget) - 0.05) take = kBig;
-    }
+    //
+    // A launch that stands alone takes the grid of tiles with the least estimated time:
+    // 256 x 64 tiles (eight waves of 64 x 32, 3 x 40 KiB of LDS) where the wider ones would leave
+    // compute units idle; 256 x 256 for large products: four waves of 128 x 128 (all 512
+    // registers of a lane: 256 accumulators and two fragment sets), two thirds of the
+    // operand bytes fetched per flop and half the LDS reads of 256 x 128 (K steps of 32 over
+    // four stages of 32 KiB fit the same LDS and give the loads twice as long to land, but
+    // fetch every 128-byte line of A and B in two halves a K step apart, by which time the
+    // line has left the L1: twice the L2 requests, and 27 % more cycles); 256 x 192, four
+    // waves of 128 x 96 in the same schedule, where its tiles fill whole turns of the compute
+    // units and the others do not ([8192 x 8192] x [8192 x 1280]: 158 -> 130 us); and the smaller shapes of
+    // tw_gemm_tile.hip. The costs are us per 64-deep K step of a tile with every compute unit busy,
+    // measured on MI355X; with few of them busy the part clocks up to a quarter higher (the
+    // 256 x 128 tiles, bound by what a unit takes in, gain nothing from that).
+    //
     // Next to other kernels (tw_overlap_launch, the split schedules of
-    // tw_weave_layer) the 256 x 128 tiles are kept: the compute units are not idle
-    // there, the narrow tiles' extra operand traffic competes for the same L1
-    // request slots (a woven layer measured level to 3 % slower with them), and
-    // the 256 x 256 tiles leave no registers for a co-resident workgroup.
-
-    // Where 256-row tiles leave compute units idle or half their rows empty, a smaller
-    // shape takes the product: whichever grid of tiles the estimates put ahead (us per
-    // 64-deep K step of a tile, measured; for the smaller shapes see tw_gemm_tile.hip).
-    // The 256 x 64 and 256 x 256 tiles run at the power limit when every compute unit has
-    // one, and up to a quarter faster when few do.
-    const double fill = take == kBig      ? wave_fill(tiles_m * ((g.N + 255) / 256), budget)
-                        : take == kNarrow ? wave_fill(tiles_m * ((g.N + 63) / 64), budget)
-                                          : 1.0;
-    const double cool = 0.75 + 0.25 * fill;
-    const double us = take == kBig      ? tile_grid_us(g.M, g.N, g.K, BM, 256, 64, 1.38 * cool, budget)
-                      : take == kNarrow ? tile_grid_us(g.M, g.N, g.K, BM, 64, 64, 0.60 * cool, budget)
-                                        : tile_grid_us(g.M, g.N, g.K, BM, kGemmTileN, 64,
-                                                       g.b_layout == TW_B_KN ? 0.83 : 0.735, budget);
+    // tw_weave_layer) the 256 x 128 tiles are kept unless a smaller shape is ahead: the
+    // compute units are not idle there, the narrow tiles' extra operand traffic competes
+    // for the same L1 request slots (a woven layer measured level to 3 % slower with
+    // them), and the larger tiles leave no registers for a co-resident workgroup. (256 x 192
+    // tiles held to 384 registers leave room for one; a woven train took 3.5 % longer with them.)
+    enum { kWide, kNarrow, kBig, kBroad } take = kWide;
+    double us = 1e300;
+    const auto consider = [&](int shape, int cols, double us_per_step, double us_per_turn) {
+        const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + cols - 1) / cols);
+        const double cool = shape == kWide ? 1.0 : 0.78 + 0.22 * wave_fill(tiles, budget);
+        const double t = tile_grid_us(g.M, g.N, g.K, BM, cols, 64, us_per_step * cool, us_per_turn, budget);
+        if (t < us) {
+            us = t;
+            take = static_cast<decltype(take)>(shape);
+        }
+    };
+    consider(kWide, kGemmTileN, g.b_layout == TW_B_KN ? 0.84 : 0.745, 2.7);
+    if (g.b_layout == TW_B_NK && !beside_other_kernels) {
+        consider(kNarrow, 64, 0.60, 2.7);
+        consider(kBig, 256, 1.40, 6.2);
+        consider(kBroad, 192, 1.08, 4.7);
+    }
     double small_us = 0.0;
     const int small = best_small_tile(g, budget, &small_us);
-    if (small >= 0 && small_us < 0.97 * us) return launch_small_tile(g, small, budget, cus, stream);
+    if (small >= 0 && small_us < 0.98 * us) return launch_small_tile(g, small, budget, cus, stream);
     if (g.b_layout == TW_B_KN) return launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
     switch (take) {
     case kNarrow: return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);
     case kBig: return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream);
+    case kBroad: return launch_cfg<false, 8, 6, 2, 64>(g, budget, stream);
     default: return launch_cfg<false, 4, 4, 3, 64>(g, budget, stream);
     }
 }

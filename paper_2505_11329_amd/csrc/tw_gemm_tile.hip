@@ -410,20 +410,21 @@ static const SmallTileShape kSmallTiles[] = {
     {96, 64, 64, 0.255f, 0.280f, launch_tile_t<false, 3, 2, 2, 2, 64, 6>, launch_tile_t<true, 3, 2, 2, 2, 64, 6>},
     {96, 96, 64, 0.338f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6>, nullptr},
     {96, 128, 64, 0.405f, 0.430f, launch_tile_t<false, 3, 4, 2, 2, 64, 5>, launch_tile_t<true, 3, 4, 2, 2, 64, 5>},
-    {192, 64, 64, 0.430f, 0.450f, launch_tile_t<false, 3, 2, 4, 2, 64, 4>, launch_tile_t<true, 3, 2, 4, 2, 64, 4>},
+    {192, 64, 64, 0.430f, 0.500f, launch_tile_t<false, 3, 2, 4, 2, 64, 4>, launch_tile_t<true, 3, 2, 4, 2, 64, 4>},
     {128, 128, 64, 0.530f, 0.550f, launch_tile_t<false, 2, 4, 4, 2, 64, 4>, launch_tile_t<true, 2, 4, 4, 2, 64, 4>},
-    {192, 128, 64, 0.710f, 0.740f, launch_tile_t<false, 3, 4, 4, 2, 64, 3>, launch_tile_t<true, 3, 4, 4, 2, 64, 3>},
+    {192, 128, 64, 0.700f, 0.690f, launch_tile_t<false, 3, 4, 4, 2, 64, 3>, launch_tile_t<true, 3, 4, 4, 2, 64, 3>},
 };
 
-// A grid's tiles are worked off in turns of one to a compute unit. The first turn's
-// pipeline fill and the last one's stores cost any grid about the same; each further
-// turn adds its own.
-double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_step, double us_per_step, int budget)
+// A grid's tiles are worked off in turns of one to a compute unit. The launch, the first
+// turn's pipeline fill and the last one's stores cost any grid about the same; each
+// further turn adds a fill and stores of its own.
+double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_step, double us_per_step,
+                    double us_per_turn, int budget)
 {
     const int64_t tiles = ((M + rows - 1) / rows) * ((N + cols - 1) / cols);
     const int64_t turns = (tiles + budget - 1) / budget;
     const int64_t k_steps = (K + k_step - 1) / k_step * (k_step / 64);
-    return double(turns) * double(k_steps) * us_per_step + double(turns - 1) * 2.7 + 4.0;
+    return double(turns) * double(k_steps) * us_per_step + double(turns - 1) * us_per_turn + 4.0;
 }
 
 int best_small_tile(const tw_gemm_args &g, int budget, double *us)
@@ -433,7 +434,7 @@ int best_small_tile(const tw_gemm_args &g, int budget, double *us)
         const SmallTileShape &t = kSmallTiles[i];
         const float per_step = g.b_layout == TW_B_KN ? t.us_kn : t.us_nk;
         if (per_step == 0.0f) continue;
-        const double est = tile_grid_us(g.M, g.N, g.K, t.rows, t.cols, t.k_step, per_step, budget);
+        const double est = tile_grid_us(g.M, g.N, g.K, t.rows, t.cols, t.k_step, per_step, 2.7, budget);
         if (best < 0 || est < *us) {
             best = i;
             *us = est;

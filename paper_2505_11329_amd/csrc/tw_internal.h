@@ -99,7 +99,8 @@ static constexpr int kGemmTileM = 256, kGemmTileN = 128;
 int tile_group_m(int64_t tiles_m, int tile_rows, int tile_cols, int budget);
 // The tile shapes for products of few tiles (tw_gemm_tile.hip): the estimated time of a
 // grid of tiles, the shape of the least (-1: none for the layout), and its launch.
-double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_step, double us_per_step, int budget);
+double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_step, double us_per_step,
+                    double us_per_turn, int budget);
 int best_small_tile(const tw_gemm_args &g, int budget, double *us);
 tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, hipStream_t stream);
 
