@@ -80,10 +80,11 @@ __device__ __forceinline__ void each_chunk(std::integer_sequence<int, I...>, F &
 }
 
 // How many chunks are kept in flight per thread (register budget: 128 VGPRs).
+// (P = 10 and one chunk a row: two buffers would spill.)
 template <int PT, int VPT>
 constexpr int buffers_in_flight()
 {
-    return (PT == 0) ? 1 : (((PT + 1) * 8 + 12 * VPT <= (VPT == 4 ? 92 : 100)) ? 2 : 1);
+    return (PT == 0) ? 1 : (((PT + 1) * 8 + 12 * VPT <= (VPT == 2 ? 100 : 92)) ? 2 : 1);
 }
 
 template <int PT, int VPT, bool TRACE, bool STREAMED>
@@ -141,16 +142,20 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
         cvalid[j] = v < hv;
         lane_off[j] = static_cast<uint32_t>(row_in_iter * hv + v) * 16u;
         if constexpr (!RELOAD_W) wv[j] = load_w(j);
-        if constexpr (KEEP_W) unpack8(wv[j], wf[j]);
     }
+    // (after the first chunks are requested, so that those do not wait for the weights)
+    auto unpack_w = [&] {
+        if constexpr (KEEP_W) {
+#pragma unroll
+            for (int j = 0; j < VPT; ++j) unpack8(wv[j], wf[j]);
+        }
+    };
 
     const uint32_t stride = gridDim.x;
     const uint32_t n_groups = prm.n_groups;
     const uint32_t group_bytes = prm.group_bytes;
 
-    // Offset of chunk (group, j). A group at or past n_groups lands at or past
-    // n_bytes (the host keeps n_bytes + 2 * stride * group_bytes below 2^32), so
-    // prefetching past the end reads zeros and never needs a branch.
+    // Offset of chunk (group, j); rows past the end of the last group lie past n_bytes.
     auto chunk_off = [&](uint32_t group, int j) -> uint32_t {
         return cvalid[j] ? lane_off[j] + group * group_bytes : kOutOfRange;
     };
@@ -195,73 +200,97 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
 
     // Chunks are numbered q = trip * VPT + j; trip t handles row group
     // blockIdx.x + t * gridDim.x. NB chunk buffers rotate, chunk q sits in buffer
-    // q % NB; a loop body covers a multiple of NB chunks (two trips when VPT == 1).
-    constexpr int TRIPS = (VPT == 1 && NB == 2) ? 2 : 1;
+    // q % NB and is refilled with chunk q + NB as soon as it has been summed.
     Chunk<PT> buf[NB];
-    if constexpr (NB == 2) {
-        if constexpr (VPT == 1) {
-            issue(buf[0], chunk_off(blockIdx.x, 0));
-            issue(buf[1], chunk_off(blockIdx.x + stride, 0));
+    int parity = 0;
+    // One trip, its first chunk in buffer FIRST. MORE: the row group that the refills past
+    // this row reach into exists. (A compile-time choice, hence the copies of the trip below: a
+    // load past the end is dropped by the range check but still takes its turn in the L1's
+    // request queue, and the last trips have all of them. With such loads, and the weights
+    // waited for ahead of the first chunk, 64 rows of 4096 elements, P = 8, on 64 compute units
+    // took 8.5 us and take 5.7; 256 rows of 2048 9.0 -> 5.9; 64 rows of 16384 10.5 -> 9.2.)
+    auto trip = [&](uint32_t group, auto first_tag, auto more_tag) {
+        constexpr int FIRST = decltype(first_tag)::value;
+        constexpr bool MORE = decltype(more_tag)::value;
+        float x[VPT][8];
+        float ss = 0.0f;
+        each_chunk(std::make_integer_sequence<int, VPT>{}, [&](auto j_tag) {
+            constexpr int j = decltype(j_tag)::value;
+            Chunk<PT> &b = buf[(FIRST + j) % NB];
+            const uint32_t off = chunk_off(group, j);
+            reduce_chunk(b, off, x[j]);
+            constexpr int nj = (j + NB) % VPT;
+            if constexpr (j + NB < VPT) issue(b, chunk_off(group, nj));
+            else if constexpr (MORE) issue(b, chunk_off(group + (VPT == 1 ? NB : 1) * stride, nj));
+            if constexpr (!LATE_RES) st(r_res_out, off, pack8(x[j]), streamed);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ss = __builtin_fmaf(x[j][e], x[j][e], ss);
+        });
+
+        // Row sum of squares: the row's lanes inside this wave, then (rows
+        // wider than a wave) the row's waves through LDS.
+        ss = wpr ? group_sum(ss, 6) : group_sum(ss, tpr_log2);
+        if (wpr) {
+            // the row's wave sums, padded with zeros to 16, through a 16-lane butterfly
+            if (lane == 0) s_wave_sum[parity][wave] = ss;
+            __syncthreads();
+            const int k = lane & 15;
+            const float part = k < wpr ? s_wave_sum[parity][row_in_iter * wpr + k] : 0.0f;
+            ss = group_sum(part, 4);
+            parity ^= 1;
+        }
+        const float s = rsqrtf(ss * prm.inv_h + prm.eps);
+
+#pragma unroll
+        for (int j = 0; j < VPT; ++j) {
+            float y[8];
+            if constexpr (KEEP_W) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[e] = (x[j][e] * s) * wf[j][e];
+            } else {
+                float w[8];
+                if constexpr (RELOAD_W) unpack8(load_w(j), w);
+                else unpack8(wv[j], w);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[e] = (x[j][e] * s) * w[e];
+            }
+            if constexpr (LATE_RES) st(r_res_out, chunk_off(group, j), pack8(x[j]), streamed);
+            st(r_out, chunk_off(group, j), pack8(y), streamed);
+        }
+    };
+
+    using Zero = std::integral_constant<int, 0>;
+    using One = std::integral_constant<int, 1>;
+    uint32_t group = blockIdx.x;  // (the grid has at most n_groups workgroups)
+    if constexpr (VPT == 1 && NB == 2) {
+        // two trips ahead: the buffers alternate from trip to trip
+        issue(buf[0], chunk_off(group, 0));
+        if (group + stride < n_groups) {
+            issue(buf[1], chunk_off(group + stride, 0));
+            unpack_w();
+            while (group + 2 * stride < n_groups) {
+                trip(group, Zero{}, std::true_type{});
+                group += stride;
+                if (group + 2 * stride >= n_groups) {
+                    trip(group, One{}, std::false_type{});
+                    trip(group + stride, Zero{}, std::false_type{});
+                    return;
+                }
+                trip(group, One{}, std::true_type{});
+                group += stride;
+            }
+            trip(group, Zero{}, std::false_type{});
+            trip(group + stride, One{}, std::false_type{});
         } else {
-            issue(buf[0], chunk_off(blockIdx.x, 0));
-            issue(buf[1], chunk_off(blockIdx.x, 1));
+            unpack_w();
+            trip(group, Zero{}, std::false_type{});
         }
     } else {
-        issue(buf[0], chunk_off(blockIdx.x, 0));
-    }
-
-    int parity = 0;
-    for (uint32_t g0 = blockIdx.x; g0 < n_groups; g0 += stride * TRIPS) {
-#pragma unroll
-        for (int t = 0; t < TRIPS; ++t) {
-            const uint32_t group = g0 + t * stride;
-            float x[VPT][8];
-            float ss = 0.0f;
-#pragma unroll
-            for (int j = 0; j < VPT; ++j) {
-                Chunk<PT> &b = buf[(t * VPT + j) % NB];
-                const uint32_t off = chunk_off(group, j);
-                reduce_chunk(b, off, x[j]);
-                // refill this buffer with chunk q + NB
-                const int nj = (j + NB) % VPT;
-                const uint32_t ng = (VPT == 1) ? group + NB * stride : (j + NB >= VPT ? group + stride : group);
-                issue(b, chunk_off(ng, nj));
-                if constexpr (!LATE_RES) st(r_res_out, off, pack8(x[j]), streamed);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ss = __builtin_fmaf(x[j][e], x[j][e], ss);
-            }
-
-            // Row sum of squares: the row's lanes inside this wave, then (rows
-            // wider than a wave) the row's waves through LDS.
-            ss = wpr ? group_sum(ss, 6) : group_sum(ss, tpr_log2);
-            if (wpr) {
-                // the row's wave sums, padded with zeros to 16, through a 16-lane butterfly
-                if (lane == 0) s_wave_sum[parity][wave] = ss;
-                __syncthreads();
-                const int k = lane & 15;
-                const float part = k < wpr ? s_wave_sum[parity][row_in_iter * wpr + k] : 0.0f;
-                ss = group_sum(part, 4);
-                parity ^= 1;
-            }
-            const float s = rsqrtf(ss * prm.inv_h + prm.eps);
-
-#pragma unroll
-            for (int j = 0; j < VPT; ++j) {
-                float y[8];
-                if constexpr (KEEP_W) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) y[e] = (x[j][e] * s) * wf[j][e];
-                } else {
-                    float w[8];
-                    if constexpr (RELOAD_W) unpack8(load_w(j), w);
-                    else unpack8(wv[j], w);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) y[e] = (x[j][e] * s) * w[e];
-                }
-                if constexpr (LATE_RES) st(r_res_out, chunk_off(group, j), pack8(x[j]), streamed);
-                st(r_out, chunk_off(group, j), pack8(y), streamed);
-            }
-        }
+        issue(buf[0], chunk_off(group, 0));
+        if constexpr (NB == 2) issue(buf[1], chunk_off(group, 1));
+        unpack_w();
+        for (; group + stride < n_groups; group += stride) trip(group, Zero{}, std::true_type{});
+        trip(group, Zero{}, std::false_type{});
     }
 }
 
@@ -774,7 +803,7 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
                    grid == n_groups && n_groups <= cus && n_rows * row_bytes * (a.P + 1) <= kDeepInputBytes;
         } else {
             grid = fused_grid_size(n_rows, g, budget);
-            if (grid > 1024) return TW_ERR_UNSUPPORTED;  // offset arithmetic in the kernel assumes this
+            if (grid > 1024) return TW_ERR_UNSUPPORTED;  // (no device has as many compute units)
         }
         if (trace && hw_ids_len < grid) return TW_ERR_SHAPE;
 
