@@ -12,9 +12,12 @@ PYMODULE = os.path.join(HERE, "_twpy" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["tw_host.hip", "tw_fused.hip", "tw_unfused.hip", "tw_gemm.hip", "tw_gemm_tile.hip", "tw_probe.hip"]
 
 # Packed fp32 VALU instructions are switched off for every kernel (the compiler
-# would otherwise form them from plain float code).
+# would otherwise form them from plain float code). Kernel arguments that stand ahead of the
+# first struct arrive in scalar registers with the wave, as many as fit (14), instead of being
+# fetched from memory by its first instructions.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+               "-mllvm", "-amdgpu-kernarg-preload-count=14",
                "-Wall", "-Wno-unused-command-line-argument"]
 
 

@@ -95,17 +95,6 @@ struct TileCfg {
     static constexpr int kLdsBytes = kRing ? kRingBOffset + 2 * kStageBBytes : STAGES * kStageBytes;
 };
 
-struct GemmParams {
-    const char *A;
-    const char *B;
-    char *C;
-    long long M, N, K;
-    int tiles_m, tiles_n;
-    int group_m;        // tile rows per block of the tile ordering
-    int tiles_per_xcd;  // ceil(tiles / 8)
-    unsigned long long *phase_cycles;  // tracing variant only: kGemmPhases counters per wave
-};
-
 // Byte offset inside a stage's A (or B) area of the 16-byte piece c of row r,
 // rows of BK_ bf16, with the piece index xor-swizzled so that an MFMA operand
 // fetch (lane l reads piece l / 16 of row l % 16) is free of bank conflicts. A
@@ -194,8 +183,14 @@ __device__ __forceinline__ void wait_lgkm(Frags<B_KN, WM, WN> &f)
 // its end (tw_gemm_bf16_traced). Reading the clock costs a scalar memory read and
 // a wait for it each time, so the traced kernel is a few percent slower than the
 // plain one and its figures are for comparing phases, not for the total.
+// Arguments as of gemm_tile_kernel; group_m: tile rows per block of the tile ordering;
+// tiles_per_xcd: ceil(tiles / 8); phase_cycles: tracing variant only, kGemmPhases counters
+// per wave. (The step of the walk over tiles is gridDim.x: the same number as an argument
+// made every launch of this kernel 0.4 us slower.)
 template <bool B_KN, int WM, int WN, int STAGES, int BK, bool TRACE = false>
-__global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(const GemmParams prm)
+__global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
+    const char *A, const char *B, char *C, int N, int K, int tiles_m, int tiles_n, int last_rows, int group_m,
+    int tiles_per_xcd, unsigned long long *phase_cycles)
 {
     // The body is for the device pass only: the host pass needs the launch stub,
     // and silently drops it when it cannot make sense of the target-specific
@@ -238,14 +233,14 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
     const int l15 = lane & 15;   // the lane's row (A) or column (B) inside a block
     const int lgrp = lane >> 4;  // its group of eight k inside the MFMA's 32
 
-    const long long row_bytes = prm.K * 2;      // of A, and of B when it is stored [N x K]
-    const long long bkn_row_bytes = prm.N * 2;  // of B when it is stored [K x N]
+    const long long row_bytes = K * 2ll;      // of A, and of B when it is stored [N x K]
+    const long long bkn_row_bytes = N * 2ll;  // of B when it is stored [K x N]
     // An offset that is out of range whatever scalar offset (< 2^31) is added to it,
     // without wrapping: a tile's descriptor covers at most 256 rows of 2^23 bytes.
     constexpr uint32_t kPastK = 0x80000000u;
     // (at least one: with K = 0 it loads nothing but zeros)
-    const int k_tiles = prm.K > 0 ? static_cast<int>((prm.K + BK - 1) / BK) : 1;
-    const int total_tiles = prm.tiles_m * prm.tiles_n;
+    const int k_tiles = K > 0 ? (K + BK - 1) / BK : 1;
+    const int total_tiles = tiles_m * tiles_n;
 
     // global -> LDS duty: wave instruction i of this wave fills slots
     // [(i * NW + wave) * 64, +64); this lane's slot inside a line and the row and
@@ -297,21 +292,21 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
     using F = Frags<B_KN, WM, WN>;
     constexpr int kFragReads = F::kReads;  // LDS reads of one sub-step: what read_one issues and wait_lgkm names
 
-    for (int w = blockIdx.x; w < prm.tiles_per_xcd * kXcds; w += gridDim.x) {
+    for (int w = blockIdx.x; w < tiles_per_xcd * kXcds; w += gridDim.x) {
         const int slot_w = w / kXcds;
-        const int lin = (w % kXcds) * prm.tiles_per_xcd + slot_w;
+        const int lin = (w % kXcds) * tiles_per_xcd + slot_w;
         if (lin >= total_tiles) continue;
-        const TileAt at = tile_at(lin, prm.tiles_m, prm.tiles_n, prm.group_m);
+        const TileAt at = tile_at(lin, tiles_m, tiles_n, group_m);
         const int tm = at.m, tn = at.n;
 
         unsigned long long t_tile = 0;
         if constexpr (TRACE) t_tile = now();
         const long long m0 = static_cast<long long>(tm) * BM;
-        const long long n0 = static_cast<long long>(tn) * BN;
-        const int rows_a = static_cast<int>(min(static_cast<long long>(BM), prm.M - m0));
-        const int rows_b = static_cast<int>(min(static_cast<long long>(BN), prm.N - n0));
-        const __amdgpu_buffer_rsrc_t ra = make_rsrc(prm.A + m0 * row_bytes, static_cast<uint32_t>(rows_a * row_bytes));
-        const __amdgpu_buffer_rsrc_t rb = make_rsrc(prm.B + n0 * row_bytes, static_cast<uint32_t>(rows_b * row_bytes));
+        const int n0 = tn * BN;
+        const int rows_a = at.m == tiles_m - 1 ? last_rows : BM;
+        const int rows_b = min(BN, N - n0);
+        const __amdgpu_buffer_rsrc_t ra = make_rsrc(A + m0 * row_bytes, static_cast<uint32_t>(rows_a * row_bytes));
+        const __amdgpu_buffer_rsrc_t rb = make_rsrc(B + n0 * row_bytes, static_cast<uint32_t>(rows_b * row_bytes));
 
         f32x4 acc[WN][WM];
 #pragma unroll
@@ -355,11 +350,11 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         auto fetch_ctx = [&](int kt, uint32_t area_a, uint32_t area_b) {
             FetchCtx c;
             const int k = kt * BK + piece * 8;  // K < 2^23, K steps run two past it at most
-            c.voff = k < static_cast<int>(prm.K) ? lane_off + static_cast<uint32_t>(kt) * (BK * 2) : kPastK;
+            c.voff = k < K ? lane_off + static_cast<uint32_t>(kt) * (BK * 2) : kPastK;
             c.sa = (lds_char_ptr_t)(lds + area_a);
             c.sb = (lds_char_ptr_t)(lds + area_b);
             const long long k0 = static_cast<long long>(kt) * BK;
-            const long long k_left = prm.K - k0;
+            const long long k_left = K - k0;
             const int rows_k = static_cast<int>(k_left < 0 ? 0 : (k_left > BK ? BK : k_left));
             c.bk_off = (k_left > 0 ? k0 : 0) * bkn_row_bytes;
             c.bk_len = static_cast<uint32_t>(rows_k * bkn_row_bytes);
@@ -380,12 +375,12 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
                 // rows k0 .. k0+63 of B through a descriptor of their own: rows past K
                 // fall outside it, columns past N are redirected out of range
                 const int i = idx - A_LOADS;
-                const __amdgpu_buffer_rsrc_t rbk = make_rsrc(prm.B + c.bk_off, c.bk_len);
-                const long long n = n0 + bkn_piece * 8;
+                const __amdgpu_buffer_rsrc_t rbk = make_rsrc(B + c.bk_off, c.bk_len);
+                const int n = n0 + bkn_piece * 8;
                 const uint32_t off = static_cast<uint32_t>((bkn_row_lo + 4 * NW * i) * bkn_row_bytes + n * 2);
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     rbk, (lds_ptr_t)(c.sb + (i * NW + wave) * 1024), 16,
-                    n < prm.N ? off : kOutOfRange, 0, 0, 0);
+                    n < N ? off : kOutOfRange, 0, 0, 0);
             }
         };
         auto stage_ctx = [&](int kt, int stage) {
@@ -619,8 +614,8 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
 
         // Stores. The view of C covers the tile's rows: rows past M are dropped by the range
         // check, which counts the scalar offset (the rows of the store instruction) too.
-        const long long c_row_bytes = prm.N * 2;
-        const __amdgpu_buffer_rsrc_t rc = make_rsrc(prm.C + m0 * c_row_bytes, static_cast<uint32_t>(rows_a * c_row_bytes));
+        const long long c_row_bytes = N * 2ll;
+        const __amdgpu_buffer_rsrc_t rc = make_rsrc(C + m0 * c_row_bytes, static_cast<uint32_t>(rows_a * c_row_bytes));
         // The tile goes out through LDS (idle at this point; the next tile refills it):
         // each wave writes its bf16 results into a region of its own, rows padded by 32
         // bytes, and reads them back as 16-byte pieces, so that a store instruction
@@ -660,8 +655,8 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         const uint32_t store_rows_bytes = static_cast<uint32_t>(kRowsPerStore * c_row_bytes);
 #pragma unroll
         for (int run = 0; run < kRuns; ++run) {
-            const int n = static_cast<int>(n0) + wave_n * (kBlk * WN) + (run * kPieces + piece_c) * 8;  // N < 2^23
-            const uint32_t g_off = n < static_cast<int>(prm.N) ? row_off + n * 2 : kPastK;
+            const int n = n0 + wave_n * (kBlk * WN) + (run * kPieces + piece_c) * 8;
+            const uint32_t g_off = n < N ? row_off + n * 2 : kPastK;
             const uint32_t r_addr = region + row_c * kRowPitch + (run * kPieces + piece_c) * 16;
 #pragma unroll
             for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
@@ -675,12 +670,10 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
     if constexpr (TRACE) {
         phase[kPhaseTotal] = now() - t_kernel;
         if (lane == 0) {
-            unsigned long long *dst = prm.phase_cycles + (static_cast<size_t>(blockIdx.x) * NW + wave) * kGemmPhases;
+            unsigned long long *dst = phase_cycles + (static_cast<size_t>(blockIdx.x) * NW + wave) * kGemmPhases;
             for (int i = 0; i < kGemmPhases; ++i) dst[i] = phase[i];
         }
     }
-#else
-    (void)prm;
 #endif
 }
 
@@ -735,30 +728,21 @@ static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t strea
 {
     using Cfg = TileCfg<WM, WN, STAGES, BK>;
     constexpr int BN = Cfg::kBN;
-    GemmParams prm;
-    prm.A = static_cast<const char *>(g.A);
-    prm.B = static_cast<const char *>(g.B);
-    prm.C = static_cast<char *>(g.C);
-    prm.M = g.M;
-    prm.N = g.N;
-    prm.K = g.K;
-    prm.phase_cycles = phase_cycles;
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
-    prm.tiles_m = static_cast<int>(tiles_m);
-    prm.tiles_n = static_cast<int>(tiles_n);
-    const int64_t total = tiles_m * tiles_n;
-    prm.tiles_per_xcd = static_cast<int>((total + kXcds - 1) / kXcds);
-    prm.group_m = tile_group_m(tiles_m, BM, BN, budget);
-
-    const int64_t slots = int64_t(prm.tiles_per_xcd) * kXcds;
+    const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
+    const int64_t slots = int64_t(tiles_per_xcd) * kXcds;
     const unsigned grid = static_cast<unsigned>(slots < budget ? slots : budget);
 
     if (TRACE && phase_len < int64_t(grid) * Cfg::kWaves * kGemmPhases) return TW_ERR_SHAPE;
     auto kern = gemm_bf16_kernel<B_KN, WM, WN, STAGES, BK, TRACE>;
     static std::atomic<int> allowed[kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), Cfg::kLdsBytes, allowed));
-    TW_HIP(launch_kernel(kern, dim3(grid), dim3(Cfg::kThreads), Cfg::kLdsBytes, stream, prm));
+    TW_HIP(launch_kernel(kern, dim3(grid), dim3(Cfg::kThreads), Cfg::kLdsBytes, stream,
+                         static_cast<const char *>(g.A), static_cast<const char *>(g.B), static_cast<char *>(g.C),
+                         static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
+                         static_cast<int>(tiles_n), static_cast<int>(g.M - (tiles_m - 1) * BM),
+                         tile_group_m(tiles_m, BM, BN, budget), tiles_per_xcd, phase_cycles));
     return TW_OK;
 }
 

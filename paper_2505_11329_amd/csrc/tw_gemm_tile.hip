@@ -39,16 +39,6 @@
 
 namespace tw {
 
-struct TileParams {
-    const char *A;
-    const char *B;
-    char *C;
-    long long M, N, K;
-    int tiles_m, tiles_n;
-    int group_m;
-    int tiles_per_xcd;
-};
-
 template <int WM, int WN, int WVM, int WVN, int BK, int S>
 struct SmallTile {
     static constexpr int kCompute = WVM * WVN;                 // waves that own outputs
@@ -95,8 +85,16 @@ struct StageFrags {
     u32x2 blo[B_KN ? SUBS : 1][B_KN ? WN : 1], bhi[B_KN ? SUBS : 1][B_KN ? WN : 1];
 };
 
+// The arguments are scalars, not a struct: 13 scalar registers' worth, which the wave finds
+// loaded when it starts (see the compiler flags), where fetching them was a round trip to
+// memory ahead of everything else. Also ahead of the first load stands only what it needs:
+// no division that tile_at can spare, the fragment addresses later. (16 rows, K = 1024, N =
+// 8192: 5.6 -> 5.1 us; K = 8192, N = 3584: 13.7 -> 13.2; 512 x 4096 x 2048: 15.0 -> 14.7.)
+// last_rows: rows of A in the last row of tiles.
 template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, bool STREAM_B>
-__global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_tile_kernel(const TileParams prm)
+__global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_tile_kernel(
+    const char *A, const char *B, char *C, int N, int K, int tiles_m, int tiles_n, int last_rows, int group_m,
+    int tiles_per_xcd)
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // as in tw_gemm.hip: the host pass needs the launch stub only
     using T = SmallTile<WM, WN, WVM, WVN, BK, S>;
@@ -108,11 +106,10 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l15 = lane & 15, lgrp = lane >> 4;
     const bool computes = wave < T::kCompute;
     const int wave_m = computes ? wave / WVN : 0, wave_n = computes ? wave % WVN : 0;
-    const long long row_bytes = prm.K * 2, bkn_row_bytes = prm.N * 2;
-    const int k_tiles = prm.K > 0 ? static_cast<int>((prm.K + BK - 1) / BK) : 1;
+    const long long row_bytes = K * 2ll, bkn_row_bytes = N * 2ll;
+    const int k_tiles = K > 0 ? (K + BK - 1) / BK : 1;
     constexpr uint32_t kPastK = 0x80000000u;  // out of range whatever scalar offset (< 2^31) is added
 
     // Load duty: instruction i of this wave fills the 64 pieces from (i * NW + wave) * 64 on.
@@ -130,35 +127,19 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
     const int kn_row = wave * kKnInstrRows + lane / kKnPieces;  // + i * NW * kKnInstrRows
     const int kn_piece = (lane % kKnPieces) ^ (kn_swizzle<BN>(kn_row) << 1);
 
-    // fragment addresses inside a stage; block i lies 16 rows further on
-    uint32_t fa[SUBS], fb[SUBS], fbkn[B_KN ? WN : 1];
-#pragma unroll
-    for (int s = 0; s < SUBS; ++s) {
-        const int at = swizzled<BK>(l15, s * 4 + lgrp) * 16;
-        fa[s] = (wave_m * kBlk * WM + l15) * kRowBytes + at;
-        fb[s] = T::kABytes + (wave_n * kBlk * WN + l15) * kRowBytes + at;
-    }
-    if constexpr (B_KN) {
-        const int a4 = l15 & 3, row = lgrp * 8 + (l15 >> 2);  // see lds_read_tr8
-#pragma unroll
-        for (int i = 0; i < WN; ++i) {
-            const int col = wave_n * kBlk * WN + i * kBlk + 4 * a4;
-            fbkn[i] = T::kABytes + row * (BN * 2) + (((col >> 3) ^ (kn_swizzle<BN>(row) << 1)) << 4) + (col & 7) * 2;
-        }
-    }
-
-    for (int w = blockIdx.x; w < prm.tiles_per_xcd * kXcds; w += gridDim.x) {
-        const int lin = (w % kXcds) * prm.tiles_per_xcd + w / kXcds;
-        if (lin >= prm.tiles_m * prm.tiles_n) continue;
-        const TileAt at = tile_at(lin, prm.tiles_m, prm.tiles_n, prm.group_m);
-        const long long m0 = static_cast<long long>(at.m) * BM, n0 = static_cast<long long>(at.n) * BN;
-        const int rows_a = static_cast<int>(min(static_cast<long long>(BM), prm.M - m0));
-        const int rows_b = static_cast<int>(min(static_cast<long long>(BN), prm.N - n0));
-        const __amdgpu_buffer_rsrc_t ra = make_rsrc(prm.A + m0 * row_bytes, static_cast<uint32_t>(rows_a * row_bytes));
-        const __amdgpu_buffer_rsrc_t rb = make_rsrc(prm.B + n0 * row_bytes, static_cast<uint32_t>(rows_b * row_bytes));
+    for (int w = blockIdx.x; w < tiles_per_xcd * kXcds; w += gridDim.x) {
+        const int lin = (w % kXcds) * tiles_per_xcd + w / kXcds;
+        if (lin >= tiles_m * tiles_n) continue;
+        const TileAt at = tile_at(lin, tiles_m, tiles_n, group_m);
+        const long long m0 = static_cast<long long>(at.m) * BM;
+        const int n0 = at.n * BN;
+        const int rows_a = at.m == tiles_m - 1 ? last_rows : BM;
+        const int rows_b = min(BN, N - n0);
+        const __amdgpu_buffer_rsrc_t ra = make_rsrc(A + m0 * row_bytes, static_cast<uint32_t>(rows_a * row_bytes));
+        const __amdgpu_buffer_rsrc_t rb = make_rsrc(B + n0 * row_bytes, static_cast<uint32_t>(rows_b * row_bytes));
         const uint32_t load_row_off = static_cast<uint32_t>(load_row * row_bytes);
         const uint32_t step_bytes = static_cast<uint32_t>(kStepRows * row_bytes);
-        const uint32_t kn_off = n0 + kn_piece * 8 < prm.N
+        const uint32_t kn_off = n0 + kn_piece * 8 < N
                                     ? static_cast<uint32_t>(kn_row * bkn_row_bytes + (n0 + kn_piece * 8) * 2)
                                     : kPastK;
         const uint32_t kn_step_bytes = static_cast<uint32_t>(NW * kKnInstrRows * bkn_row_bytes);
@@ -181,13 +162,13 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
 #pragma unroll
             for (int q = 0; q < kRepeat; ++q) {
                 const int k = kt * BK + load_piece[q] * 8;  // K <= 2^22, K steps run S past it at most
-                c.off[q] = k < static_cast<int>(prm.K) ? load_row_off + static_cast<uint32_t>(k) * 2 : kPastK;
+                c.off[q] = k < K ? load_row_off + static_cast<uint32_t>(k) * 2 : kPastK;
             }
             if constexpr (B_KN) {
                 // rows k0 ... of B through a descriptor of their own: rows past K lie outside it
-                const long long k0 = static_cast<long long>(kt) * BK, left = prm.K - k0;
+                const long long k0 = static_cast<long long>(kt) * BK, left = K - k0;
                 const int rows_k = static_cast<int>(left < 0 ? 0 : left > BK ? BK : left);
-                c.rbk = make_rsrc(prm.B + (left > 0 ? k0 : 0) * bkn_row_bytes, static_cast<uint32_t>(rows_k * bkn_row_bytes));
+                c.rbk = make_rsrc(B + (left > 0 ? k0 : 0) * bkn_row_bytes, static_cast<uint32_t>(rows_k * bkn_row_bytes));
             } else {
                 c.rbk = rb;
             }
@@ -206,6 +187,7 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
             }
         };
         auto fetch = [&](const Fetch &c) { static_for<T::kLoads>([&](auto i) { fetch_one(c, i); }); };
+        uint32_t fa[SUBS], fb[SUBS], fbkn[B_KN ? WN : 1];  // see below
         using F = StageFrags<B_KN, WM, WN, SUBS>;
         constexpr int kPerSub = WM + (B_KN ? 2 * WN : WN);
         constexpr int kReads = SUBS * kPerSub, kMma = SUBS * WM * WN;
@@ -274,6 +256,26 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         static_for<S>([&](auto s) { fetch(fetch_ctx(decltype(s)::value, decltype(s)::value)); });
+        // Fragment addresses inside a stage; block i lies 16 rows further on. (The lane passes
+        // through an asm statement so that all this is computed here, the first loads on their
+        // way; with [K x N] weights that made the K loop of 192 x 128 tiles 1 % slower.)
+        int at_lane = lane;
+        if constexpr (!B_KN) asm volatile("" : "+v"(at_lane));
+        const int l15 = at_lane & 15, lgrp = at_lane >> 4;
+#pragma unroll
+        for (int s = 0; s < SUBS; ++s) {
+            const int at = swizzled<BK>(l15, s * 4 + lgrp) * 16;
+            fa[s] = (wave_m * kBlk * WM + l15) * kRowBytes + at;
+            fb[s] = T::kABytes + (wave_n * kBlk * WN + l15) * kRowBytes + at;
+        }
+        if constexpr (B_KN) {
+            const int a4 = l15 & 3, row = lgrp * 8 + (l15 >> 2);  // see lds_read_tr8
+#pragma unroll
+            for (int i = 0; i < WN; ++i) {
+                const int col = wave_n * kBlk * WN + i * kBlk + 4 * a4;
+                fbkn[i] = T::kABytes + row * (BN * 2) + (((col >> 3) ^ (kn_swizzle<BN>(row) << 1)) << 4) + (col & 7) * 2;
+            }
+        }
         wait_vm(std::integral_constant<int, (S - 1) * T::kLoads>{});
         F f0, f1;
         if (computes) read_all(f0, 0);
@@ -296,8 +298,8 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
         // A lane holds row l15 and four consecutive columns of each block. Rows past M and
         // columns past N are dropped by the range check.
-        const long long c_row_bytes = prm.N * 2;
-        const __amdgpu_buffer_rsrc_t rc = make_rsrc(prm.C + m0 * c_row_bytes, static_cast<uint32_t>(rows_a * c_row_bytes));
+        const long long c_row_bytes = N * 2;
+        const __amdgpu_buffer_rsrc_t rc = make_rsrc(C + m0 * c_row_bytes, static_cast<uint32_t>(rows_a * c_row_bytes));
         if constexpr (T::kStagedStores) {
             // Through LDS, each wave in a region of its own, rows padded by 32 bytes, so that a
             // store covers whole rows of the wave's outputs (as in tw_gemm.hip).
@@ -320,9 +322,9 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
                 }
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
             const int piece_c = lane % kPieces, row_c = lane / kPieces;
-            const long long n = n0 + wave_n * (kBlk * WN) + piece_c * 8;
+            const int n = n0 + wave_n * (kBlk * WN) + piece_c * 8;
             const uint32_t g_off =
-                n < prm.N ? static_cast<uint32_t>((wave_m * (kBlk * WM) + row_c) * c_row_bytes + n * 2) : kPastK;
+                n < N ? static_cast<uint32_t>((wave_m * (kBlk * WM) + row_c) * c_row_bytes + n * 2) : kPastK;
             const uint32_t r_addr = region + row_c * kRowPitch + piece_c * 16;
             const uint32_t store_rows_bytes = static_cast<uint32_t>(kRowsPerStore * c_row_bytes);
 #pragma unroll
@@ -334,21 +336,19 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
         } else if (computes) {
 #pragma unroll
             for (int j = 0; j < WN; ++j) {
-                const long long n = n0 + (wave_n * WN + j) * kBlk + lgrp * 4;
+                const int n = n0 + (wave_n * WN + j) * kBlk + lgrp * 4;
 #pragma unroll
                 for (int i = 0; i < WM; ++i) {
                     u32x2 v;
                     v.x = pack_bf16x2(acc[i][j][0], acc[i][j][1]);
                     v.y = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
                     const uint32_t off =
-                        n < prm.N ? static_cast<uint32_t>(((wave_m * WM + i) * kBlk + l15) * c_row_bytes + n * 2) : kPastK;
+                        n < N ? static_cast<uint32_t>(((wave_m * WM + i) * kBlk + l15) * c_row_bytes + n * 2) : kPastK;
                     __builtin_amdgcn_raw_buffer_store_b64(v, rc, off, 0, 0);
                 }
             }
         }
     }
-#else
-    (void)prm;
 #endif
 }
 
@@ -364,18 +364,8 @@ static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, hipSt
     if constexpr (STREAM_B)
         if (tiles_m > 1) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, false>(g, budget, cus, stream);
     if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
-    TileParams prm;
-    prm.A = static_cast<const char *>(g.A);
-    prm.B = static_cast<const char *>(g.B);
-    prm.C = static_cast<char *>(g.C);
-    prm.M = g.M;
-    prm.N = g.N;
-    prm.K = g.K;
-    prm.tiles_m = static_cast<int>(tiles_m);
-    prm.tiles_n = static_cast<int>(tiles_n);
-    prm.group_m = tile_group_m(tiles_m, T::BM, T::BN, budget);
-    prm.tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
-    const int64_t slots = int64_t(prm.tiles_per_xcd) * kXcds;
+    const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
+    const int64_t slots = int64_t(tiles_per_xcd) * kXcds;
     // The whole device: a workgroup per tile, as many to a compute unit as fit. Under a
     // budget one to a compute unit: more than half of its LDS is asked for.
     constexpr int kAloneBytes = T::kLdsBytes > 81 * 1024 ? T::kLdsBytes : 81 * 1024;
@@ -385,7 +375,11 @@ static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, hipSt
     static std::atomic<int> allowed[kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), kAloneBytes, allowed));
     TW_HIP(launch_kernel(kern, dim3(grid), dim3(64 * T::kWaves),
-                         static_cast<unsigned>(whole ? T::kLdsBytes : kAloneBytes), stream, prm));
+                         static_cast<unsigned>(whole ? T::kLdsBytes : kAloneBytes), stream,
+                         static_cast<const char *>(g.A), static_cast<const char *>(g.B), static_cast<char *>(g.C),
+                         static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
+                         static_cast<int>(tiles_n), static_cast<int>(g.M - (tiles_m - 1) * T::BM),
+                         tile_group_m(tiles_m, T::BM, T::BN, budget), tiles_per_xcd));
     return TW_OK;
 }
 

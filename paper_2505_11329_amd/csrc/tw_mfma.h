@@ -61,12 +61,19 @@ struct TileAt {
 };
 __device__ __forceinline__ TileAt tile_at(int lin, int tiles_m, int tiles_n, int group_m)
 {
-    const int per_group = group_m * tiles_n;
-    const int grp = lin / per_group;
-    const int first_tm = grp * group_m;
+    // (a division by a number that is not a constant is a chain of some forty instructions,
+    // ahead of a tile's first load: branches spare the ones that few rows of tiles do not need)
+    int in_grp = lin, first_tm = 0;
+    if (tiles_m > group_m) {
+        const int per_group = group_m * tiles_n;
+        const int grp = lin / per_group;
+        first_tm = grp * group_m;
+        in_grp = lin - grp * per_group;
+    }
     const int gsz = min(group_m, tiles_m - first_tm);
-    const int in_grp = lin - grp * per_group;
-    return {first_tm + in_grp % gsz, in_grp / gsz};
+    if (gsz == 1) return {first_tm, in_grp};
+    const int n = in_grp / gsz;
+    return {first_tm + in_grp - n * gsz, n};
 }
 
 }  // namespace tw
