@@ -53,6 +53,11 @@ struct SmallTile {
     static_assert(S >= 3 && kLdsBytes <= 160 * 1024, "LDS of one compute unit");
     static_assert(BK == 64 || BK == 128 || BK == 256, "LDS layouts below");
     static constexpr bool kStagedStores = WN == 2 || WN == 4;
+    // Whether the last S steps are compiled without loads. Past the end of K there is nothing to
+    // load, and an out-of-range load takes its turn in the L1's queue like any other: 16 rows,
+    // K = 3584, N = 8192 12.4 -> 12.1 us, 333 rows, K = 8192, N = 3584 38.2 -> 37.5. With three
+    // stages there is little to save, and 192 x 128 tiles came out 1 to 3 % slower.
+    static constexpr bool kTail = S > 3;
 };
 
 // Position of the 16-byte piece c of row r, of the 2 BK bytes a row takes: two rows of
@@ -221,9 +226,10 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
                 }
             }
         };
-        // the matrix instructions of one stage, and between them the reads of the next one's fragments and the loads
-        // of a later stage
-        auto multiply = [&](F &cur, F &nxt, int nxt_slot, const Fetch &c) {
+        // the matrix instructions of one stage, and between them the reads of the next one's fragments and (LOADS)
+        // the loads of a later stage
+        auto multiply = [&](F &cur, F &nxt, int nxt_slot, const Fetch &c, auto loads_tag) {
+            constexpr bool LOADS = decltype(loads_tag)::value;
             const uint32_t base = nxt_slot * T::kStageBytes;
             static_for<kMma>([&](auto m_tag) {
                 constexpr int m = decltype(m_tag)::value, s = m / (WM * WN), j = m % (WM * WN) / WM, i = m % WM;
@@ -241,21 +247,29 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
                     if constexpr (decltype(t)::value * kReadSlots / kReads == m) read_one(nxt, base, t);
                 });
                 static_for<T::kLoads>([&](auto t) {
-                    if constexpr (decltype(t)::value * kMma / T::kLoads == m) fetch_one(c, t);
+                    if constexpr (LOADS && decltype(t)::value * kMma / T::kLoads == m) fetch_one(c, t);
                 });
                 __builtin_amdgcn_sched_barrier(0);
             });
         };
-        auto wait_vm = [&](auto n_tag) {  // at most n of this wave's loads outstanding; then the same for all waves
-            constexpr int n = decltype(n_tag)::value;
-            __builtin_amdgcn_s_waitcnt(((n >> 4) << 14) | 0x0F70 | (n & 15));
+        // Waits until at most the loads of the last `newer` stages are outstanding (any number from LIMIT on: of the
+        // last LIMIT), then for the same of all waves.
+        auto wait_vm = [&](int newer, auto limit_tag) {
+            constexpr int LIMIT = decltype(limit_tag)::value;
+            static_for<LIMIT + 1>([&](auto v) {
+                constexpr int n = (LIMIT - decltype(v)::value) * T::kLoads;
+                if (decltype(v)::value == 0 ? newer >= LIMIT : decltype(v)::value == LIMIT ? newer <= 0 : newer * T::kLoads == n)
+                    __builtin_amdgcn_s_waitcnt(((n >> 4) << 14) | 0x0F70 | (n & 15));
+            });
             __builtin_amdgcn_s_barrier();
         };
 
         // the previous tile's loads have landed and nobody reads LDS any more
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
-        static_for<S>([&](auto s) { fetch(fetch_ctx(decltype(s)::value, decltype(s)::value)); });
+        static_for<S>([&](auto s) {
+            if (!T::kTail || decltype(s)::value < k_tiles) fetch(fetch_ctx(decltype(s)::value, decltype(s)::value));
+        });
         // Fragment addresses inside a stage; block i lies 16 rows further on. (The lane passes
         // through an asm statement so that all this is computed here, the first loads on their
         // way; with [K x N] weights that made the K loop of 192 x 128 tiles 1 % slower.)
@@ -276,26 +290,46 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
                 fbkn[i] = T::kABytes + row * (BN * 2) + (((col >> 3) ^ (kn_swizzle<BN>(row) << 1)) << 4) + (col & 7) * 2;
             }
         }
-        wait_vm(std::integral_constant<int, (S - 1) * T::kLoads>{});
+        wait_vm(T::kTail ? k_tiles - 1 : S, std::integral_constant<int, S - 1>{});
         F f0, f1;
-        if (computes) read_all(f0, 0);
-        int slot = 0;
-        auto step = [&](F &cur, F &nxt, int kt) {
-            if (computes) settle(cur);
-            wait_vm(std::integral_constant<int, (S - 2) * T::kLoads>{});  // stage kt + 1 has landed, stage kt is read
-            const Fetch c = fetch_ctx(kt + S, slot);  // (past the end: out of range, so the counts stay the same)
-            slot = slot + 1 == S ? 0 : slot + 1;
-            __builtin_amdgcn_sched_barrier(0);
-            if (computes) multiply(cur, nxt, slot, c);
-            else fetch(c);
-        };
-        for (int kt = 0; kt < k_tiles; kt += 2) {  // a step past an odd end works on zeros
-            step(f0, f1, kt);
-            step(f1, f0, kt + 1);
+        if (computes) {
+            read_all(f0, 0);
+            settle(f0);
         }
-        // the reads past the end are still in flight, and so are loads into LDS
-        if (computes) settle(f0);
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        int slot = 0, kt = 0;
+        // Step kt, its fragments in cur; those of the next one have arrived in nxt at its end (no read is under way where
+        // the control flow branches or joins). MAIN: stage kt + S is loaded meanwhile.
+        auto step = [&](F &cur, F &nxt, auto main_tag) {
+            constexpr bool MAIN = decltype(main_tag)::value;
+            // stage kt + 1 has landed, stage kt is read
+            wait_vm(MAIN ? S : k_tiles - 2 - kt, std::integral_constant<int, S - 2>{});
+            const Fetch c = fetch_ctx(kt + S, slot);
+            if constexpr (!MAIN)
+                if (kt + S < k_tiles) fetch(c);
+            slot = slot + 1 == S ? 0 : slot + 1;
+            ++kt;
+            __builtin_amdgcn_sched_barrier(0);
+            if (computes) {
+                multiply(cur, nxt, slot, c, main_tag);
+                settle(nxt);
+            } else if constexpr (MAIN) {
+                fetch(c);
+            }
+        };
+        while (kt + (T::kTail ? S + 1 : 0) < k_tiles) {  // (without a tail, a step past an odd end works on zeros)
+            step(f0, f1, std::true_type{});
+            step(f1, f0, std::true_type{});
+        }
+        if constexpr (T::kTail) {
+            for (;;) {
+                step(f0, f1, std::false_type{});
+                if (kt == k_tiles) break;
+                step(f1, f0, std::false_type{});
+                if (kt == k_tiles) break;
+            }
+        } else {
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): loads past the end
+        }
         // A lane holds row l15 and four consecutive columns of each block. Rows past M and
         // columns past N are dropped by the range check.
         const long long c_row_bytes = N * 2;

@@ -116,6 +116,23 @@ def test_gemm_of_few_rows_gives_the_bits_of_the_same_rows_of_a_large_product(tw,
     gemm_check(oracle.bf16_to_f64(want)[ms, ns], ref, K, 0.5, "sampled")
 
 
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("M,N", [(5, 4096), (64, 8192), (130, 3592), (500, 3608)])
+def test_gemm_from_one_k_step_to_past_the_pipeline(tw, torch_cuda, M, N, layout):
+    torch = torch_cuda
+    code = tw.B_NK if layout == "nk" else tw.B_KN
+    for K in (8, 64, 72, 128, 192, 256, 320, 384, 392, 448, 512, 640, 768, 1024, 1032, 1280, 1536, 1800):
+        g = W.make_gemm_inputs(M, K, N, 0.5, seed=M + K, b_layout=layout)
+        A, B = to_gpu(g["A"]), to_gpu(g["B"])
+        big = torch.cat([A, torch.ones((4096 - M, K), dtype=torch.bfloat16, device="cuda:0")])
+        want = to_bits(tw.gemm_bf16(big, B, b_layout=code)[:M])
+        for budget in (0, 7):
+            C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+            tw.gemm_bf16(A, B, C, b_layout=code, cu_budget=budget)
+            torch.cuda.synchronize()
+            assert np.array_equal(to_bits(C), want), "M=%d N=%d K=%d %s budget %d" % (M, N, K, layout, budget)
+
+
 def test_gemm_k_zero_gives_zeros(tw, torch_cuda):
     torch = torch_cuda
     for (M, N, budget) in ((40, 24, 0), (512, 512, 4)):      # the second takes the 256 x 256 tiles
