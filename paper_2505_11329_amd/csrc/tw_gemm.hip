@@ -777,7 +777,10 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_oth
     // units and the others do not ([8192 x 8192] x [8192 x 1280]: 158 -> 130 us); and the smaller shapes of
     // tw_gemm_tile.hip. The costs are us per 64-deep K step of a tile with every compute unit busy,
     // measured on MI355X; with few of them busy the part clocks up to a quarter higher (the
-    // 256 x 128 tiles, bound by what a unit takes in, gain nothing from that).
+    // 256 x 128 tiles, bound by what a unit takes in, gain nothing from that). Each further turn
+    // adds a fill and stores: the costs per turn decide where K is small, and are those that lose
+    // least over 760 products of 100 to 8192 rows, K and N 256 to 8192 (every shape timed: the
+    // choice is 0.5 % off the best on average; 6706 x 3208, K = 280: 29.7 -> 23.8 us).
     //
     // Next to other kernels (tw_overlap_launch, the split schedules of
     // tw_weave_layer) the 256 x 128 tiles are kept unless a smaller shape is ahead: the
@@ -799,8 +802,8 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_oth
     consider(kWide, kGemmTileN, g.b_layout == TW_B_KN ? 0.84 : 0.745, 2.7);
     if (g.b_layout == TW_B_NK && !beside_other_kernels) {
         consider(kNarrow, 64, 0.60, 2.7);
-        consider(kBig, 256, 1.40, 6.2);
-        consider(kBroad, 192, 1.08, 4.7);
+        consider(kBig, 256, 1.40, 7.5);
+        consider(kBroad, 192, 1.08, 6.6);
     }
     double small_us = 0.0;
     const int small = best_small_tile(g, budget, &small_us);

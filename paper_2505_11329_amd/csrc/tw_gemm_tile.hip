@@ -462,7 +462,7 @@ int best_small_tile(const tw_gemm_args &g, int budget, double *us)
         const SmallTileShape &t = kSmallTiles[i];
         const float per_step = g.b_layout == TW_B_KN ? t.us_kn : t.us_nk;
         if (per_step == 0.0f) continue;
-        const double est = tile_grid_us(g.M, g.N, g.K, t.rows, t.cols, t.k_step, per_step, 2.7, budget);
+        const double est = tile_grid_us(g.M, g.N, g.K, t.rows, t.cols, t.k_step, per_step, 3.0, budget);
         if (best < 0 || est < *us) {
             best = i;
             *us = est;
