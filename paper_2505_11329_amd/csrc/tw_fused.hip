@@ -718,6 +718,16 @@ static constexpr bool wide_fits()
     return wide_fits(PT, VPT);
 }
 
+// With more than eight partials the specialised kernels' way to the first load, and to the
+// first request of a row's last partial, is longer (up to sixteen descriptors do not fit the
+// scalar registers); a launch of one row group per workgroup is over before they gain from
+// keeping all loads in flight, and from P = 12 on one of two (64 rows of 4096 elements on 32
+// compute units, P = 12: 7.2 us against 6.3 in the run-time loop; 512 rows 40.8 against 42.8).
+static bool few_trips(int P, int64_t grid, uint32_t n_groups)
+{
+    return P > 8 && n_groups <= grid * (P >= 12 ? 2 : 1);
+}
+
 template <int PT>
 static tw_status launch_vpt(const FusedParams &prm, const FusedGeometry &g, bool trace, bool streamed, int64_t grid,
                             hipStream_t s)
@@ -757,6 +767,11 @@ static bool takes_thin_kernel(int cu_budget, int cus, const FusedGeometry &g, in
     if (cu_budget == TW_CU_SHARED) return true;
     if (resolve_budget(cu_budget, cus) != cus) return false;
     const int q = g.hv > kThinThreads ? (g.hv + kThinThreads - 1) / kThinThreads : 1;
+    // One row to a compute unit, more than eight partials, wide rows: one chunk of registers
+    // after another in a thin workgroup, where the wide kernel's waves have one each (64 rows
+    // of 8192 elements: P = 12 7.8 us against 6.8, P = 16 9.4 against 8.2; from P = 9 to 11 the
+    // small workgroups are ahead above 64 rows).
+    if (P > 8 && q >= 3 && n_rows <= (P >= 12 ? cus : cus / 4)) return false;
     int64_t vectors_per_cu;
     if (g.hv <= 128) vectors_per_cu = int64_t(12) * g.hv;
     else if (P == 1) vectors_per_cu = 5120;
@@ -828,7 +843,7 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
 
         // the run-time loop over P: where no specialised kernel has the registers, or is built to be traced
         const bool traced_p = a.P == 1 || a.P == 2 || a.P == 4 || a.P == 8;
-        const bool any_p = (trace && !traced_p) || (!thin && !wide_fits(a.P, g.vpt));
+        const bool any_p = (trace && !traced_p) || (!thin && (!wide_fits(a.P, g.vpt) || few_trips(a.P, grid, prm.n_groups)));
         if (thin) {
             if (any_p) TW_TRY((launch_thin<0>(prm, tg.q, trace, streamed, false, grid, stream)));
             else
