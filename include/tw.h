@@ -229,11 +229,9 @@ int64_t tw_split_point(int64_t N, int64_t multiple);
  *   cu_budget persistent grid of at most this many workgroups (one per compute
  *             unit); <= 0 or >= the CU count: whole device
  * The result bits depend on A, B and K only: not on the budget, the layout of B,
- * nor on the tile shape the launch picks (256 x 128 outputs per workgroup; 256 x
- * 64 when the wider tiles would fill at most half of the compute units; 256 x
- * 256 for a large product launched on its own, when such tiles fill the compute
- * units about as well; from 16 x 16 to 192 x 128 where those leave compute units
- * idle, as for a few rows or a few hundred). Every output element is the sum of its K / 32 partial
+ * nor on the tile shape the launch picks (from 16 x 16 to 256 x 256 outputs per
+ * workgroup, the one with the least estimated time; next to other kernels 256 x
+ * 128 or smaller). Every output element is the sum of its K / 32 partial
  * dot products of depth 32, accumulated in fp32 in the order of increasing k.
  */
 #define TW_B_NK 0
