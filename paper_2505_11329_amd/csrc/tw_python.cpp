@@ -172,7 +172,25 @@ Ref given_or_new(PyObject *o, const at::Tensor &like, int64_t rows, int64_t cols
     return t;
 }
 
+// The items of a sequence that has a length, as a tuple nobody else can change. Room for the
+// items is made by length, so one that iterates over another number of them is refused.
+Ref items(PyObject *o, const char *name)
+{
+    const Py_ssize_t n = PyObject_Size(o);
+    if (n < 0) fail();
+    Ref t(PySequence_Tuple(o));
+    if (!t.o) fail();
+    if (PyTuple_GET_SIZE(t.o) != n)
+        fail(PyExc_ValueError, "%s has a length of %zd and iterates over %zd", name, n, PyTuple_GET_SIZE(t.o));
+    return t;
+}
+
 // ---- argument structs ----
+
+struct PointerArray {  // the caller's, for the partials' device pointers
+    void **p;
+    size_t capacity;
+};
 
 struct Fused {
     tw_fused_args a;
@@ -187,8 +205,9 @@ struct Fused {
         many.resize(static_cast<size_t>(P));
         return many.data();
     }
+    // given: where the partials' pointers go; without one, into this object
     void fill(PyObject *partials, PyObject *residual, PyObject *weight, PyObject *eps, PyObject *budget, PyObject *o,
-              PyObject *ro, void **ptrs = nullptr)
+              PyObject *ro, const PointerArray *given = nullptr)
     {
         const at::Tensor &res = matrix(residual, "residual", "residual must be [N, H]");
         rows = res.size(0);
@@ -196,12 +215,14 @@ struct Fused {
         if (o == Py_None || ro == Py_None) gpu_tensor(residual, {"residual"});
         out = o == Py_None ? like(res) : given_or_new(o, res, rows, H);
         residual_out = ro == Py_None ? like(res) : given_or_new(ro, res, rows, H);
-        seq = Ref(PySequence_Fast(partials, "partials must be a sequence of tensors"));
-        if (!seq.o) fail();
-        const Py_ssize_t P = PySequence_Fast_GET_SIZE(seq.o);
-        if (!ptrs) ptrs = room(P);
+        seq = items(partials, "partials");
+        const Py_ssize_t P = PyTuple_GET_SIZE(seq.o);
+        if (given && static_cast<size_t>(P) > given->capacity)
+            fail(PyExc_ValueError, "the pointer array has room for %zd of %zd partials",
+                 static_cast<Py_ssize_t>(given->capacity), P);
+        void **ptrs = given ? given->p : room(P);
         for (Py_ssize_t p = 0; p < P; ++p)
-            ptrs[p] = bf16_ptr(PySequence_Fast_GET_ITEM(seq.o, p), {"partials", static_cast<int>(p)}, 2, rows, H);
+            ptrs[p] = bf16_ptr(PyTuple_GET_ITEM(seq.o, p), {"partials", static_cast<int>(p)}, 2, rows, H);
         a.partials = ptrs;
         a.residual = bf16_ptr(residual, {"residual"});
         a.weight = bf16_ptr(weight, {"weight"}, 1, H);
@@ -247,9 +268,9 @@ struct Layer {
     Ref Y;
     void fill(tw_layer_args &l, PyObject *X1, PyObject *W1, PyObject *partials, PyObject *residual, PyObject *weight,
               PyObject *eps, PyObject *W2, PyObject *fused_budget, PyObject *gemm_budget, PyObject *out, PyObject *ro,
-              PyObject *y, PyObject *schedule, void **ptrs = nullptr)
+              PyObject *y, PyObject *schedule, const PointerArray *given = nullptr)
     {
-        f.fill(partials, residual, weight, eps, fused_budget, out, ro, ptrs);
+        f.fill(partials, residual, weight, eps, fused_budget, out, ro, given);
         const int64_t K1 = matrix(X1, "X1", "X1 must be [T, K1]").size(1);
         const int64_t N2 = matrix(W2, "W2", "W2 must be [N2, H]").size(0);
         Y = given_or_new(y, THPVariable_Unpack(residual), f.rows, N2);
@@ -437,10 +458,10 @@ PyObject *py_weave_layer_cuts(PyObject *, PyObject *const *v, Py_ssize_t n)
 {
     return entry("weave_layer_cuts", n, kLayerArgs + 1, [&] {
         LayerCall c(v);
-        Ref seq(PySequence_Fast(v[kLayerArgs], "cuts must be a sequence of rows"));
+        Ref seq(PySequence_Tuple(v[kLayerArgs]));
         if (!seq.o) fail();
-        std::vector<int64_t> cuts(static_cast<size_t>(PySequence_Fast_GET_SIZE(seq.o)));
-        for (size_t i = 0; i < cuts.size(); ++i) cuts[i] = as_int(PySequence_Fast_GET_ITEM(seq.o, i));
+        std::vector<int64_t> cuts(static_cast<size_t>(PyTuple_GET_SIZE(seq.o)));
+        for (size_t i = 0; i < cuts.size(); ++i) cuts[i] = as_int(PyTuple_GET_ITEM(seq.o, i));
         const int n_cuts = static_cast<int>(cuts.size());
         cuts.push_back(0);  // never an empty array
         call("tw_weave_layer_cuts", [&] {
@@ -469,13 +490,12 @@ PyObject *py_weave_layer_auto(PyObject *, PyObject *const *v, Py_ssize_t n)
 PyObject *py_weave_train(PyObject *, PyObject *const *v, Py_ssize_t n)
 {
     return entry("weave_train", n, 10, [&]() -> PyObject * {
-        Ref seq(PySequence_Fast(v[0], "boundaries must be a sequence of dicts"));
-        if (!seq.o) fail();
-        const size_t count = static_cast<size_t>(PySequence_Fast_GET_SIZE(seq.o));
+        const Ref seq = items(v[0], "boundaries");
+        const size_t count = static_cast<size_t>(PyTuple_GET_SIZE(seq.o));
         std::vector<Layer> layers(count);
         std::vector<tw_layer_args> args(count + 1);
         for (size_t i = 0; i < count; ++i) {
-            PyObject *b = PySequence_Fast_GET_ITEM(seq.o, i);
+            PyObject *b = PyTuple_GET_ITEM(seq.o, i);
             layers[i].fill(args[i], item(b, "X1"), item(b, "W1"), item(b, "partials"), item(b, "residual"),
                            item(b, "weight"), item(b, "eps"), item(b, "W2"), v[7], v[8], item(b, "out"),
                            item(b, "residual_out"), item(b, "Y"), v[9]);
@@ -503,6 +523,7 @@ struct Buffer {
         }
     }
     ~Buffer() { PyBuffer_Release(&b); }
+    PointerArray pointers() const { return {static_cast<void **>(b.buf), static_cast<size_t>(b.len) / sizeof(void *)}; }
 };
 
 // fill_fused(struct, pointer_array, partials, residual, weight, eps, cu_budget, out, residual_out) -> (out, residual_out)
@@ -510,11 +531,10 @@ PyObject *py_fill_fused(PyObject *, PyObject *const *v, Py_ssize_t n)
 {
     return entry("fill_fused", n, 9, [&] {
         Buffer s(v[0], sizeof(tw_fused_args));
-        const Py_ssize_t P = PySequence_Size(v[2]);
-        if (P < 0) fail();
-        Buffer ptrs(v[1], static_cast<size_t>(P) * sizeof(void *));
+        Buffer ptrs(v[1], 0);
         Fused f;
-        f.fill(v[2], v[3], v[4], v[5], v[6], v[7], v[8], static_cast<void **>(ptrs.b.buf));
+        const PointerArray to = ptrs.pointers();
+        f.fill(v[2], v[3], v[4], v[5], v[6], v[7], v[8], &to);
         *static_cast<tw_fused_args *>(s.b.buf) = f.a;
         return pair(f.out, f.residual_out);
     });
@@ -526,12 +546,11 @@ PyObject *py_fill_layer(PyObject *, PyObject *const *v, Py_ssize_t n)
 {
     return entry("fill_layer", n, 15, [&] {
         Buffer s(v[0], sizeof(tw_layer_args));
-        const Py_ssize_t P = PySequence_Size(v[4]);
-        if (P < 0) fail();
-        Buffer ptrs(v[1], static_cast<size_t>(P) * sizeof(void *));
+        Buffer ptrs(v[1], 0);
+        const PointerArray to = ptrs.pointers();
         Layer l;
         l.fill(*static_cast<tw_layer_args *>(s.b.buf), v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], v[10], v[11],
-               v[12], v[13], v[14], static_cast<void **>(ptrs.b.buf));
+               v[12], v[13], v[14], &to);
         return PyTuple_Pack(3, l.f.out.o, l.f.residual_out.o, l.Y.o);
     });
 }
