@@ -320,18 +320,31 @@ PyObject *pair(Ref &a, Ref &b)
     return t;
 }
 
-// d[key], or `otherwise` (borrowed) if the dict has none and one is given.
-PyObject *item(PyObject *d, const char *key, PyObject *otherwise = nullptr)
+// d[key], of a dict or any other mapping, the way Python looks it up.
+Ref item(PyObject *d, const char *key)
 {
-    if (!PyDict_Check(d)) fail(PyExc_TypeError, "expected a dict, got %s", Py_TYPE(d)->tp_name);
     Ref k(PyUnicode_InternFromString(key));
     if (!k.o) fail();
+    Ref v(PyObject_GetItem(d, k.o));
+    if (!v.o) fail();
+    return v;
+}
+// d.get(key, otherwise)
+Ref item(PyObject *d, const char *key, PyObject *otherwise)
+{
+    static PyObject *get = PyUnicode_InternFromString("get");
+    Ref k(PyUnicode_InternFromString(key));
+    if (!k.o) fail();
+    if (!PyDict_CheckExact(d)) {
+        Ref v(PyObject_CallMethodObjArgs(d, get, k.o, otherwise, nullptr));
+        if (!v.o) fail();
+        return v;
+    }
     PyObject *v = PyDict_GetItemWithError(d, k.o);
-    if (v) return v;
-    if (PyErr_Occurred()) fail();
-    if (otherwise) return otherwise;
-    PyErr_SetObject(PyExc_KeyError, k.o);
-    fail();
+    if (!v && PyErr_Occurred()) fail();
+    if (!v) v = otherwise;
+    Py_INCREF(v);
+    return Ref(v);
 }
 
 // Runs one entry of the module: n positional arguments, C++ and Python errors kept apart.
@@ -406,12 +419,25 @@ PyObject *py_overlap_launch(PyObject *, PyObject *const *v, Py_ssize_t n)
         Gemm m;
         Ref zero(PyLong_FromLong(0)), nk(PyLong_FromLong(TW_B_NK));
         const bool has_f = v[0] != Py_None, has_g = v[1] != Py_None;
-        if (has_f)
-            f.fill(item(v[0], "partials"), item(v[0], "residual"), item(v[0], "weight"), item(v[0], "eps"),
-                   item(v[0], "cu_budget", zero.o), item(v[0], "out", Py_None), item(v[0], "residual_out", Py_None));
-        if (has_g)
-            m.fill(item(v[1], "A"), item(v[1], "B"), item(v[1], "C", Py_None), item(v[1], "b_layout", nk.o),
-                   item(v[1], "cu_budget", zero.o));
+        Ref of_f[7], of_g[5];  // held until the call has been made
+        if (has_f) {
+            of_f[0] = item(v[0], "partials");
+            of_f[1] = item(v[0], "residual");
+            of_f[2] = item(v[0], "weight");
+            of_f[3] = item(v[0], "eps");
+            of_f[4] = item(v[0], "cu_budget", zero.o);
+            of_f[5] = item(v[0], "out", Py_None);
+            of_f[6] = item(v[0], "residual_out", Py_None);
+            f.fill(of_f[0].o, of_f[1].o, of_f[2].o, of_f[3].o, of_f[4].o, of_f[5].o, of_f[6].o);
+        }
+        if (has_g) {
+            of_g[0] = item(v[1], "A");
+            of_g[1] = item(v[1], "B");
+            of_g[2] = item(v[1], "C", Py_None);
+            of_g[3] = item(v[1], "b_layout", nk.o);
+            of_g[4] = item(v[1], "cu_budget", zero.o);
+            m.fill(of_g[0].o, of_g[1].o, of_g[2].o, of_g[3].o, of_g[4].o);
+        }
         void *comm = stream_handle(v[2]), *compute = stream_handle(v[3]);
         const Parent p(v[4], v[5], v[6]);
         call("tw_overlap_launch", [&] {
@@ -492,13 +518,18 @@ PyObject *py_weave_train(PyObject *, PyObject *const *v, Py_ssize_t n)
     return entry("weave_train", n, 10, [&]() -> PyObject * {
         const Ref seq = items(v[0], "boundaries");
         const size_t count = static_cast<size_t>(PyTuple_GET_SIZE(seq.o));
-        std::vector<Layer> layers(count);
+        struct Boundary {
+            Ref of[10];  // the items of its dict, held until the call has been made
+            Layer l;
+        };
+        static const char *const kKeys[10] = {"X1", "W1", "partials", "residual", "weight", "eps", "W2", "out", "residual_out", "Y"};
+        std::vector<Boundary> boundaries(count);
         std::vector<tw_layer_args> args(count + 1);
         for (size_t i = 0; i < count; ++i) {
-            PyObject *b = PyTuple_GET_ITEM(seq.o, i);
-            layers[i].fill(args[i], item(b, "X1"), item(b, "W1"), item(b, "partials"), item(b, "residual"),
-                           item(b, "weight"), item(b, "eps"), item(b, "W2"), v[7], v[8], item(b, "out"),
-                           item(b, "residual_out"), item(b, "Y"), v[9]);
+            Ref *of = boundaries[i].of;
+            for (int j = 0; j < 10; ++j) of[j] = item(PyTuple_GET_ITEM(seq.o, i), kKeys[j]);
+            boundaries[i].l.fill(args[i], of[0].o, of[1].o, of[2].o, of[3].o, of[4].o, of[5].o, of[6].o, v[7], v[8], of[7].o,
+                                 of[8].o, of[9].o, v[9]);
         }
         const int64_t row = as_int(v[1]);
         void *sx = stream_handle(v[2]), *sc = stream_handle(v[3]);

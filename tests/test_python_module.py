@@ -1,6 +1,8 @@
 """What the Python module over libtw (csrc/tw_python.cpp) takes and refuses, as far as that can be seen
 without a GPU: tensors in host memory stand where a check ahead of the tensors' own has to speak first."""
+import collections
 import ctypes
+import types
 
 import pytest
 import torch
@@ -58,3 +60,46 @@ def test_sequences_without_a_length_are_refused_and_cuts_may_be_any_iterable():
     with pytest.raises(TypeError, match="len"):
         tw.overlap_launch(dict(partials=iter([HOST]), residual=HOST, weight=WEIGHT, eps=1e-5, out=HOST, residual_out=HOST),
                           None, *streams)
+
+
+class MissingIsHost(dict):
+    """Every key that is not there stands for a tensor in host memory."""
+
+    def __missing__(self, key):
+        return HOST
+
+
+class Lookup(dict):
+    """A dict whose items are made when they are asked for."""
+
+    def __getitem__(self, key):
+        return HOST
+
+
+FUSED = dict(partials=[HOST], residual=HOST, weight=WEIGHT, eps=1e-5, out=HOST, residual_out=HOST)
+
+
+@pytest.mark.parametrize("make", [dict, collections.OrderedDict, types.MappingProxyType, collections.UserDict,
+                                  collections.ChainMap], ids=lambda m: m.__name__)
+def test_argument_groups_may_be_any_mapping(make):
+    """... and get as far as the tensors, which are refused for lying in host memory."""
+    with pytest.raises(TypeError, match=r"partials\[0\] must be a GPU tensor"):
+        tw.overlap_launch(make(FUSED), None, None, None)
+    with pytest.raises(TypeError, match="B must be a GPU tensor"):
+        tw.overlap_launch(None, make(dict(A=HOST, B=HOST, C=None, b_layout=tw.B_NK)), None, None)
+    with pytest.raises(TypeError, match=r"partials\[0\] must be a GPU tensor"):
+        tw.weave_train([make(dict(FUSED, X1=HOST, W1=HOST, W2=HOST, Y=HOST))], 0, None, None)
+    with pytest.raises(KeyError, match="weight"):
+        tw.overlap_launch(make({k: v for k, v in FUSED.items() if k != "weight"}), None, None, None)
+
+
+def test_argument_groups_are_asked_the_way_python_asks():
+    with pytest.raises(TypeError, match="B must be a GPU tensor"):
+        tw.overlap_launch(None, MissingIsHost(A=HOST), None, None)
+    with pytest.raises(TypeError, match="B must be a GPU tensor"):
+        tw.overlap_launch(None, Lookup(A=None, B=None), None, None)
+    with pytest.raises(TypeError):
+        tw.overlap_launch([HOST], None, None, None)
+    # optional ones through get(): __missing__ does not stand in for them
+    with pytest.raises(TypeError, match="B must be a GPU tensor"):
+        tw.overlap_launch(None, MissingIsHost(A=HOST, B=HOST), None, None)
