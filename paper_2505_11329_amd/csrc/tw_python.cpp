@@ -75,15 +75,28 @@ int64_t as_int(PyObject *o)
 int as_c_int(PyObject *o) { return static_cast<int>(as_int(o)); }
 float as_float(PyObject *o)
 {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) fail();
-    return static_cast<float>(v);
+    if (PyFloat_CheckExact(o)) return static_cast<float>(PyFloat_AS_DOUBLE(o));
+    Ref n(PyNumber_Float(o));
+    if (!n.o) fail();
+    return static_cast<float>(PyFloat_AS_DOUBLE(n.o));
 }
 int as_bool(PyObject *o)
 {
     const int v = PyObject_IsTrue(o);
     if (v < 0) fail();
     return v;
+}
+
+// The layout that equals o, as Python compares: 1.0 is one, 0.5 and "0" are none.
+int64_t b_layout(PyObject *o)
+{
+    for (const int64_t layout : {int64_t(TW_B_NK), int64_t(TW_B_KN)}) {
+        Ref v(PyLong_FromLongLong(layout));
+        const int same = v.o ? PyObject_RichCompareBool(o, v.o, Py_EQ) : -1;
+        if (same < 0) fail();
+        if (same) return layout;
+    }
+    fail(PyExc_ValueError, "b_layout must be B_NK or B_KN");
 }
 
 // hipStream_t of a torch stream; None means torch's current stream.
@@ -248,8 +261,7 @@ struct Gemm {
     void fill(PyObject *A, PyObject *B, PyObject *c, PyObject *layout, PyObject *budget)
     {
         const at::Tensor &a = matrix(A, "A", "A and B must be matrices"), &b = matrix(B, "B", "A and B must be matrices");
-        const int64_t M = a.size(0), K = a.size(1), lay = as_int(layout);
-        if (lay != TW_B_NK && lay != TW_B_KN) fail(PyExc_ValueError, "b_layout must be B_NK or B_KN");
+        const int64_t M = a.size(0), K = a.size(1), lay = b_layout(layout);
         const int64_t N = lay == TW_B_NK ? b.size(0) : b.size(1);
         g.B = lay == TW_B_NK ? bf16_ptr(B, {"B"}, 2, N, K) : bf16_ptr(B, {"B"}, 2, K, N);
         C = given_or_new(c, a, M, N);

@@ -103,3 +103,22 @@ def test_argument_groups_are_asked_the_way_python_asks():
     # optional ones through get(): __missing__ does not stand in for them
     with pytest.raises(TypeError, match="B must be a GPU tensor"):
         tw.overlap_launch(None, MissingIsHost(A=HOST, B=HOST), None, None)
+
+
+def test_numbers_are_read_as_int_and_float_read_them():
+    """b_layout is compared with the two layouts, not rounded to one."""
+    for bad in (0.5, "0", 2, -1, None, 1.25):
+        with pytest.raises(ValueError, match="b_layout must be B_NK or B_KN"):
+            tw.gemm_bf16(HOST, HOST, b_layout=bad)
+    for good in (0, 1.0, False, True):
+        with pytest.raises((TypeError, ValueError), match="B must be a GPU tensor"):
+            tw.gemm_bf16(HOST, HOST, b_layout=good)
+
+
+@pytest.mark.gpu
+def test_eps_is_whatever_float_takes():
+    x, w = torch.randn((3, 64), device="cuda:0").bfloat16(), torch.ones((64,), dtype=torch.bfloat16, device="cuda:0")
+    want = tw.reduce_add_rmsnorm([x], x, w, 1e-5)[0]
+    for eps in ("1e-5", torch.tensor(1e-5, dtype=torch.float64)):
+        assert torch.equal(tw.reduce_add_rmsnorm([x], x, w, eps)[0], want)
+    assert torch.equal(tw.reduce_add_rmsnorm([x], x, w, True)[0], tw.reduce_add_rmsnorm([x], x, w, 1.0)[0])
