@@ -540,6 +540,9 @@ PyObject *py_weave_train(PyObject *, PyObject *const *v, Py_ssize_t n)
         for (size_t i = 0; i < count; ++i) {
             Ref *of = boundaries[i].of;
             for (int j = 0; j < 10; ++j) of[j] = item(PyTuple_GET_ITEM(seq.o, i), kKeys[j]);
+            // an output made here would be gone before the kernels that write it have run
+            for (int j = 7; j < 10; ++j)
+                if (of[j].o == Py_None) fail(PyExc_TypeError, "%s must be a GPU tensor", kKeys[j]);
             boundaries[i].l.fill(args[i], of[0].o, of[1].o, of[2].o, of[3].o, of[4].o, of[5].o, of[6].o, v[7], v[8], of[7].o,
                                  of[8].o, of[9].o, v[9]);
         }

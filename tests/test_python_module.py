@@ -105,6 +105,13 @@ def test_argument_groups_are_asked_the_way_python_asks():
         tw.overlap_launch(None, MissingIsHost(A=HOST, B=HOST), None, None)
 
 
+@pytest.mark.parametrize("name", ["out", "residual_out", "Y"])
+def test_a_train_makes_no_outputs_of_its_own(name):
+    """It returns none, so one made for it would be freed with kernels still to write it."""
+    with pytest.raises(TypeError, match="%s must be a GPU tensor" % name):
+        tw.weave_train([dict(FUSED, X1=HOST, W1=HOST, W2=HOST, Y=HOST) | {name: None}], 0, None, None)
+
+
 def test_numbers_are_read_as_int_and_float_read_them():
     """b_layout is compared with the two layouts, not rounded to one."""
     for bad in (0.5, "0", 2, -1, None, 1.25):
