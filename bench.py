@@ -40,13 +40,13 @@ TRAFFIC_FROM_PROFILE = {
         "profile": "profiles/fused_kernel_c3_70b_shard_tp8_budget32.md",
         "kernel": "tw::fused_kernel<8, 1, false, false>",
         "fetched_KiB": 147728, "written_KiB": 32768,
-        "kernel_source_sha256_12": "c281c28c163c",
+        "kernel_source_sha256_12": "7b29a0a3d1ea",
     },
     (WORKLOAD, 0): {
         "profile": "profiles/fused_kernel_c3_whole_device_and_shared.md",
         "kernel": "tw::fused_thin_kernel<8, 4, false, false>",
         "fetched_KiB": 147682, "written_KiB": 32750,
-        "kernel_source_sha256_12": "c281c28c163c",
+        "kernel_source_sha256_12": "7b29a0a3d1ea",
     },
 }
 KERNEL_SOURCES = ("paper_2505_11329_amd/csrc/tw_fused.hip", "paper_2505_11329_amd/csrc/tw_device.h")

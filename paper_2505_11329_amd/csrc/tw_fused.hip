@@ -718,14 +718,43 @@ static constexpr bool wide_fits()
     return wide_fits(PT, VPT);
 }
 
-// With more than eight partials the specialised kernels' way to the first load, and to the
-// first request of a row's last partial, is longer (up to sixteen descriptors do not fit the
-// scalar registers); a launch of one row group per workgroup is over before they gain from
-// keeping all loads in flight, and from P = 12 on one of two (64 rows of 4096 elements on 32
-// compute units, P = 12: 7.2 us against 6.3 in the run-time loop; 512 rows 40.8 against 42.8).
-static bool few_trips(int P, int64_t grid, uint32_t n_groups)
+// Where the run-time loop over P is ahead of the kernel made for the P at hand. That one asks
+// for all P + 1 vectors of a chunk at once, which pays while a workgroup goes through row after
+// row; but its way to the first load is longer (from P = 12 on up to nineteen descriptors do
+// not fit the scalar registers and the small workgroups with 768 vectors a row and more spill
+// 100 to 190 of them, at P = 15 and 16 vector registers too), and where many workgroups run in
+// step, P + 1 streams a power of two apart meet in the same memory channels; the loop goes
+// through them a few at a time. Measured on MI355X, launches on rotating buffers.
+//
+// Wide kernel, loop against instance:
+//   - one row group per workgroup: over before anything is pipelined (whole device, P = 3 to 16,
+//     512 to 8192 elements: the loop is ahead by 1 to 16 % where half of the device is filled, by 1
+//     to 8 % where all of it is; rows of two vectors and more per thread: level to 6 % behind);
+//   - rows of one wave and less, from P = 10 on: 3 to 20 %;
+//   - P = 12, 15 and 16 (the loop's batches of four are full, or all but one): up to grid / 8 trips
+//     (64 compute units, 256 rows of 8192 elements, P = 12: 24.4 us against 27.2, P = 16: 29.4
+//     against 34.4; 1280 rows, 20 trips, P = 12: 114 against 109); P = 13 and 14, where one load
+//     in five or eight is empty: up to grid / 32.
+static bool wide_loops(int P, const FusedGeometry &g, int64_t grid, uint32_t n_groups)
 {
-    return P > 8 && n_groups <= grid * (P >= 12 ? 2 : 1);
+    if (P < 3 || g.vpt != 1) return false;
+    if (n_groups <= grid) return true;
+    if (P >= 10 && g.wpr == 0) return true;
+    const int64_t trips = grid / (P == 12 || P >= 15 ? 8 : 32);
+    return P >= 12 && n_groups <= grid * (trips > 2 ? trips : 2);
+}
+
+// The small workgroups, likewise (vectors: of one tensor, over the device's compute units). Rows
+// of 256 vectors and fewer, P = 12 to 16: 3 to 10 % (shared mode, 2048 rows of 2048 elements, P =
+// 16: 30.7 us against 34.1); wider ones from P = 15 on 3 to 6 % (512 rows of 8192, P = 16: 27.0
+// against 28.2), and fewer rows than that 11 to 24 % the other way (one row's chain of round
+// trips); at four rows of 8192 to a unit and more level to 6 % the other way.
+static bool thin_loops(int P, const FusedGeometry &g, int64_t n_rows, int cus)
+{
+    const int64_t vectors = n_rows * g.hv;
+    const bool narrow = g.hv <= 2 * kThinThreads;
+    return P >= (g.hv <= kThinThreads ? 12 : 15) && vectors > int64_t(narrow ? 512 : 1024) * cus &&
+           vectors <= int64_t(narrow ? 3072 : 4096) * cus;
 }
 
 template <int PT>
@@ -841,9 +870,11 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
         prm.eps = a.eps;
         prm.inv_h = 1.0f / static_cast<float>(a.H);
 
-        // the run-time loop over P: where no specialised kernel has the registers, or is built to be traced
+        // the run-time loop over P: where it is faster, no specialised kernel has the registers, or none is built to be traced
         const bool traced_p = a.P == 1 || a.P == 2 || a.P == 4 || a.P == 8;
-        const bool any_p = (trace && !traced_p) || (!thin && (!wide_fits(a.P, g.vpt) || few_trips(a.P, grid, prm.n_groups)));
+        const bool any_p = (trace && !traced_p) ||
+                           (thin ? thin_loops(a.P, g, row_end - row_begin, cus)
+                                 : !wide_fits(a.P, g.vpt) || wide_loops(a.P, g, grid, prm.n_groups));
         if (thin) {
             if (any_p) TW_TRY((launch_thin<0>(prm, tg.q, trace, streamed, false, grid, stream)));
             else

@@ -158,6 +158,31 @@ def test_kernels_of_every_partial_count(tw, torch_cuda, H, P):
             assert np.array_equal(out, want[0]) and np.array_equal(res, want[1]), (N, budget)
 
 
+# Sizes on both sides of where a launch goes through the partials in a loop instead of in the kernel made for their
+# number: one row group per workgroup and more (on 5, 32, 64 compute units and all), rows of one wave and less, and the
+# small workgroups' band of vectors per compute unit, for P of a whole number of the loop's batches and others.
+@pytest.mark.parametrize("N,H,P", [(500, 2048, 12), (530, 2048, 13), (3073, 2048, 16), (250, 8192, 16), (300, 8192, 15),
+                                   (1030, 8192, 16), (1500, 4096, 16), (90, 512, 10), (4097, 512, 11), (64, 5120, 12),
+                                   (65, 5120, 12), (257, 5120, 14), (2049, 1016, 12), (31, 4096, 3), (33, 4096, 5)])
+def test_partials_in_a_loop_give_the_bits_of_the_kernel_for_their_number(tw, torch_cuda, N, H, P):
+    torch = torch_cuda
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(N + P)
+    def draw(*shape):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda:0").normal_(generator=gen)
+    parts, resid, w = [draw(N, H) for _ in range(P)], draw(N, H), draw(H)
+    rows = sorted({0, 1, N // 2, N - 2, N - 1})
+    d = dict(partials=[to_bits(p[rows]) for p in parts], residual=to_bits(resid[rows]), weight=to_bits(w), eps=1e-5,
+             N=len(rows), H=H, P=P)
+    want = None
+    for budget in (3, 0, tw.CU_SHARED, 5, 32, 64):
+        out, res = (to_bits(t) for t in tw.reduce_add_rmsnorm(parts, resid, w, 1e-5, cu_budget=budget))
+        if want is None:
+            want = out, res
+            check_against_oracle(d, out[rows], res[rows], "N=%d H=%d P=%d" % (N, H, P))
+        assert np.array_equal(out, want[0]) and np.array_equal(res, want[1]), budget
+
+
 @pytest.mark.parametrize("N,H,P", [(4100, 8192, 8), (4611, 4096, 2), (4099, 8192, 12), (6200, 5120, 5), (4097, 8184, 1),
                                    (9000, 1032, 3)])
 def test_small_workgroups_with_several_rows_each(tw, torch_cuda, N, H, P):
