@@ -721,27 +721,33 @@ static constexpr bool wide_fits()
 // Where the run-time loop over P is ahead of the kernel made for the P at hand. That one asks
 // for all P + 1 vectors of a chunk at once, which pays while a workgroup goes through row after
 // row; but its way to the first load is longer (from P = 12 on up to nineteen descriptors do
-// not fit the scalar registers and the small workgroups with 768 vectors a row and more spill
-// 100 to 190 of them, at P = 15 and 16 vector registers too), and where many workgroups run in
-// step, P + 1 streams a power of two apart meet in the same memory channels; the loop goes
-// through them a few at a time. Measured on MI355X, launches on rotating buffers.
+// not fit the scalar registers, and the small workgroups with 768 vectors a row and more spill
+// 100 to 190 of them, at P = 15 and 16 vector registers too). The loop goes through the
+// partials a few at a time. Measured on MI355X, launches on rotating buffers.
 //
-// Wide kernel, loop against instance:
+// Wide kernel, loop against instance (tensor_bytes: size of one tensor):
 //   - one row group per workgroup: over before anything is pipelined (whole device, P = 3 to 16,
 //     512 to 8192 elements: the loop is ahead by 1 to 16 % where half of the device is filled, by 1
 //     to 8 % where all of it is; rows of two vectors and more per thread: level to 6 % behind);
 //   - rows of one wave and less, from P = 10 on: 3 to 20 %;
-//   - P = 12, 15 and 16 (the loop's batches of four are full, or all but one): up to grid / 8 trips
-//     (64 compute units, 256 rows of 8192 elements, P = 12: 24.4 us against 27.2, P = 16: 29.4
-//     against 34.4; 1280 rows, 20 trips, P = 12: 114 against 109); P = 13 and 14, where one load
-//     in five or eight is empty: up to grid / 32.
-static bool wide_loops(int P, const FusedGeometry &g, int64_t grid, uint32_t n_groups)
+//   - from P = 12 on up to two trips, from P = 15 on four: level to 8 %;
+//   - many compute units on tensors of 4, 8 or 16 MiB: such tensors lie a power of two apart,
+//     and workgroups in step that ask for P + 1 of them at once meet in the same memory
+//     channels. 64 compute units, 256 rows of 8192 elements, P = 12: 24.4 us against 27.2, P =
+//     16: 29.4 against 34.4 (192 rows: 18.8 against 19.2 and 22.8 against 23.0); all, 4096 rows of
+//     2048, P = 7: 31.3 against 34.2, P = 16: 54.8 against 58.6. It fades with the number of
+//     trips (64 compute units, 512 rows of 8192, P = 12: 46.6 against 47.7) and with fewer
+//     compute units (32, 256 rows of 8192, P = 8 to 14: the loop is 4 to 16 % behind); on 32 and
+//     64 MiB either is up to 9 % ahead, from one allocation to another.
+static bool wide_loops(int P, const FusedGeometry &g, int64_t grid, uint32_t n_groups, int64_t tensor_bytes)
 {
     if (P < 3 || g.vpt != 1) return false;
     if (n_groups <= grid) return true;
     if (P >= 10 && g.wpr == 0) return true;
-    const int64_t trips = grid / (P == 12 || P >= 15 ? 8 : 32);
-    return P >= 12 && n_groups <= grid * (trips > 2 ? trips : 2);
+    if (P >= 12 && n_groups <= grid * (P >= 15 ? 4 : 2)) return true;
+    const bool same_channels =
+        tensor_bytes >= 4 << 20 && tensor_bytes <= 16 << 20 && (tensor_bytes & (tensor_bytes - 1)) == 0;
+    return same_channels && grid >= 64 && P >= (grid >= 256 ? 7 : 10) && n_groups <= grid * (grid / (P >= 12 ? 8 : 16));
 }
 
 // The small workgroups, likewise (vectors: of one tensor, over the device's compute units). Rows
@@ -776,38 +782,46 @@ static tw_status launch_vpt(const FusedParams &prm, const FusedGeometry &g, bool
     return TW_ERR_UNSUPPORTED;
 }
 
-// Which kernel a launch takes. Shared mode has a kernel for rows of up to 1024
-// vectors; wider rows run on the wide kernel over the whole device. A
-// whole-device launch also takes the small workgroups up to a number of vectors
-// per compute unit: they are placed faster and put every row in flight at once,
-// where the wide kernel's software pipeline has only a few rows per workgroup to
-// run over; beyond it the wide kernel's fewer, longer streams are ahead. Measured
-// on MI355X, trains of launches on rotating buffers, small workgroups against the
-// wide kernel: faster by 15 to 20 % at 1024 rows whatever P and H; level at (rows per
-// compute unit, H = 8192 / 4096 / 5120 / 2048) 6 / 16 / 9 / 20 for P = 1, 16 / 24 / 10 / 32
-// for P = 2, 16 / 26 / 10 / 32 for P = 3 and 4, 32 / 32 / 14 / 32 for P = 5 to 8, 12 / 12 / 9 /
-// 18 from P = 9 on; past twice that 2 to 8 % slower. (Rows of an even number of
-// 256-vector pieces keep two chunks in flight per thread up to P = 8, hence their later
-// crossing.) Rows of 128 vectors and fewer share workgroups and cross at 12. Both
-// kernels give the same bits.
+// Which kernel a launch takes. Shared mode has a kernel for rows of up to 1024 vectors; wider
+// rows run on the wide kernel over the whole device. Of a whole-device launch either kernel may
+// be the faster one, with the same bits. The small workgroups are placed as compute units fall
+// free and have every row in flight at once; the wide kernel works in trips of a row group per
+// compute unit, its loads running ahead over the trips. So a last trip that leaves most compute
+// units idle costs the wide kernel as much as a full one (2048 elements, P = 8: 1024 rows, one
+// full trip, 9.3 us against 10.8 in small workgroups; 1075 rows, two trips, 13.3 against 10.1),
+// full trips are its best case, and over many trips the last one no longer counts. Where it is
+// taken, by row width and P, from 4300 sizes of 256 to 8192 elements and 51 to 65536 rows
+// timed on MI355X in trains of launches on rotating buffers (the kernel chosen is 0.7 % off the
+// faster one on average; one number of vectors per compute unit for each kind of row, without a
+// look at trips, was 3 % off, and up to 25 % where trips are full):
+struct WideFrom {
+    int one;   // percent of the compute units that a single trip has to fill
+    int full;  // trips, the last of them 92 % full or more
+    int any;   // trips, whatever the last one
+};
+static constexpr int kNever = 1 << 20;
+static constexpr WideFrom kWideFrom[5][5] = {
+    // P = 1, 2           3, 4                   5 to 8              9 to 11               12 to 16
+    {{kNever, kNever, 17}, {85, kNever, 17}, {70, 2, 6}, {85, 2, 6}, {85, 2, 5}},        // rows of up to 64 vectors
+    {{kNever, 2, 6}, {85, 2, 6}, {70, 2, 6}, {85, 2, 5}, {85, 2, 5}},                    // 256
+    {{kNever, 3, 6}, {kNever, kNever, 9}, {55, kNever, 17}, {55, 3, 6}, {55, 3, 6}},     // 512
+    {{kNever, kNever, 7}, {kNever, kNever, 9}, {kNever, kNever, 17}, {kNever, kNever, 13}, {0, kNever, 9}},  // 768
+    {{kNever, 4, 6}, {kNever, kNever, 17}, {kNever, kNever, 33}, {kNever, kNever, 33}, {0, 4, 6}},           // 1024
+};
 static bool takes_thin_kernel(int cu_budget, int cus, const FusedGeometry &g, int64_t n_rows, int P)
 {
     if (g.vpt != 1) return false;
     if (cu_budget == TW_CU_SHARED) return true;
     if (resolve_budget(cu_budget, cus) != cus) return false;
-    const int q = g.hv > kThinThreads ? (g.hv + kThinThreads - 1) / kThinThreads : 1;
-    // One row to a compute unit, more than eight partials, wide rows: one chunk of registers
-    // after another in a thin workgroup, where the wide kernel's waves have one each (64 rows
-    // of 8192 elements: P = 12 7.8 us against 6.8, P = 16 9.4 against 8.2; from P = 9 to 11 the
-    // small workgroups are ahead above 64 rows).
-    if (P > 8 && q >= 3 && n_rows <= (P >= 12 ? cus : cus / 4)) return false;
-    int64_t vectors_per_cu;
-    if (g.hv <= 128) vectors_per_cu = int64_t(12) * g.hv;
-    else if (P == 1) vectors_per_cu = 5120;
-    else if (P > 8) vectors_per_cu = q % 2 == 0 ? 6144 : 4608;
-    else if (q % 2 == 0) vectors_per_cu = P > 4 ? 8192 * q : P > 2 && q == 4 ? 16384 : 12288;
-    else vectors_per_cu = q == 1 || P > 4 ? 8192 : 5120;
-    return n_rows * g.hv <= vectors_per_cu * cus;
+    const int width = g.hv <= 64 ? 0 : (g.hv + kThinThreads - 1) / kThinThreads;
+    // Few wide rows of more than eight partials: one chunk of registers after another in a thin
+    // workgroup, where the wide kernel's waves have one each (64 rows of 8192 elements: P = 12
+    // 7.8 us against 6.8, P = 16 9.4 against 8.2).
+    if (P > 8 && P < 12 && width >= 3 && n_rows <= cus / 4) return false;
+    const WideFrom &w = kWideFrom[width][P <= 2 ? 0 : P <= 4 ? 1 : P <= 8 ? 2 : P <= 11 ? 3 : 4];
+    const int64_t groups = (n_rows + g.rows_per_iter - 1) / g.rows_per_iter, trips = (groups + cus - 1) / cus;
+    if (trips <= 1) return groups * 100 < int64_t(w.one) * cus;
+    return trips < w.any && (trips < w.full || groups * 100 < 92 * trips * cus);
 }
 
 tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_end, uint32_t *hw_ids,
@@ -874,7 +888,7 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
         const bool traced_p = a.P == 1 || a.P == 2 || a.P == 4 || a.P == 8;
         const bool any_p = (trace && !traced_p) ||
                            (thin ? thin_loops(a.P, g, row_end - row_begin, cus)
-                                 : !wide_fits(a.P, g.vpt) || wide_loops(a.P, g, grid, prm.n_groups));
+                                 : !wide_fits(a.P, g.vpt) || wide_loops(a.P, g, grid, prm.n_groups, a.N * row_bytes));
         if (thin) {
             if (any_p) TW_TRY((launch_thin<0>(prm, tg.q, trace, streamed, false, grid, stream)));
             else

@@ -158,6 +158,30 @@ def test_kernels_of_every_partial_count(tw, torch_cuda, H, P):
             assert np.array_equal(out, want[0]) and np.array_equal(res, want[1]), (N, budget)
 
 
+# Whole-device launches of one row less and more than where the wide kernel takes over from the small workgroups
+# (256 compute units): by the share of them that a single trip fills, by a nearly full last trip, by the number of trips,
+# for rows of every width class; and just past a full trip, where the small workgroups take over again.
+@pytest.mark.parametrize("N,H,P", [(716, 2048, 6), (717, 2048, 8), (1025, 2048, 8), (1881, 2048, 4), (1885, 2048, 4),
+                                   (5120, 2048, 1), (5121, 2048, 2), (3480, 512, 9), (3485, 512, 9), (65537, 512, 1),
+                                   (281, 4096, 8), (283, 4096, 8), (1480, 4096, 12), (4097, 4096, 4), (2048, 6144, 3),
+                                   (2049, 6144, 3), (942, 8192, 2), (943, 8192, 2), (1280, 8192, 13), (1281, 8192, 13)])
+def test_whole_device_launches_on_both_sides_of_the_kernel_choice(tw, torch_cuda, N, H, P):
+    torch = torch_cuda
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(N + P)
+    def draw(*shape):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda:0").normal_(generator=gen)
+    parts, resid, w = [draw(N, H) for _ in range(P)], draw(N, H), draw(H)
+    want = [to_bits(t) for t in tw.reduce_add_rmsnorm(parts, resid, w, 1e-5, cu_budget=64)]
+    rows = sorted({0, 1, N // 2, N - 2, N - 1})
+    d = dict(partials=[to_bits(p[rows]) for p in parts], residual=to_bits(resid[rows]), weight=to_bits(w), eps=1e-5,
+             N=len(rows), H=H, P=P)
+    check_against_oracle(d, want[0][rows], want[1][rows], "N=%d H=%d P=%d" % (N, H, P))
+    for _ in range(2):
+        out, res = (to_bits(t) for t in tw.reduce_add_rmsnorm(parts, resid, w, 1e-5, cu_budget=0))
+        assert np.array_equal(out, want[0]) and np.array_equal(res, want[1])
+
+
 # Sizes on both sides of where a launch goes through the partials in a loop instead of in the kernel made for their
 # number: one row group per workgroup and more (on 5, 32, 64 compute units and all), rows of one wave and less, and the
 # small workgroups' band of vectors per compute unit, for P of a whole number of the loop's batches and others.
