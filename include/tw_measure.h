@@ -33,9 +33,10 @@ tw_status tw_reduce_add_rmsnorm_traced(const void *const *partials, const void *
 /*
  * tw_gemm_bf16 (B stored [N x K], whole device) with a kernel that also counts,
  * per wave, the shader clocks it spends in each phase of its K loop: evidence for
- * where the cycles of the 256 x 256 tile's pipeline go. Only products that
- * tw_gemm_bf16 would run on 256 x 256 tiles are accepted (TW_ERR_UNSUPPORTED
- * otherwise). Wave w of workgroup g writes TW_GEMM_PHASES 64-bit sums to
+ * where the cycles of the 256 x 256 tile's pipeline go. The traced launch always
+ * takes those tiles; products they leave too many compute units idle for are
+ * refused (TW_ERR_UNSUPPORTED: 256 x 128 tiles for at most half of them, or 256 x 256
+ * tiles filling whole turns of them 5 percent worse than 256 x 128). Wave w of workgroup g writes TW_GEMM_PHASES 64-bit sums to
  * phase_cycles[(g * 4 + w) * TW_GEMM_PHASES + i]:
  *   0  first sub-step of the K steps (64 MFMAs = 1024 clocks of matrix work each,
  *      with the loads of one operand and the fragment reads of the second)
@@ -78,11 +79,21 @@ tw_status tw_fused_layout(int64_t H, int *waves_per_row, int *vectors_per_thread
 int tw_weave_schedule(int64_t T, int64_t K1, int64_t H, int P, int64_t N2, int fused_cu_budget, int schedule,
                       int cus);
 
-/* Rows and columns of the output tile a GEMM workgroup computes by default, and
- * always when the GEMM runs beside another kernel (a product launched on its own
- * may be cut into tiles of half or twice this width instead, see tw_gemm_bf16;
- * tw_smart_split_point counts in tiles of this shape). */
+/* Rows and columns of the output tile that tw_smart_split_point counts in: of the
+ * largest one a GEMM takes beside another kernel (tw_gemm_tile_choice says which
+ * one a given launch takes). */
 void tw_gemm_tile_shape(int *tile_m, int *tile_n);
+
+/*
+ * Rows and columns of the output tiles that tw_gemm_bf16 cuts a product of these
+ * sizes into on `cus` compute units (the budget, or the device's number without
+ * one). beside_other_kernels != 0: as a launch that is meant to overlap with another
+ * kernel takes them (tw_overlap_launch, the woven schedules). Host arithmetic only;
+ * either pointer may be NULL. TW_ERR_SHAPE for M, N or cus below 1, K below 0 or an
+ * unknown layout.
+ */
+tw_status tw_gemm_tile_choice(int64_t M, int64_t N, int64_t K, int b_layout, int cus, int beside_other_kernels,
+                              int *tile_m, int *tile_n);
 
 /*
  * Measurement aid (not part of the method): a streaming kernel with the same

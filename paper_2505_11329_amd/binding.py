@@ -140,6 +140,9 @@ def lib():
         L.tw_should_split.restype = ctypes.c_int
         L.tw_gemm_tile_shape.argtypes = [ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
         L.tw_gemm_tile_shape.restype = None
+        L.tw_gemm_tile_choice.argtypes = [_i64, _i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                                          ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
+        L.tw_gemm_tile_choice.restype = ctypes.c_int
         L.tw_hbm_probe_mixed.argtypes = [_vp, _vp, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp]
         L.tw_hbm_probe_mixed.restype = ctypes.c_int
         L.tw_hbm_probe_shaped.argtypes = [_vp, _vp, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp]
@@ -363,6 +366,14 @@ def smart_split_point(T, multiple, gemm_n_out, cus, gemm_k=None):
 def gemm_tile_shape():
     m, n = ctypes.c_int(0), ctypes.c_int(0)
     lib().tw_gemm_tile_shape(ctypes.byref(m), ctypes.byref(n))
+    return m.value, n.value
+
+
+def gemm_tile_choice(M, N, K, b_layout=B_NK, cus=256, beside_other_kernels=False):
+    """tw_gemm_tile_choice: (rows, columns) of the output tiles a product of these sizes is cut into."""
+    m, n = ctypes.c_int(0), ctypes.c_int(0)
+    _check(lib().tw_gemm_tile_choice(int(M), int(N), int(K), int(b_layout), int(cus), 1 if beside_other_kernels else 0,
+                                     ctypes.byref(m), ctypes.byref(n)), "tw_gemm_tile_choice")
     return m.value, n.value
 
 

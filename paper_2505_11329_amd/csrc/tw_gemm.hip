@@ -754,12 +754,13 @@ static double wave_fill(int64_t tiles, int budget)
     return double(tiles) / double(waves * budget);
 }
 
-tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_other_kernels)
+// The tiles a launch on `budget` compute units is cut into.
+struct GemmTiles {
+    int rows, cols;
+    int small;  // shape of tw_gemm_tile.hip, -1: one of this file's, 256 rows high
+};
+static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, bool beside_other_kernels)
 {
-    if (g.M == 0 || g.N == 0) return TW_OK;
-    int cus = 0;
-    TW_TRY(current_cu_count(&cus));
-    const int budget = resolve_budget(g.cu_budget, cus);
     // The default: eight waves of 64 x 64, tile 256 x 128 x 64, three LDS stages.
     // The part runs this kernel at its power limit (1.2-1.9 GHz on N(0, 0.02^2)
     // operands against 2.4 GHz idle), so what a tile shape is worth is decided by
@@ -788,31 +789,45 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_oth
     // for the same L1 request slots (a woven layer measured level to 3 % slower with
     // them), and the larger tiles leave no registers for a co-resident workgroup. (256 x 192
     // tiles held to 384 registers leave room for one; a woven train took 3.5 % longer with them.)
-    enum { kWide, kNarrow, kBig, kBroad } take = kWide;
+    GemmTiles take = {BM, kGemmTileN, -1};
     double us = 1e300;
-    const auto consider = [&](int shape, int cols, double us_per_step, double us_per_turn) {
+    const auto consider = [&](int cols, double us_per_step, double us_per_turn) {
         const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + cols - 1) / cols);
-        const double cool = shape == kWide ? 1.0 : 0.78 + 0.22 * wave_fill(tiles, budget);
+        const double cool = cols == kGemmTileN ? 1.0 : 0.78 + 0.22 * wave_fill(tiles, budget);
         const double t = tile_grid_us(g.M, g.N, g.K, BM, cols, 64, us_per_step * cool, us_per_turn, budget);
         if (t < us) {
             us = t;
-            take = static_cast<decltype(take)>(shape);
+            take.cols = cols;
         }
     };
-    consider(kWide, kGemmTileN, g.b_layout == TW_B_KN ? 0.84 : 0.745, 2.7);
+    consider(kGemmTileN, g.b_layout == TW_B_KN ? 0.84 : 0.745, 2.7);
     if (g.b_layout == TW_B_NK && !beside_other_kernels) {
-        consider(kNarrow, 64, 0.60, 2.7);
-        consider(kBig, 256, 1.40, 7.5);
-        consider(kBroad, 192, 1.08, 6.6);
+        consider(64, 0.60, 2.7);
+        consider(256, 1.40, 7.5);
+        consider(192, 1.08, 6.6);
     }
     double small_us = 0.0;
     const int small = best_small_tile(g, budget, &small_us);
-    if (small >= 0 && small_us < 0.98 * us) return launch_small_tile(g, small, budget, cus, stream);
+    if (small >= 0 && small_us < 0.98 * us) {
+        take.small = small;
+        small_tile_size(small, &take.rows, &take.cols);
+    }
+    return take;
+}
+
+tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_other_kernels)
+{
+    if (g.M == 0 || g.N == 0) return TW_OK;
+    int cus = 0;
+    TW_TRY(current_cu_count(&cus));
+    const int budget = resolve_budget(g.cu_budget, cus);
+    const GemmTiles t = choose_tiles(g, budget, beside_other_kernels);
+    if (t.small >= 0) return launch_small_tile(g, t.small, budget, cus, stream);
     if (g.b_layout == TW_B_KN) return launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
-    switch (take) {
-    case kNarrow: return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);
-    case kBig: return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream);
-    case kBroad: return launch_cfg<false, 8, 6, 2, 64>(g, budget, stream);
+    switch (t.cols) {
+    case 64: return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);
+    case 256: return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream);
+    case 192: return launch_cfg<false, 8, 6, 2, 64>(g, budget, stream);
     default: return launch_cfg<false, 4, 4, 3, 64>(g, budget, stream);
     }
 }
@@ -830,11 +845,22 @@ extern "C" tw_status tw_gemm_bf16_traced(const void *A, const void *B, void *C, 
     if (g.M == 0 || g.N == 0) return TW_ERR_UNSUPPORTED;
     int cus = 0;
     TW_TRY(current_cu_count(&cus));
-    // only a product that takes the 256 x 256 tiles on the whole device is traced
+    // only a product whose 256 x 256 tiles fill the device is traced
     const int64_t tiles_m = (g.M + BM - 1) / BM;
     const int64_t wide_tiles = tiles_m * ((g.N + kGemmTileN - 1) / kGemmTileN), big_tiles = tiles_m * ((g.N + 255) / 256);
     if (2 * wide_tiles <= cus || wave_fill(big_tiles, cus) < wave_fill(wide_tiles, cus) - 0.05) return TW_ERR_UNSUPPORTED;
     return launch_cfg<false, 8, 8, 2, 64, true>(g, cus, static_cast<hipStream_t>(stream), phase_cycles, phase_len);
+}
+
+extern "C" tw_status tw_gemm_tile_choice(int64_t M, int64_t N, int64_t K, int b_layout, int cus,
+                                         int beside_other_kernels, int *tile_m, int *tile_n)
+{
+    if (M < 1 || N < 1 || K < 0 || cus < 1 || (b_layout != TW_B_NK && b_layout != TW_B_KN)) return TW_ERR_SHAPE;
+    const tw_gemm_args g = {nullptr, nullptr, nullptr, M, N, K, b_layout, 0};
+    const GemmTiles t = choose_tiles(g, cus, beside_other_kernels != 0);
+    if (tile_m) *tile_m = t.rows;
+    if (tile_n) *tile_n = t.cols;
+    return TW_OK;
 }
 
 extern "C" tw_status tw_gemm_bf16(const void *A, const void *B, void *C, int64_t M, int64_t N, int64_t K,

@@ -471,6 +471,12 @@ int best_small_tile(const tw_gemm_args &g, int budget, double *us)
     return best;
 }
 
+void small_tile_size(int shape, int *rows, int *cols)
+{
+    *rows = kSmallTiles[shape].rows;
+    *cols = kSmallTiles[shape].cols;
+}
+
 tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, hipStream_t stream)
 {
     const SmallTileShape &t = kSmallTiles[shape];

@@ -91,17 +91,18 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
 // ---- GEMM stand-in (tw_gemm.hip) ----
 tw_status validate_gemm(const tw_gemm_args &g);
 // `beside_other_kernels`: the launch is meant to overlap with another kernel (the
-// fused step, a second GEMM): then the wide tiles are kept even where few of them
-// fill the device.
+// fused step, a second GEMM): of the 256-row tiles it then takes the 256 x 128 ones
+// only; smaller tiles where they are estimated faster, as on its own.
 tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_other_kernels = false);
 static constexpr int kGemmTileM = 256, kGemmTileN = 128;
 // Tile rows per block of the tile ordering.
 int tile_group_m(int64_t tiles_m, int tile_rows, int tile_cols, int budget);
 // The tile shapes for products of few tiles (tw_gemm_tile.hip): the estimated time of a
-// grid of tiles, the shape of the least (-1: none for the layout), and its launch.
+// grid of tiles, the shape of the least (-1: none for the layout), its size and its launch.
 double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_step, double us_per_step,
                     double us_per_turn, int budget);
 int best_small_tile(const tw_gemm_args &g, int budget, double *us);
+void small_tile_size(int shape, int *rows, int *cols);
 tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, hipStream_t stream);
 
 // ---- fork/join events (tw_host.hip) ----

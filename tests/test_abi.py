@@ -36,7 +36,7 @@ def test_header_declares_the_documented_entry_points():
     # measurement and introspection aids are declared apart from the method's interface
     aids = declared_functions(("tw_measure.h",))
     for must in ("tw_hbm_probe", "tw_hbm_probe_mixed", "tw_hbm_probe_shaped", "tw_hbm_probe_mixed_shaped",
-                 "tw_fused_grid", "tw_fused_layout", "tw_weave_schedule", "tw_gemm_tile_shape",
+                 "tw_fused_grid", "tw_fused_layout", "tw_weave_schedule", "tw_gemm_tile_shape", "tw_gemm_tile_choice",
                  "tw_reduce_add_rmsnorm_traced", "tw_streams_overlap", "tw_gemm_bf16_traced",
                  "tw_stream_create_cu_masked", "tw_stream_destroy"):
         assert must in aids and must not in names
@@ -250,6 +250,31 @@ def test_gemm_argument_checks():
     assert gemm_call(A=addr(0) + 2) == E_ALIGN
     assert gemm_call(C=addr(0)) == E_ALIAS
     assert gemm_call(C=addr(20) + 16) == E_ALIAS
+
+
+def test_gemm_tile_choice_and_the_shapes_the_gpu_tests_cover():
+    """Every tile shape that is built is taken by some case of the GPU tests, in each layout it is built for
+    (the choice is host arithmetic, so a change of one of its constants shows here); next to other kernels no
+    256-row tile but the 256 x 128 one is taken."""
+    import random
+    import test_gemm_gpu as cases
+    for tile, layouts, M, N, K, budget in cases.TILE_CASES:
+        for code in {"nk": (tw.B_NK,), "kn": (tw.B_KN,), "both": (tw.B_NK, tw.B_KN)}[layouts]:
+            assert tw.gemm_tile_choice(M, N, K, code, budget) == tile, (tile, layouts, M, N, K, budget)
+    for tiles, code, name in ((cases.NK_TILES, tw.B_NK, "nk"), (cases.KN_TILES, tw.B_KN, "kn")):
+        covered = {t for t, layouts, *_ in cases.TILE_CASES if layouts in (name, "both")}
+        assert covered == set(tiles)
+        rng = random.Random(3)
+        for _ in range(4000):
+            M, N, K = int(2 ** rng.uniform(0, 13.5)), 8 * int(2 ** rng.uniform(0, 11)), 8 * int(2 ** rng.uniform(0, 11))
+            cus = rng.choice((1, 3, 16, 64, 256))
+            assert tw.gemm_tile_choice(M, N, K, code, cus) in tiles
+            m, n = tw.gemm_tile_choice(M, N, K, code, cus, beside_other_kernels=True)
+            assert (m, n) in tiles and (m < 256 or n == 128)
+    L = tw.lib()
+    assert L.tw_gemm_tile_choice(16, 16, 16, tw.B_NK, 256, 0, None, None) == OK
+    for bad in ((0, 16, 16, 0, 256), (16, 0, 16, 0, 256), (16, 16, -8, 0, 256), (16, 16, 16, 2, 256), (16, 16, 16, 0, 0)):
+        assert L.tw_gemm_tile_choice(*bad, 0, None, None) == E_SHAPE, bad
 
 
 def test_overlap_launch_argument_checks():

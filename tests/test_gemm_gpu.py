@@ -60,21 +60,21 @@ def test_gemm_both_layouts_give_the_same_bits(tw, torch_cuda):
     assert np.array_equal(to_bits(C1), to_bits(C2))
 
 
-@pytest.mark.parametrize("M,N,K,budget", [(4096, 4096, 2048, 0), (1000, 1096, 520, 10), (2304, 2048, 4104, 72),
-                                          (513, 520, 96, 9), (512, 512, 40, 4), (768, 1024, 64, 6), (520, 264, 200, 3)])
-def test_gemm_large_product_tiles_give_the_same_bits(tw, torch_cuda, M, N, K, budget):
-    """A large product launched on its own takes 256 x 256 tiles (four waves of 128 x 128, K steps of 64
-    through a ring of five LDS slots) where those fill the compute units of the launch; stored [K x N] the same
-    product always takes the 256 x 128 ones. Same bits (ragged edges and a K that is no multiple of the
-    K step included), checked against the oracle on sampled outputs."""
+@pytest.mark.parametrize("M,N,K,budget,tile_nk,tile_kn", [
+    (4096, 4096, 2048, 0, (256, 256), (256, 128)), (1000, 1096, 520, 10, (256, 256), (256, 128)),
+    (2304, 2048, 4104, 72, (256, 256), (256, 128)), (513, 520, 96, 9, (256, 192), (192, 128)),
+    (512, 512, 40, 4, (256, 256), (256, 128)), (768, 1024, 64, 6, (256, 256), (256, 128)),
+    (520, 264, 200, 3, (256, 128), (192, 128))])
+def test_gemm_large_product_tiles_give_the_same_bits(tw, torch_cuda, M, N, K, budget, tile_nk, tile_kn):
+    """The tiles of large products launched on their own: 256 x 256 and 256 x 192 (four waves, K steps of 64,
+    three LDS slots for A and two for B), and the 256 x 128 and 192 x 128 ones that the same product takes when
+    it is stored [K x N]. Same bits (ragged edges and a K that is no multiple of the K step included),
+    checked against the oracle on sampled outputs."""
     a = W.make_gemm_inputs(M, K, N, 0.05, seed=M + K, b_layout="nk")
     b = W.make_gemm_inputs(M, K, N, 0.05, seed=M + K, b_layout="kn")
-    cus = tw.device_cu_count()
-    use = budget if 0 < budget < cus else cus
-    fill = lambda tiles: tiles / (-(-tiles // use) * use)
-    tm = -(-M // 256)
-    assert 2 * tm * -(-N // 128) > use and fill(tm * -(-N // 256)) >= fill(tm * -(-N // 128)) - 0.05, \
-        "the case is meant to take the 256 x 256 tiles"
+    use = budget or tw.device_cu_count()
+    assert tw.gemm_tile_choice(M, N, K, tw.B_NK, use) == tile_nk, "the case is meant to take other tiles"
+    assert tw.gemm_tile_choice(M, N, K, tw.B_KN, use) == tile_kn
     C = torch_cuda.full((M, N), float("nan"), dtype=torch_cuda.bfloat16, device="cuda:0")
     tw.gemm_bf16(to_gpu(a["A"]), to_gpu(a["B"]), C=C, b_layout=tw.B_NK, cu_budget=budget)
     C2 = tw.gemm_bf16(to_gpu(b["A"]), to_gpu(b["B"]), b_layout=tw.B_KN, cu_budget=budget)
@@ -135,7 +135,8 @@ def test_gemm_from_one_k_step_to_past_the_pipeline(tw, torch_cuda, M, N, layout)
 
 def test_gemm_k_zero_gives_zeros(tw, torch_cuda):
     torch = torch_cuda
-    for (M, N, budget) in ((40, 24, 0), (512, 512, 4)):      # the second takes the 256 x 256 tiles
+    for (M, N, budget) in ((40, 24, 0), (512, 512, 4)):      # 256 x 128 tiles, and 256 x 256
+        assert tw.gemm_tile_choice(M, N, 0, tw.B_NK, budget or 256) == (256, 256 if budget else 128)
         A = torch.empty((M, 0), dtype=torch.bfloat16, device="cuda:0")
         B = torch.empty((N, 0), dtype=torch.bfloat16, device="cuda:0")
         C = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda:0")
@@ -145,11 +146,9 @@ def test_gemm_k_zero_gives_zeros(tw, torch_cuda):
 
 
 def test_gemm_at_the_largest_k(tw, torch_cuda):
-    """K = 2^22, the deepest product the entry point accepts: rows of 8 MiB, a full 256-row tile of A is
-    2 GiB, and every byte offset inside it still has to fit the 32 bits a buffer instruction adds up.
-    Inputs drawn on the GPU; rows 0, 63, 64, 191 and 255 of the tile (the first and last rows of the
-    first, second and last load instruction) and two rows of a ragged second tile against the fp64
-    product of those rows."""
+    """K = 2^22, the deepest product the entry point accepts, on the whole device: 16 x 16 tiles, whose rows
+    of A start up to 2 GiB into it. Inputs drawn on the GPU; rows from the first to the last tile against the
+    fp64 product of those rows."""
     torch = torch_cuda
     M, N, K, std = 256 + 3, 16, 1 << 22, 0.02
     gen = torch.Generator(device="cuda:0")
@@ -166,14 +165,88 @@ def test_gemm_at_the_largest_k(tw, torch_cuda):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("layout", ["nk", "kn"])
-def test_gemm_taller_than_four_gib(tw, torch_cuda, layout):
-    """M = 1.1 M rows: C is 4.5 GB, so tile base addresses run past 2^32 bytes (row 1048576 of C starts
-    there, row 524288 at 2^31; A passes 2^30 at row 1048576). Rows around those seams, the first, the
-    last (a ragged tile) and random ones against the fp64 product of those rows; [N x K] operands take
-    the 256 x 256 tiles, [K x N] the 256 x 128 ones."""
+def _every_tile_shape():
+    for rows, cols in NK_TILES:
+        for layout in ("nk", "kn") if (rows, cols) in KN_TILES else ("nk",):
+            yield rows, cols, layout
+
+
+# the tile shapes that are built, by layout of B (and, below, sizes and budgets that take each of them)
+KN_TILES = [(32, 32), (64, 32), (64, 64), (96, 64), (96, 128), (192, 64), (128, 128), (192, 128), (256, 128)]
+NK_TILES = [(16, 16), (32, 16), (96, 96), (256, 64), (256, 192), (256, 256)] + KN_TILES
+
+
+@pytest.mark.parametrize("rows,cols,layout", list(_every_tile_shape()))
+def test_gemm_full_tile_of_the_largest_k(tw, torch_cuda, rows, cols, layout):
+    """One full tile of each shape at K = 2^22: rows of 8 MiB, so that a tile of 256 rows is 2 GiB of A (and
+    one of 256 columns 2 GiB of B), and every byte offset inside it still has to fit the 32 bits a buffer
+    instruction adds up. On one compute unit, which makes each shape the choice for its own size. The first
+    and last rows and columns and some between against the fp64 product, and all of it against the bits of
+    the tiles that the whole device takes."""
     torch = torch_cuda
-    M, N, K, std = 1100000 + 37, 2048, 512, 0.05
+    K, std = 1 << 22, 0.02
+    code = tw.B_NK if layout == "nk" else tw.B_KN
+    assert tw.gemm_tile_choice(rows, cols, K, code, 1) == (rows, cols)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(rows + cols)
+    A = torch.empty((rows, K), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, std, generator=gen)
+    Bnk = torch.empty((cols, K), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, std, generator=gen)
+    B = Bnk if layout == "nk" else Bnk.t().contiguous()
+    C = torch.full((rows, cols), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    tw.gemm_bf16(A, B, C=C, b_layout=code, cu_budget=1)
+    other = tw.gemm_bf16(A, B, b_layout=code)
+    torch.cuda.synchronize()
+    assert rows * cols <= 1024 or tw.gemm_tile_choice(rows, cols, K, code, tw.device_cu_count()) != (rows, cols)
+    assert np.array_equal(to_bits(C), to_bits(other))
+    ms, ns = [0, rows // 2, rows - 1], [0, cols // 2 - 1, cols - 1]
+    ref = oracle.gemm(to_bits(A[ms]), to_bits(Bnk[ns]), "nk")
+    gemm_check(oracle.bf16_to_f64(to_bits(C[ms][:, ns])), ref, K, std, "%d x %d tile at K = 2^22" % (rows, cols))
+    del A, B, Bnk, C
+    torch.cuda.empty_cache()
+
+
+# (tile, layouts, M, N, K, budget): ragged, several tiles per workgroup and K past the pipeline's depth where the
+# shape is ever chosen for that.
+TILE_CASES = [((16, 16), "nk", 17, 24, 1032, 4), ((16, 16), "nk", 1, 8, 200, 1),
+              ((32, 16), "nk", 33, 24, 1032, 4), ((32, 16), "nk", 17, 8, 200, 1),
+              ((32, 32), "both", 33, 40, 1032, 4), ((32, 32), "both", 1, 8, 72, 1),
+              ((64, 32), "both", 65, 40, 1032, 4), ((64, 32), "both", 33, 8, 72, 1),
+              ((64, 64), "both", 65, 72, 1032, 4), ((64, 64), "both", 1, 40, 72, 1),
+              ((96, 64), "both", 129, 72, 1032, 4), ((96, 64), "both", 1, 8, 8, 1),
+              ((96, 96), "nk", 97, 136, 1032, 4), ((96, 96), "nk", 1, 264, 72, 1),
+              ((96, 128), "both", 97, 200, 1032, 4), ((96, 128), "both", 1, 328, 72, 1),
+              ((192, 64), "both", 300, 136, 1032, 6), ((192, 64), "both", 257, 8, 72, 1),
+              ((128, 128), "both", 193, 136, 1032, 4), ((128, 128), "both", 97, 264, 72, 1),
+              ((192, 128), "both", 257, 136, 1032, 4), ((192, 128), "both", 129, 72, 200, 1),
+              ((256, 64), "nk", 389, 136, 1032, 6), ((256, 64), "nk", 389, 8, 72, 1),
+              ((256, 128), "kn", 389, 136, 1032, 1), ((256, 128), "nk", 389, 136, 1032, 4),
+              ((256, 128), "kn", 389, 8, 72, 1), ((256, 128), "nk", 257, 72, 72, 1),
+              ((256, 192), "nk", 257, 264, 1032, 4), ((256, 192), "nk", 257, 136, 72, 1),
+              ((256, 256), "nk", 257, 712, 1032, 2), ((256, 256), "nk", 257, 200, 72, 1)]
+
+
+@pytest.mark.parametrize("tile,layouts,M,N,K,budget", TILE_CASES)
+def test_gemm_every_tile_shape(tw, torch_cuda, tile, layouts, M, N, K, budget):
+    for layout in ("nk", "kn") if layouts == "both" else (layouts,):
+        code = tw.B_NK if layout == "nk" else tw.B_KN
+        assert tw.gemm_tile_choice(M, N, K, code, budget) == tile
+        g = W.make_gemm_inputs(M, K, N, 0.5, seed=M + N + K, b_layout=layout)
+        C = torch_cuda.full((M, N), float("nan"), dtype=torch_cuda.bfloat16, device="cuda:0")
+        tw.gemm_bf16(to_gpu(g["A"]), to_gpu(g["B"]), C=C, b_layout=code, cu_budget=budget)
+        torch_cuda.cuda.synchronize()
+        ref = oracle.gemm(g["A"], g["B"], layout)
+        gemm_check(oracle.bf16_to_f64(to_bits(C)), ref, K, 0.5, "%s tiles, %s %dx%dx%d" % (tile, layout, M, N, K))
+
+
+@pytest.mark.parametrize("layout,K,tile", [("nk", 512, (256, 128)), ("nk", 2048, (256, 256)), ("kn", 512, (256, 128))])
+def test_gemm_taller_than_four_gib(tw, torch_cuda, layout, K, tile):
+    """M = 1.1 M rows: C is 4.5 GB, so tile base addresses run past 2^32 bytes (row 1048576 of C starts
+    there, row 524288 at 2^31; A passes 2^30 at row 1048576, and 2^32 at K = 2048). Rows around those seams,
+    the first, the last (a ragged tile) and random ones against the fp64 product of those rows, for the two
+    tile shapes that such a product takes."""
+    torch = torch_cuda
+    M, N, std = 1100000 + 37, 2048, 0.05
+    assert tw.gemm_tile_choice(M, N, K, tw.B_NK if layout == "nk" else tw.B_KN, tw.device_cu_count()) == tile
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(5)
     A = torch.empty((M, K), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, std, generator=gen)
@@ -242,9 +315,9 @@ def test_overlap_launch_shared_mode_equals_the_two_calls(tw, torch_cuda, M, K, N
     the GEMM's. Same bits as the plain calls, on every one of many launches: next
     to the fused kernel the GEMM's LDS reads and loads take longer, which is when
     a missing wait shows (C starts as NaNs, so a store that went astray is seen).
-    The shapes cover the narrow tiles (at most half of the compute units filled by
-    wide ones) and the wide tiles, for both storage orders of B (the [K x N] one
-    reads its fragments with the transposing LDS read and has waits of its own)."""
+    The shapes take 96 x 96 (or 96 x 128) tiles, 96 x 128 and 256 x 128 ones, for both
+    storage orders of B (the [K x N] one reads its fragments with the transposing LDS
+    read and has waits of its own)."""
     torch = torch_cuda
     cfg = W.CONFIGS["c5_overlap_tp8"]
     d = W.make_fused_inputs(cfg, N=1024)
@@ -254,7 +327,10 @@ def test_overlap_launch_shared_mode_equals_the_two_calls(tw, torch_cuda, M, K, N
     bl = tw.B_NK if layout == "nk" else tw.B_KN
     A, B = to_gpu(gm["A"]), to_gpu(gm["B"])
     out0, res0 = tw.reduce_add_rmsnorm(g["partials"], g["residual"], g["weight"], g["eps"], cu_budget=32)
-    C0 = tw.gemm_bf16(A, B, b_layout=bl, cu_budget=16)      # alone, wide tiles
+    C0 = tw.gemm_bf16(A, B, b_layout=bl, cu_budget=16)      # alone, 256-row tiles
+    assert tw.gemm_tile_choice(M, N, K, bl, 16)[0] == 256
+    beside = {1536: (96, 96) if layout == "nk" else (96, 128), 1280: (96, 128), 4096: (96, 128) if M == 512 else (256, 128)}
+    assert tw.gemm_tile_choice(M, N, K, bl, tw.device_cu_count(), beside_other_kernels=True) == beside[N]
     torch.cuda.synchronize()
     assert np.array_equal(to_bits(tw.gemm_bf16(A, B, b_layout=bl)), to_bits(C0))
     if layout == "kn":      # and the same bits as the other storage order of the same matrix
@@ -273,7 +349,7 @@ def test_overlap_launch_shared_mode_equals_the_two_calls(tw, torch_cuda, M, K, N
                                   use_parent=True, join=True)
             else:
                 # the two calls made by hand on two streams: tw_gemm_bf16 picks its tiles as for a
-                # launch on its own (the narrow ones where few wide tiles would fill the device)
+                # launch on its own
                 comp.wait_stream(parent)
                 comm.wait_stream(parent)
                 tw.gemm_bf16(A, B, C=C, b_layout=bl, cu_budget=0, stream=comp)
