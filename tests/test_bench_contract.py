@@ -2,6 +2,7 @@
 the line it prints."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -41,6 +42,25 @@ def test_traffic_figure_matches_the_profile_it_cites_and_the_kernel_it_was_taken
         assert tp["kernel_source_sha256_12"] == current, (
             "tw_fused.hip / tw_device.h changed since %s was taken: take the counter profile again and "
             "update TRAFFIC_FROM_PROFILE" % tp["profile"])
+
+
+def test_measurements_beside_the_headline_stay_out_of_the_line():
+    """The line has to be short: its readers keep the last 8000 characters of the output, and a longer line
+    is no JSON to them. However much else a run measures, the line holds the contract's fields, the roofline,
+    the CPU baseline and a summary of the overlap."""
+    sys.path.insert(0, ROOT)
+    import bench
+    source = open(BENCH).read()
+    extras = sorted(set(re.findall(r'result\["(\w+)"\] =', source)) - {"cpu_baseline"})
+    assert "overlap" in extras and len(extras) > 8
+    result = {k: "x" * 100 for k in bench.HEADLINE_KEYS}
+    result.update({k: {"rows": [{"us": 1.0 / 3}] * 500} for k in extras})
+    summary = re.findall(r'"(\w+)"', source[source.index('line["overlap_makespan"] = '):source.index("return line, details")])
+    result["overlap"].update({k: "x" * 100 for k in summary})
+    line, details = bench.headline(result)
+    assert sorted(details) == extras and not set(line) & set(extras)
+    assert set(bench.HEADLINE_KEYS) <= set(line) and len(line["overlap_makespan"]) == 9
+    assert len(json.dumps(line)) < 5000
 
 
 @pytest.mark.gpu
