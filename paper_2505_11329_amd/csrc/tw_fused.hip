@@ -69,8 +69,33 @@ struct FusedParams {
 // The P+1 vectors that feed one output vector, in flight.
 template <int PT>
 struct Chunk {
-    u32x4 v[PT + 1];
+    u32x4 v[PT > 0 ? PT + 1 : 1];
 };
+
+// Kernels for a P known only at run time, in the place of P: a multiple of the loop's batch, or
+// any number (1 to 5 % slower on short launches, for the padding's sign).
+static constexpr int kAnyWhole = 0, kAnyPadded = -1;
+static constexpr int kWideBatch = 4;
+
+// Adds partials p0 ... p0 + BATCH - 1 to x, all requested at once. PAD: there may be fewer. Past
+// the last one a load through a zero-length descriptor fetches nothing and reads as +0.0, and
+// what is added is -0.0, the one value that leaves any sum as it is (a sum of -0.0 as well), so
+// that a row's bits are those of the kernels without padding. (A branch around the addition in
+// its place: up to 25 % slower. Without PAD every partial is live; with the selects left out
+// the compiler orders the loads otherwise, 1 to 3 % slower.)
+template <int BATCH, bool PAD>
+__device__ __forceinline__ void add_batch(const FusedParams &prm, int p0, uint32_t lane_off, uint32_t scalar_off, float (&x)[8])
+{
+    u32x4 t[BATCH];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+        const bool live = p0 + i < prm.P;
+        t[i] = ld(make_rsrc(prm.partials[live ? p0 + i : 0], live ? prm.n_bytes : 0u), lane_off, scalar_off);
+    }
+    if (p0 == 0) unpack8(t[0], x); else add8(t[0], x);
+#pragma unroll
+    for (int i = 1; i < BATCH; ++i) add8(PAD ? t[i] | (p0 + i < prm.P ? 0u : 0x80008000u) : t[i], x);
+}
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
 template <int... I, typename F>
@@ -84,7 +109,7 @@ __device__ __forceinline__ void each_chunk(std::integer_sequence<int, I...>, F &
 template <int PT, int VPT>
 constexpr int buffers_in_flight()
 {
-    return (PT == 0) ? 1 : (((PT + 1) * 8 + 12 * VPT <= (VPT == 2 ? 100 : 92)) ? 2 : 1);
+    return (PT <= 0) ? 1 : (((PT + 1) * 8 + 12 * VPT <= (VPT == 2 ? 100 : 92)) ? 2 : 1);
 }
 
 template <int PT, int VPT, bool TRACE, bool STREAMED>
@@ -178,22 +203,9 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
             for (int p = 1; p < PT; ++p) add8(c.v[p], x);
             add8(c.v[PT], x);
         } else {
-            // P known only at run time: four loads at a time, padded with
-            // zero-length descriptors (which read as +0.0 and fetch nothing).
-            // (Eight at a time measured 4 % slower at P = 12 and 16.)
-            constexpr int kBatch = 4;
+            // four at a time (eight at a time measured 4 % slower at P = 12 and 16)
             const u32x4 r = ld(r_res, off);
-            for (int p0 = 0; p0 < prm.P; p0 += kBatch) {
-                u32x4 t[kBatch];
-#pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    const bool live = p0 + i < prm.P;
-                    t[i] = ld(make_rsrc(prm.partials[live ? p0 + i : 0], live ? prm.n_bytes : 0u), off);
-                }
-                if (p0 == 0) unpack8(t[0], x); else add8(t[0], x);
-#pragma unroll
-                for (int i = 1; i < kBatch; ++i) add8(t[i], x);
-            }
+            for (int p0 = 0; p0 < prm.P; p0 += kWideBatch) add_batch<kWideBatch, PT == kAnyPadded>(prm, p0, off, 0, x);
             add8(r, x);
         }
     };
@@ -408,22 +420,13 @@ __device__ __forceinline__ void thin_body(const FusedParams &prm)
             for (int p = 1; p < PT; ++p) add8(c.v[p], x);
             add8(c.v[PT], x);
         } else {
-            // any P: eight loads at a time, padded with zero-length descriptors; a
-            // thread here has four times the wide kernel's work per row and fewer
-            // waves to hide a round trip behind (four at a time: 10-25 % slower)
-            constexpr int kBatch = 8;
+            // eight at a time: a thread here has four times the wide kernel's work per row and
+            // fewer waves to hide a round trip behind (four at a time: 10-25 % slower); the
+            // padded batch on its own (1 to 3 % faster than padding in every one)
             const u32x4 r = ld(r_res, off.lane, off.scalar);
-            for (int p0 = 0; p0 < prm.P; p0 += kBatch) {
-                u32x4 t[kBatch];
-#pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    const bool live = p0 + i < prm.P;
-                    t[i] = ld(make_rsrc(prm.partials[live ? p0 + i : 0], live ? prm.n_bytes : 0u), off.lane, off.scalar);
-                }
-                if (p0 == 0) unpack8(t[0], x); else add8(t[0], x);
-#pragma unroll
-                for (int i = 1; i < kBatch; ++i) add8(t[i], x);
-            }
+            int p0 = 0;
+            for (; p0 + 8 <= prm.P; p0 += 8) add_batch<8, false>(prm, p0, off.lane, off.scalar, x);
+            if (p0 < prm.P) add_batch<8, true>(prm, p0, off.lane, off.scalar, x);
             add8(r, x);
         }
     };
@@ -614,7 +617,7 @@ template <int PT, int VPT>
 static tw_status launch_t(const FusedParams &prm, bool trace, bool streamed, int64_t grid, int block, hipStream_t stream)
 {
     auto kern = streamed ? fused_kernel<PT, VPT, false, true> : fused_kernel<PT, VPT, false, false>;
-    if constexpr (PT == 0 || kTracedP<PT>)
+    if constexpr (PT <= 0 || kTracedP<PT>)
         if (trace) kern = fused_kernel<PT, VPT, true, false>;
     static std::atomic<int> allowed[2][kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kOccupancyPadBytes),
@@ -629,7 +632,7 @@ static tw_status launch_thin_t(const FusedParams &prm, bool trace, bool streamed
                                hipStream_t stream)
 {
     auto kern = streamed ? fused_thin_kernel<PT, Q, false, true> : fused_thin_kernel<PT, Q, false, false>;
-    if constexpr (PT == 0 || kTracedP<PT>)
+    if constexpr (PT <= 0 || kTracedP<PT>)
         if (trace) kern = fused_thin_kernel<PT, Q, true, false>;
     TW_HIP(launch_kernel(kern, dim3(static_cast<unsigned>(grid)), dim3(kThinThreads), 0u, stream, prm));
     return TW_OK;
@@ -710,7 +713,7 @@ static int64_t thin_grid(int64_t n_rows, const ThinGeometry &t, int cus)
 // same order of additions) does.
 static constexpr bool wide_fits(int P, int vpt)
 {
-    return P == 0 || vpt == 1 || (vpt <= 4 ? P <= 8 : P == 1 || P == 2 || P == 4);
+    return P <= 0 || vpt == 1 || (vpt <= 4 ? P <= 8 : P == 1 || P == 2 || P == 4);
 }
 template <int PT, int VPT>
 static constexpr bool wide_fits()
@@ -890,13 +893,14 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
                            (thin ? thin_loops(a.P, g, row_end - row_begin, cus)
                                  : !wide_fits(a.P, g.vpt) || wide_loops(a.P, g, grid, prm.n_groups, a.N * row_bytes));
         if (thin) {
-            if (any_p) TW_TRY((launch_thin<0>(prm, tg.q, trace, streamed, false, grid, stream)));
+            if (any_p) TW_TRY((launch_thin<kAnyPadded>(prm, tg.q, trace, streamed, false, grid, stream)));
             else
                 TW_TRY(with_partials(a.P, [&](auto pt) {
                     return launch_thin<decltype(pt)::value>(prm, tg.q, trace, streamed, deep, grid, stream);
                 }));
         } else {
-            if (any_p) TW_TRY((launch_vpt<0>(prm, g, trace, streamed, grid, stream)));
+            if (any_p && a.P % kWideBatch == 0) TW_TRY((launch_vpt<kAnyWhole>(prm, g, trace, streamed, grid, stream)));
+            else if (any_p) TW_TRY((launch_vpt<kAnyPadded>(prm, g, trace, streamed, grid, stream)));
             else
                 TW_TRY(with_partials(a.P, [&](auto pt) {
                     return launch_vpt<decltype(pt)::value>(prm, g, trace, streamed, grid, stream);

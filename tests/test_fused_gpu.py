@@ -322,6 +322,23 @@ def test_zero_rows_and_zero_eps(tw, torch_cuda):
     check_against_oracle(d, out, res, "eps>0 with a zero row")
 
 
+@pytest.mark.parametrize("H", [512, 2048, 5120, 8192, 16384])
+def test_a_sum_of_negative_zeros_keeps_its_sign_in_every_launch(tw, torch_cuda, H):
+    """-0.0 + -0.0 = -0.0: whichever kernel a launch takes for a number of partials, with a loop over them that is
+    padded to whole batches or without, and whatever is padded. (One row of other values beside it.)"""
+    torch = torch_cuda
+    for P in (2, 3, 5, 7, 8, 9, 11, 12, 13, 14, 16):
+        for N in (2, 600):
+            t = torch.full((N, H), -0.0, dtype=torch.bfloat16, device="cuda:0")
+            t[1] = 1.0
+            w = torch.ones((H,), dtype=torch.bfloat16, device="cuda:0")
+            for budget in (3, 0, tw.CU_SHARED, 64):
+                out, res = run(tw, torch, dict(partials=[t] * P, residual=t, weight=w, eps=1e-5), cu_budget=budget)
+                for got in (out, res):
+                    assert (np.delete(got, 1, axis=0) == 0x8000).all(), (P, N, budget)
+                assert (res[1] == to_bits(torch.tensor([P + 1.0], dtype=torch.bfloat16, device="cuda:0"))[0]).all()
+
+
 def test_empty_batch(tw, torch_cuda):
     torch = torch_cuda
     z = torch.empty((0, 512), dtype=torch.bfloat16, device="cuda:0")
