@@ -41,13 +41,13 @@ TRAFFIC_FROM_PROFILE = {
         "profile": "profiles/fused_kernel_c3_70b_shard_tp8_budget32.md",
         "kernel": "tw::fused_kernel<8, 1, false, false>",
         "fetched_KiB": 147717, "written_KiB": 32768,
-        "kernel_source_sha256_12": "0b707642662b",
+        "kernel_source_sha256_12": "18f8a1c4b5b0",
     },
     (WORKLOAD, 0): {
         "profile": "profiles/fused_kernel_c3_whole_device_and_shared.md",
         "kernel": "tw::fused_thin_kernel<8, 4, false, false>",
         "fetched_KiB": 147681, "written_KiB": 32750,
-        "kernel_source_sha256_12": "0b707642662b",
+        "kernel_source_sha256_12": "18f8a1c4b5b0",
     },
 }
 KERNEL_SOURCES = ("paper_2505_11329_amd/csrc/tw_fused.hip", "paper_2505_11329_amd/csrc/tw_device.h")
@@ -108,7 +108,7 @@ def main():
     ap.add_argument("--counters-run", choices=("fused", "gemm", "weave", "probe", "train"), default=None,
                     help="for rocprofv3 --pmc. fused: a few fused launches plus plain copy launches of known "
                          "size (tw_hbm_probe, 192 MiB read + 192 MiB written each) to scale the byte counters "
-                         "by. gemm: a few launches of the bf16 GEMM on the overlap demo's shape. weave (for "
+                         "by. gemm: a few launches of the bf16 GEMM on products of seven tile shapes. weave (for "
                          "rocprofv3 --kernel-trace): the T=4096 layer boundary unsplit, then woven in the "
                          "ordered schedule, then as one chain per split, five calls each with a device "
                          "synchronisation after every call, so that the trace shows which kernels overlap")
@@ -418,23 +418,29 @@ def main():
                           "order": ["unsplit"] * 3 + ["woven"] * 3}))
         return
     if args.counters_run == "gemm":
-        # the three tile shapes the library builds: the overlap demo's product takes 256 x 128 tiles, the
-        # MLP-side down projection of the same layer ([2048 x 8192] x [8192 x 1280], 80 wide tiles) 256 x 64,
-        # a large square product 256 x 256
+        # from a large square product down to a decode step's, one tile shape each, and one product whose
+        # weights are stored [K x N]; weights rotate so that they come from HBM (where they exceed the cache by
+        # themselves, one set does)
         gc = W.CONFIGS["c5_overlap_tp8"]["gemm"]
-        shapes = [(gc["M"], gc["K"], gc["N"]), (gc["M"], gc["K"], 1280), (8192, 8192, 8192)]   # the last: 256 x 256
-        for (M, K, N) in shapes:
+        shapes = [(8192, 8192, 8192, "nk"), (8192, 8192, 1280, "nk"), (gc["M"], gc["K"], gc["N"], "nk"),
+                  (gc["M"], gc["K"], 1280, "nk"), (333, 8192, 3584, "nk"), (16, 8192, 3584, "nk"),
+                  (3001, 4104, 4096, "kn")]
+        for (M, K, N, layout) in shapes:
             gen = torch.Generator(device=dev)
             gen.manual_seed(M + N)
             A = torch.empty((M, K), dtype=torch.bfloat16, device=dev).normal_(0.0, gc["std"], generator=gen)
-            B = torch.empty((N, K), dtype=torch.bfloat16, device=dev).normal_(0.0, gc["std"], generator=gen)
+            Bs = [torch.empty((N, K) if layout == "nk" else (K, N), dtype=torch.bfloat16,
+                              device=dev).normal_(0.0, gc["std"], generator=gen)
+                  for _ in range(max(1, min(12, (300 << 20) // (N * K * 2))))]
             C = torch.empty((M, N), dtype=torch.bfloat16, device=dev)
             torch.cuda.synchronize()
             for i in range(12):
-                tw.gemm_bf16(A, B, C=C, cu_budget=0, stream=stream)
+                tw.gemm_bf16(A, Bs[i % len(Bs)], C=C, b_layout=tw.B_NK if layout == "nk" else tw.B_KN, stream=stream)
             torch.cuda.synchronize()
         print(json.dumps({"counters_run": "gemm", "launches_per_shape": 12,
-                          "flops_per_launch": [2.0 * M * K * N for (M, K, N) in shapes]}))
+                          "products": ["%d x %d x %d %s" % s for s in shapes],
+                          "tiles": [tw.gemm_tile_choice(M, N, K, tw.B_NK if layout == "nk" else tw.B_KN)
+                                    for (M, K, N, layout) in shapes]}))
         return
     if args.counters_run == "probe":
         # plain streaming kernels with the fused kernel's budgeted launch shape, for the L1 request counters

@@ -311,8 +311,9 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
 // on the same compute unit (256 threads, at most 128 VGPRs, 128 bytes of LDS): the
 // "shared" launch mode. Instead of taking a few compute units away from the
 // GEMM, the fused kernel is spread thinly over all of them and uses the HBM
-// bandwidth the matrix-core-bound GEMM leaves idle. (The GEMM's two waves per
-// SIMD hold 2 x 167 registers per lane, which leaves room for one such wave.)
+// bandwidth the matrix-core-bound GEMM leaves idle. (The two waves per SIMD of a
+// GEMM on 256 x 128 tiles hold 2 x 152 of a lane's 512 registers, [K x N] 2 x 160,
+// which leaves room for one such wave.)
 //
 // Bits are identical to fused_kernel's: a thread here plays Q (a row's vectors
 // over 256, rounded up: 1 ... 4) of the wide kernel's threads (columns tid,
@@ -619,9 +620,9 @@ static tw_status launch_t(const FusedParams &prm, bool trace, bool streamed, int
     auto kern = streamed ? fused_kernel<PT, VPT, false, true> : fused_kernel<PT, VPT, false, false>;
     if constexpr (PT <= 0 || kTracedP<PT>)
         if (trace) kern = fused_kernel<PT, VPT, true, false>;
-    static std::atomic<int> allowed[2][kMaxDevices];
+    static std::atomic<int> allowed[3][kMaxDevices];  // a kernel each: plain, streamed, traced
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kOccupancyPadBytes),
-                             allowed[trace]));
+                             allowed[kern == fused_kernel<PT, VPT, false, false> ? 0 : trace ? 2 : 1]));
     TW_HIP(launch_kernel(kern, dim3(static_cast<unsigned>(grid)), dim3(static_cast<unsigned>(block)),
                          kOccupancyPadBytes, stream, prm));
     return TW_OK;
