@@ -586,8 +586,8 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         // columns wide or more) instead of sixteen rows of 32 bytes, with half as many
         // store instructions. And no global store is in flight while the accumulators
         // are read: with all 256 accumulator registers of the 256 x 256 tile taken the
-        // register allocator spills one, and a reload in the middle of the stores would
-        // wait for all of them.
+        // register allocator spills (13, none in the K loop), and a reload in the middle of
+        // the stores would wait for all of them.
         constexpr int kRowPitch = kBlk * WN * 2 + 32;
         constexpr int kRegion = kBlk * WM * kRowPitch;
         // A row of the sub-tile goes out as runs of kPieces 16-byte pieces (a row of 96 columns in three runs of 64 bytes).
@@ -738,13 +738,13 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, bool beside_oth
     // fetch every 128-byte line of A and B in two halves a K step apart, by which time the
     // line has left the L1: twice the L2 requests, and 27 % more cycles); 256 x 192, four
     // waves of 128 x 96 in the same schedule, where its tiles fill whole turns of the compute
-    // units and the others do not ([8192 x 8192] x [8192 x 1280]: 158 -> 130 us); and the smaller shapes of
-    // tw_gemm_tile.hip. The costs are us per 64-deep K step of a tile with every compute unit busy,
+    // units and the others do not ([8192 x 8192] x [8192 x 1280]: 158 -> 127 to 137 us); and the smaller
+    // shapes of tw_gemm_tile.hip. The costs are us per 64-deep K step of a tile with every compute unit busy,
     // measured on MI355X; with few of them busy the part clocks up to a quarter higher (the
     // 256 x 128 tiles, bound by what a unit takes in, gain nothing from that). Each further turn
-    // adds a fill and stores: the costs per turn decide where K is small, and are those that lose
-    // least over 760 products of 100 to 8192 rows, K and N 256 to 8192 (every shape timed: the
-    // choice is 0.5 % off the best on average; 6706 x 3208, K = 280: 29.7 -> 23.8 us).
+    // adds a fill and stores: the costs per turn decide where K is small. They were fitted to 760
+    // products with every shape timed; over 1160 of 100 to 8192 rows, K and N 256 to 8192, the
+    // choice is 0.5 % off the best on average (6706 x 3208, K = 280: 29.7 -> 23.8 us).
     //
     // Next to other kernels (tw_overlap_launch, the split schedules of
     // tw_weave_layer) the 256 x 128 tiles are kept unless a smaller shape is ahead: the

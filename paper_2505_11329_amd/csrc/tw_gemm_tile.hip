@@ -5,16 +5,16 @@
 // products (v_mfma_f32_16x16x32_bf16) in the order of increasing k, so K is never
 // split, and parallelism comes from the tile shape alone.
 //
-// What bounds it: what a compute unit can pull into its LDS. Whatever the tile, and
-// whether its operands come from HBM or from the L2, a compute unit takes in 60 to
-// 85 GB/s (about 19 KB of requests in flight, 0.25 to 0.33 us a round trip), so a
-// tile of BM x BN outputs costs (BM + BN) * K * 2 bytes of that, and the best shape
-// is the smallest that still gives every compute unit at most one tile. A kernel
-// with the LDS reads and matrix instructions taken out ran within 4 to 13 % of the
-// whole. Tried and not kept: fetching lines into the L2 ahead of time, each
-// workgroup a share of the panels its XCD reads (3 to 20 % slower); rotating the
-// order in which the workgroups of an XCD ask for a shared panel's rows (nothing at
-// these sizes).
+// What bounds it: what a compute unit can pull into its LDS. Whatever the tile, a
+// compute unit takes in 64 to 72 GB/s of operands (90 to 100 requests, 11 to 13 KB,
+// in flight, 370 to 420 clocks each, four fifths of them L2 hits; with the weights
+// from HBM 43 GB/s over a launch of 12 us), so a tile of BM x BN outputs costs (BM +
+// BN) * K * 2 bytes of that, and the best shape is the smallest that still gives
+// every compute unit at most one tile. A kernel with the LDS reads and matrix
+// instructions taken out ran within 4 to 13 % of the whole. Tried and not kept:
+// fetching lines into the L2 ahead of time, each workgroup a share of the panels its
+// XCD reads (3 to 20 % slower); rotating the order in which the workgroups of an XCD
+// ask for a shared panel's rows (nothing at these sizes).
 //
 // Measured on MI355X, weights from HBM, us (the 256-row tiles before / now / the
 // vendor library): [16 x 8192] x [8192 x 3584] 64 / 13.1 / 20 (59 MB of weights: 4.5
