@@ -112,9 +112,47 @@ constexpr int buffers_in_flight()
     return (PT <= 0) ? 1 : (((PT + 1) * 8 + 12 * VPT <= (VPT == 2 ? 100 : 92)) ? 2 : 1);
 }
 
-template <int PT, int VPT, bool TRACE, bool STREAMED>
-__global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
+// Helpers of a short launch. A compute unit has some 150 lines of 128 bytes outstanding and gets
+// them back in the order it asked, so the one that works on a row waits for HBM once per 150 of
+// the row's (P + 1) * H / 64 lines, while the units that got no row idle. The workgroups from
+// helper_base() on therefore ask for a row group's lines, a dword of each, all at the same time,
+// from the XCD of the workgroup that owns the group (workgroups are dealt to the eight XCDs in turn),
+// which then finds all but its first requests in that XCD's L2. Nothing depends on it: a helper
+// on another XCD, or a late one, only helps less.
+__host__ __device__ __forceinline__ uint32_t helper_base(uint32_t n_groups) { return (n_groups + 7u) & ~7u; }
+static constexpr uint32_t kHelperBytes = 64 * 128;  // what one load of a wave asks for
+// Loads that ask for a group's rows of the P partials and the residual, and for the weights.
+__host__ __device__ __forceinline__ uint32_t helper_pieces(uint32_t group_bytes, int P)
 {
+    return (group_bytes + kHelperBytes - 1) / kHelperBytes * (P + 2);
+}
+// tensor(t): partial t, the residual (P), the weights (P + 1).
+template <typename F>
+__device__ __forceinline__ void help(uint32_t n_groups, uint32_t group_bytes, uint32_t n_bytes, int hv, int P, F &&tensor)
+{
+    const uint32_t base = helper_base(n_groups);
+    if (blockIdx.x < base) return;  // between the last row group and the first helper
+    const uint32_t share = (blockIdx.x - base) / base, group = (blockIdx.x - base) - share * base;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t piece = share * (blockDim.x >> 6) + wave;
+    const uint32_t per_tensor = (group_bytes + kHelperBytes - 1) / kHelperBytes;
+    const int t = __builtin_amdgcn_readfirstlane(piece / per_tensor);
+    if (group >= n_groups || t > P + 1) return;
+    const uint32_t at = (piece - t * per_tensor) * kHelperBytes + lane * 128u;
+    const uint32_t off = at >= group_bytes ? kOutOfRange : t <= P ? group * group_bytes + at : at;
+    const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(tensor(t), t <= P ? n_bytes : hv * 16u), off, 0, 0);
+    asm volatile("" ::"v"(v));
+}
+
+template <int PT, int VPT, bool TRACE, bool STREAMED>
+__global__ __launch_bounds__(kThreads) void fused_kernel(uint32_t n_owners, const FusedParams prm)
+{
+    if constexpr (!TRACE)
+        if (blockIdx.x >= n_owners)
+            return help(prm.n_groups, prm.group_bytes, prm.n_bytes, prm.hv, PT > 0 ? PT : prm.P, [&](int t) {
+                const int P = PT > 0 ? PT : prm.P;
+                return t < P ? prm.partials[t < P ? t : 0] : t == P ? prm.residual : prm.weight;
+            });
     constexpr bool streamed = STREAMED;  // see st()
     __shared__ float s_wave_sum[2][kWaves];
     constexpr int NB = buffers_in_flight<PT, VPT>();
@@ -273,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
 
     using Zero = std::integral_constant<int, 0>;
     using One = std::integral_constant<int, 1>;
-    uint32_t group = blockIdx.x;  // (the grid has at most n_groups workgroups)
+    uint32_t group = blockIdx.x;  // (the grid has at most n_groups workgroups, but for helpers)
     if constexpr (VPT == 1 && NB == 2) {
         // two trips ahead: the buffers alternate from trip to trip
         issue(buf[0], chunk_off(group, 0));
@@ -329,7 +367,8 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
 // 1024-row, H = 8192, P = 8 launch: 33.5 -> 32.2 us with both changes, 256 rows
 // 10.6 -> 9.7 us).
 //
-// What bounds it: HBM from a few thousand rows on; below that the chain of round
+// What bounds it: HBM from a few thousand rows on; with a row per workgroup what the
+// row's compute unit takes in (see help()); in between the chain of round
 // trips of one row. Three things lengthened the chain: each output vector's weights
 // were asked for on their own, behind the stores of the vector before, so that a row's
 // stores went out one round trip after the other; loads past the end, dropped but
@@ -352,6 +391,8 @@ static constexpr int64_t kDeepInputBytes = 6 << 20;
 // refilled. It needs ~200 registers, so it is a kernel of its own
 // (fused_deep_kernel) without the 128-register bound that lets the other one
 // sit beside a GEMM workgroup. Same arithmetic in the same order: same bits.
+static constexpr int kDeepMaxP = 8;   // most partials it has registers for
+static constexpr int kDeepFirst = 6;  // tensors whose addresses arrive in registers (see fused_deep_kernel)
 template <int PT, int Q, bool TRACE, bool STREAMED, bool DEEP>
 __device__ __forceinline__ void thin_body(const FusedParams &prm)
 {
@@ -401,10 +442,6 @@ __device__ __forceinline__ void thin_body(const FusedParams &prm)
     auto chunk_off = [&](uint32_t group, int q) -> Off {
         return {q == Q - 1 ? lane_off_last : lane_off, group * group_bytes + q * (kThinThreads * 16u)};
     };
-    auto load_w = [&](int q) {
-        return __builtin_amdgcn_raw_buffer_load_b128(r_w, q < Q - 1 || last_col < hv ? col0 * 16u : kPastTensor,
-                                                     q * (kThinThreads * 16u), 0);
-    };
     auto issue = [&](Chunk<PT> &c, Off off) {
         if constexpr (PT > 0) {
             __builtin_amdgcn_sched_barrier(0);
@@ -445,16 +482,37 @@ __device__ __forceinline__ void thin_body(const FusedParams &prm)
     constexpr int NB = DEEP ? Q : (Q % 2 == 0 && PT <= 8) ? 2 : 1;  // (registers: 128)
     static_assert(!DEEP || PT > 0, "the run-time loop over P keeps nothing in flight");
     Chunk<PT> buf[NB];
-    issue(buf[0], chunk_off(first, 0));
-    if constexpr (NB >= 2) issue(buf[1], chunk_off(first, 1));
-    if constexpr (NB >= 3) issue(buf[2], chunk_off(first, 2));
-    if constexpr (NB >= 4) issue(buf[3], chunk_off(first, 3));
-    static_assert(NB <= 4, "chunks issued above");
+    if constexpr (DEEP) {
+        // Tensor by tensor, the ones whose addresses the wave finds in registers first; the asm
+        // statement is where the others' addresses are waited for.
+        each_chunk(std::make_integer_sequence<int, PT + 1>{}, [&](auto p_tag) {
+            constexpr int p = decltype(p_tag)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            const void *from = p < PT ? prm.partials[p < PT ? p : 0] : prm.residual;
+            if constexpr (p >= kDeepFirst) asm volatile("" : "+s"(from));
+            const __amdgpu_buffer_rsrc_t r = make_rsrc(from, prm.n_bytes);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const Off at = chunk_off(first, q);
+                buf[q].v[p] = ld(r, at.lane, at.scalar);
+            }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    } else {
+        issue(buf[0], chunk_off(first, 0));
+        if constexpr (NB >= 2) issue(buf[1], chunk_off(first, 1));
+        static_assert(NB <= 2, "chunks issued above");
+    }
     u32x4 wv[Q];
     auto load_weights = [&]() {
         __builtin_amdgcn_sched_barrier(0);
+        const void *from = prm.weight;
+        if constexpr (DEEP) asm volatile("" : "+s"(from));
+        const __amdgpu_buffer_rsrc_t r = DEEP ? make_rsrc(from, static_cast<uint32_t>(hv) * 16u) : r_w;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) wv[q] = load_w(q);
+        for (int q = 0; q < Q; ++q)
+            wv[q] = __builtin_amdgcn_raw_buffer_load_b128(r, q < Q - 1 || last_col < hv ? col0 * 16u : kPastTensor,
+                                                          q * (kThinThreads * 16u), 0);
         __builtin_amdgcn_sched_barrier(0);
     };
     if constexpr (DEEP) load_weights();
@@ -531,9 +589,42 @@ void fused_thin_kernel(const FusedParams prm)
     thin_body<PT, Q, TRACE, STREAMED, false>(prm);
 }
 
+// The arguments of the form for small batches: the first fourteen words arrive in scalar
+// registers with the wave, the rest is a round trip to (host) memory away, over which the loads of
+// the first six tensors are on their way. Tensors in the order of help(): partials, residual, weights.
+struct DeepRest {
+    const void *tensor[kDeepMaxP + 2 - kDeepFirst];
+    void *out, *residual_out;
+    float eps, inv_h;
+};
+typedef uint64_t Words2 __attribute__((ext_vector_type(2)));
+typedef uint64_t Words4 __attribute__((ext_vector_type(4)));  // (few arguments: the runtime handles each on its own)
 template <int PT, int Q>
-__global__ __launch_bounds__(kThinThreads) void fused_deep_kernel(const FusedParams prm)
+__global__ __launch_bounds__(kThinThreads) void fused_deep_kernel(Words4 t0123, Words2 t45, uint64_t shape, const DeepRest rest)
 {
+    auto tensor = [&](int i) -> const void * {
+        return reinterpret_cast<const void *>(i == 0 ? t0123.x : i == 1 ? t0123.y : i == 2 ? t0123.z : i == 3 ? t0123.w : i == 4 ? t45.x : t45.y);
+    };
+    FusedParams prm;
+    prm.n_bytes = static_cast<uint32_t>(shape);
+    prm.hv = shape >> 32 & 0xfff;
+    prm.tpr_log2 = shape >> 44 & 0xf;
+    prm.n_groups = static_cast<uint32_t>(shape >> 48);
+    prm.group_bytes = (Q > 1 ? 1 : kThinThreads >> prm.tpr_log2) * prm.hv * 16u;
+    if (blockIdx.x >= prm.n_groups)
+        return help(prm.n_groups, prm.group_bytes, prm.n_bytes, prm.hv, PT,
+                    [&](int t) { return t < kDeepFirst ? tensor(t) : rest.tensor[t < kDeepFirst ? 0 : t - kDeepFirst]; });
+    each_chunk(std::make_integer_sequence<int, PT + 2>{}, [&](auto i_tag) {
+        constexpr int i = decltype(i_tag)::value;
+        const void *t = i < kDeepFirst ? tensor(i) : rest.tensor[i < kDeepFirst ? 0 : i - kDeepFirst];
+        if constexpr (i < PT) prm.partials[i] = t;
+        else if constexpr (i == PT) prm.residual = t;
+        else prm.weight = t;
+    });
+    prm.out = rest.out;
+    prm.residual_out = rest.residual_out;
+    prm.eps = rest.eps;
+    prm.inv_h = rest.inv_h;
     thin_body<PT, Q, false, false, true>(prm);
 }
 
@@ -611,8 +702,6 @@ tw_status validate_fused(const tw_fused_args &a)
 // traced with the run-time loop over P (same grid, same bits).
 template <int PT>
 static constexpr bool kTracedP = PT == 1 || PT == 2 || PT == 4 || PT == 8;
-// Most partials the all-at-once form has registers for.
-static constexpr int kDeepMaxP = 8;
 
 template <int PT, int VPT>
 static tw_status launch_t(const FusedParams &prm, bool trace, bool streamed, int64_t grid, int block, hipStream_t stream)
@@ -624,7 +713,7 @@ static tw_status launch_t(const FusedParams &prm, bool trace, bool streamed, int
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kOccupancyPadBytes),
                              allowed[kern == fused_kernel<PT, VPT, false, false> ? 0 : trace ? 2 : 1]));
     TW_HIP(launch_kernel(kern, dim3(static_cast<unsigned>(grid)), dim3(static_cast<unsigned>(block)),
-                         kOccupancyPadBytes, stream, prm));
+                         kOccupancyPadBytes, stream, static_cast<uint32_t>(prm.n_groups), prm));
     return TW_OK;
 }
 
@@ -643,8 +732,19 @@ template <int PT, int Q>
 static tw_status launch_deep_t(const FusedParams &prm, int64_t grid, hipStream_t stream)
 {
     if constexpr (PT > 0 && PT <= kDeepMaxP) {
-        TW_HIP(launch_kernel(fused_deep_kernel<PT, Q>, dim3(static_cast<unsigned>(grid)), dim3(kThinThreads), 0u,
-                             stream, prm));
+        uint64_t t[kDeepMaxP + 2] = {};
+        for (int i = 0; i < PT + 2; ++i)
+            t[i] = reinterpret_cast<uint64_t>(i < PT ? prm.partials[i < PT ? i : 0] : i == PT ? prm.residual : prm.weight);
+        DeepRest rest;
+        for (int i = kDeepFirst; i < kDeepMaxP + 2; ++i) rest.tensor[i - kDeepFirst] = reinterpret_cast<const void *>(t[i]);
+        rest.out = prm.out;
+        rest.residual_out = prm.residual_out;
+        rest.eps = prm.eps;
+        rest.inv_h = prm.inv_h;
+        TW_HIP(launch_kernel(fused_deep_kernel<PT, Q>, dim3(static_cast<unsigned>(grid)), dim3(kThinThreads), 0u, stream,
+                             Words4{t[0], t[1], t[2], t[3]}, Words2{t[4], t[5]},
+                             prm.n_bytes | uint64_t(prm.hv) << 32 | uint64_t(prm.tpr_log2) << 44 | uint64_t(prm.n_groups) << 48,
+                             rest));
         return TW_OK;
     }
     return TW_ERR_UNSUPPORTED;
@@ -828,6 +928,22 @@ static bool takes_thin_kernel(int cu_budget, int cus, const FusedGeometry &g, in
     return trips < w.any && (trips < w.full || groups * 100 < 92 * trips * cus);
 }
 
+// Workgroups of a launch in which each of the n_groups row groups has a workgroup of `waves` waves
+// of its own, helpers included (see help()). They are taken where the row groups and all their
+// helpers have a compute unit each, and a group's lines are more than a unit can have outstanding.
+// Measured on MI355X, us without / with in replayed trains, inputs from HBM: 8192 elements, P = 8: 1 row
+// 4.66 / 4.28, 16 rows 5.5 / 4.8, 32 rows 5.9 / 5.1 (from the cache 3.98 / 3.88); past the rule, with an earlier
+// form of the kernel, 42 rows 6.22 / 6.12, 64 6.0 / 6.7, 128 7.2 / 8.3. P = 16: 16 rows 7.5 / 6.0, 64 rows 8.3 /
+// 7.1 (100 rows, P = 12 7.9 / 8.4); 16384 elements, P = 8: 16 rows 8.6 / 6.9; 512 elements, P = 4, 4 rows, 20 KiB:
+// 1.80 / 1.85. (More than one load to a wave, for fewer helpers: 2 to 20 % slower.)
+static int64_t grid_with_helpers(uint32_t n_groups, uint32_t group_bytes, int P, int waves, int cus)
+{
+    if (group_bytes * (P + 1ll) <= 20 * 1024) return n_groups;
+    const int64_t shares = (helper_pieces(group_bytes, P) + waves - 1) / waves;
+    const int64_t grid = helper_base(n_groups) * (1 + shares);
+    return grid <= cus ? grid : n_groups;
+}
+
 tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_end, uint32_t *hw_ids,
                        int64_t hw_ids_len, hipStream_t stream)
 {
@@ -893,6 +1009,8 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
         const bool any_p = (trace && !traced_p) ||
                            (thin ? thin_loops(a.P, g, row_end - row_begin, cus)
                                  : !wide_fits(a.P, g.vpt) || wide_loops(a.P, g, grid, prm.n_groups, a.N * row_bytes));
+        if (deep || (!thin && !trace && budget == cus && grid == prm.n_groups))
+            grid = grid_with_helpers(prm.n_groups, prm.group_bytes, a.P, thin ? kThinThreads / 64 : g.block / 64, cus);
         if (thin) {
             if (any_p) TW_TRY((launch_thin<kAnyPadded>(prm, tg.q, trace, streamed, false, grid, stream)));
             else

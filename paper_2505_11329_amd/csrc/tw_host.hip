@@ -20,25 +20,21 @@ tw_status hip_fail(hipError_t e, const char *where)
 }
 
 static std::mutex g_mu;
-static int g_cu_count[kMaxDevices];  // 0 = not queried yet
+static std::atomic<int> g_cu_count[kMaxDevices];  // 0 = not queried yet
 
 tw_status current_cu_count(int *cu_count)
 {
     int dev = 0;
     TW_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) return hip_fail(hipErrorInvalidDevice, "tw_host.hip: device id out of range");
-    {
-        std::lock_guard<std::mutex> lk(g_mu);
-        if (g_cu_count[dev] > 0) {
-            *cu_count = g_cu_count[dev];
-            return TW_OK;
-        }
+    int n = g_cu_count[dev].load(std::memory_order_relaxed);
+    if (n > 0) {
+        *cu_count = n;
+        return TW_OK;
     }
-    int n = 0;
     TW_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
     if (n <= 0) return hip_fail(hipErrorInvalidDevice, "tw_host.hip: the device reports no compute units");
-    std::lock_guard<std::mutex> lk(g_mu);
-    g_cu_count[dev] = n;
+    g_cu_count[dev].store(n, std::memory_order_relaxed);
     *cu_count = n;
     return TW_OK;
 }

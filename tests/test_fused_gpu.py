@@ -144,6 +144,24 @@ def test_decode_sized_whole_device_launches_on_both_sides_of_the_all_at_once_lim
 # Each P has kernels of its own, in small workgroups (1 to 4 vectors per thread, one chunk of loads in flight or
 # two) and in the wide geometry (1 to 8 vectors per thread): every launch mode against the confined one, which is
 # checked against the oracle, on one row and on row counts around the edges.
+@pytest.mark.parametrize("N,H,P", [(1, 8192, 8), (8, 8192, 8), (9, 8176, 8), (40, 8192, 8), (41, 8192, 8), (1, 520, 8),
+                                   (33, 2056, 5), (64, 8192, 4), (65, 8192, 4), (17, 1024, 8), (18, 1024, 6), (3, 512, 7),
+                                   (5, 5120, 1), (16, 8192, 16), (64, 8192, 16), (65, 8192, 9), (10, 16392, 3), (16, 16384, 8),
+                                   (7, 65536, 2), (12, 40000, 16)])
+def test_short_launches_with_helper_workgroups(tw, torch_cuda, N, H, P):
+    """Few row groups: idle compute units read the rows too (both sides of the rule; last groups and last lines that are
+    not whole; every kernel that has such helpers). Bits as of a launch on two compute units, which has none; and with
+    the outputs over the residual and a partial, which the helpers read while they are written."""
+    d = small(N, H, P, seed=N + H)
+    g = upload(d)
+    out, res = run(tw, torch_cuda, g)
+    check_against_oracle(d, out, res, "N%d H%d P%d" % (N, H, P))
+    out2, res2 = run(tw, torch_cuda, g, cu_budget=2)
+    assert np.array_equal(out, out2) and np.array_equal(res, res2)
+    out3, res3 = run(tw, torch_cuda, g, out=g["partials"][P - 1], residual_out=g["residual"])
+    assert np.array_equal(out, out3) and np.array_equal(res, res3)
+
+
 @pytest.mark.parametrize("H", [504, 2056, 4096, 6136, 8192, 8200, 16392, 40000])
 @pytest.mark.parametrize("P", [3, 5, 6, 7, 9, 11, 13, 16])
 def test_kernels_of_every_partial_count(tw, torch_cuda, H, P):
