@@ -145,14 +145,8 @@ __device__ __forceinline__ void help(uint32_t n_groups, uint32_t group_bytes, ui
 }
 
 template <int PT, int VPT, bool TRACE, bool STREAMED>
-__global__ __launch_bounds__(kThreads) void fused_kernel(uint32_t n_owners, const FusedParams prm)
+__device__ __forceinline__ void wide_body(const FusedParams &prm)
 {
-    if constexpr (!TRACE)
-        if (blockIdx.x >= n_owners)
-            return help(prm.n_groups, prm.group_bytes, prm.n_bytes, prm.hv, PT > 0 ? PT : prm.P, [&](int t) {
-                const int P = PT > 0 ? PT : prm.P;
-                return t < P ? prm.partials[t < P ? t : 0] : t == P ? prm.residual : prm.weight;
-            });
     constexpr bool streamed = STREAMED;  // see st()
     __shared__ float s_wave_sum[2][kWaves];
     constexpr int NB = buffers_in_flight<PT, VPT>();
@@ -311,7 +305,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(uint32_t n_owners, cons
 
     using Zero = std::integral_constant<int, 0>;
     using One = std::integral_constant<int, 1>;
-    uint32_t group = blockIdx.x;  // (the grid has at most n_groups workgroups, but for helpers)
+    uint32_t group = blockIdx.x;  // (but for helpers the grid has at most n_groups workgroups)
     if constexpr (VPT == 1 && NB == 2) {
         // two trips ahead: the buffers alternate from trip to trip
         issue(buf[0], chunk_off(group, 0));
@@ -342,6 +336,25 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(uint32_t n_owners, cons
         for (; group + stride < n_groups; group += stride) trip(group, Zero{}, std::true_type{});
         trip(group, Zero{}, std::false_type{});
     }
+}
+
+template <int PT, int VPT, bool TRACE, bool STREAMED>
+__global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
+{
+    wide_body<PT, VPT, TRACE, STREAMED>(prm);
+}
+
+// A launch with helpers. (A kernel of its own: the branch costs launches without them up to 4 %. The
+// number of workgroups that are none arrives in a register with the wave.)
+template <int PT, int VPT>
+__global__ __launch_bounds__(kThreads) void fused_helped_kernel(uint32_t n_owners, const FusedParams prm)
+{
+    if (blockIdx.x >= n_owners) {
+        const int P = PT > 0 ? PT : prm.P;
+        return help(n_owners, prm.group_bytes, prm.n_bytes, prm.hv, P,
+                    [&](int t) { return t < P ? prm.partials[t < P ? t : 0] : t == P ? prm.residual : prm.weight; });
+    }
+    wide_body<PT, VPT, false, false>(prm);
 }
 
 // ---------------------------------------------------------------------------
@@ -709,11 +722,17 @@ static tw_status launch_t(const FusedParams &prm, bool trace, bool streamed, int
     auto kern = streamed ? fused_kernel<PT, VPT, false, true> : fused_kernel<PT, VPT, false, false>;
     if constexpr (PT <= 0 || kTracedP<PT>)
         if (trace) kern = fused_kernel<PT, VPT, true, false>;
-    static std::atomic<int> allowed[3][kMaxDevices];  // a kernel each: plain, streamed, traced
+    static std::atomic<int> allowed[4][kMaxDevices];  // a kernel each: plain, streamed, traced, with helpers
+    if (grid > prm.n_groups) {
+        TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(fused_helped_kernel<PT, VPT>), static_cast<int>(kOccupancyPadBytes), allowed[3]));
+        TW_HIP(launch_kernel(fused_helped_kernel<PT, VPT>, dim3(static_cast<unsigned>(grid)), dim3(static_cast<unsigned>(block)),
+                             kOccupancyPadBytes, stream, prm.n_groups, prm));
+        return TW_OK;
+    }
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kOccupancyPadBytes),
                              allowed[kern == fused_kernel<PT, VPT, false, false> ? 0 : trace ? 2 : 1]));
     TW_HIP(launch_kernel(kern, dim3(static_cast<unsigned>(grid)), dim3(static_cast<unsigned>(block)),
-                         kOccupancyPadBytes, stream, static_cast<uint32_t>(prm.n_groups), prm));
+                         kOccupancyPadBytes, stream, prm));
     return TW_OK;
 }
 
