@@ -785,7 +785,7 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_oth
     TW_TRY(current_cu_count(&cus));
     const int budget = resolve_budget(g.cu_budget, cus);
     const GemmTiles t = choose_tiles(g, budget, beside_other_kernels);
-    if (t.small >= 0) return launch_small_tile(g, t.small, budget, cus, stream);
+    if (t.small >= 0) return launch_small_tile(g, t.small, budget, cus, beside_other_kernels, stream);
     if (g.b_layout == TW_B_KN) return launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
     switch (t.cols) {
     case 64: return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);

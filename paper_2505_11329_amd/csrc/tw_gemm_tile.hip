@@ -39,10 +39,20 @@
 
 namespace tw {
 
-template <int WM, int WN, int WVM, int WVN, int BK, int S>
+// Waves that only load, beside the ones that multiply (LOADERS). A multiplying wave that also
+// loads has the address arithmetic and the loads of a step in the way of its matrix
+// instructions, which for a small tile are a chain with one wave to a SIMD: a step of 256 in K of a
+// 16 x 16 tile took 600 clocks even with everything in the L2. With waves for each, us, operands from
+// the cache / from HBM: [16 x 8192] x [8192 x 1280] 10.5 -> 8.9 / 11.2 -> 10.8; [64 x 8192] x [8192 x 3584]
+// (32 x 32) 15.6 -> 14.2 / 21.3 -> 21.2; [K x N]: [1000 x 4096] x [4096 x 3000] (128 x 128) 33.4 -> 30.0. The
+// workgroups start later, with twice the waves: 1 to 5 % slower where K is short (see kSmallTiles).
+static constexpr int kLoaders = 4;
+
+template <int WM, int WN, int WVM, int WVN, int BK, int S, bool LOADERS>
 struct SmallTile {
-    static constexpr int kCompute = WVM * WVN;                 // waves that own outputs
-    static constexpr int kWaves = kCompute < 4 ? 4 : kCompute;  // waves that load
+    static constexpr int kCompute = WVM * WVN;                                          // waves that own outputs
+    static constexpr int kWaves = LOADERS ? kLoaders : kCompute < 4 ? 4 : kCompute;      // waves that load
+    static constexpr int kThreads = 64 * (LOADERS ? kCompute + kLoaders : kWaves);
     static constexpr int BM = kBlk * WM * WVM, BN = kBlk * WN * WVN;
     static constexpr int kABytes = BM * BK * 2, kBBytes = BN * BK * 2, kStageBytes = kABytes + kBBytes;
     static constexpr int kLdsBytes = S * kStageBytes;
@@ -58,6 +68,7 @@ struct SmallTile {
     // K = 3584, N = 8192 12.4 -> 12.1 us, 333 rows, K = 8192, N = 3584 38.2 -> 37.5. With three
     // stages there is little to save, and 192 x 128 tiles came out 1 to 3 % slower.
     static constexpr bool kTail = S > 3;
+    static_assert(!LOADERS || kTail, "loading waves load nothing past the end of K");
 };
 
 // Position of the 16-byte piece c of row r, of the 2 BK bytes a row takes: two rows of
@@ -96,13 +107,13 @@ struct StageFrags {
 // no division that tile_at can spare, the fragment addresses later. (16 rows, K = 1024, N =
 // 8192: 5.6 -> 5.1 us; K = 8192, N = 3584: 13.7 -> 13.2; 512 x 4096 x 2048: 15.0 -> 14.7.)
 // last_rows: rows of A in the last row of tiles.
-template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, bool STREAM_B>
-__global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_tile_kernel(
+template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, bool LOADERS, bool STREAM_B>
+__global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThreads)) void gemm_tile_kernel(
     const char *A, const char *B, char *C, int N, int K, int tiles_m, int tiles_n, int last_rows, int group_m,
     int tiles_per_xcd)
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // as in tw_gemm.hip: the host pass needs the launch stub only
-    using T = SmallTile<WM, WN, WVM, WVN, BK, S>;
+    using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
     constexpr int SUBS = BK / kSubK, NW = T::kWaves, BM = T::BM, BN = T::BN, kRowBytes = BK * 2;
     static_assert(!B_KN || BN == 32 || BN == 64 || BN == 128, "kn_swizzle");
     // Weights that one row of tiles reads once are not worth keeping in the caches (16 rows,
@@ -117,19 +128,21 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
     const int k_tiles = K > 0 ? (K + BK - 1) / BK : 1;
     constexpr uint32_t kPastK = 0x80000000u;  // out of range whatever scalar offset (< 2^31) is added
 
-    // Load duty: instruction i of this wave fills the 64 pieces from (i * NW + wave) * 64 on.
+    const bool loads = !LOADERS || wave >= T::kCompute;
+    const int loader = LOADERS ? (loads ? wave - T::kCompute : 0) : wave;  // among the waves that load
+    // Load duty: instruction i of this wave fills the 64 pieces from (i * NW + loader) * 64 on.
     constexpr int kRowPieces = kRowBytes / 16, kInstrRows = 64 / kRowPieces;
     constexpr int kStepRows = NW * kInstrRows;                 // rows all waves' instruction i covers
     constexpr int kRepeat = kStepRows % 16 == 0 || BK == 64 ? 1 : 16 / kStepRows;  // instructions after which the swizzle repeats
     static_assert(BK == 64 ? kStepRows % 16 == 0 : 16 % kStepRows == 0 || kStepRows % 16 == 0, "swizzle period");
-    const int load_row = wave * kInstrRows + lane / kRowPieces;  // + i * kStepRows
+    const int load_row = loader * kInstrRows + lane / kRowPieces;  // + i * kStepRows
     int load_piece[kRepeat];
 #pragma unroll
     for (int q = 0; q < kRepeat; ++q) load_piece[q] = swizzled<BK>(load_row + q * kStepRows, lane % kRowPieces);
     // and of B stored [K x N]
     constexpr int kKnPieces = BN / 8, kKnInstrRows = 64 / kKnPieces;
     static_assert(!B_KN || (NW * kKnInstrRows) % 16 == 0, "the swizzle's row bits do not depend on the instruction");
-    const int kn_row = wave * kKnInstrRows + lane / kKnPieces;  // + i * NW * kKnInstrRows
+    const int kn_row = loader * kKnInstrRows + lane / kKnPieces;  // + i * NW * kKnInstrRows
     const int kn_piece = (lane % kKnPieces) ^ (kn_swizzle<BN>(kn_row) << 1);
 
     for (int w = blockIdx.x; w < tiles_per_xcd * kXcds; w += gridDim.x) {
@@ -163,7 +176,7 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
         };
         auto fetch_ctx = [&](int kt, int slot) {
             Fetch c;
-            c.base = (lds_char_ptr_t)(lds + slot * T::kStageBytes + wave * 1024);
+            c.base = (lds_char_ptr_t)(lds + slot * T::kStageBytes + loader * 1024);
 #pragma unroll
             for (int q = 0; q < kRepeat; ++q) {
                 const int k = kt * BK + load_piece[q] * 8;  // K <= 2^22, K steps run S past it at most
@@ -242,12 +255,13 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
                 }
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, cur.a[s][i], acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                constexpr int kReadSlots = kMma >= 8 ? kMma * 3 / 4 : kMma;  // the last quarter lets them arrive
+                // the last quarter (few instructions, and none of them a load: the last half) lets them arrive
+                constexpr int kReadSlots = LOADERS && kMma < 12 ? kMma / 2 : kMma >= 8 ? kMma * 3 / 4 : kMma;
                 static_for<kReads>([&](auto t) {
                     if constexpr (decltype(t)::value * kReadSlots / kReads == m) read_one(nxt, base, t);
                 });
                 static_for<T::kLoads>([&](auto t) {
-                    if constexpr (LOADS && decltype(t)::value * kMma / T::kLoads == m) fetch_one(c, t);
+                    if constexpr (LOADS && !LOADERS && decltype(t)::value * kMma / T::kLoads == m) fetch_one(c, t);
                 });
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -256,7 +270,7 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
         // last LIMIT), then for the same of all waves.
         auto wait_vm = [&](int newer, auto limit_tag) {
             constexpr int LIMIT = decltype(limit_tag)::value;
-            static_for<LIMIT + 1>([&](auto v) {
+            if (loads) static_for<LIMIT + 1>([&](auto v) {
                 constexpr int n = (LIMIT - decltype(v)::value) * T::kLoads;
                 if (decltype(v)::value == 0 ? newer >= LIMIT : decltype(v)::value == LIMIT ? newer <= 0 : newer * T::kLoads == n)
                     __builtin_amdgcn_s_waitcnt(((n >> 4) << 14) | 0x0F70 | (n & 15));
@@ -268,7 +282,7 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         static_for<S>([&](auto s) {
-            if (!T::kTail || decltype(s)::value < k_tiles) fetch(fetch_ctx(decltype(s)::value, decltype(s)::value));
+            if (loads && (!T::kTail || decltype(s)::value < k_tiles)) fetch(fetch_ctx(decltype(s)::value, decltype(s)::value));
         });
         // Fragment addresses inside a stage; block i lies 16 rows further on. (The lane passes
         // through an asm statement so that all this is computed here, the first loads on their
@@ -303,16 +317,17 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
             constexpr bool MAIN = decltype(main_tag)::value;
             // stage kt + 1 has landed, stage kt is read
             wait_vm(MAIN ? S : k_tiles - 2 - kt, std::integral_constant<int, S - 2>{});
-            const Fetch c = fetch_ctx(kt + S, slot);
-            if constexpr (!MAIN)
-                if (kt + S < k_tiles) fetch(c);
+            Fetch c;
+            if (loads) c = fetch_ctx(kt + S, slot);
+            if constexpr (LOADERS || !MAIN)
+                if (loads && kt + S < k_tiles) fetch(c);
             slot = slot + 1 == S ? 0 : slot + 1;
             ++kt;
             __builtin_amdgcn_sched_barrier(0);
             if (computes) {
                 multiply(cur, nxt, slot, c, main_tag);
                 settle(nxt);
-            } else if constexpr (MAIN) {
+            } else if constexpr (MAIN && !LOADERS) {
                 fetch(c);
             }
         };
@@ -339,33 +354,35 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
             // store covers whole rows of the wave's outputs (as in tw_gemm.hip).
             constexpr int kRowPitch = kBlk * WN * 2 + 32, kRegion = kBlk * WM * kRowPitch;
             constexpr int kPieces = kBlk * WN * 2 / 16, kRowsPerStore = 64 / kPieces;
-            static_assert(NW == T::kCompute && NW * kRegion <= T::kLdsBytes, "the waves' regions");
+            static_assert(T::kCompute * kRegion <= T::kLdsBytes, "the waves' regions");
             static_assert(64 % kPieces == 0 && (kBlk * WM) % kRowsPerStore == 0, "whole store instructions");
             __builtin_amdgcn_s_barrier();  // every wave's loads have landed and its fragments are read
-            const uint32_t region = static_cast<uint32_t>(wave * kRegion);
-            const uint32_t w_addr = region + l15 * kRowPitch + lgrp * 8;
+            if (computes) {
+                const uint32_t region = static_cast<uint32_t>(wave * kRegion);
+                const uint32_t w_addr = region + l15 * kRowPitch + lgrp * 8;
 #pragma unroll
-            for (int i = 0; i < WM; ++i)
+                for (int i = 0; i < WM; ++i)
 #pragma unroll
-                for (int j = 0; j < WN; ++j) {
-                    u32x2 v;
-                    v.x = pack_bf16x2(acc[i][j][0], acc[i][j][1]);
-                    v.y = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
-                    *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(
-                        static_cast<uintptr_t>(w_addr + i * kBlk * kRowPitch + j * kBlk * 2)) = v;
+                    for (int j = 0; j < WN; ++j) {
+                        u32x2 v;
+                        v.x = pack_bf16x2(acc[i][j][0], acc[i][j][1]);
+                        v.y = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
+                        *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>(
+                            static_cast<uintptr_t>(w_addr + i * kBlk * kRowPitch + j * kBlk * 2)) = v;
+                    }
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+                const int piece_c = lane % kPieces, row_c = lane / kPieces;
+                const int n = n0 + wave_n * (kBlk * WN) + piece_c * 8;
+                const uint32_t g_off =
+                    n < N ? static_cast<uint32_t>((wave_m * (kBlk * WM) + row_c) * c_row_bytes + n * 2) : kPastK;
+                const uint32_t r_addr = region + row_c * kRowPitch + piece_c * 16;
+                const uint32_t store_rows_bytes = static_cast<uint32_t>(kRowsPerStore * c_row_bytes);
+#pragma unroll
+                for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
+                    const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) u32x4 *>(
+                        static_cast<uintptr_t>(r_addr + i * kRowsPerStore * kRowPitch));
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, 0);  // (no scalar offset: see st())
                 }
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-            const int piece_c = lane % kPieces, row_c = lane / kPieces;
-            const int n = n0 + wave_n * (kBlk * WN) + piece_c * 8;
-            const uint32_t g_off =
-                n < N ? static_cast<uint32_t>((wave_m * (kBlk * WM) + row_c) * c_row_bytes + n * 2) : kPastK;
-            const uint32_t r_addr = region + row_c * kRowPitch + piece_c * 16;
-            const uint32_t store_rows_bytes = static_cast<uint32_t>(kRowsPerStore * c_row_bytes);
-#pragma unroll
-            for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
-                const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) u32x4 *>(
-                    static_cast<uintptr_t>(r_addr + i * kRowsPerStore * kRowPitch));
-                __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, 0);  // (no scalar offset: see st())
             }
         } else if (computes) {
 #pragma unroll
@@ -390,13 +407,19 @@ __global__ __launch_bounds__(WVM * WVN < 4 ? 256 : 64 * WVM * WVN) void gemm_til
 // host side
 // ---------------------------------------------------------------------------
 
-template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, bool STREAM_B = false>
-static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, hipStream_t stream)
+// LONG_K: from which K on there are loading waves (0: always, kNeverLoaders: not for this shape).
+static constexpr int kNeverLoaders = 1 << 30;
+template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, bool STREAM_B = false, bool LOADERS = LONG_K == 0>
+static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, bool beside, hipStream_t stream)
 {
-    using T = SmallTile<WM, WN, WVM, WVN, BK, S>;
+    // (eight waves that multiply and four that load leave no registers for a workgroup beside them)
+    if constexpr (LONG_K > 0 && LONG_K < kNeverLoaders && !LOADERS)
+        if (g.K >= LONG_K && !(beside && WVM * WVN == 8))
+            return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM_B, true>(g, budget, cus, beside, stream);
+    using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
     const int64_t tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
     if constexpr (STREAM_B)
-        if (tiles_m > 1) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, false>(g, budget, cus, stream);
+        if (tiles_m > 1) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, false, LOADERS>(g, budget, cus, beside, stream);
     if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
     const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
     const int64_t slots = int64_t(tiles_per_xcd) * kXcds;
@@ -405,10 +428,10 @@ static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, hipSt
     constexpr int kAloneBytes = T::kLdsBytes > 81 * 1024 ? T::kLdsBytes : 81 * 1024;
     const bool whole = budget >= cus;
     const unsigned grid = static_cast<unsigned>(whole || slots < budget ? slots : budget);
-    auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, S, STREAM_B>;
+    auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, S, LOADERS, STREAM_B>;
     static std::atomic<int> allowed[kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), kAloneBytes, allowed));
-    TW_HIP(launch_kernel(kern, dim3(grid), dim3(64 * T::kWaves),
+    TW_HIP(launch_kernel(kern, dim3(grid), dim3(T::kThreads),
                          static_cast<unsigned>(whole ? T::kLdsBytes : kAloneBytes), stream,
                          static_cast<const char *>(g.A), static_cast<const char *>(g.B), static_cast<char *>(g.C),
                          static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
@@ -417,6 +440,11 @@ static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, hipSt
     return TW_OK;
 }
 
+// The loading waves' K: measured, loading waves against none, for 96 and 256 tiles, K = 512, 1024, 4096 and 8192, from
+// the cache and from HBM: tiles of 16 x 16 -7 to -14 % from K = 4096 on and up to +7 % at 512; 32 x 32 -19 to 0 %, [K x N]
+// -12 to +1 % and up to +6 % at 1024; 64 x 32 and 64 x 64 -10 to +2 % and +1 to +5 % up to 1024; 96 x 64 -6 to 0 % and up to +2 %,
+// [K x N] -13 to +1 % at any K; 96 x 96 and 96 x 128 -11 to 0 % at any K; 192 x 64 [K x N] -10 to 0 %, +2 to +6 % at 512; 128 x 128
+// [K x N] -18 to -4 %, up to +5 % at 512; 192 x 64 and 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: none.
 // The shapes, smallest first, and what one 64-deep K step of a tile takes when about
 // every compute unit has one (us, measured on MI355X at K = 3584 and 8192). Several
 // tiles to a compute unit take their times in turn, also where two fit at once. [K x N]
@@ -426,21 +454,21 @@ static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, hipSt
 struct SmallTileShape {
     int rows, cols, k_step;
     float us_nk, us_kn;  // 0: not built for that layout
-    tw_status (*nk)(const tw_gemm_args &, int, int, hipStream_t);
-    tw_status (*kn)(const tw_gemm_args &, int, int, hipStream_t);
+    tw_status (*nk)(const tw_gemm_args &, int, int, bool, hipStream_t);
+    tw_status (*kn)(const tw_gemm_args &, int, int, bool, hipStream_t);
 };
 static const SmallTileShape kSmallTiles[] = {
-    {16, 16, 256, 0.075f, 0.0f, launch_tile_t<false, 1, 1, 1, 1, 256, 4, true>, nullptr},
-    {32, 16, 256, 0.097f, 0.0f, launch_tile_t<false, 1, 1, 2, 1, 256, 4, true>, nullptr},
-    {32, 32, 128, 0.132f, 0.150f, launch_tile_t<false, 1, 1, 2, 2, 128, 4, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4>},
-    {64, 32, 128, 0.180f, 0.200f, launch_tile_t<false, 2, 1, 2, 2, 128, 4>, launch_tile_t<true, 2, 1, 2, 2, 128, 4>},
-    {64, 64, 128, 0.200f, 0.230f, launch_tile_t<false, 2, 2, 2, 2, 128, 4>, launch_tile_t<true, 2, 2, 2, 2, 128, 4>},
-    {96, 64, 64, 0.255f, 0.280f, launch_tile_t<false, 3, 2, 2, 2, 64, 6>, launch_tile_t<true, 3, 2, 2, 2, 64, 6>},
-    {96, 96, 64, 0.338f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6>, nullptr},
-    {96, 128, 64, 0.405f, 0.430f, launch_tile_t<false, 3, 4, 2, 2, 64, 5>, launch_tile_t<true, 3, 4, 2, 2, 64, 5>},
-    {192, 64, 64, 0.430f, 0.500f, launch_tile_t<false, 3, 2, 4, 2, 64, 4>, launch_tile_t<true, 3, 2, 4, 2, 64, 4>},
-    {128, 128, 64, 0.530f, 0.550f, launch_tile_t<false, 2, 4, 4, 2, 64, 4>, launch_tile_t<true, 2, 4, 4, 2, 64, 4>},
-    {192, 128, 64, 0.700f, 0.690f, launch_tile_t<false, 3, 4, 4, 2, 64, 3>, launch_tile_t<true, 3, 4, 4, 2, 64, 3>},
+    {16, 16, 256, 0.075f, 0.0f, launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, true>, nullptr},
+    {32, 16, 256, 0.097f, 0.0f, launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, true>, nullptr},
+    {32, 32, 128, 0.132f, 0.150f, launch_tile_t<false, 1, 1, 2, 2, 128, 4, 0, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
+    {64, 32, 128, 0.180f, 0.200f, launch_tile_t<false, 2, 1, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 1, 2, 2, 128, 4, 2048>},
+    {64, 64, 128, 0.200f, 0.230f, launch_tile_t<false, 2, 2, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 2, 2, 2, 128, 4, 2048>},
+    {96, 64, 64, 0.255f, 0.280f, launch_tile_t<false, 3, 2, 2, 2, 64, 6, 2048>, launch_tile_t<true, 3, 2, 2, 2, 64, 6, 0>},
+    {96, 96, 64, 0.338f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6, 0>, nullptr},
+    {96, 128, 64, 0.405f, 0.430f, launch_tile_t<false, 3, 4, 2, 2, 64, 5, 0>, launch_tile_t<true, 3, 4, 2, 2, 64, 5, 0>},
+    {192, 64, 64, 0.430f, 0.500f, launch_tile_t<false, 3, 2, 4, 2, 64, 4, kNeverLoaders>, launch_tile_t<true, 3, 2, 4, 2, 64, 4, 2048>},
+    {128, 128, 64, 0.530f, 0.550f, launch_tile_t<false, 2, 4, 4, 2, 64, 4, kNeverLoaders>, launch_tile_t<true, 2, 4, 4, 2, 64, 4, 2048>},
+    {192, 128, 64, 0.700f, 0.690f, launch_tile_t<false, 3, 4, 4, 2, 64, 3, kNeverLoaders>, launch_tile_t<true, 3, 4, 4, 2, 64, 3, kNeverLoaders>},
 };
 
 // A grid's tiles are worked off in turns of one to a compute unit. The launch, the first
@@ -477,10 +505,10 @@ void small_tile_size(int shape, int *rows, int *cols)
     *cols = kSmallTiles[shape].cols;
 }
 
-tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, hipStream_t stream)
+tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, bool beside, hipStream_t stream)
 {
     const SmallTileShape &t = kSmallTiles[shape];
-    return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, budget, cus, stream);
+    return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, budget, cus, beside, stream);
 }
 
 }  // namespace tw

@@ -103,7 +103,7 @@ double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_s
                     double us_per_turn, int budget);
 int best_small_tile(const tw_gemm_args &g, int budget, double *us);
 void small_tile_size(int shape, int *rows, int *cols);
-tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, hipStream_t stream);
+tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, bool beside, hipStream_t stream);
 
 // ---- fork/join events (tw_host.hip) ----
 // A small per-device pool of timing-disabled events used to order streams.

@@ -238,6 +238,26 @@ def test_gemm_every_tile_shape(tw, torch_cuda, tile, layouts, M, N, K, budget):
         gemm_check(oracle.bf16_to_f64(to_bits(C)), ref, K, 0.5, "%s tiles, %s %dx%dx%d" % (tile, layout, M, N, K))
 
 
+@pytest.mark.parametrize("tile,layouts,M,N,budget", [(c[0], c[1], c[2], c[3], c[5]) for c in TILE_CASES if c[0][0] < 256 and c[4] == 1032])
+def test_gemm_tiles_with_loading_waves(tw, torch_cuda, tile, layouts, M, N, budget):
+    """Both sides of the K from which on some shapes have waves that only load, and every number of K steps past a whole
+    round of the LDS stages (three to six of 64 to 256); several tiles to a workgroup."""
+    for layout in ("nk", "kn") if layouts == "both" else (layouts,):
+        code = tw.B_NK if layout == "nk" else tw.B_KN
+        for K in (2040, 2048, 2056, 2120, 2184, 2304, 2440, 2568):
+            assert tw.gemm_tile_choice(M, N, K, code, budget) == tile
+            g = W.make_gemm_inputs(M, K, N, 0.5, seed=M + N + K, b_layout=layout)
+            C = torch_cuda.full((M, N), float("nan"), dtype=torch_cuda.bfloat16, device="cuda:0")
+            tw.gemm_bf16(to_gpu(g["A"]), to_gpu(g["B"]), C=C, b_layout=code, cu_budget=budget)
+            torch_cuda.cuda.synchronize()
+            rng = np.random.default_rng(K)
+            ms, ns = np.append(rng.integers(0, M, 400), [0, M - 1]), np.append(rng.integers(0, N, 400), [0, N - 1])
+            ref = oracle.gemm_samples(g["A"], g["B"], layout, ms, ns)
+            got = oracle.bf16_to_f64(to_bits(C))
+            assert np.isfinite(got).all()
+            gemm_check(got[ms, ns], ref, K, 0.5, "%s tiles, %s K = %d" % (tile, layout, K))
+
+
 @pytest.mark.parametrize("layout,K,tile", [("nk", 512, (256, 128)), ("nk", 2048, (256, 256)), ("kn", 512, (256, 128))])
 def test_gemm_taller_than_four_gib(tw, torch_cuda, layout, K, tile):
     """M = 1.1 M rows: C is 4.5 GB, so tile base addresses run past 2^32 bytes (row 1048576 of C starts
