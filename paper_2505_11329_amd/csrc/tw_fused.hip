@@ -144,9 +144,18 @@ __device__ __forceinline__ void help(uint32_t n_groups, uint32_t group_bytes, ui
     asm volatile("" ::"v"(v));
 }
 
-template <int PT, int VPT, bool TRACE, bool STREAMED>
-__device__ __forceinline__ void wide_body(const FusedParams &prm)
+// OWNERS: empty, or uint32_t: a launch with helpers, and its argument the number of workgroups that
+// are none (it arrives in a register with the wave). Launches without have kernels of their own: the
+// branch costs them up to 4 %.
+template <int PT, int VPT, bool TRACE, bool STREAMED, typename... OWNERS>
+__global__ __launch_bounds__(kThreads) void fused_kernel(OWNERS... owners, const FusedParams prm)
 {
+    if constexpr (sizeof...(OWNERS) > 0)
+        if (blockIdx.x >= (owners + ...)) {
+            const int P = PT > 0 ? PT : prm.P;
+            return help(prm.n_groups, prm.group_bytes, prm.n_bytes, prm.hv, P,
+                        [&](int t) { return t < P ? prm.partials[t < P ? t : 0] : t == P ? prm.residual : prm.weight; });
+        }
     constexpr bool streamed = STREAMED;  // see st()
     __shared__ float s_wave_sum[2][kWaves];
     constexpr int NB = buffers_in_flight<PT, VPT>();
@@ -336,25 +345,6 @@ __device__ __forceinline__ void wide_body(const FusedParams &prm)
         for (; group + stride < n_groups; group += stride) trip(group, Zero{}, std::true_type{});
         trip(group, Zero{}, std::false_type{});
     }
-}
-
-template <int PT, int VPT, bool TRACE, bool STREAMED>
-__global__ __launch_bounds__(kThreads) void fused_kernel(const FusedParams prm)
-{
-    wide_body<PT, VPT, TRACE, STREAMED>(prm);
-}
-
-// A launch with helpers. (A kernel of its own: the branch costs launches without them up to 4 %. The
-// number of workgroups that are none arrives in a register with the wave.)
-template <int PT, int VPT>
-__global__ __launch_bounds__(kThreads) void fused_helped_kernel(uint32_t n_owners, const FusedParams prm)
-{
-    if (blockIdx.x >= n_owners) {
-        const int P = PT > 0 ? PT : prm.P;
-        return help(n_owners, prm.group_bytes, prm.n_bytes, prm.hv, P,
-                    [&](int t) { return t < P ? prm.partials[t < P ? t : 0] : t == P ? prm.residual : prm.weight; });
-    }
-    wide_body<PT, VPT, false, false>(prm);
 }
 
 // ---------------------------------------------------------------------------
@@ -719,18 +709,20 @@ static constexpr bool kTracedP = PT == 1 || PT == 2 || PT == 4 || PT == 8;
 template <int PT, int VPT>
 static tw_status launch_t(const FusedParams &prm, bool trace, bool streamed, int64_t grid, int block, hipStream_t stream)
 {
-    auto kern = streamed ? fused_kernel<PT, VPT, false, true> : fused_kernel<PT, VPT, false, false>;
+    void (*const plain)(FusedParams) = fused_kernel<PT, VPT, false, false>;
+    void (*kern)(FusedParams) = streamed ? static_cast<void (*)(FusedParams)>(fused_kernel<PT, VPT, false, true>) : plain;
     if constexpr (PT <= 0 || kTracedP<PT>)
         if (trace) kern = fused_kernel<PT, VPT, true, false>;
     static std::atomic<int> allowed[4][kMaxDevices];  // a kernel each: plain, streamed, traced, with helpers
     if (grid > prm.n_groups) {
-        TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(fused_helped_kernel<PT, VPT>), static_cast<int>(kOccupancyPadBytes), allowed[3]));
-        TW_HIP(launch_kernel(fused_helped_kernel<PT, VPT>, dim3(static_cast<unsigned>(grid)), dim3(static_cast<unsigned>(block)),
-                             kOccupancyPadBytes, stream, prm.n_groups, prm));
+        void (*helped)(uint32_t, FusedParams) = fused_kernel<PT, VPT, false, false, uint32_t>;
+        TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(helped), static_cast<int>(kOccupancyPadBytes), allowed[3]));
+        TW_HIP(launch_kernel(helped, dim3(static_cast<unsigned>(grid)), dim3(static_cast<unsigned>(block)), kOccupancyPadBytes,
+                             stream, prm.n_groups, prm));
         return TW_OK;
     }
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), static_cast<int>(kOccupancyPadBytes),
-                             allowed[kern == fused_kernel<PT, VPT, false, false> ? 0 : trace ? 2 : 1]));
+                             allowed[kern == plain ? 0 : trace ? 2 : 1]));
     TW_HIP(launch_kernel(kern, dim3(static_cast<unsigned>(grid)), dim3(static_cast<unsigned>(block)),
                          kOccupancyPadBytes, stream, prm));
     return TW_OK;
