@@ -673,11 +673,11 @@ int tile_group_m(int64_t tiles_m, int tile_rows, int tile_cols, int budget)
     const int64_t at_once = (int64_t(budget) + kXcds - 1) / kXcds;
     int best_gm = 1;
     int64_t best_cost = INT64_MAX;
-    for (int gm = 1; gm <= 8; gm *= 2) {
-        if (gm > tiles_m && gm != 1) break;
+    for (int gm = 1; gm <= 8 && gm <= tiles_m; ++gm) {
         const int64_t gn = (at_once + gm - 1) / gm;
         const int64_t cost = int64_t(gm) * tile_rows + gn * tile_cols;
-        if (cost < best_cost) {
+        // (of two as square, one that leaves no lower block at the end)
+        if (cost < best_cost || (cost == best_cost && tiles_m % best_gm != 0 && tiles_m % gm == 0)) {
             best_cost = cost;
             best_gm = gm;
         }
@@ -720,9 +720,10 @@ static double wave_fill(int64_t tiles, int budget)
 // The tiles a launch on `budget` compute units is cut into.
 struct GemmTiles {
     int rows, cols;
-    int small;  // shape of tw_gemm_tile.hip, -1: one of this file's, 256 rows high
+    int small;    // shape of tw_gemm_tile.hip, -1: one of this file's, 256 rows high
+    bool helped;  // with helper workgroups
 };
-static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, bool beside_other_kernels)
+static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place)
 {
     // The default: eight waves of 64 x 64, tile 256 x 128 x 64, three LDS stages.
     // The part runs this kernel at its power limit (1.2-1.9 GHz on N(0, 0.02^2)
@@ -752,7 +753,7 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, bool beside_oth
     // for the same L1 request slots (a woven layer measured level to 3 % slower with
     // them), and the larger tiles leave no registers for a co-resident workgroup. (256 x 192
     // tiles held to 384 registers leave room for one; a woven train took 3.5 % longer with them.)
-    GemmTiles take = {BM, kGemmTileN, -1};
+    GemmTiles take = {BM, kGemmTileN, -1, false};
     double us = 1e300;
     const auto consider = [&](int cols, double us_per_step, double us_per_turn) {
         const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + cols - 1) / cols);
@@ -764,28 +765,30 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, bool beside_oth
         }
     };
     consider(kGemmTileN, g.b_layout == TW_B_KN ? 0.84 : 0.745, 2.7);
-    if (g.b_layout == TW_B_NK && !beside_other_kernels) {
+    if (g.b_layout == TW_B_NK && place != GemmPlace::kBeside) {
         consider(64, 0.60, 2.7);
         consider(256, 1.40, 7.5);
         consider(192, 1.08, 6.6);
     }
     double small_us = 0.0;
-    const int small = best_small_tile(g, budget, &small_us);
+    bool helped = false;
+    const int small = best_small_tile(g, budget, place, &small_us, &helped);
     if (small >= 0 && small_us < 0.98 * us) {
         take.small = small;
+        take.helped = helped;
         small_tile_size(small, &take.rows, &take.cols);
     }
     return take;
 }
 
-tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_other_kernels)
+tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, GemmPlace place)
 {
     if (g.M == 0 || g.N == 0) return TW_OK;
     int cus = 0;
     TW_TRY(current_cu_count(&cus));
     const int budget = resolve_budget(g.cu_budget, cus);
-    const GemmTiles t = choose_tiles(g, budget, beside_other_kernels);
-    if (t.small >= 0) return launch_small_tile(g, t.small, budget, cus, beside_other_kernels, stream);
+    const GemmTiles t = choose_tiles(g, budget, place);
+    if (t.small >= 0) return launch_small_tile(g, t.small, t.helped, budget, cus, place == GemmPlace::kBeside, stream);
     if (g.b_layout == TW_B_KN) return launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
     switch (t.cols) {
     case 64: return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);
@@ -820,7 +823,7 @@ extern "C" tw_status tw_gemm_tile_choice(int64_t M, int64_t N, int64_t K, int b_
 {
     if (M < 1 || N < 1 || K < 0 || cus < 1 || (b_layout != TW_B_NK && b_layout != TW_B_KN)) return TW_ERR_SHAPE;
     const tw_gemm_args g = {nullptr, nullptr, nullptr, M, N, K, b_layout, 0};
-    const GemmTiles t = choose_tiles(g, cus, beside_other_kernels != 0);
+    const GemmTiles t = choose_tiles(g, cus, beside_other_kernels ? GemmPlace::kBeside : GemmPlace::kAlone);
     if (tile_m) *tile_m = t.rows;
     if (tile_n) *tile_n = t.cols;
     return TW_OK;

@@ -32,6 +32,7 @@
 // of them, room for two reads: 15.2 -> 13.7 us at 16 rows against reads first).
 // Rows are laid out as in tw_gemm.hip: 16-byte pieces xor-swizzled so that a fragment
 // read touches every bank once.
+#include <algorithm>
 #include <atomic>
 
 #include "tw_internal.h"
@@ -94,6 +95,80 @@ __device__ __forceinline__ int kn_swizzle(int r)
     else return (r >> 3) & 1;
 }
 
+// Helpers: workgroups on the compute units that got no tile fetch what their XCD's tiles read into
+// its L2, ahead of them. A compute unit gets its lines back in the order it asked for them, so
+// among lines that come from the L2 every one that comes from HBM holds up all behind it: what the
+// weights cost is not their share of the requests but HBM's latency for all of them (a panel
+// shared by seven compute units of an XCD comes in at 60 GB/s a unit from HBM and at 105 from the
+// caches). Touching lines ahead from the compute units that work on tiles costs the requests it
+// saves; from others it is free. Measured in us, without / with helpers, operands from HBM: [128 x
+// 8192] x [8192 x 3584] 25.8 / 20.4, [333 x 8192] x [8192 x 3584] 42.3 / 34.5, [64 x 8192] x [8192 x 1280]
+// 14.2 / 10.7; [K x N], whose rows of a narrow tile are less than a line: [16 x 4096] x [4096 x 4096] 18.7 /
+// 9.6 (from the cache 11.0 / 8.8), [128 x 8192] x [8192 x 2048] 38.8 / 18.2.
+//
+// They keep `lead` windows (kHelpWindow bytes of K) ahead of a window every `pace` ticks of the
+// 100 MHz clock: further ahead they would push out of the 4 MiB what the tiles have yet to read (128
+// rows as above: 27 us).
+struct HelpTiming {
+    uint32_t pace, lead_ticks;
+};
+static constexpr uint32_t kHelpWindow = 1024;
+static constexpr double kHelpLeadBytes = 1.5e6, kHelperBytesPerUs = 50e3, kHbmBytesPerUs = 5.3e6;
+static constexpr int64_t kHelpFromK = 2048;
+// What an XCD's tiles, [first, first + count) of the list, read: rows [a_lo, a_hi) of A, and columns
+// [c_lo, c_lo + n1) and [0, n2) of B (two runs where its tiles lie in two blocks of tile rows).
+struct Operands {
+    uint32_t a_lo, a_hi, c_lo, n1, n2;
+};
+__host__ __device__ inline Operands operands_of(uint32_t first, uint32_t count, uint32_t M, uint32_t N, uint32_t tiles_m,
+                                                uint32_t tiles_n, uint32_t group_m, uint32_t BM, uint32_t BN)
+{
+    const uint32_t tiles = tiles_m * tiles_n;
+    if (first >= tiles) return {0, 0, 0, 0, 0};
+    const uint32_t last = (first + count < tiles ? first + count : tiles) - 1, per_block = group_m * tiles_n;
+    const uint32_t b0 = first / per_block, b1 = last / per_block;
+    const auto least = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
+    const auto column = [&](uint32_t tile, uint32_t b) { return (tile - b * per_block) / least(group_m, tiles_m - b * group_m); };
+    const uint32_t c0 = column(first, b0), c1 = column(last, b1);
+    const uint32_t end1 = least((b0 == b1 ? c1 + 1 : tiles_n) * BN, N);
+    return {b0 * group_m * BM, least((b1 + 1) * group_m * BM, M), c0 * BN, end1 - c0 * BN,
+            b0 == b1 ? 0 : b1 == b0 + 1 ? least((c1 + 1) * BN, N) : N};
+}
+// One of n_helpers workgroups of an XCD. A wave's load asks for 64 lines, a dword of each.
+template <bool B_KN>
+__device__ __forceinline__ void fetch_ahead(const char *A, const char *B, uint32_t N, uint32_t K, const Operands o,
+                                            uint32_t helper, uint32_t n_helpers, const HelpTiming timing)
+{
+    const int64_t begun = __builtin_amdgcn_s_memrealtime();
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    const uint32_t row_bytes = K * 2, windows = (row_bytes + kHelpWindow - 1) / kHelpWindow;
+    constexpr uint32_t kRunLines = kHelpWindow / 128, kRows = 64 / kRunLines;  // a load: eight rows of a window
+    // B stored [K x N]: a window is kHelpWindow / 2 rows of B, of which a run of columns takes some lines each
+    const uint32_t kn_lines1 = (o.n1 * 2 + 127) / 128, kn_lines = kn_lines1 + (o.n2 * 2 + 127) / 128;
+    const uint32_t a_loads = (o.a_hi - o.a_lo + kRows - 1) / kRows;
+    const uint32_t b_loads = B_KN ? kHelpWindow / 2 * kn_lines / 64 : (o.n1 + o.n2 + kRows - 1) / kRows;
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, o.a_hi * row_bytes), rb = make_rsrc(B, K * N * 2);
+    for (uint32_t i = wave * n_helpers + helper; i < windows * (a_loads + b_loads); i += waves * n_helpers) {
+        const uint32_t window = i / (a_loads + b_loads), l = i - window * (a_loads + b_loads);
+        const int64_t not_before = begun + static_cast<int64_t>(window) * timing.pace - timing.lead_ticks;
+        while (static_cast<int64_t>(__builtin_amdgcn_s_memrealtime()) < not_before) __builtin_amdgcn_s_sleep(2);
+        const uint32_t in_row = window * kHelpWindow + lane % kRunLines * 128;
+        uint32_t v;
+        if (l < a_loads) {
+            const uint32_t row = o.a_lo + l * kRows + lane / kRunLines;
+            v = __builtin_amdgcn_raw_buffer_load_b32(ra, in_row < row_bytes ? row * row_bytes + in_row : kOutOfRange, 0, 0);
+        } else if constexpr (!B_KN) {
+            const uint32_t at = (l - a_loads) * kRows + lane / kRunLines, row = at < o.n1 ? o.c_lo + at : at - o.n1;
+            v = __builtin_amdgcn_raw_buffer_load_b32(rb, in_row < row_bytes ? row * row_bytes + in_row : kOutOfRange, 0, 0);
+        } else {
+            const uint32_t at = (l - a_loads) * 64 + lane, k = at / kn_lines, line = at - k * kn_lines;
+            const uint32_t column = line < kn_lines1 ? o.c_lo * 2 + line * 128 : (line - kn_lines1) * 128;
+            v = __builtin_amdgcn_raw_buffer_load_b32(rb, (window * (kHelpWindow / 2) + k) * (N * 2) + column, 0, 0);
+        }
+        asm volatile("" ::"v"(v));
+    }
+}
+
 template <bool B_KN, int WM, int WN, int SUBS>
 struct StageFrags {
     bf16x8 a[SUBS][WM];
@@ -110,7 +185,7 @@ struct StageFrags {
 template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, bool LOADERS, bool STREAM_B>
 __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThreads)) void gemm_tile_kernel(
     const char *A, const char *B, char *C, int N, int K, int tiles_m, int tiles_n, int last_rows, int group_m,
-    int tiles_per_xcd)
+    int tiles_per_xcd, uint32_t help)
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // as in tw_gemm.hip: the host pass needs the launch stub only
     using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
@@ -120,6 +195,13 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
     // K = 8192, N = 3584: 13.7 -> 13.1 us; with three rows of tiles 40 % slower).
     constexpr int kBPolicy = STREAM_B ? kStreamPolicy : 0;
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    // (with loading waves only: shapes without helpers came out up to 2 % slower with the branch)
+    if (LOADERS && static_cast<int>(blockIdx.x) >= tiles_per_xcd * kXcds) {
+        const Operands o = operands_of(blockIdx.x % kXcds * tiles_per_xcd, tiles_per_xcd, (tiles_m - 1) * BM + last_rows, N,
+                                       tiles_m, tiles_n, group_m, BM, BN);
+        return fetch_ahead<B_KN>(A, B, N, K, o, blockIdx.x / kXcds - tiles_per_xcd, gridDim.x / kXcds - tiles_per_xcd,
+                                 {help & 0xffff, help >> 16});
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool computes = wave < T::kCompute;
@@ -407,27 +489,33 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
 // host side
 // ---------------------------------------------------------------------------
 
+struct TileLaunch {
+    int budget, cus;
+    bool beside;
+    int helpers;    // for each XCD (kXcds * helpers more workgroups than tiles)
+    uint32_t help;  // their HelpTiming: pace, and the ticks of the lead in the upper half
+};
 // LONG_K: from which K on there are loading waves (0: always, kNeverLoaders: not for this shape).
-static constexpr int kNeverLoaders = 1 << 30;
+static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
 template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, bool STREAM_B = false, bool LOADERS = LONG_K == 0>
-static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, bool beside, hipStream_t stream)
+static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipStream_t stream)
 {
     // (eight waves that multiply and four that load leave no registers for a workgroup beside them)
     if constexpr (LONG_K > 0 && LONG_K < kNeverLoaders && !LOADERS)
-        if (g.K >= LONG_K && !(beside && WVM * WVN == 8))
-            return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM_B, true>(g, budget, cus, beside, stream);
+        if ((LONG_K == kLoadersIfHelped ? l.helpers > 0 : g.K >= LONG_K) && !(l.beside && WVM * WVN == 8))
+            return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM_B, true>(g, l, stream);
     using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
     const int64_t tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
     if constexpr (STREAM_B)
-        if (tiles_m > 1) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, false, LOADERS>(g, budget, cus, beside, stream);
+        if (tiles_m > 1) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, false, LOADERS>(g, l, stream);
     if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
     const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
     const int64_t slots = int64_t(tiles_per_xcd) * kXcds;
     // The whole device: a workgroup per tile, as many to a compute unit as fit. Under a
-    // budget one to a compute unit: more than half of its LDS is asked for.
+    // budget, and with helpers, one to a compute unit: more than half of its LDS is asked for.
     constexpr int kAloneBytes = T::kLdsBytes > 81 * 1024 ? T::kLdsBytes : 81 * 1024;
-    const bool whole = budget >= cus;
-    const unsigned grid = static_cast<unsigned>(whole || slots < budget ? slots : budget);
+    const bool whole = l.budget >= l.cus && l.helpers == 0;
+    const unsigned grid = static_cast<unsigned>((whole || slots < l.budget ? slots : l.budget) + l.helpers * kXcds);
     auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, S, LOADERS, STREAM_B>;
     static std::atomic<int> allowed[kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), kAloneBytes, allowed));
@@ -436,7 +524,7 @@ static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, bool 
                          static_cast<const char *>(g.A), static_cast<const char *>(g.B), static_cast<char *>(g.C),
                          static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
                          static_cast<int>(tiles_n), static_cast<int>(g.M - (tiles_m - 1) * T::BM),
-                         tile_group_m(tiles_m, T::BM, T::BN, budget), tiles_per_xcd));
+                         tile_group_m(tiles_m, T::BM, T::BN, l.budget), tiles_per_xcd, l.help));
     return TW_OK;
 }
 
@@ -444,7 +532,8 @@ static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, bool 
 // the cache and from HBM: tiles of 16 x 16 -7 to -14 % from K = 4096 on and up to +7 % at 512; 32 x 32 -19 to 0 %, [K x N]
 // -12 to +1 % and up to +6 % at 1024; 64 x 32 and 64 x 64 -10 to +2 % and +1 to +5 % up to 1024; 96 x 64 -6 to 0 % and up to +2 %,
 // [K x N] -13 to +1 % at any K; 96 x 96 and 96 x 128 -11 to 0 % at any K; 192 x 64 [K x N] -10 to 0 %, +2 to +6 % at 512; 128 x 128
-// [K x N] -18 to -4 %, up to +5 % at 512; 192 x 64 and 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: none.
+// [K x N] -18 to -4 %, up to +5 % at 512; 64 x 64 [K x N] 0 to +7 % but -4 % with helpers; 192 x 64 and 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: with
+// helpers only.
 // The shapes, smallest first, and what one 64-deep K step of a tile takes when about
 // every compute unit has one (us, measured on MI355X at K = 3584 and 8192). Several
 // tiles to a compute unit take their times in turn, also where two fit at once. [K x N]
@@ -453,22 +542,23 @@ static tw_status launch_tile_t(const tw_gemm_args &g, int budget, int cus, bool 
 // lines but half as many workgroups, came out level to 7 % slower than 32 x 32 there).
 struct SmallTileShape {
     int rows, cols, k_step;
-    float us_nk, us_kn;  // 0: not built for that layout
-    tw_status (*nk)(const tw_gemm_args &, int, int, bool, hipStream_t);
-    tw_status (*kn)(const tw_gemm_args &, int, int, bool, hipStream_t);
+    float us_nk, us_kn;            // 0: not built for that layout
+    float us_help_nk, us_help_kn;  // with helpers (0: none)
+    tw_status (*nk)(const tw_gemm_args &, const TileLaunch &, hipStream_t);
+    tw_status (*kn)(const tw_gemm_args &, const TileLaunch &, hipStream_t);
 };
 static const SmallTileShape kSmallTiles[] = {
-    {16, 16, 256, 0.075f, 0.0f, launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, true>, nullptr},
-    {32, 16, 256, 0.097f, 0.0f, launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, true>, nullptr},
-    {32, 32, 128, 0.132f, 0.150f, launch_tile_t<false, 1, 1, 2, 2, 128, 4, 0, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
-    {64, 32, 128, 0.180f, 0.200f, launch_tile_t<false, 2, 1, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 1, 2, 2, 128, 4, 2048>},
-    {64, 64, 128, 0.200f, 0.230f, launch_tile_t<false, 2, 2, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 2, 2, 2, 128, 4, 2048>},
-    {96, 64, 64, 0.255f, 0.280f, launch_tile_t<false, 3, 2, 2, 2, 64, 6, 2048>, launch_tile_t<true, 3, 2, 2, 2, 64, 6, 0>},
-    {96, 96, 64, 0.338f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6, 0>, nullptr},
-    {96, 128, 64, 0.405f, 0.430f, launch_tile_t<false, 3, 4, 2, 2, 64, 5, 0>, launch_tile_t<true, 3, 4, 2, 2, 64, 5, 0>},
-    {192, 64, 64, 0.430f, 0.500f, launch_tile_t<false, 3, 2, 4, 2, 64, 4, kNeverLoaders>, launch_tile_t<true, 3, 2, 4, 2, 64, 4, 2048>},
-    {128, 128, 64, 0.530f, 0.550f, launch_tile_t<false, 2, 4, 4, 2, 64, 4, kNeverLoaders>, launch_tile_t<true, 2, 4, 4, 2, 64, 4, 2048>},
-    {192, 128, 64, 0.700f, 0.690f, launch_tile_t<false, 3, 4, 4, 2, 64, 3, kNeverLoaders>, launch_tile_t<true, 3, 4, 4, 2, 64, 3, kNeverLoaders>},
+    {16, 16, 256, 0.075f, 0.0f, 0.051f, 0.0f, launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, true>, nullptr},
+    {32, 16, 256, 0.097f, 0.0f, 0.060f, 0.0f, launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, true>, nullptr},
+    {32, 32, 128, 0.132f, 0.150f, 0.078f, 0.102f, launch_tile_t<false, 1, 1, 2, 2, 128, 4, 0, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
+    {64, 32, 128, 0.180f, 0.200f, 0.109f, 0.122f, launch_tile_t<false, 2, 1, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 1, 2, 2, 128, 4, 2048>},
+    {64, 64, 128, 0.200f, 0.230f, 0.139f, 0.155f, launch_tile_t<false, 2, 2, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 2, 2, 2, 128, 4, kLoadersIfHelped>},
+    {96, 64, 64, 0.255f, 0.280f, 0.182f, 0.240f, launch_tile_t<false, 3, 2, 2, 2, 64, 6, 2048>, launch_tile_t<true, 3, 2, 2, 2, 64, 6, 0>},
+    {96, 96, 64, 0.338f, 0.0f, 0.245f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6, 0>, nullptr},
+    {96, 128, 64, 0.405f, 0.430f, 0.260f, 0.290f, launch_tile_t<false, 3, 4, 2, 2, 64, 5, 0>, launch_tile_t<true, 3, 4, 2, 2, 64, 5, 0>},
+    {192, 64, 64, 0.430f, 0.500f, 0.320f, 0.400f, launch_tile_t<false, 3, 2, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 3, 2, 4, 2, 64, 4, 2048>},
+    {128, 128, 64, 0.530f, 0.550f, 0.370f, 0.460f, launch_tile_t<false, 2, 4, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 2, 4, 4, 2, 64, 4, 2048>},
+    {192, 128, 64, 0.700f, 0.690f, 0.0f, 0.0f, launch_tile_t<false, 3, 4, 4, 2, 64, 3, kNeverLoaders>, launch_tile_t<true, 3, 4, 4, 2, 64, 3, kNeverLoaders>},
 };
 
 // A grid's tiles are worked off in turns of one to a compute unit. The launch, the first
@@ -483,9 +573,47 @@ double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_s
     return double(turns) * double(k_steps) * us_per_step + double(turns - 1) * us_per_turn + 4.0;
 }
 
-int best_small_tile(const tw_gemm_args &g, int budget, double *us)
+// Helpers for g cut into tiles of shape t: false where they do not pay. A helper gets some 50 KB a us, so
+// enough of them to fetch what the XCD with the most to read needs within the product's time, and a
+// quarter more; with too few the tiles wait for the helpers (three where eight are needed: 10 to 60 %
+// slower than none).
+static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget, TileLaunch *l, double *us)
+{
+    const float per_step = g.b_layout == TW_B_KN ? t.us_help_kn : t.us_help_nk;
+    const int64_t max_bytes = int64_t(1) << 31;
+    if (per_step == 0.0f || g.K < kHelpFromK || g.N > (1 << 20) || g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return false;
+    const int64_t tiles_m = (g.M + t.rows - 1) / t.rows, tiles_n = (g.N + t.cols - 1) / t.cols;
+    const int64_t per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds, idle = budget / kXcds - per_xcd;
+    if (idle < 1) return false;
+    const int group_m = tile_group_m(tiles_m, t.rows, t.cols, budget);
+    int64_t lines = 0;  // rows of A and columns of B that an XCD reads
+    for (int x = 0; x < kXcds; ++x) {
+        const Operands o = operands_of(x * per_xcd, per_xcd, g.M, g.N, tiles_m, tiles_n, group_m, t.rows, t.cols);
+        lines = std::max<int64_t>(lines, o.a_hi - o.a_lo + o.n1 + o.n2);
+    }
+    const double from_memory = double(g.M + g.N) * g.K * 2 / kHbmBytesPerUs;
+    // (rows that do not start on a line: two lines for every 64 of K)
+    const double time = std::max(double(per_step) * (g.K % 64 ? 1.2 : 1.0) * g.K / 64, from_memory);
+    const double needed = double(lines) * g.K * 2 / (time * kHelperBytesPerUs);
+    if (needed > 0.85 * idle) return false;
+    const int windows = static_cast<int>((g.K * 2 + kHelpWindow - 1) / kHelpWindow);
+    const double pace = std::min(65535.0, 1.15 * time * 100 / windows);
+    const double lead = std::max(2.0, kHelpLeadBytes / (double(lines) * kHelpWindow));
+    l->helpers = static_cast<int>(std::min<int64_t>(idle, int64_t(1.25 * needed) + 1));
+    l->help = static_cast<uint32_t>(pace) | static_cast<uint32_t>(std::min(65535.0, pace * lead)) << 16;
+    *us = time + 4.0;
+    return true;
+}
+
+// A layer's weights of at least this many bytes come from HBM: the last-level cache holds 256 MiB, and
+// the model's other weights pass through it between two uses of one.
+static constexpr int64_t kFromHbmBytes = int64_t(32) << 20;
+
+// The shape of the least estimated time, -1: none for the layout.
+int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *us, bool *helped)
 {
     int best = -1;
+    *helped = false;
     for (int i = 0; i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i) {
         const SmallTileShape &t = kSmallTiles[i];
         const float per_step = g.b_layout == TW_B_KN ? t.us_kn : t.us_nk;
@@ -494,6 +622,23 @@ int best_small_tile(const tw_gemm_args &g, int budget, double *us)
         if (best < 0 || est < *us) {
             best = i;
             *us = est;
+        }
+    }
+    if (best < 0 || place == GemmPlace::kBeside || place == GemmPlace::kWoven) return best;
+    // Larger tiles that leave compute units to helpers gain nothing where the operands are in the
+    // cache, where [N x K] weights of 59 MB and 64 rows take 19 us with them and 15 without (from HBM
+    // 17 and 21): they are taken for [K x N] weights, which gain either way, and for a layer's weights, unless small.
+    const bool keep = g.b_layout == TW_B_NK && (place != GemmPlace::kChain || g.N * g.K * 2 < kFromHbmBytes);
+    const int only = best;
+    const double plain = *us;
+    for (int i = 0; i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i) {
+        TileLaunch l;
+        double est;
+        if ((keep && i != only) || !plan_help(g, kSmallTiles[i], budget, &l, &est)) continue;
+        if (i == only || (est < 0.94 * plain && est < *us)) {
+            best = i;
+            *us = std::min(est, *us);
+            *helped = true;
         }
     }
     return best;
@@ -505,10 +650,13 @@ void small_tile_size(int shape, int *rows, int *cols)
     *cols = kSmallTiles[shape].cols;
 }
 
-tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, bool beside, hipStream_t stream)
+tw_status launch_small_tile(const tw_gemm_args &g, int shape, bool helped, int budget, int cus, bool beside, hipStream_t stream)
 {
     const SmallTileShape &t = kSmallTiles[shape];
-    return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, budget, cus, beside, stream);
+    TileLaunch l = {budget, cus, beside, 0, 0};
+    double us;
+    if (helped && !plan_help(g, t, budget, &l, &us)) return TW_ERR_UNSUPPORTED;
+    return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, l, stream);
 }
 
 }  // namespace tw

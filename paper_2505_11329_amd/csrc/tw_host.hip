@@ -218,9 +218,9 @@ tw_status tw_overlap_launch(const tw_fused_args *fused, const tw_gemm_args *gemm
     // the small fused workgroups then fill in beside it (launched first, they
     // would pile up five to a compute unit and keep the GEMM out until done).
     const bool gemm_first = fused && gemm && fused->cu_budget == TW_CU_SHARED;
-    if (gemm && gemm_first) TW_TRY(launch_gemm(*gemm, sx, fused != nullptr));
+    if (gemm && gemm_first) TW_TRY(launch_gemm(*gemm, sx, fused ? GemmPlace::kBeside : GemmPlace::kAlone));
     if (fused && fused->N > 0) TW_TRY(launch_fused(*fused, 0, fused->N, nullptr, 0, sc));
-    if (gemm && !gemm_first) TW_TRY(launch_gemm(*gemm, sx, fused != nullptr));
+    if (gemm && !gemm_first) TW_TRY(launch_gemm(*gemm, sx, fused ? GemmPlace::kBeside : GemmPlace::kAlone));
     if (parent_is_set && join) {
         if (fused && sc != sp) TW_TRY(stream_wait_stream(sp, sc));
         if (gemm && sx != sp) TW_TRY(stream_wait_stream(sp, sx));
@@ -321,9 +321,9 @@ static tw_status weave_pair(const tw_fused_args &f, const tw_gemm_args &g1, cons
                             bool stagger, int64_t lo, int64_t mid, int64_t hi, hipStream_t sx, hipStream_t sc)
 {
     if (mid >= hi) {
-        TW_TRY(launch_gemm(rows_of(g1, lo, hi), sx, false));
+        TW_TRY(launch_gemm(rows_of(g1, lo, hi), sx, GemmPlace::kWoven));
         TW_TRY(launch_fused(f, lo, hi, nullptr, 0, sx));
-        return launch_gemm(rows_of(g2, lo, hi), sx, false);
+        return launch_gemm(rows_of(g2, lo, hi), sx, GemmPlace::kWoven);
     }
     if (chains) {
         // one chain per split. Where both chains start from the same point (the first
@@ -336,7 +336,7 @@ static tw_status weave_pair(const tw_fused_args &f, const tw_gemm_args &g1, cons
         // The first GEMM of the first chain and the last of the second have no fused
         // kernel of this pair beside them (the one runs before any, the other after
         // both): they take the tile shape of a GEMM launched on its own.
-        TW_TRY(launch_gemm(rows_of(g1, lo, mid), sx, false));
+        TW_TRY(launch_gemm(rows_of(g1, lo, mid), sx, GemmPlace::kWoven));
         if (stagger) {
             hipEvent_t g1a_done;
             TW_TRY(borrow_event(&g1a_done));
@@ -344,17 +344,17 @@ static tw_status weave_pair(const tw_fused_args &f, const tw_gemm_args &g1, cons
             TW_HIP(hipStreamWaitEvent(sc, g1a_done, 0));
         }
         TW_TRY(launch_fused(f, lo, mid, nullptr, 0, sx));
-        TW_TRY(launch_gemm(rows_of(g2, lo, mid), sx, true));
-        TW_TRY(launch_gemm(rows_of(g1, mid, hi), sc, true));
+        TW_TRY(launch_gemm(rows_of(g2, lo, mid), sx, GemmPlace::kBeside));
+        TW_TRY(launch_gemm(rows_of(g1, mid, hi), sc, GemmPlace::kBeside));
         TW_TRY(launch_fused(f, mid, hi, nullptr, 0, sc));
-        return launch_gemm(rows_of(g2, mid, hi), sc, false);
+        return launch_gemm(rows_of(g2, mid, hi), sc, GemmPlace::kWoven);
     }
     // compute stream: both G1 first, so the second split's projection is what
     // runs next to the first split's fused kernel
     const int64_t cuts[3] = {lo, mid, hi};
     hipEvent_t g1_done[2], f_done[2];
     for (int s = 0; s < 2; ++s) {
-        TW_TRY(launch_gemm(rows_of(g1, cuts[s], cuts[s + 1]), sx, true));
+        TW_TRY(launch_gemm(rows_of(g1, cuts[s], cuts[s + 1]), sx, GemmPlace::kBeside));
         TW_TRY(borrow_event(&g1_done[s]));
         TW_HIP(hipEventRecord(g1_done[s], sx));
     }
@@ -364,7 +364,7 @@ static tw_status weave_pair(const tw_fused_args &f, const tw_gemm_args &g1, cons
         TW_TRY(borrow_event(&f_done[s]));
         TW_HIP(hipEventRecord(f_done[s], sc));
         TW_HIP(hipStreamWaitEvent(sx, f_done[s], 0));
-        TW_TRY(launch_gemm(rows_of(g2, cuts[s], cuts[s + 1]), sx, true));
+        TW_TRY(launch_gemm(rows_of(g2, cuts[s], cuts[s + 1]), sx, GemmPlace::kBeside));
     }
     return TW_OK;
 }
@@ -389,11 +389,11 @@ tw_status tw_weave_layer_cuts(const tw_layer_args *layer, const int64_t *cuts, i
         // fused step that was to share the compute units has them to itself here and
         // takes whichever kernel the whole device runs fastest (same bits).
         if (parent_is_set && sx != sp) TW_TRY(stream_wait_stream(sx, sp));
-        TW_TRY(launch_gemm(g1, sx));
+        TW_TRY(launch_gemm(g1, sx, GemmPlace::kChain));
         tw_fused_args alone = f;
         if (alone.cu_budget == TW_CU_SHARED) alone.cu_budget = 0;
         TW_TRY(launch_fused(alone, 0, T, nullptr, 0, sx));
-        TW_TRY(launch_gemm(g2, sx));
+        TW_TRY(launch_gemm(g2, sx, GemmPlace::kChain));
         if (parent_is_set && join && sx != sp) TW_TRY(stream_wait_stream(sp, sx));
         return TW_OK;
     }

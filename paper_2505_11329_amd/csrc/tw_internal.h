@@ -90,10 +90,13 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
 
 // ---- GEMM stand-in (tw_gemm.hip) ----
 tw_status validate_gemm(const tw_gemm_args &g);
-// `beside_other_kernels`: the launch is meant to overlap with another kernel (the
-// fused step, a second GEMM): of the 256-row tiles it then takes the 256 x 128 ones
-// only; smaller tiles where they are estimated faster, as on its own.
-tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, bool beside_other_kernels = false);
+// Where a launch stands. Beside: meant to overlap with another kernel (the fused step, a
+// second GEMM): of the 256-row tiles it then takes the 256 x 128 ones only; smaller tiles where
+// they are estimated faster, as on its own. Woven: nothing beside it for most of the time, tiles
+// as on its own, but the compute units without a tile are not its to use. Chain: on its own, one of a
+// layer's products in a row.
+enum class GemmPlace { kAlone, kBeside, kWoven, kChain };
+tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, GemmPlace place = GemmPlace::kAlone);
 static constexpr int kGemmTileM = 256, kGemmTileN = 128;
 // Tile rows per block of the tile ordering.
 int tile_group_m(int64_t tiles_m, int tile_rows, int tile_cols, int budget);
@@ -101,9 +104,9 @@ int tile_group_m(int64_t tiles_m, int tile_rows, int tile_cols, int budget);
 // grid of tiles, the shape of the least (-1: none for the layout), its size and its launch.
 double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_step, double us_per_step,
                     double us_per_turn, int budget);
-int best_small_tile(const tw_gemm_args &g, int budget, double *us);
+int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *us, bool *helped);
 void small_tile_size(int shape, int *rows, int *cols);
-tw_status launch_small_tile(const tw_gemm_args &g, int shape, int budget, int cus, bool beside, hipStream_t stream);
+tw_status launch_small_tile(const tw_gemm_args &g, int shape, bool helped, int budget, int cus, bool beside, hipStream_t stream);
 
 // ---- fork/join events (tw_host.hip) ----
 // A small per-device pool of timing-disabled events used to order streams.

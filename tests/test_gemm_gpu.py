@@ -258,6 +258,53 @@ def test_gemm_tiles_with_loading_waves(tw, torch_cuda, tile, layouts, M, N, budg
             gemm_check(got[ms, ns], ref, K, 0.5, "%s tiles, %s K = %d" % (tile, layout, K))
 
 
+HELPED = [("nk", 16, 1280, 8192), ("nk", 1, 8, 2048), ("nk", 64, 1280, 4096), ("nk", 40, 1272, 2056), ("nk", 150, 600, 4104),
+          ("nk", 333, 1280, 4096), ("nk", 700, 1000, 2560), ("kn", 16, 4096, 2048), ("kn", 5, 4104, 2056), ("kn", 64, 4096, 2112),
+          ("kn", 130, 1280, 4096), ("kn", 146, 1288, 4104), ("kn", 300, 1000, 3000), ("kn", 433, 328, 4104), ("kn", 1000, 1000, 2504),
+          ("kn", 1200, 2000, 2240), ("kn", 16, 8192, 4096)]
+
+
+@pytest.mark.parametrize("layout,M,N,K", HELPED)
+def test_gemm_with_helper_workgroups(tw, torch_cuda, layout, M, N, K):
+    """Products of few tiles and long K, where compute units without a tile fetch operands ahead: tiles in one and in
+    two blocks of rows, rows that are not whole lines, windows of K that are not whole. Bits as on 8 compute units,
+    which leave none to spare, and samples against the fp64 product; launch after launch on other weights."""
+    torch = torch_cuda
+    code = tw.B_NK if layout == "nk" else tw.B_KN
+    for seed in (0, 1):
+        g = W.make_gemm_inputs(M, K, N, 0.5, seed=M + N + K + seed, b_layout=layout)
+        A, B = to_gpu(g["A"]), to_gpu(g["B"])
+        C, D = (torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
+        tw.gemm_bf16(A, B, C=C, b_layout=code)
+        tw.gemm_bf16(A, B, C=D, b_layout=code, cu_budget=8)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_bits(C), to_bits(D))
+        rng = np.random.default_rng(K + seed)
+        ms, ns = np.append(rng.integers(0, M, 200), [0, M - 1]), np.append(rng.integers(0, N, 200), [0, N - 1])
+        gemm_check(oracle.bf16_to_f64(to_bits(C))[ms, ns], oracle.gemm_samples(g["A"], g["B"], layout, ms, ns), K, 0.5,
+                   "%s %dx%dx%d" % (layout, M, N, K))
+
+
+@pytest.mark.parametrize("T", [33, 64, 100, 200])
+def test_layer_whose_gemm_has_helper_workgroups_equals_the_three_calls(tw, torch_cuda, T):
+    """A chain's long product with weights of more than 32 MB takes larger tiles and helpers than on its own."""
+    torch = torch_cuda
+    H, P, K1, N2 = 8192, 2, 512, 3584
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(T)
+    rand = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.5, generator=gen)
+    X1, W1, W2, parts, res, w = rand(T, K1), rand(H, K1), rand(N2, H), [rand(T, H) for _ in range(P)], rand(T, H), rand(H)
+    out, res_out, Y, row = tw.weave_layer_auto(X1, W1, parts, res, w, 1e-5, W2, torch.cuda.current_stream(), torch.cuda.Stream())
+    torch.cuda.synchronize()
+    assert row == T
+    parts[0] = tw.gemm_bf16(X1, W1)
+    out2, res2 = tw.reduce_add_rmsnorm(parts, res, w, 1e-5)
+    Y2 = tw.gemm_bf16(out2, W2)
+    torch.cuda.synchronize()
+    for a, b in ((out, out2), (res_out, res2), (Y, Y2)):
+        assert np.array_equal(to_bits(a), to_bits(b))
+
+
 @pytest.mark.parametrize("layout,K,tile", [("nk", 512, (256, 128)), ("nk", 2048, (256, 256)), ("kn", 512, (256, 128))])
 def test_gemm_taller_than_four_gib(tw, torch_cuda, layout, K, tile):
     """M = 1.1 M rows: C is 4.5 GB, so tile base addresses run past 2^32 bytes (row 1048576 of C starts
