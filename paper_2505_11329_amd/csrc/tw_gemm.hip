@@ -59,8 +59,10 @@
 //   - B stored [K x N] (B_KN): the B tile lands as 64 k-rows of 256 bytes and the
 //     MFMA operand (8 consecutive k of one column n) is gathered with the
 //     transposing LDS read ds_read_b64_tr_b16.
+#include <algorithm>
 #include <atomic>
 
+#include "tw_help.h"
 #include "tw_internal.h"
 #include "tw_mfma.h"
 
@@ -170,20 +172,25 @@ __device__ __forceinline__ void wait_lgkm(Frags<B_KN, WM, WN> &f)
 // its end (tw_gemm_bf16_traced). Reading the clock costs a scalar memory read and
 // a wait for it each time, so the traced kernel is a few percent slower than the
 // plain one and its figures are for comparing phases, not for the total.
+// HELPED: the workgroups past the tiles' are helpers (tw_help.h).
 // Arguments as of gemm_tile_kernel; group_m: tile rows per block of the tile ordering;
 // tiles_per_xcd: ceil(tiles / 8); phase_cycles: tracing variant only, kGemmPhases counters
 // per wave. (The step of the walk over tiles is gridDim.x: the same number as an argument
 // made every launch of this kernel 0.4 us slower.)
-template <bool B_KN, int WM, int WN, int STAGES, int BK, bool TRACE = false>
+template <bool B_KN, int WM, int WN, int STAGES, int BK, bool TRACE, bool HELPED>
 __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
     const char *A, const char *B, char *C, int N, int K, int tiles_m, int tiles_n, int last_rows, int group_m,
-    int tiles_per_xcd, unsigned long long *phase_cycles)
+    int tiles_per_xcd, uint32_t help, unsigned long long *phase_cycles)
 {
     // The body is for the device pass only: the host pass needs the launch stub,
     // and silently drops it when it cannot make sense of the target-specific
     // builtins and inline assembly below.
 #if defined(__HIP_DEVICE_COMPILE__)
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    if constexpr (HELPED)
+        if (static_cast<int>(blockIdx.x) >= tiles_per_xcd * kXcds)
+            return help_tiles<B_KN>(A, B, (tiles_m - 1) * BM + last_rows, N, K, tiles_m, tiles_n, group_m, tiles_per_xcd, BM,
+                                    TileCfg<WM, WN, STAGES, BK>::kBN, help);
     using Cfg = TileCfg<WM, WN, STAGES, BK>;
     constexpr int NW = Cfg::kWaves;
     constexpr int BN = Cfg::kBN;
@@ -685,8 +692,24 @@ int tile_group_m(int64_t tiles_m, int tile_rows, int tile_cols, int budget)
     return best_gm;
 }
 
-template <bool B_KN, int WM, int WN, int STAGES, int BK, bool TRACE = false>
-static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t stream,
+// Helpers (a multiple of the XCDs) for a launch that leaves `idle` compute units without a tile and lasts
+// some `us`: enough to fetch A and B once in that time, and a quarter more; none if there are fewer. They
+// fetch for the last-level cache (what an XCD's tiles of this size read is more than its idle units
+// can fetch), as fast as they can. us without / with, operands from HBM and from the cache: 256 x 128
+// tiles, 2048 x 8192 x 3584 108 / 100 and 94.5 / 96, K = 4096 56.7 / 52.1 and 49.0 / 49.5. On the larger tiles, which
+// the matrix cores bound, only where rows are not whole lines: 3001 x 4104 x 4096 110 / 91 and 85.1 / 86.3, 2000 x
+// 3000 x 5000 67 / 59.4, but K = 4096 84.6 / 87.2; [K x N] weights 0 to 2 % either way.
+static int plan_help_all(const tw_gemm_args &g, int64_t idle, double us)
+{
+    const int64_t max_bytes = int64_t(1) << 31, bytes = (g.M + g.N) * g.K * 2;
+    if (idle < kXcds || g.K < kHelpFromK || g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return 0;
+    const double needed = double(bytes) / (us * kHelperBytesPerUs);
+    if (needed > 0.85 * double(idle)) return 0;
+    return static_cast<int>(std::min<int64_t>(idle, int64_t(1.25 * needed) + kXcds) / kXcds * kXcds);
+}
+
+template <bool B_KN, int WM, int WN, int STAGES, int BK, bool TRACE = false, bool HELPED = false>
+static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t stream, double helped_us = 0.0,
                             unsigned long long *phase_cycles = nullptr, int64_t phase_len = 0)
 {
     using Cfg = TileCfg<WM, WN, STAGES, BK>;
@@ -695,17 +718,20 @@ static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t strea
     if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
     const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
     const int64_t slots = int64_t(tiles_per_xcd) * kXcds;
-    const unsigned grid = static_cast<unsigned>(slots < budget ? slots : budget);
+    const int helpers = helped_us > 0.0 ? plan_help_all(g, budget - slots, helped_us) : 0;
+    if constexpr (!HELPED && !TRACE && !B_KN && WN > 2)
+        if (helpers > 0) return launch_cfg<B_KN, WM, WN, STAGES, BK, false, true>(g, budget, stream, helped_us);
+    const unsigned grid = static_cast<unsigned>((slots < budget ? slots : budget) + helpers);
 
     if (TRACE && phase_len < int64_t(grid) * Cfg::kWaves * kGemmPhases) return TW_ERR_SHAPE;
-    auto kern = gemm_bf16_kernel<B_KN, WM, WN, STAGES, BK, TRACE>;
+    auto kern = gemm_bf16_kernel<B_KN, WM, WN, STAGES, BK, TRACE, HELPED>;
     static std::atomic<int> allowed[kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), Cfg::kLdsBytes, allowed));
     TW_HIP(launch_kernel(kern, dim3(grid), dim3(Cfg::kThreads), Cfg::kLdsBytes, stream,
                          static_cast<const char *>(g.A), static_cast<const char *>(g.B), static_cast<char *>(g.C),
                          static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
                          static_cast<int>(tiles_n), static_cast<int>(g.M - (tiles_m - 1) * BM),
-                         tile_group_m(tiles_m, BM, BN, budget), tiles_per_xcd, phase_cycles));
+                         tile_group_m(tiles_m, BM, BN, budget), tiles_per_xcd, kHelpAll, phase_cycles));
     return TW_OK;
 }
 
@@ -722,6 +748,7 @@ struct GemmTiles {
     int rows, cols;
     int small;    // shape of tw_gemm_tile.hip, -1: one of this file's, 256 rows high
     bool helped;  // with helper workgroups
+    double us;    // estimated time
 };
 static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place)
 {
@@ -753,7 +780,7 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place
     // for the same L1 request slots (a woven layer measured level to 3 % slower with
     // them), and the larger tiles leave no registers for a co-resident workgroup. (256 x 192
     // tiles held to 384 registers leave room for one; a woven train took 3.5 % longer with them.)
-    GemmTiles take = {BM, kGemmTileN, -1, false};
+    GemmTiles take = {BM, kGemmTileN, -1, false, 0.0};
     double us = 1e300;
     const auto consider = [&](int cols, double us_per_step, double us_per_turn) {
         const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + cols - 1) / cols);
@@ -762,6 +789,7 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place
         if (t < us) {
             us = t;
             take.cols = cols;
+            take.us = t;
         }
     };
     consider(kGemmTileN, g.b_layout == TW_B_KN ? 0.84 : 0.745, 2.7);
@@ -790,11 +818,13 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, GemmPlace place
     const GemmTiles t = choose_tiles(g, budget, place);
     if (t.small >= 0) return launch_small_tile(g, t.small, t.helped, budget, cus, place == GemmPlace::kBeside, stream);
     if (g.b_layout == TW_B_KN) return launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
+    const bool alone = place == GemmPlace::kAlone || place == GemmPlace::kChain;
+    const double helped_us = alone && (t.cols == kGemmTileN || g.K % 64 != 0) ? t.us : 0.0;
     switch (t.cols) {
     case 64: return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);
-    case 256: return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream);
-    case 192: return launch_cfg<false, 8, 6, 2, 64>(g, budget, stream);
-    default: return launch_cfg<false, 4, 4, 3, 64>(g, budget, stream);
+    case 256: return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream, helped_us);
+    case 192: return launch_cfg<false, 8, 6, 2, 64>(g, budget, stream, helped_us);
+    default: return launch_cfg<false, 4, 4, 3, 64>(g, budget, stream, helped_us);
     }
 }
 
@@ -815,7 +845,7 @@ extern "C" tw_status tw_gemm_bf16_traced(const void *A, const void *B, void *C, 
     const int64_t tiles_m = (g.M + BM - 1) / BM;
     const int64_t wide_tiles = tiles_m * ((g.N + kGemmTileN - 1) / kGemmTileN), big_tiles = tiles_m * ((g.N + 255) / 256);
     if (2 * wide_tiles <= cus || wave_fill(big_tiles, cus) < wave_fill(wide_tiles, cus) - 0.05) return TW_ERR_UNSUPPORTED;
-    return launch_cfg<false, 8, 8, 2, 64, true>(g, cus, static_cast<hipStream_t>(stream), phase_cycles, phase_len);
+    return launch_cfg<false, 8, 8, 2, 64, true>(g, cus, static_cast<hipStream_t>(stream), 0.0, phase_cycles, phase_len);
 }
 
 extern "C" tw_status tw_gemm_tile_choice(int64_t M, int64_t N, int64_t K, int b_layout, int cus,

@@ -35,6 +35,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "tw_help.h"
 #include "tw_internal.h"
 #include "tw_mfma.h"
 
@@ -95,80 +96,6 @@ __device__ __forceinline__ int kn_swizzle(int r)
     else return (r >> 3) & 1;
 }
 
-// Helpers: workgroups on the compute units that got no tile fetch what their XCD's tiles read into
-// its L2, ahead of them. A compute unit gets its lines back in the order it asked for them, so
-// among lines that come from the L2 every one that comes from HBM holds up all behind it: what the
-// weights cost is not their share of the requests but HBM's latency for all of them (a panel
-// shared by seven compute units of an XCD comes in at 60 GB/s a unit from HBM and at 105 from the
-// caches). Touching lines ahead from the compute units that work on tiles costs the requests it
-// saves; from others it is free. Measured in us, without / with helpers, operands from HBM: [128 x
-// 8192] x [8192 x 3584] 25.8 / 20.4, [333 x 8192] x [8192 x 3584] 42.3 / 34.5, [64 x 8192] x [8192 x 1280]
-// 14.2 / 10.7; [K x N], whose rows of a narrow tile are less than a line: [16 x 4096] x [4096 x 4096] 18.7 /
-// 9.6 (from the cache 11.0 / 8.8), [128 x 8192] x [8192 x 2048] 38.8 / 18.2.
-//
-// They keep `lead` windows (kHelpWindow bytes of K) ahead of a window every `pace` ticks of the
-// 100 MHz clock: further ahead they would push out of the 4 MiB what the tiles have yet to read (128
-// rows as above: 27 us).
-struct HelpTiming {
-    uint32_t pace, lead_ticks;
-};
-static constexpr uint32_t kHelpWindow = 1024;
-static constexpr double kHelpLeadBytes = 1.5e6, kHelperBytesPerUs = 50e3, kHbmBytesPerUs = 5.3e6;
-static constexpr int64_t kHelpFromK = 2048;
-// What an XCD's tiles, [first, first + count) of the list, read: rows [a_lo, a_hi) of A, and columns
-// [c_lo, c_lo + n1) and [0, n2) of B (two runs where its tiles lie in two blocks of tile rows).
-struct Operands {
-    uint32_t a_lo, a_hi, c_lo, n1, n2;
-};
-__host__ __device__ inline Operands operands_of(uint32_t first, uint32_t count, uint32_t M, uint32_t N, uint32_t tiles_m,
-                                                uint32_t tiles_n, uint32_t group_m, uint32_t BM, uint32_t BN)
-{
-    const uint32_t tiles = tiles_m * tiles_n;
-    if (first >= tiles) return {0, 0, 0, 0, 0};
-    const uint32_t last = (first + count < tiles ? first + count : tiles) - 1, per_block = group_m * tiles_n;
-    const uint32_t b0 = first / per_block, b1 = last / per_block;
-    const auto least = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
-    const auto column = [&](uint32_t tile, uint32_t b) { return (tile - b * per_block) / least(group_m, tiles_m - b * group_m); };
-    const uint32_t c0 = column(first, b0), c1 = column(last, b1);
-    const uint32_t end1 = least((b0 == b1 ? c1 + 1 : tiles_n) * BN, N);
-    return {b0 * group_m * BM, least((b1 + 1) * group_m * BM, M), c0 * BN, end1 - c0 * BN,
-            b0 == b1 ? 0 : b1 == b0 + 1 ? least((c1 + 1) * BN, N) : N};
-}
-// One of n_helpers workgroups of an XCD. A wave's load asks for 64 lines, a dword of each.
-template <bool B_KN>
-__device__ __forceinline__ void fetch_ahead(const char *A, const char *B, uint32_t N, uint32_t K, const Operands o,
-                                            uint32_t helper, uint32_t n_helpers, const HelpTiming timing)
-{
-    const int64_t begun = __builtin_amdgcn_s_memrealtime();
-    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
-    const uint32_t row_bytes = K * 2, windows = (row_bytes + kHelpWindow - 1) / kHelpWindow;
-    constexpr uint32_t kRunLines = kHelpWindow / 128, kRows = 64 / kRunLines;  // a load: eight rows of a window
-    // B stored [K x N]: a window is kHelpWindow / 2 rows of B, of which a run of columns takes some lines each
-    const uint32_t kn_lines1 = (o.n1 * 2 + 127) / 128, kn_lines = kn_lines1 + (o.n2 * 2 + 127) / 128;
-    const uint32_t a_loads = (o.a_hi - o.a_lo + kRows - 1) / kRows;
-    const uint32_t b_loads = B_KN ? kHelpWindow / 2 * kn_lines / 64 : (o.n1 + o.n2 + kRows - 1) / kRows;
-    const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, o.a_hi * row_bytes), rb = make_rsrc(B, K * N * 2);
-    for (uint32_t i = wave * n_helpers + helper; i < windows * (a_loads + b_loads); i += waves * n_helpers) {
-        const uint32_t window = i / (a_loads + b_loads), l = i - window * (a_loads + b_loads);
-        const int64_t not_before = begun + static_cast<int64_t>(window) * timing.pace - timing.lead_ticks;
-        while (static_cast<int64_t>(__builtin_amdgcn_s_memrealtime()) < not_before) __builtin_amdgcn_s_sleep(2);
-        const uint32_t in_row = window * kHelpWindow + lane % kRunLines * 128;
-        uint32_t v;
-        if (l < a_loads) {
-            const uint32_t row = o.a_lo + l * kRows + lane / kRunLines;
-            v = __builtin_amdgcn_raw_buffer_load_b32(ra, in_row < row_bytes ? row * row_bytes + in_row : kOutOfRange, 0, 0);
-        } else if constexpr (!B_KN) {
-            const uint32_t at = (l - a_loads) * kRows + lane / kRunLines, row = at < o.n1 ? o.c_lo + at : at - o.n1;
-            v = __builtin_amdgcn_raw_buffer_load_b32(rb, in_row < row_bytes ? row * row_bytes + in_row : kOutOfRange, 0, 0);
-        } else {
-            const uint32_t at = (l - a_loads) * 64 + lane, k = at / kn_lines, line = at - k * kn_lines;
-            const uint32_t column = line < kn_lines1 ? o.c_lo * 2 + line * 128 : (line - kn_lines1) * 128;
-            v = __builtin_amdgcn_raw_buffer_load_b32(rb, (window * (kHelpWindow / 2) + k) * (N * 2) + column, 0, 0);
-        }
-        asm volatile("" ::"v"(v));
-    }
-}
-
 template <bool B_KN, int WM, int WN, int SUBS>
 struct StageFrags {
     bf16x8 a[SUBS][WM];
@@ -196,12 +123,8 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
     constexpr int kBPolicy = STREAM_B ? kStreamPolicy : 0;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     // (with loading waves only: shapes without helpers came out up to 2 % slower with the branch)
-    if (LOADERS && static_cast<int>(blockIdx.x) >= tiles_per_xcd * kXcds) {
-        const Operands o = operands_of(blockIdx.x % kXcds * tiles_per_xcd, tiles_per_xcd, (tiles_m - 1) * BM + last_rows, N,
-                                       tiles_m, tiles_n, group_m, BM, BN);
-        return fetch_ahead<B_KN>(A, B, N, K, o, blockIdx.x / kXcds - tiles_per_xcd, gridDim.x / kXcds - tiles_per_xcd,
-                                 {help & 0xffff, help >> 16});
-    }
+    if (LOADERS && static_cast<int>(blockIdx.x) >= tiles_per_xcd * kXcds)
+        return help_tiles<B_KN>(A, B, (tiles_m - 1) * BM + last_rows, N, K, tiles_m, tiles_n, group_m, tiles_per_xcd, BM, BN, help);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool computes = wave < T::kCompute;
@@ -493,7 +416,7 @@ struct TileLaunch {
     int budget, cus;
     bool beside;
     int helpers;    // for each XCD (kXcds * helpers more workgroups than tiles)
-    uint32_t help;  // their HelpTiming: pace, and the ticks of the lead in the upper half
+    uint32_t help;  // pack_help()
 };
 // LONG_K: from which K on there are loading waves (0: always, kNeverLoaders: not for this shape).
 static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
@@ -597,10 +520,10 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
     const double needed = double(lines) * g.K * 2 / (time * kHelperBytesPerUs);
     if (needed > 0.85 * idle) return false;
     const int windows = static_cast<int>((g.K * 2 + kHelpWindow - 1) / kHelpWindow);
-    const double pace = std::min(65535.0, 1.15 * time * 100 / windows);
+    const double pace = 1.15 * time * 100 / windows;
     const double lead = std::max(2.0, kHelpLeadBytes / (double(lines) * kHelpWindow));
     l->helpers = static_cast<int>(std::min<int64_t>(idle, int64_t(1.25 * needed) + 1));
-    l->help = static_cast<uint32_t>(pace) | static_cast<uint32_t>(std::min(65535.0, pace * lead)) << 16;
+    l->help = pack_help(pace, pace * lead);
     *us = time + 4.0;
     return true;
 }

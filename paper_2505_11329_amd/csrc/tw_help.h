@@ -1,0 +1,105 @@
+// Helper workgroups of the GEMM kernels: they fetch operands into a cache ahead of the workgroups
+// that work on tiles.
+#pragma once
+
+#include "tw_mfma.h"
+
+namespace tw {
+
+// Helpers: workgroups on the compute units that got no tile fetch what their XCD's tiles read into
+// its L2, ahead of them. A compute unit gets its lines back in the order it asked for them, so
+// among lines that come from the L2 every one that comes from HBM holds up all behind it: what the
+// weights cost is not their share of the requests but HBM's latency for all of them (a panel
+// shared by seven compute units of an XCD comes in at 60 GB/s a unit from HBM and at 105 from the
+// caches). Touching lines ahead from the compute units that work on tiles costs the requests it
+// saves; from others it is free. Measured in us, without / with helpers, operands from HBM: [128 x
+// 8192] x [8192 x 3584] 25.8 / 20.7, [64 x 8192] x [8192 x 1280] 14.2 / 10.7, [16 x 8192] x [8192 x 1280] 10.9 / 9.5; [K x N], whose rows of a narrow tile are less than a line: [16 x 4096] x [4096 x 4096] 18.7 /
+// 9.6 (from the cache 11.0 / 8.8), [128 x 8192] x [8192 x 2048] 38.8 / 18.2.
+//
+// They keep `lead` windows (kHelpWindow bytes of K) ahead of a window every `pace` ticks of the
+// 100 MHz clock: further ahead they would push out of the 4 MiB what the tiles have yet to read (128
+// rows as above: 27 us).
+//
+// Where the XCD's share is more than its idle units can fetch, the helpers of all XCDs fetch every
+// operand once, for the last-level cache, and keep no pace (kHelpAll).
+static constexpr uint32_t kHelpWindow = 1024;
+static constexpr uint32_t kHelpAll = 0x80000000u;
+// The argument of a launch with helpers: ticks of a window and of the lead, or kHelpAll.
+inline uint32_t pack_help(double pace, double lead_ticks)
+{
+    return static_cast<uint32_t>(pace < 65535.0 ? pace : 65535.0) |
+           static_cast<uint32_t>(lead_ticks < 32767.0 ? lead_ticks : 32767.0) << 16;
+}
+static constexpr double kHelpLeadBytes = 1.5e6, kHelperBytesPerUs = 50e3, kHbmBytesPerUs = 5.3e6;
+static constexpr int64_t kHelpFromK = 2048;
+// What an XCD's tiles, [first, first + count) of the list, read: rows [a_lo, a_hi) of A, and columns
+// [c_lo, c_lo + n1) and [0, n2) of B (two runs where its tiles lie in two blocks of tile rows).
+struct Operands {
+    uint32_t a_lo, a_hi, c_lo, n1, n2;
+};
+__host__ __device__ inline Operands operands_of(uint32_t first, uint32_t count, uint32_t M, uint32_t N, uint32_t tiles_m,
+                                                uint32_t tiles_n, uint32_t group_m, uint32_t BM, uint32_t BN)
+{
+    const uint32_t tiles = tiles_m * tiles_n;
+    if (first >= tiles) return {0, 0, 0, 0, 0};
+    const uint32_t last = (first + count < tiles ? first + count : tiles) - 1, per_block = group_m * tiles_n;
+    const uint32_t b0 = first / per_block, b1 = last / per_block;
+    const auto least = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
+    const auto column = [&](uint32_t tile, uint32_t b) { return (tile - b * per_block) / least(group_m, tiles_m - b * group_m); };
+    const uint32_t c0 = column(first, b0), c1 = column(last, b1);
+    const uint32_t end1 = least((b0 == b1 ? c1 + 1 : tiles_n) * BN, N);
+    return {b0 * group_m * BM, least((b1 + 1) * group_m * BM, M), c0 * BN, end1 - c0 * BN,
+            b0 == b1 ? 0 : b1 == b0 + 1 ? least((c1 + 1) * BN, N) : N};
+}
+// One of n_helpers workgroups of an XCD. A wave's load asks for 64 lines, a dword of each.
+template <bool B_KN>
+__device__ __forceinline__ void fetch_ahead(const char *A, const char *B, uint32_t N, uint32_t K, const Operands o,
+                                            uint32_t helper, uint32_t n_helpers, uint32_t help)
+{
+    const uint32_t pace = help & 0xffff, lead_ticks = help >> 16 & 0x7fff;
+    const int64_t begun = __builtin_amdgcn_s_memrealtime();
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    const uint32_t row_bytes = K * 2, windows = (row_bytes + kHelpWindow - 1) / kHelpWindow;
+    constexpr uint32_t kRunLines = kHelpWindow / 128, kRows = 64 / kRunLines;  // a load: eight rows of a window
+    // B stored [K x N]: a window is kHelpWindow / 2 rows of B, of which a run of columns takes some lines each
+    const uint32_t kn_lines1 = (o.n1 * 2 + 127) / 128, kn_lines = kn_lines1 + (o.n2 * 2 + 127) / 128;
+    const uint32_t a_loads = (o.a_hi - o.a_lo + kRows - 1) / kRows;
+    const uint32_t b_loads = B_KN ? kHelpWindow / 2 * kn_lines / 64 : (o.n1 + o.n2 + kRows - 1) / kRows;
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, o.a_hi * row_bytes), rb = make_rsrc(B, K * N * 2);
+    for (uint32_t i = wave * n_helpers + helper; i < windows * (a_loads + b_loads); i += waves * n_helpers) {
+        const uint32_t window = i / (a_loads + b_loads), l = i - window * (a_loads + b_loads);
+        const int64_t not_before = begun + static_cast<int64_t>(window) * pace - lead_ticks;
+        while (static_cast<int64_t>(__builtin_amdgcn_s_memrealtime()) < not_before) __builtin_amdgcn_s_sleep(2);
+        const uint32_t in_row = window * kHelpWindow + lane % kRunLines * 128;
+        uint32_t v;
+        if (l < a_loads) {
+            const uint32_t row = o.a_lo + l * kRows + lane / kRunLines;
+            v = __builtin_amdgcn_raw_buffer_load_b32(ra, in_row < row_bytes ? row * row_bytes + in_row : kOutOfRange, 0, 0);
+        } else if constexpr (!B_KN) {
+            const uint32_t at = (l - a_loads) * kRows + lane / kRunLines, row = at < o.n1 ? o.c_lo + at : at - o.n1;
+            v = __builtin_amdgcn_raw_buffer_load_b32(rb, in_row < row_bytes ? row * row_bytes + in_row : kOutOfRange, 0, 0);
+        } else {
+            const uint32_t at = (l - a_loads) * 64 + lane, k = at / kn_lines, line = at - k * kn_lines;
+            const uint32_t column = line < kn_lines1 ? o.c_lo * 2 + line * 128 : (line - kn_lines1) * 128;
+            v = __builtin_amdgcn_raw_buffer_load_b32(rb, (window * (kHelpWindow / 2) + k) * (N * 2) + column, 0, 0);
+        }
+        asm volatile("" ::"v"(v));
+    }
+}
+
+// What workgroup `slots` + i of a launch of `slots` workgroups for tiles and some helpers does.
+template <bool B_KN>
+__device__ __forceinline__ void help_tiles(const char *A, const char *B, uint32_t M, uint32_t N, uint32_t K, uint32_t tiles_m,
+                                           uint32_t tiles_n, uint32_t group_m, uint32_t tiles_per_xcd, uint32_t BM, uint32_t BN,
+                                           uint32_t help)
+{
+    const uint32_t slots = tiles_per_xcd * kXcds;
+    if (help & kHelpAll) {
+        fetch_ahead<B_KN>(A, B, N, K, {0, M, 0, N, 0}, blockIdx.x - slots, gridDim.x - slots, help);
+    } else {
+        const Operands o = operands_of(blockIdx.x % kXcds * tiles_per_xcd, tiles_per_xcd, M, N, tiles_m, tiles_n, group_m, BM, BN);
+        fetch_ahead<B_KN>(A, B, N, K, o, blockIdx.x / kXcds - tiles_per_xcd, gridDim.x / kXcds - tiles_per_xcd, help);
+    }
+}
+
+}  // namespace tw

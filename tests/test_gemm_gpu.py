@@ -261,14 +261,15 @@ def test_gemm_tiles_with_loading_waves(tw, torch_cuda, tile, layouts, M, N, budg
 HELPED = [("nk", 16, 1280, 8192), ("nk", 1, 8, 2048), ("nk", 64, 1280, 4096), ("nk", 40, 1272, 2056), ("nk", 150, 600, 4104),
           ("nk", 333, 1280, 4096), ("nk", 700, 1000, 2560), ("kn", 16, 4096, 2048), ("kn", 5, 4104, 2056), ("kn", 64, 4096, 2112),
           ("kn", 130, 1280, 4096), ("kn", 146, 1288, 4104), ("kn", 300, 1000, 3000), ("kn", 433, 328, 4104), ("kn", 1000, 1000, 2504),
-          ("kn", 1200, 2000, 2240), ("kn", 16, 8192, 4096)]
+          ("kn", 1200, 2000, 2240), ("kn", 16, 8192, 4096),
+          ("nk", 2048, 3584, 2048), ("nk", 1990, 3528, 2056), ("nk", 3001, 4096, 2056), ("nk", 2000, 5000, 2504)]
 
 
 @pytest.mark.parametrize("layout,M,N,K", HELPED)
 def test_gemm_with_helper_workgroups(tw, torch_cuda, layout, M, N, K):
     """Products of few tiles and long K, where compute units without a tile fetch operands ahead: tiles in one and in
-    two blocks of rows, rows that are not whole lines, windows of K that are not whole. Bits as on 8 compute units,
-    which leave none to spare, and samples against the fp64 product; launch after launch on other weights."""
+    two blocks of rows, rows that are not whole lines, windows of K that are not whole; the 256-row tiles. Bits as on 8
+    compute units, which leave none to spare, and samples against the fp64 product; launch after launch on other weights."""
     torch = torch_cuda
     code = tw.B_NK if layout == "nk" else tw.B_KN
     for seed in (0, 1):
