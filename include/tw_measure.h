@@ -89,8 +89,9 @@ void tw_gemm_tile_shape(int *tile_m, int *tile_n);
  * sizes into on `cus` compute units (the budget, or the device's number without
  * one). beside_other_kernels != 0: as a launch that is meant to overlap with another
  * kernel takes them (tw_overlap_launch, the woven schedules). Host arithmetic only;
- * either pointer may be NULL. TW_ERR_SHAPE for M, N or cus below 1, K below 0 or an
- * unknown layout.
+ * either pointer may be NULL. (A workgroup may work on two neighbouring 256 x 128
+ * tiles of weights stored [K x N] at a time.) TW_ERR_SHAPE for M, N or cus below 1,
+ * K below 0 or an unknown layout.
  */
 tw_status tw_gemm_tile_choice(int64_t M, int64_t N, int64_t K, int b_layout, int cus, int beside_other_kernels,
                               int *tile_m, int *tile_n);

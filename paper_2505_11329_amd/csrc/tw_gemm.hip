@@ -36,7 +36,8 @@
 //     K step kt + 2; the "next stage has landed" check (vmcnt + workgroup
 //     barrier) sits before the last MFMA group of a K step, when every wave
 //     still has matrix work queued.
-//   - Large products launched on their own take 256 x 256 tiles instead: four
+//   - Large products launched on their own take 256 x 256 tiles instead (of B
+//     stored [K x N]: pairs of tiles, in a schedule of their own, see the K loop): four
 //     waves of 128 x 128 (256 accumulator registers per lane), K steps of 64 whose
 //     operand areas rotate through three LDS slots (A) and two (B), one operand's
 //     loads per sub-step (see the K loop). With one wave per SIMD every
@@ -56,7 +57,7 @@
 //     workgroup w takes tile (w mod 8) * ceil(T/8) + w / 8 of a list ordered in
 //     compact blocks: the tiles an XCD works on share rows of A and columns of
 //     B in that XCD's L2.
-//   - B stored [K x N] (B_KN): the B tile lands as 64 k-rows of 256 bytes and the
+//   - B stored [K x N] (B_KN): the B tile lands as 64 k-rows of 256 or 512 bytes and the
 //     MFMA operand (8 consecutive k of one column n) is gathered with the
 //     transposing LDS read ds_read_b64_tr_b16.
 #include <algorithm>
@@ -81,7 +82,8 @@ static_assert(kPhaseTotal + 1 == kGemmPhases, "phase list");
 // eight waves of 64 x 32, tile 256 x 64, 3 x 40 KiB; and for large products
 // <8, 8, 2, 64>: four waves of 128 x 128, tile 256 x 256, and <8, 6, 2, 64>: four of
 // 128 x 96, tile 256 x 192, with three LDS slots for A and two for B (STAGES = 2
-// stands for that, see the K loop).
+// stands for that, see the K loop); <8, 8, 5, 64>, B stored [K x N] only: two 256 x 128 tiles side by
+// side, with two slots for A and three for B (STAGES = 5).
 template <int WM, int WN, int STAGES, int BK_>
 struct TileCfg {
     static constexpr int kWaves = 2 * BM / (kBlk * WM);
@@ -92,8 +94,13 @@ struct TileCfg {
     static constexpr int kStageBytes = kStageABytes + kStageBBytes;
     // Two stages and a third slot for A: A's areas rotate through three, B's through two.
     static constexpr bool kRing = STAGES == 2;
+    // Two slots for A and three for B (STAGES = 5): the rolling schedule.
+    static constexpr bool kRoll = STAGES == 5;
+    static constexpr int kRollBOffset = 2 * kStageABytes;
     static constexpr int kRingBOffset = 3 * kStageABytes;
-    static constexpr int kLdsBytes = kRing ? kRingBOffset + 2 * kStageBBytes : STAGES * kStageBytes;
+    static constexpr int kLdsBytes = kRing   ? kRingBOffset + 2 * kStageBBytes
+                                     : kRoll ? kRollBOffset + 3 * kStageBBytes
+                                             : STAGES * kStageBytes;
 };
 
 // Byte offset inside a stage's A (or B) area of the 16-byte piece c of row r,
@@ -167,6 +174,44 @@ __device__ __forceinline__ void wait_lgkm(Frags<B_KN, WM, WN> &f)
     if constexpr (!B_KN && WM == 8 && WN == 8) TW_WAIT_LGKM(N, f, TW_FRAG_A8, TW_FRAG_B8);
 }
 
+// Fragments of the rolling schedule ([K x N] only): A of two sub-steps, and of B a window of four
+// blocks: the one being multiplied, the next, the one after it on its way, and a fourth so that the
+// blocks of a sub-step are whole rounds of it.
+template <int WM>
+struct Rolling {
+    bf16x8 a[2][WM];
+    u32x2 blo[4], bhi[4];
+    template <int AT>
+    __device__ __forceinline__ bf16x8 b() const
+    {
+        const u32x4 t = {blo[AT].x, blo[AT].y, bhi[AT].x, bhi[AT].y};
+        return __builtin_bit_cast(bf16x8, t);
+    }
+    // Until at most N of this wave's LDS reads are outstanding, and block AT of B is there
+    template <int AT, int N>
+    __device__ __forceinline__ void wait()
+    {
+        asm volatile("s_waitcnt lgkmcnt(%[n])" : "+v"(blo[AT]), "+v"(bhi[AT]) : [n] "n"(N) : "memory");
+    }
+    // ... and all of set SET of A
+    template <int SET, int AT, int N>
+    __device__ __forceinline__ void wait_all()
+    {
+        wait<AT, N>();
+#pragma unroll
+        for (int i = 0; i < WM; ++i) asm volatile("" : "+v"(a[SET][i]));
+    }
+    // Until no read is under way: what the last trip asked for past the end of K as well.
+    __device__ __forceinline__ void settle()
+    {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < WM; ++i) asm volatile("" ::"v"(a[0][i]), "v"(a[1][i]));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" ::"v"(blo[i]), "v"(bhi[i]));
+    }
+};
+
 // TRACE (256 x 256 tiles only): every wave also adds up the shader clocks it
 // spends in each phase of the K loop and of a tile, and writes the sums out at
 // its end (tw_gemm_bf16_traced). Reading the clock costs a scalar memory read and
@@ -198,16 +243,15 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
     constexpr int kStageBytes = Cfg::kStageBytes;
     constexpr int kStages = STAGES;
     constexpr int kSubs = BK / kSubK;                        // K sub-steps (one MFMA deep) per K step
-    constexpr bool kRing = Cfg::kRing;
+    constexpr bool kRing = Cfg::kRing, kRoll = Cfg::kRoll;
     constexpr int kBlockBytes = kBlk * BK * 2;               // LDS distance between 16-row blocks
     constexpr int A_LOADS = kStageABytes / 1024 / NW;        // wave instructions (1 KiB each) per wave that
     constexpr int B_LOADS = Cfg::kStageBBytes / 1024 / NW;   // fill a stage's A area, and its B area
     constexpr int kLoads = A_LOADS + B_LOADS;                // loads of one K step per lane
     static_assert(BK == 64, "LDS layouts and schedules below");
-    static_assert(STAGES >= 2 && (STAGES - 1) * kLoads < 64 && 2 * kLoads < 64, "vmcnt field");
-    static_assert(!B_KN || WN == 4, "[K x N] operands: 256 x 128 tiles only");
+    static_assert(STAGES >= 2 && (kRoll || (STAGES - 1) * kLoads < 64) && 2 * kLoads < 64, "vmcnt field");
+    static_assert(!B_KN || (kRoll ? WN == 8 : WN == 4), "[K x N] operands: 256 x 128 tiles and pairs of them only");
     static_assert(Cfg::kLdsBytes <= 160 * 1024, "LDS of one compute unit");
-    static_assert(!kRing || !B_KN, "the ring schedule below");
     static_assert(!TRACE || kRing, "phases are counted in the ring schedule");
     // shader clock, with nothing of this wave's outstanding on the LDS/scalar counter afterwards
     auto now = [&]() {
@@ -247,19 +291,21 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
     const int piece = (slot % kPieces) ^ line_low;
     const int row_lo = kRowsPerLine * (wave * 4 + line_in_instr) + slot / kPieces;  // + 4 * kRowsPerLine * NW * i
     constexpr int kRowsPerInstr = 4 * kRowsPerLine * NW;  // rows all waves' instruction i cover
-    // B stored [K x N]: its LDS area holds 64 k-rows of 256 bytes (128 n); a wave
-    // instruction fills four rows; row r keeps 16-byte piece s at slot
+    // B stored [K x N]: its LDS area holds 64 k-rows of 256 bytes (128 n) or 512 (256 n); a wave
+    // instruction fills four rows, or two; row r keeps 16-byte piece s at slot
     // s ^ ((r & 3) << 1) ^ ((r & 8) ? 8 : 0), so that the eight rows the first (and
     // the second) half of a wave's transposing read touches fall into different
     // banks: four rows per 16-lane group, two groups eight rows apart.
-    const int bkn_row_lo = wave * 4 + line_in_instr;                  // + 4 * NW * i
-    static_assert(!B_KN || NW == 8, "bit 3 of a row number below");
-    const int bkn_piece = slot ^ (line_in_instr << 1) ^ (((wave >> 1) & 1) << 3);
+    constexpr int kKnRowBytes = BN * 2, kKnPieces = BN / 8, kKnRows = 64 / kKnPieces;
+    const int bkn_row_lo = wave * kKnRows + lane / kKnPieces;         // + kKnRows * NW * i
+    // (128 columns: bit 3 of the row number is the same for every i. 256: it is set for the odd ones.)
+    static_assert(!B_KN || kKnRows * NW == (BN == 128 ? 32 : 8), "bit 3 of a row number");
+    const int bkn_piece = (lane % kKnPieces) ^ ((bkn_row_lo & 3) << 1) ^ (BN == 128 ? bkn_row_lo & 8 : 0);
 
     // fragment read addresses inside a stage's A area and inside its B area for
     // the wave's first 16-row block; block i lies 16 rows = kBlockBytes further
     // (the swizzle repeats within that), which goes into the read's offset field
-    uint32_t fa_addr[kSubs], fb_addr[kSubs], fbkn_addr[B_KN ? WN : 1];
+    uint32_t fa_addr[kSubs], fb_addr[kSubs], fbkn_addr[B_KN && !kRoll ? WN : 1];
 #pragma unroll
     for (int kk = 0; kk < kSubs; ++kk) {
         fa_addr[kk] = lds_piece(wave_m * (kBlk * WM) + l15, kk * 4 + lgrp);
@@ -273,10 +319,10 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         const int a4 = l15 & 3, j = l15 >> 2;
         const int row = lgrp * 8 + j;
 #pragma unroll
-        for (int i = 0; i < WN; ++i) {
+        for (int i = 0; i < (kRoll ? 1 : WN); ++i) {
             const int col = wave_n * (kBlk * WN) + i * kBlk + 4 * a4;
             const int piece_slot = (col >> 3) ^ (j << 1) ^ ((lgrp & 1) << 3);
-            fbkn_addr[i] = row * 256 + (piece_slot << 4) + (col & 7) * 2;
+            fbkn_addr[i] = row * kKnRowBytes + (piece_slot << 4) + (col & 7) * 2;
         }
     } else {
         fbkn_addr[0] = 0;
@@ -339,6 +385,16 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
             long long bk_off;  // [K x N] only: byte offset of row k0 of B, and how many
             uint32_t bk_len;   // bytes of B the rows k0 .. k0+63 that exist take
         };
+        // [K x N], 256 columns: the lane's offset in the rows of even and odd instructions, to which a scalar
+        // offset leads, as above
+        uint32_t kn_voff[2] = {};
+        if constexpr (kRoll)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int n = n0 + (bkn_piece ^ (q * 8)) * 8;
+                kn_voff[q] = n < N ? static_cast<uint32_t>(bkn_row_lo * bkn_row_bytes + n * 2) : kPastK;
+            }
+        const uint32_t kn_instr_bytes = static_cast<uint32_t>(kKnRows * NW * bkn_row_bytes);
         // (area_a, area_b: byte offsets of the LDS areas that take the K step)
         auto fetch_ctx = [&](int kt, uint32_t area_a, uint32_t area_b) {
             FetchCtx c;
@@ -369,11 +425,16 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
                 // fall outside it, columns past N are redirected out of range
                 const int i = idx - A_LOADS;
                 const __amdgpu_buffer_rsrc_t rbk = make_rsrc(B + c.bk_off, c.bk_len);
-                const int n = n0 + bkn_piece * 8;
-                const uint32_t off = static_cast<uint32_t>((bkn_row_lo + 4 * NW * i) * bkn_row_bytes + n * 2);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rbk, (lds_ptr_t)(c.sb + (i * NW + wave) * 1024), 16,
-                    n < N ? off : kOutOfRange, 0, 0, 0);
+                if constexpr (kRoll) {
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rbk, (lds_ptr_t)(c.sb + (i * NW + wave) * 1024), 16,
+                                                             kn_voff[i & 1], kn_instr_bytes * i, 0, 0);
+                } else {
+                    const int n = n0 + bkn_piece * 8;
+                    const uint32_t off = static_cast<uint32_t>((bkn_row_lo + 4 * NW * i) * bkn_row_bytes + n * 2);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                        rbk, (lds_ptr_t)(c.sb + (i * NW + wave) * 1024), 16,
+                        n < N ? off : kOutOfRange, 0, 0, 0);
+                }
             }
         };
         auto stage_ctx = [&](int kt, int stage) {
@@ -394,9 +455,9 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
                 f.b[j - WM] = lds_read16<kBlockBytes * (j - WM)>(base_b + fb_addr[kk]);
             } else {
                 constexpr int i = (j - WM) >> 1;
-                constexpr int kRowBytes = 256, kOff = kk * kSubK * kRowBytes;
+                constexpr int kOff = kk * kSubK * kKnRowBytes;
                 if constexpr (((j - WM) & 1) == 0) f.blo[i] = lds_read_tr8<kOff>(base_b + fbkn_addr[i]);
-                else f.bhi[i] = lds_read_tr8<kOff + 4 * kRowBytes>(base_b + fbkn_addr[i]);
+                else f.bhi[i] = lds_read_tr8<kOff + 4 * kKnRowBytes>(base_b + fbkn_addr[i]);
             }
         };
         auto load_frags = [&](F &f, uint32_t base_a, uint32_t base_b, auto kk_tag) {
@@ -466,7 +527,102 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
 
         F f0, f1;
         int stage = 0;
-        if constexpr (kRing) {
+        if constexpr (kRoll) {
+            // Rolling schedule, pairs of 256 x 128 tiles of B stored [K x N]. A transposing read brings half of
+            // what a plain one does, so a sub-step takes 24 reads, and two whole sets of fragments beside the 256
+            // accumulators and the read addresses are more registers than a lane has: the ring
+            // schedule below compiled to 300 moves to and from the accumulator registers in a K step, and was
+            // slower than single tiles. So only A has two sets; the reads of B run two blocks
+            // ahead of the multiplications and each block's are waited for by count, the newer ones still on
+            // their way. B is thus read to the end of its second sub-step, when the loads of
+            // the next K steps have long to be out: three slots for B, two for A, whose reads all go out
+            // in the first half of a sub-step. One barrier a K step, in its middle: K step kt + 1 has
+            // landed, A(kt) and B(kt - 1) are read by every wave (a wave waits for its last read of a
+            // sub-step inside it), and the loads of K step kt + 2 into their slots follow in the second
+            // sub-step. Single / paired, us, operands from HBM and from the cache: 4096^3 115 / 105 and 108 / 96,
+            // 8192^3 882 / 756 and 873 / 741, 8192 x 3584, K = 8192 418 / 376 and 394 / 330, 5000^3 307 / 252 and 288 / 232. (For B stored [N x K] the ring schedule is 1 to 20 % ahead of this one.)
+            auto slot_a = [&](int sl) { return static_cast<uint32_t>(sl * kStageABytes); };
+            auto slot_b = [&](int sl) { return static_cast<uint32_t>(Cfg::kRollBOffset + sl * Cfg::kStageBBytes); };
+            static_for<2>([&](auto st) {
+                constexpr int j = decltype(st)::value;
+                const FetchCtx c = fetch_ctx(j, slot_a(j), slot_b(j));
+                static_for<kLoads>([&](auto i) { fetch_one(c, decltype(i)::value); });
+            });
+            wait_vm(std::integral_constant<int, kLoads>{});  // K step 0 has landed
+            Rolling<WM> r;
+            constexpr int kBReads = 2;
+            // half h of the fragment of block nb, sub-step kk, of the B area base_b, into place `at` of the window
+            // (block nb's columns flip bits of the address that neither the swizzle nor the area carries into)
+            auto read_b = [&](uint32_t base_b, auto kk_tag, auto nb_tag, auto at_tag, auto h_tag) {
+                constexpr int kk = decltype(kk_tag)::value, nb = decltype(nb_tag)::value, at = decltype(at_tag)::value & 3;
+                constexpr int kOff = kk * kSubK * kKnRowBytes;
+                const uint32_t addr = (base_b + fbkn_addr[0]) ^ (nb << 5);
+                if constexpr (decltype(h_tag)::value == 0) r.blo[at] = lds_read_tr8<kOff>(addr);
+                else r.bhi[at] = lds_read_tr8<kOff + 4 * kKnRowBytes>(addr);
+            };
+            auto read_a = [&](uint32_t base_a, auto kk_tag, auto set_tag, auto i_tag) {
+                constexpr int i = decltype(i_tag)::value;
+                r.a[decltype(set_tag)::value][i] = lds_read16<kBlockBytes * i>(base_a + fa_addr[decltype(kk_tag)::value]);
+            };
+            using I0 = std::integral_constant<int, 0>;
+            using I1 = std::integral_constant<int, 1>;
+            static_for<WM>([&](auto i) { read_a(slot_a(0), I0{}, I0{}, i); });
+            static_for<2>([&](auto nb) {
+                static_for<kBReads>([&](auto h) { read_b(slot_b(0), I0{}, nb, nb, h); });
+            });
+            // reads of A that go out during block nb of a sub-step (negative: of the one before)
+            constexpr auto a_reads = [](int nb) { return (nb < 0 ? nb + WN : nb) < WM / 2 ? 2 : 0; };
+            static_assert(WN >= WM / 2 + 2, "every fragment of A is asked for before the next sub-step's first of B");
+            // Sub-step `sub`, its A in set `sub`; b_here: the B area of this K step. A of the next sub-step comes
+            // from next_a, its first two blocks of B from next_b.
+            auto roll = [&](auto sub_tag, uint32_t b_here, uint32_t next_a, uint32_t next_b, const FetchCtx &fc, auto &&late) {
+                constexpr int sub = decltype(sub_tag)::value, first = sub * WN;
+                using Next = std::integral_constant<int, 1 - sub>;
+                static_for<WN>([&](auto nb_tag) {
+                    constexpr int nb = decltype(nb_tag)::value, at = (first + nb) & 3;
+                    // reads issued after those of this block's fragment
+                    constexpr int newer = a_reads(nb - 2) + kBReads + a_reads(nb - 1);
+                    if constexpr (nb == 0) r.template wait_all<sub, at, kBReads>();
+                    else r.template wait<at, newer>();
+                    static_for<WM>([&](auto mb_tag) {
+                        constexpr int mb = decltype(mb_tag)::value, m = nb * WM + mb;
+                        acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r.template b<at>(), r.a[sub][mb], acc[nb][mb], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if constexpr (mb < kBReads) {
+                            using To = std::integral_constant<int, first + nb + 2>;
+                            if constexpr (nb + 2 < WN)
+                                read_b(b_here, sub_tag, std::integral_constant<int, nb + 2>{}, To{}, mb_tag);
+                            else
+                                read_b(next_b, Next{}, std::integral_constant<int, nb + 2 - WN>{}, To{}, mb_tag);
+                        }
+                        if constexpr (a_reads(nb) > 0 && (mb == 3 || mb == 5))
+                            read_a(next_a, Next{}, Next{}, std::integral_constant<int, 2 * nb + (mb == 5)>{});
+                        if constexpr (sub == 1)
+                            static_for<kLoads>([&](auto t_tag) {
+                                constexpr int t = decltype(t_tag)::value;
+                                if constexpr (t * (WN * WM) / kLoads + 2 == m) fetch_one(fc, t);
+                            });
+                        if constexpr (m == WN * WM * 3 / 4) late();
+                        __builtin_amdgcn_sched_barrier(0);
+                    });
+                });
+            };
+            // areas of this K step and the next (o_n..), and the one of B that is free
+            uint32_t o_a = slot_a(0), o_na = slot_a(1), o_b = slot_b(0), o_nb = slot_b(1), o_fb = slot_b(2);
+            FetchCtx fc = {};
+            for (int kt = 0; kt < k_tiles; ++kt) {
+                roll(I0{}, o_b, o_a, o_b, fc, [&] { fc = fetch_ctx(kt + 2, o_a, o_fb); });
+                wait_vm(I0{});
+                roll(I1{}, o_b, o_na, o_nb, fc, [] {});
+                const uint32_t t_a = o_a, t_b = o_b;
+                o_a = o_na;
+                o_na = t_a;
+                o_b = o_nb;
+                o_nb = o_fb;
+                o_fb = t_b;
+            }
+            r.settle();
+        } else if constexpr (kRing) {
             // Three slots for A and two for B, each one operand's share of a K step: K step j
             // keeps A in slot j mod 3 and B in slot j mod 2. While step j is worked on, step
             // j + 1 sits in the next ones (landed, or landing) and the third slot of A is free:
@@ -571,8 +727,10 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         // takes an inline ds_read for complete, is free to reuse their destination
         // registers for the store addresses below. Wait for them while both
         // fragment sets are still live.
-        wait_lgkm<0>(f0);
-        wait_lgkm<0>(f1);
+        if constexpr (!kRoll) {
+            wait_lgkm<0>(f0);
+            wait_lgkm<0>(f1);
+        }  // (the rolling schedule has settled its own)
         unsigned long long t_stores = 0;
         if constexpr (TRACE) {
             t_stores = now();
@@ -698,7 +856,8 @@ int tile_group_m(int64_t tiles_m, int tile_rows, int tile_cols, int budget)
 // can fetch), as fast as they can. us without / with, operands from HBM and from the cache: 256 x 128
 // tiles, 2048 x 8192 x 3584 108 / 100 and 94.5 / 96, K = 4096 56.7 / 52.1 and 49.0 / 49.5. On the larger tiles, which
 // the matrix cores bound, only where rows are not whole lines: 3001 x 4104 x 4096 110 / 91 and 85.1 / 86.3, 2000 x
-// 3000 x 5000 67 / 59.4, but K = 4096 84.6 / 87.2; [K x N] weights 0 to 2 % either way.
+// 3000 x 5000 67 / 59.4, but K = 4096 84.6 / 87.2; [K x N] weights on single 256 x 128 tiles 0 to 2 % either way, on
+// pairs 3001 x 4096, K = 4104 122 / 104 and 97.2 / 97.9, K = 4096 95.7 / 85.1 and 83.0 / 85.1.
 static int plan_help_all(const tw_gemm_args &g, int64_t idle, double us)
 {
     const int64_t max_bytes = int64_t(1) << 31, bytes = (g.M + g.N) * g.K * 2;
@@ -719,7 +878,7 @@ static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t strea
     const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
     const int64_t slots = int64_t(tiles_per_xcd) * kXcds;
     const int helpers = helped_us > 0.0 ? plan_help_all(g, budget - slots, helped_us) : 0;
-    if constexpr (!HELPED && !TRACE && !B_KN && WN > 2)
+    if constexpr (!HELPED && !TRACE && (!B_KN || WN == 8) && WN > 2)
         if (helpers > 0) return launch_cfg<B_KN, WM, WN, STAGES, BK, false, true>(g, budget, stream, helped_us);
     const unsigned grid = static_cast<unsigned>((slots < budget ? slots : budget) + helpers);
 
@@ -748,6 +907,7 @@ struct GemmTiles {
     int rows, cols;
     int small;    // shape of tw_gemm_tile.hip, -1: one of this file's, 256 rows high
     bool helped;  // with helper workgroups
+    bool paired;  // two neighbouring 256 x 128 tiles to a workgroup, as one of 256 x 256 (B stored [K x N])
     double us;    // estimated time
 };
 static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place)
@@ -780,15 +940,22 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place
     // for the same L1 request slots (a woven layer measured level to 3 % slower with
     // them), and the larger tiles leave no registers for a co-resident workgroup. (256 x 192
     // tiles held to 384 registers leave room for one; a woven train took 3.5 % longer with them.)
-    GemmTiles take = {BM, kGemmTileN, -1, false, 0.0};
+    //
+    // Products of B stored [K x N] come in 256 x 128 tiles; alone, a workgroup takes two side by side, in
+    // the registers and LDS of a 256 x 256 one, where that has the least estimated time (us as above, 256 x 128 singly /
+    // paired, operands from HBM and from the cache: 4096 x 4096, K = 2048 64.4 / 59.4 and 59.7 / 55.0; 4096^3 on 64
+    // compute units 384 / 334 and 338 / 302). Not for shorter K, where what a pair pays for its fill and stores
+    // counts: 4096 x 4096, K = 1024 38.1 / 36.3 and 33.4 / 33.3, but 2447 x 3584 27.9 / 30.3 and 27.5 / 29.1.
+    GemmTiles take = {BM, kGemmTileN, -1, false, false, 0.0};
     double us = 1e300;
-    const auto consider = [&](int cols, double us_per_step, double us_per_turn) {
+    const auto consider = [&](int cols, double us_per_step, double us_per_turn, bool pairs = false) {
         const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + cols - 1) / cols);
         const double cool = cols == kGemmTileN ? 1.0 : 0.78 + 0.22 * wave_fill(tiles, budget);
         const double t = tile_grid_us(g.M, g.N, g.K, BM, cols, 64, us_per_step * cool, us_per_turn, budget);
         if (t < us) {
             us = t;
-            take.cols = cols;
+            take.cols = pairs ? cols / 2 : cols;
+            take.paired = pairs;
             take.us = t;
         }
     };
@@ -798,6 +965,7 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place
         consider(256, 1.40, 7.5);
         consider(192, 1.08, 6.6);
     }
+    if (g.b_layout == TW_B_KN && place != GemmPlace::kBeside && g.K >= 2048) consider(2 * kGemmTileN, 1.40, 9.0, true);
     double small_us = 0.0;
     bool helped = false;
     const int small = best_small_tile(g, budget, place, &small_us, &helped);
@@ -817,9 +985,12 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, GemmPlace place
     const int budget = resolve_budget(g.cu_budget, cus);
     const GemmTiles t = choose_tiles(g, budget, place);
     if (t.small >= 0) return launch_small_tile(g, t.small, t.helped, budget, cus, place == GemmPlace::kBeside, stream);
-    if (g.b_layout == TW_B_KN) return launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
     const bool alone = place == GemmPlace::kAlone || place == GemmPlace::kChain;
-    const double helped_us = alone && (t.cols == kGemmTileN || g.K % 64 != 0) ? t.us : 0.0;
+    const bool kn = g.b_layout == TW_B_KN;
+    const double helped_us = alone && (kn || t.cols == kGemmTileN || g.K % 64 != 0) ? t.us : 0.0;
+    if (kn)
+        return t.paired ? launch_cfg<true, 8, 8, 5, 64>(g, budget, stream, helped_us)
+                        : launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
     switch (t.cols) {
     case 64: return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);
     case 256: return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream, helped_us);

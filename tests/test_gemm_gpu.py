@@ -286,6 +286,31 @@ def test_gemm_with_helper_workgroups(tw, torch_cuda, layout, M, N, K):
                    "%s %dx%dx%d" % (layout, M, N, K))
 
 
+@pytest.mark.parametrize("M,N,K,budget", [(3001, 4096, 4104, 0), (4096, 4096, 2176, 0), (4040, 7944, 2112, 0), (4000, 4072, 2344, 100),
+                                          (500, 1000, 4168, 4), (700, 1000, 3200, 3), (256, 200, 2456, 1)])
+def test_gemm_pairs_of_tiles_of_weights_stored_k_by_n(tw, torch_cuda, M, N, K, budget):
+    """Sizes at which a workgroup takes two 256 x 128 tiles of B stored [K x N] at a time (two LDS slots for A, three for
+    B): K steps of every remainder of the two rotations, whole and ragged; an odd number of tiles in a row; one pair
+    to a workgroup (with and without helpers) and several. The bits of the other storage order and of the
+    small tiles that a part of the rows takes, and samples against the fp64 product."""
+    torch = torch_cuda
+    a = W.make_gemm_inputs(M, K, N, 0.5, seed=M + K, b_layout="nk")
+    b = W.make_gemm_inputs(M, K, N, 0.5, seed=M + K, b_layout="kn")
+    assert tw.gemm_tile_choice(M, N, K, tw.B_KN, budget or tw.device_cu_count()) == (256, 128)
+    A, B = to_gpu(b["A"]), to_gpu(b["B"])
+    want = to_bits(tw.gemm_bf16(A, to_gpu(a["B"])))
+    for _ in range(2):
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        tw.gemm_bf16(A, B, C=C, b_layout=tw.B_KN, cu_budget=budget)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_bits(C), want)
+    assert tw.gemm_tile_choice(90, N, K, tw.B_KN, tw.device_cu_count())[0] < 256
+    assert np.array_equal(to_bits(tw.gemm_bf16(A[:90], B, b_layout=tw.B_KN)), want[:90])
+    rng = np.random.default_rng(K)
+    ms, ns = np.append(rng.integers(0, M, 400), [0, M - 1]), np.append(rng.integers(0, N, 400), [0, N - 1])
+    gemm_check(oracle.bf16_to_f64(want)[ms, ns], oracle.gemm_samples(b["A"], b["B"], "kn", ms, ns), K, 0.5, "kn %dx%dx%d" % (M, N, K))
+
+
 @pytest.mark.parametrize("T", [33, 64, 100, 200])
 def test_layer_whose_gemm_has_helper_workgroups_equals_the_three_calls(tw, torch_cuda, T):
     """A chain's long product with weights of more than 32 MB takes larger tiles and helpers than on its own."""
