@@ -451,11 +451,12 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
     return TW_OK;
 }
 
-// The loading waves' K: measured, loading waves against none, for 96 and 256 tiles, K = 512, 1024, 4096 and 8192, from
-// the cache and from HBM: tiles of 16 x 16 -7 to -14 % from K = 4096 on and up to +7 % at 512; 32 x 32 -19 to 0 %, [K x N]
-// -12 to +1 % and up to +6 % at 1024; 64 x 32 and 64 x 64 -10 to +2 % and +1 to +5 % up to 1024; 96 x 64 -6 to 0 % and up to +2 %,
-// [K x N] -13 to +1 % at any K; 96 x 96 and 96 x 128 -11 to 0 % at any K; 192 x 64 [K x N] -10 to 0 %, +2 to +6 % at 512; 128 x 128
-// [K x N] -18 to -4 %, up to +5 % at 512; 64 x 64 [K x N] 0 to +7 % but -4 % with helpers; 192 x 64 and 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: with
+// The loading waves' K: measured, loading waves against none, for 96 and 256 tiles, K = 512, 1024, 4096 and 8192 and some
+// shorter ones, from the cache and from HBM: tiles of 16 x 16 -7 to -14 % from K = 4096 on and up to +7 % at 512; 32 x 32 -19 to
+// 0 %, but +2 to +5 % up to 1984 with one row of tiles, [K x N] -12 to +1 % and up to +6 % at 1024; 64 x 32 and 64 x 64 -10 to +2 %
+// and +1 to +5 % up to 1024; 96 x 64 -6 to 0 % and up to +2 %, [K x N] -13 to +1 %, +2 to +4 % at 176 and 256; 96 x 96 -11 to 0 %, up to
+// +2 % at 136; 96 x 128 -11 to +1 % at any K; 192 x 64 [K x N] -10 to 0 %, +2 to +6 % at 512; 128 x 128 [K x N] -18 to -4 %, up to +5 % at 512;
+// 64 x 64 [K x N] 0 to +7 % but -4 % with helpers; 192 x 64 and 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: with
 // helpers only.
 // The shapes, smallest first, and what one 64-deep K step of a tile takes when about
 // every compute unit has one (us, measured on MI355X at K = 3584 and 8192). Several
@@ -473,11 +474,11 @@ struct SmallTileShape {
 static const SmallTileShape kSmallTiles[] = {
     {16, 16, 256, 0.075f, 0.0f, 0.051f, 0.0f, launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, true>, nullptr},
     {32, 16, 256, 0.097f, 0.0f, 0.060f, 0.0f, launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, true>, nullptr},
-    {32, 32, 128, 0.132f, 0.150f, 0.078f, 0.102f, launch_tile_t<false, 1, 1, 2, 2, 128, 4, 0, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
+    {32, 32, 128, 0.132f, 0.150f, 0.078f, 0.102f, launch_tile_t<false, 1, 1, 2, 2, 128, 4, 2048, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
     {64, 32, 128, 0.180f, 0.200f, 0.109f, 0.122f, launch_tile_t<false, 2, 1, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 1, 2, 2, 128, 4, 2048>},
     {64, 64, 128, 0.200f, 0.230f, 0.139f, 0.155f, launch_tile_t<false, 2, 2, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 2, 2, 2, 128, 4, kLoadersIfHelped>},
-    {96, 64, 64, 0.255f, 0.280f, 0.182f, 0.240f, launch_tile_t<false, 3, 2, 2, 2, 64, 6, 2048>, launch_tile_t<true, 3, 2, 2, 2, 64, 6, 0>},
-    {96, 96, 64, 0.338f, 0.0f, 0.245f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6, 0>, nullptr},
+    {96, 64, 64, 0.255f, 0.280f, 0.182f, 0.240f, launch_tile_t<false, 3, 2, 2, 2, 64, 6, 2048>, launch_tile_t<true, 3, 2, 2, 2, 64, 6, 320>},
+    {96, 96, 64, 0.338f, 0.0f, 0.245f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6, 320>, nullptr},
     {96, 128, 64, 0.405f, 0.430f, 0.260f, 0.290f, launch_tile_t<false, 3, 4, 2, 2, 64, 5, 0>, launch_tile_t<true, 3, 4, 2, 2, 64, 5, 0>},
     {192, 64, 64, 0.430f, 0.500f, 0.320f, 0.400f, launch_tile_t<false, 3, 2, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 3, 2, 4, 2, 64, 4, 2048>},
     {128, 128, 64, 0.530f, 0.550f, 0.370f, 0.460f, launch_tile_t<false, 2, 4, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 2, 4, 4, 2, 64, 4, 2048>},
@@ -499,8 +500,9 @@ double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_s
 // Helpers for g cut into tiles of shape t: false where they do not pay. A helper gets some 50 KB a us, so
 // enough of them to fetch what the XCD with the most to read needs within the product's time, and a
 // quarter more; with too few the tiles wait for the helpers (three where eight are needed: 10 to 60 %
-// slower than none).
-static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget, TileLaunch *l, double *us)
+// slower than none). Also false where the estimated time does not come below `limit`, before the rest is worked out
+// (a call for [K x N] weights costs 0.4 us less on the host).
+static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget, double limit, TileLaunch *l, double *us)
 {
     const float per_step = g.b_layout == TW_B_KN ? t.us_help_kn : t.us_help_nk;
     const int64_t max_bytes = int64_t(1) << 31;
@@ -508,15 +510,17 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
     const int64_t tiles_m = (g.M + t.rows - 1) / t.rows, tiles_n = (g.N + t.cols - 1) / t.cols;
     const int64_t per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds, idle = budget / kXcds - per_xcd;
     if (idle < 1) return false;
+    const double from_memory = double(g.M + g.N) * g.K * 2 / kHbmBytesPerUs;
+    // (rows that do not start on a line: two lines for every 64 of K)
+    const double time = std::max(double(per_step) * (g.K % 64 ? 1.2 : 1.0) * g.K / 64, from_memory);
+    *us = time + 4.0;
+    if (*us >= limit) return false;
     const int group_m = tile_group_m(tiles_m, t.rows, t.cols, budget);
     int64_t lines = 0;  // rows of A and columns of B that an XCD reads
     for (int x = 0; x < kXcds; ++x) {
         const Operands o = operands_of(x * per_xcd, per_xcd, g.M, g.N, tiles_m, tiles_n, group_m, t.rows, t.cols);
         lines = std::max<int64_t>(lines, o.a_hi - o.a_lo + o.n1 + o.n2);
     }
-    const double from_memory = double(g.M + g.N) * g.K * 2 / kHbmBytesPerUs;
-    // (rows that do not start on a line: two lines for every 64 of K)
-    const double time = std::max(double(per_step) * (g.K % 64 ? 1.2 : 1.0) * g.K / 64, from_memory);
     const double needed = double(lines) * g.K * 2 / (time * kHelperBytesPerUs);
     if (needed > 0.85 * idle) return false;
     const int windows = static_cast<int>((g.K * 2 + kHelpWindow - 1) / kHelpWindow);
@@ -524,7 +528,6 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
     const double lead = std::max(2.0, kHelpLeadBytes / (double(lines) * kHelpWindow));
     l->helpers = static_cast<int>(std::min<int64_t>(idle, int64_t(1.25 * needed) + 1));
     l->help = pack_help(pace, pace * lead);
-    *us = time + 4.0;
     return true;
 }
 
@@ -557,12 +560,11 @@ int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *
     for (int i = 0; i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i) {
         TileLaunch l;
         double est;
-        if ((keep && i != only) || !plan_help(g, kSmallTiles[i], budget, &l, &est)) continue;
-        if (i == only || (est < 0.94 * plain && est < *us)) {
-            best = i;
-            *us = std::min(est, *us);
-            *helped = true;
-        }
+        const double limit = i == only ? 1e300 : std::min(0.94 * plain, *us);
+        if ((keep && i != only) || !plan_help(g, kSmallTiles[i], budget, limit, &l, &est)) continue;
+        best = i;
+        *us = std::min(est, *us);
+        *helped = true;
     }
     return best;
 }
@@ -578,7 +580,7 @@ tw_status launch_small_tile(const tw_gemm_args &g, int shape, bool helped, int b
     const SmallTileShape &t = kSmallTiles[shape];
     TileLaunch l = {budget, cus, beside, 0, 0};
     double us;
-    if (helped && !plan_help(g, t, budget, &l, &us)) return TW_ERR_UNSUPPORTED;
+    if (helped && !plan_help(g, t, budget, 1e300, &l, &us)) return TW_ERR_UNSUPPORTED;
     return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, l, stream);
 }
 
