@@ -423,9 +423,13 @@ static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
 template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, bool STREAM_B = false, bool LOADERS = LONG_K == 0>
 static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipStream_t stream)
 {
-    // (eight waves that multiply and four that load leave no registers for a workgroup beside them)
+    // (eight waves that multiply and four that load leave no registers for a workgroup beside them; weights that
+    // one row of tiles reads once each come as fast to the waves that multiply: 32 x 8192, K = 4096 13.8 us, with
+    // loading waves 14.2, 32 x 3584, K = 8192 15.6 and 16.2; with helpers they are ahead again)
+    const bool one_row = STREAM_B && g.M <= kBlk * WM * WVM;
     if constexpr (LONG_K > 0 && LONG_K < kNeverLoaders && !LOADERS)
-        if ((LONG_K == kLoadersIfHelped ? l.helpers > 0 : g.K >= LONG_K) && !(l.beside && WVM * WVN == 8))
+        if ((LONG_K == kLoadersIfHelped ? l.helpers > 0 : g.K >= LONG_K) && !(l.beside && WVM * WVN == 8) &&
+            !(one_row && l.helpers == 0))
             return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM_B, true>(g, l, stream);
     using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
     const int64_t tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
@@ -453,7 +457,7 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
 
 // The loading waves' K: measured, loading waves against none, for 96 and 256 tiles, K = 512, 1024, 4096 and 8192 and some
 // shorter ones, from the cache and from HBM: tiles of 16 x 16 -7 to -14 % from K = 4096 on and up to +7 % at 512; 32 x 32 -19 to
-// 0 %, but +2 to +5 % up to 1984 with one row of tiles, [K x N] -12 to +1 % and up to +6 % at 1024; 64 x 32 and 64 x 64 -10 to +2 %
+// 0 %, but up to +3 % at 1024, [K x N] -12 to +1 % and up to +6 % at 1024; 64 x 32 and 64 x 64 -10 to +2 %
 // and +1 to +5 % up to 1024; 96 x 64 -6 to 0 % and up to +2 %, [K x N] -13 to +1 %, +2 to +4 % at 176 and 256; 96 x 96 -11 to 0 %, up to
 // +2 % at 136; 96 x 128 -11 to +1 % at any K; 192 x 64 [K x N] -10 to 0 %, +2 to +6 % at 512; 128 x 128 [K x N] -18 to -4 %, up to +5 % at 512;
 // 64 x 64 [K x N] 0 to +7 % but -4 % with helpers; 192 x 64 and 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: with
