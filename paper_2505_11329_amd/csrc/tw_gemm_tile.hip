@@ -451,7 +451,7 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
                          static_cast<const char *>(g.A), static_cast<const char *>(g.B), static_cast<char *>(g.C),
                          static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
                          static_cast<int>(tiles_n), static_cast<int>(g.M - (tiles_m - 1) * T::BM),
-                         tile_group_m(tiles_m, T::BM, T::BN, l.budget), tiles_per_xcd, l.help));
+                         tile_group_m(tiles_m, tiles_per_xcd, T::BM, T::BN, l.budget), tiles_per_xcd, l.help));
     return TW_OK;
 }
 
@@ -519,7 +519,7 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
     const double time = std::max(double(per_step) * (g.K % 64 ? 1.2 : 1.0) * g.K / 64, from_memory);
     *us = time + 4.0;
     if (*us >= limit) return false;
-    const int group_m = tile_group_m(tiles_m, t.rows, t.cols, budget);
+    const int group_m = tile_group_m(tiles_m, per_xcd, t.rows, t.cols, budget);
     int64_t lines = 0;  // rows of A and columns of B that an XCD reads
     for (int x = 0; x < kXcds; ++x) {
         const Operands o = operands_of(x * per_xcd, per_xcd, g.M, g.N, tiles_m, tiles_n, group_m, t.rows, t.cols);

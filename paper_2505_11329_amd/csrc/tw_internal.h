@@ -99,7 +99,7 @@ enum class GemmPlace { kAlone, kBeside, kWoven, kChain };
 tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, GemmPlace place = GemmPlace::kAlone);
 static constexpr int kGemmTileM = 256, kGemmTileN = 128;
 // Tile rows per block of the tile ordering.
-int tile_group_m(int64_t tiles_m, int tile_rows, int tile_cols, int budget);
+int tile_group_m(int64_t tiles_m, int64_t tiles_per_xcd, int tile_rows, int tile_cols, int budget);
 // The tile shapes for products of few tiles (tw_gemm_tile.hip): the estimated time of a
 // grid of tiles, the shape of the least (-1: none for the layout), its size and its launch.
 double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_step, double us_per_step,
