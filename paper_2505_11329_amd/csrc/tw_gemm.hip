@@ -234,8 +234,10 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
     extern __shared__ __attribute__((aligned(16))) char lds[];
     if constexpr (HELPED)
         if (static_cast<int>(blockIdx.x) >= tiles_per_xcd * kXcds)
-            return help_tiles<B_KN>(A, B, (tiles_m - 1) * BM + last_rows, N, K, tiles_m, tiles_n, group_m, tiles_per_xcd, BM,
-                                    TileCfg<WM, WN, STAGES, BK>::kBN, help);
+            return help_tiles<B_KN, true, TileCfg<WM, WN, STAGES, BK>::kWaves>(
+                A, B, (tiles_m - 1) * BM + last_rows, N, K, tiles_m, tiles_n, group_m, tiles_per_xcd, BM,
+                TileCfg<WM, WN, STAGES, BK>::kBN, help);
+    if constexpr (HELPED) say_begun(help);
     using Cfg = TileCfg<WM, WN, STAGES, BK>;
     constexpr int NW = Cfg::kWaves;
     constexpr int BN = Cfg::kBN;
@@ -894,7 +896,8 @@ static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t strea
                          static_cast<const char *>(g.A), static_cast<const char *>(g.B), static_cast<char *>(g.C),
                          static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
                          static_cast<int>(tiles_n), static_cast<int>(g.M - (tiles_m - 1) * BM),
-                         tile_group_m(tiles_m, tiles_per_xcd, BM, BN, budget), tiles_per_xcd, kHelpAll, phase_cycles));
+                         tile_group_m(tiles_m, tiles_per_xcd, BM, BN, budget), tiles_per_xcd, HELPED ? pack_help_all(helped_us) | next_help_word() : 0u,
+                         phase_cycles));
     return TW_OK;
 }
 

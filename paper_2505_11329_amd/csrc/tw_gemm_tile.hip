@@ -124,7 +124,8 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
     extern __shared__ __attribute__((aligned(16))) char lds[];
     // (with loading waves only: shapes without helpers came out up to 2 % slower with the branch)
     if (LOADERS && static_cast<int>(blockIdx.x) >= tiles_per_xcd * kXcds)
-        return help_tiles<B_KN>(A, B, (tiles_m - 1) * BM + last_rows, N, K, tiles_m, tiles_n, group_m, tiles_per_xcd, BM, BN, help);
+        return help_tiles<B_KN, false, T::kThreads / 64>(A, B, (tiles_m - 1) * BM + last_rows, N, K, tiles_m, tiles_n, group_m,
+                                                         tiles_per_xcd, BM, BN, help);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool computes = wave < T::kCompute;
@@ -289,6 +290,7 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
         static_for<S>([&](auto s) {
             if (loads && (!T::kTail || decltype(s)::value < k_tiles)) fetch(fetch_ctx(decltype(s)::value, decltype(s)::value));
         });
+        if (LOADERS && help) say_begun(help);
         // Fragment addresses inside a stage; block i lies 16 rows further on. (The lane passes
         // through an asm statement so that all this is computed here, the first loads on their
         // way; with [K x N] weights that made the K loop of 192 x 128 tiles 1 % slower.)
@@ -416,7 +418,7 @@ struct TileLaunch {
     int budget, cus;
     bool beside;
     int helpers;    // for each XCD (kXcds * helpers more workgroups than tiles)
-    uint32_t help;  // pack_help()
+    uint32_t help;  // pack_help(), without the launch's word
 };
 // LONG_K: from which K on there are loading waves (0: always, kNeverLoaders: not for this shape).
 static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
@@ -451,7 +453,8 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
                          static_cast<const char *>(g.A), static_cast<const char *>(g.B), static_cast<char *>(g.C),
                          static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
                          static_cast<int>(tiles_n), static_cast<int>(g.M - (tiles_m - 1) * T::BM),
-                         tile_group_m(tiles_m, tiles_per_xcd, T::BM, T::BN, l.budget), tiles_per_xcd, l.help));
+                         tile_group_m(tiles_m, tiles_per_xcd, T::BM, T::BN, l.budget), tiles_per_xcd,
+                         l.helpers > 0 ? l.help | next_help_word() : 0u));
     return TW_OK;
 }
 

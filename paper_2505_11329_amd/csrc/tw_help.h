@@ -2,6 +2,8 @@
 // that work on tiles.
 #pragma once
 
+#include <atomic>
+
 #include "tw_mfma.h"
 
 namespace tw {
@@ -21,14 +23,36 @@ namespace tw {
 // rows as above: 27 us).
 //
 // Where the XCD's share is more than its idle units can fetch, the helpers of all XCDs fetch every
-// operand once, for the last-level cache, and keep no pace (kHelpAll).
+// operand once, for the last-level cache, and keep no pace (ALL).
+//
+// With kernels of other streams on the device helpers may start when the tiles are done: they must not
+// keep the launch from ending (three streams of [2048 x 8192] x [8192 x 3584] took 367 us a round, 322 without
+// helpers). Workgroup 0, which is dispatched before them, leaves the time it began in a word of the
+// launch's own; helpers look there every kHelpLookTicks (not at once: the time may still be that of an earlier
+// launch with the word) and leave when the launch's expected time is over. Should two launches with
+// the same word ever overlap, some helpers leave early or late; nothing else depends on it.
 static constexpr uint32_t kHelpWindow = 1024;
-static constexpr uint32_t kHelpAll = 0x80000000u;
-// The argument of a launch with helpers: ticks of a window and of the lead, or kHelpAll.
+static constexpr uint32_t kHelpWords = 128, kHelpLookTicks = 300;
+static __device__ uint32_t tiles_begun[kHelpWords];
+// The argument of a launch with helpers: the launch's word (bits 0 to 6), ticks of a window (11 bits) and of
+// the lead (13 bits); where the helpers fetch everything, word and expected ticks.
+inline uint32_t next_help_word()
+{
+    static std::atomic<uint32_t> launches{0};
+    return launches.fetch_add(1, std::memory_order_relaxed) % kHelpWords;
+}
 inline uint32_t pack_help(double pace, double lead_ticks)
 {
-    return static_cast<uint32_t>(pace < 65535.0 ? pace : 65535.0) |
-           static_cast<uint32_t>(lead_ticks < 32767.0 ? lead_ticks : 32767.0) << 16;
+    return static_cast<uint32_t>(pace < 2047.0 ? pace : 2047.0) << 7 |
+           static_cast<uint32_t>(lead_ticks < 8191.0 ? lead_ticks : 8191.0) << 18;
+}
+inline uint32_t pack_help_all(double us) { return static_cast<uint32_t>(us < 160e3 ? us * 100 : 16e6) << 7; }
+// By the workgroups with a tile, once
+__device__ __forceinline__ void say_begun(uint32_t help)
+{
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(&tiles_begun[help % kHelpWords], static_cast<uint32_t>(__builtin_amdgcn_s_memrealtime()),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 static constexpr double kHelpLeadBytes = 1.5e6, kHelperBytesPerUs = 50e3, kHbmBytesPerUs = 5.3e6;
 static constexpr int64_t kHelpFromK = 2048;
@@ -51,25 +75,36 @@ __host__ __device__ inline Operands operands_of(uint32_t first, uint32_t count, 
     return {b0 * group_m * BM, least((b1 + 1) * group_m * BM, M), c0 * BN, end1 - c0 * BN,
             b0 == b1 ? 0 : b1 == b0 + 1 ? least((c1 + 1) * BN, N) : N};
 }
-// One of n_helpers workgroups of an XCD. A wave's load asks for 64 lines, a dword of each.
-template <bool B_KN>
+// One of n_helpers workgroups (of an XCD; ALL: of the launch) of WAVES waves. A wave's load asks for 64 lines, a dword of each.
+template <bool B_KN, bool ALL, uint32_t WAVES>
 __device__ __forceinline__ void fetch_ahead(const char *A, const char *B, uint32_t N, uint32_t K, const Operands o,
                                             uint32_t helper, uint32_t n_helpers, uint32_t help)
 {
-    const uint32_t pace = help & 0xffff, lead_ticks = help >> 16 & 0x7fff;
+    const uint32_t pace = ALL ? 0 : help >> 7 & 0x7ff, lead_ticks = ALL ? 0 : help >> 18 & 0x1fff;
     const int64_t begun = __builtin_amdgcn_s_memrealtime();
-    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    int64_t look = begun + kHelpLookTicks;
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t row_bytes = K * 2, windows = (row_bytes + kHelpWindow - 1) / kHelpWindow;
+    const uint32_t expected = ALL ? help >> 7 : pace * windows;
     constexpr uint32_t kRunLines = kHelpWindow / 128, kRows = 64 / kRunLines;  // a load: eight rows of a window
     // B stored [K x N]: a window is kHelpWindow / 2 rows of B, of which a run of columns takes some lines each
     const uint32_t kn_lines1 = (o.n1 * 2 + 127) / 128, kn_lines = kn_lines1 + (o.n2 * 2 + 127) / 128;
     const uint32_t a_loads = (o.a_hi - o.a_lo + kRows - 1) / kRows;
     const uint32_t b_loads = B_KN ? kHelpWindow / 2 * kn_lines / 64 : (o.n1 + o.n2 + kRows - 1) / kRows;
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, o.a_hi * row_bytes), rb = make_rsrc(B, K * N * 2);
-    for (uint32_t i = wave * n_helpers + helper; i < windows * (a_loads + b_loads); i += waves * n_helpers) {
+    for (uint32_t i = wave * n_helpers + helper; i < windows * (a_loads + b_loads); i += WAVES * n_helpers) {
         const uint32_t window = i / (a_loads + b_loads), l = i - window * (a_loads + b_loads);
-        const int64_t not_before = begun + static_cast<int64_t>(window) * pace - lead_ticks;
-        while (static_cast<int64_t>(__builtin_amdgcn_s_memrealtime()) < not_before) __builtin_amdgcn_s_sleep(2);
+        int64_t now = __builtin_amdgcn_s_memrealtime();
+        if constexpr (!ALL) {
+            const int64_t not_before = begun + static_cast<int64_t>(window) * pace - lead_ticks;
+            for (; now < not_before; now = __builtin_amdgcn_s_memrealtime()) __builtin_amdgcn_s_sleep(2);
+        }
+        if (now >= look) {
+            if (static_cast<uint32_t>(now) - __hip_atomic_load(&tiles_begun[help % kHelpWords], __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT) > expected)
+                return;
+            look = now + kHelpLookTicks;
+        }
         const uint32_t in_row = window * kHelpWindow + lane % kRunLines * 128;
         uint32_t v;
         if (l < a_loads) {
@@ -88,17 +123,17 @@ __device__ __forceinline__ void fetch_ahead(const char *A, const char *B, uint32
 }
 
 // What workgroup `slots` + i of a launch of `slots` workgroups for tiles and some helpers does.
-template <bool B_KN>
+template <bool B_KN, bool ALL, uint32_t WAVES>
 __device__ __forceinline__ void help_tiles(const char *A, const char *B, uint32_t M, uint32_t N, uint32_t K, uint32_t tiles_m,
                                            uint32_t tiles_n, uint32_t group_m, uint32_t tiles_per_xcd, uint32_t BM, uint32_t BN,
                                            uint32_t help)
 {
     const uint32_t slots = tiles_per_xcd * kXcds;
-    if (help & kHelpAll) {
-        fetch_ahead<B_KN>(A, B, N, K, {0, M, 0, N, 0}, blockIdx.x - slots, gridDim.x - slots, help);
+    if constexpr (ALL) {
+        fetch_ahead<B_KN, ALL, WAVES>(A, B, N, K, {0, M, 0, N, 0}, blockIdx.x - slots, gridDim.x - slots, help);
     } else {
         const Operands o = operands_of(blockIdx.x % kXcds * tiles_per_xcd, tiles_per_xcd, M, N, tiles_m, tiles_n, group_m, BM, BN);
-        fetch_ahead<B_KN>(A, B, N, K, o, blockIdx.x / kXcds - tiles_per_xcd, gridDim.x / kXcds - tiles_per_xcd, help);
+        fetch_ahead<B_KN, ALL, WAVES>(A, B, N, K, o, blockIdx.x / kXcds - tiles_per_xcd, gridDim.x / kXcds - tiles_per_xcd, help);
     }
 }
 

@@ -505,3 +505,24 @@ def test_traced_gemm_counts_phases_and_gives_the_same_product(tw, torch_cuda):
     assert (c[ran, names.index("sub_step_1")] >= 1024 * steps).all()
     with pytest.raises(tw.TwError):
         tw.gemm_bf16_traced(A[:256], B[:128])
+
+
+def test_gemms_with_helper_workgroups_on_several_streams(tw, torch_cuda):
+    """Three streams, each with more launches than there are words to tell helpers by: launches whose helpers find no compute
+    unit until the tiles are done end as well, and every product has the bits it has alone."""
+    torch = torch_cuda
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+    rand = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.5, generator=gen)
+    for M, N, K in ((64, 1280, 4096), (2048, 3584, 2056)):
+        A, B = [rand(M, K) for _ in range(3)], [rand(N, K) for _ in range(3)]
+        want = [to_bits(tw.gemm_bf16(a, b, cu_budget=8)) for a, b in zip(A, B)]
+        C = [torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(3)]
+        streams = [torch.cuda.Stream() for _ in range(3)]
+        torch.cuda.synchronize()
+        for _ in range(50):
+            for a, b, c, s in zip(A, B, C, streams):
+                tw.gemm_bf16(a, b, C=c, stream=s)
+        torch.cuda.synchronize()
+        for c, w in zip(C, want):
+            assert np.array_equal(to_bits(c), w)
