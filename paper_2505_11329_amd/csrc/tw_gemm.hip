@@ -860,13 +860,15 @@ int tile_group_m(int64_t tiles_m, int64_t tiles_per_xcd, int tile_rows, int tile
 // some `us`: enough to fetch A and B once in that time, and a quarter more; none if there are fewer. They
 // fetch for the last-level cache (what an XCD's tiles of this size read is more than its idle units
 // can fetch), as fast as they can. us without / with, operands from HBM and from the cache: 256 x 128
-// tiles, 2048 x 8192 x 3584 108 / 100 and 94.5 / 96, K = 4096 56.7 / 52.1 and 49.0 / 49.5. On the larger tiles, which
+// tiles, 2048 x 8192 x 3584 108 / 100 and 94.5 / 96, K = 4096 56.7 / 52.1 and 49.4 / 52.5. On the larger tiles, which
 // the matrix cores bound, only where rows are not whole lines: 3001 x 4104 x 4096 110 / 91 and 85.1 / 86.3, 2000 x
-// 3000 x 5000 67 / 59.4, but K = 4096 84.6 / 87.2; [K x N] weights on single 256 x 128 tiles 0 to 2 % either way, on
+// 3000 x 5000 67 / 59.4, but K = 4096 84.6 / 87.2. As operands that are in the cache lose by it, [N x K] weights
+// only if they are large enough to come from HBM; [K x N] weights on single 256 x 128 tiles 0 to 2 % either way, on
 // pairs 3001 x 4096, K = 4104 122 / 104 and 97.2 / 97.9, K = 4096 95.7 / 85.1 and 83.0 / 85.1.
 static int plan_help_all(const tw_gemm_args &g, int64_t idle, double us)
 {
     const int64_t max_bytes = int64_t(1) << 31, bytes = (g.M + g.N) * g.K * 2;
+    if (g.b_layout == TW_B_NK && g.N * g.K * 2 < kFromHbmBytes) return 0;
     if (idle < kXcds || g.K < kHelpFromK || g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return 0;
     const double needed = double(bytes) / (us * kHelperBytesPerUs);
     if (needed > 0.85 * double(idle)) return 0;

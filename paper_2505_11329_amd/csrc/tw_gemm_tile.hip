@@ -538,10 +538,6 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
     return true;
 }
 
-// A layer's weights of at least this many bytes come from HBM: the last-level cache holds 256 MiB, and
-// the model's other weights pass through it between two uses of one.
-static constexpr int64_t kFromHbmBytes = int64_t(32) << 20;
-
 // The shape of the least estimated time, -1: none for the layout.
 int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *us, bool *helped)
 {

@@ -56,6 +56,9 @@ __device__ __forceinline__ void say_begun(uint32_t help)
 }
 static constexpr double kHelpLeadBytes = 1.5e6, kHelperBytesPerUs = 50e3, kHbmBytesPerUs = 5.3e6;
 static constexpr int64_t kHelpFromK = 2048;
+// Weights of at least this many bytes are taken to come from HBM: the last-level cache holds 256 MiB, and
+// a model's other weights pass through it between two uses of one.
+static constexpr int64_t kFromHbmBytes = int64_t(32) << 20;
 // What an XCD's tiles, [first, first + count) of the list, read: rows [a_lo, a_hi) of A, and columns
 // [c_lo, c_lo + n1) and [0, n2) of B (two runs where its tiles lie in two blocks of tile rows).
 struct Operands {

@@ -262,7 +262,8 @@ HELPED = [("nk", 16, 1280, 8192), ("nk", 1, 8, 2048), ("nk", 64, 1280, 4096), ("
           ("nk", 333, 1280, 4096), ("nk", 700, 1000, 2560), ("kn", 16, 4096, 2048), ("kn", 5, 4104, 2056), ("kn", 64, 4096, 2112),
           ("kn", 130, 1280, 4096), ("kn", 146, 1288, 4104), ("kn", 300, 1000, 3000), ("kn", 433, 328, 4104), ("kn", 1000, 1000, 2504),
           ("kn", 1200, 2000, 2240), ("kn", 16, 8192, 4096),
-          ("nk", 2048, 3584, 2048), ("nk", 1990, 3528, 2056), ("nk", 3001, 4096, 2056), ("nk", 2000, 5000, 2504)]
+          ("nk", 2048, 3584, 2048), ("nk", 1990, 3528, 2056), ("nk", 3001, 4096, 2056), ("nk", 2000, 5000, 2504),
+          ("nk", 2048, 3584, 4800), ("nk", 1990, 3528, 4904), ("nk", 3001, 4096, 4104), ("nk", 2000, 5000, 3400)]
 
 
 @pytest.mark.parametrize("layout,M,N,K", HELPED)
