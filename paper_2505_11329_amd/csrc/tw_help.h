@@ -15,8 +15,9 @@ namespace tw {
 // shared by seven compute units of an XCD comes in at 60 GB/s a unit from HBM and at 105 from the
 // caches). Touching lines ahead from the compute units that work on tiles costs the requests it
 // saves; from others it is free. Measured in us, without / with helpers, operands from HBM: [128 x
-// 8192] x [8192 x 3584] 25.8 / 20.7, [64 x 8192] x [8192 x 1280] 14.2 / 10.7, [16 x 8192] x [8192 x 1280] 10.9 / 9.5; [K x N], whose rows of a narrow tile are less than a line: [16 x 4096] x [4096 x 4096] 18.7 /
-// 9.6 (from the cache 11.0 / 8.8), [128 x 8192] x [8192 x 2048] 38.8 / 18.2.
+// 8192] x [8192 x 3584] 25.8 / 20.7, [64 x 8192] x [8192 x 1280] 14.7 / 11.1, [16 x 8192] x [8192 x 1280] 11.5 / 9.9;
+// [K x N], whose rows of a narrow tile are less than a line: [16 x 4096] x [4096 x 4096] 17.4 / 10.2 (from the cache
+// 11.8 / 9.3), [128 x 8192] x [8192 x 2048] 30.7 / 19.0.
 //
 // They keep `lead` windows (kHelpWindow bytes of K) ahead of a window every `pace` ticks of the
 // 100 MHz clock: further ahead they would push out of the 4 MiB what the tiles have yet to read (128
@@ -26,8 +27,8 @@ namespace tw {
 // operand once, for the last-level cache, and keep no pace (ALL).
 //
 // With kernels of other streams on the device helpers may start when the tiles are done: they must not
-// keep the launch from ending (three streams of [2048 x 8192] x [8192 x 3584] took 367 us a round, 322 without
-// helpers). Workgroup 0, which is dispatched before them, leaves the time it began in a word of the
+// keep the launch from ending (three streams of [2048 x 8192] x [8192 x 3584] took 367 us for a product each, 322
+// without helpers and 327 as it is). Workgroup 0, which is dispatched before them, leaves the time it began in a word of the
 // launch's own; helpers look there every kHelpLookTicks (not at once: the time may still be that of an earlier
 // launch with the word) and leave when the launch's expected time is over. Should two launches with
 // the same word ever overlap, some helpers leave early or late; nothing else depends on it.
