@@ -420,16 +420,16 @@ struct TileLaunch {
     int helpers;    // for each XCD (kXcds * helpers more workgroups than tiles)
     uint32_t help;  // pack_help(), without the launch's word
 };
-// LONG_K: from which K on there are loading waves (0: always, kNeverLoaders: not for this shape).
+// LONG_K: from which K on there are loading waves (kNeverLoaders: not for this shape).
 static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
-template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, bool STREAM_B = false, bool LOADERS = LONG_K == 0>
+template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, bool STREAM_B = false, bool LOADERS = false>
 static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipStream_t stream)
 {
     // (eight waves that multiply and four that load leave no registers for a workgroup beside them; weights that
     // one row of tiles reads once each come as fast to the waves that multiply: 32 x 8192, K = 4096 13.8 us, with
     // loading waves 14.2, 32 x 3584, K = 8192 15.6 and 16.2; with helpers they are ahead again)
     const bool one_row = STREAM_B && g.M <= kBlk * WM * WVM;
-    if constexpr (LONG_K > 0 && LONG_K < kNeverLoaders && !LOADERS)
+    if constexpr (LONG_K < kNeverLoaders && !LOADERS)
         if ((LONG_K == kLoadersIfHelped ? l.helpers > 0 : g.K >= LONG_K) && !(l.beside && WVM * WVN == 8) &&
             !(one_row && l.helpers == 0))
             return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM_B, true>(g, l, stream);
@@ -462,7 +462,7 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
 // shorter ones, from the cache and from HBM: tiles of 16 x 16 -7 to -14 % from K = 4096 on and up to +7 % at 512; 32 x 32 -19 to
 // 0 %, but up to +3 % at 1024, [K x N] -12 to +1 % and up to +6 % at 1024; 64 x 32 and 64 x 64 -10 to +2 %
 // and +1 to +5 % up to 1024; 96 x 64 -6 to 0 % and up to +2 %, [K x N] -13 to +1 %, +2 to +4 % at 176 and 256; 96 x 96 -11 to 0 %, up to
-// +2 % at 136; 96 x 128 -11 to +1 % at any K; 192 x 64 [K x N] -10 to 0 %, +2 to +6 % at 512; 128 x 128 [K x N] -18 to -4 %, up to +5 % at 512;
+// +2 % at 136; 96 x 128 -11 to +1 %, +2 to +5 % below 320 (0.2 us, what starting four more waves takes); 192 x 64 [K x N] -10 to 0 %, +2 to +6 % at 512; 128 x 128 [K x N] -18 to -4 %, up to +5 % at 512;
 // 64 x 64 [K x N] 0 to +7 % but -4 % with helpers; 192 x 64 and 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: with
 // helpers only.
 // The shapes, smallest first, and what one 64-deep K step of a tile takes when about
@@ -486,7 +486,7 @@ static const SmallTileShape kSmallTiles[] = {
     {64, 64, 128, 0.200f, 0.230f, 0.139f, 0.155f, launch_tile_t<false, 2, 2, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 2, 2, 2, 128, 4, kLoadersIfHelped>},
     {96, 64, 64, 0.255f, 0.280f, 0.182f, 0.240f, launch_tile_t<false, 3, 2, 2, 2, 64, 6, 2048>, launch_tile_t<true, 3, 2, 2, 2, 64, 6, 320>},
     {96, 96, 64, 0.338f, 0.0f, 0.245f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6, 320>, nullptr},
-    {96, 128, 64, 0.405f, 0.430f, 0.260f, 0.290f, launch_tile_t<false, 3, 4, 2, 2, 64, 5, 0>, launch_tile_t<true, 3, 4, 2, 2, 64, 5, 0>},
+    {96, 128, 64, 0.405f, 0.430f, 0.260f, 0.290f, launch_tile_t<false, 3, 4, 2, 2, 64, 5, 512>, launch_tile_t<true, 3, 4, 2, 2, 64, 5, 512>},
     {192, 64, 64, 0.430f, 0.500f, 0.320f, 0.400f, launch_tile_t<false, 3, 2, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 3, 2, 4, 2, 64, 4, 2048>},
     {128, 128, 64, 0.530f, 0.550f, 0.370f, 0.460f, launch_tile_t<false, 2, 4, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 2, 4, 4, 2, 64, 4, 2048>},
     {192, 128, 64, 0.700f, 0.690f, 0.0f, 0.0f, launch_tile_t<false, 3, 4, 4, 2, 64, 3, kNeverLoaders>, launch_tile_t<true, 3, 4, 4, 2, 64, 3, kNeverLoaders>},
