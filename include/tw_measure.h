@@ -61,6 +61,18 @@ tw_status tw_gemm_bf16_traced(const void *A, const void *B, void *C, int64_t M, 
 int64_t tw_fused_grid(int64_t N, int64_t H, int P, int cu_budget);
 
 /*
+ * The workgroups of the (first) launch of a fused step of these sizes on a device of `cus` compute
+ * units: those that work on rows, and the helpers beside them, which only read a short launch's
+ * rows ahead on compute units that got no row (0 where there are none; some may have nothing to do
+ * and leave at once). beside_other_kernels != 0: as in a call that puts other kernels beside the step
+ * (both halves of tw_split_launch, tw_overlap_launch with a GEMM, split layer boundaries). Host
+ * arithmetic only; either pointer may be NULL. TW_ERR_SHAPE for N < 0, H or cus below 1 or P out of range,
+ * TW_ERR_UNSUPPORTED for an H that no kernel takes.
+ */
+tw_status tw_fused_workgroups(int64_t N, int64_t H, int P, int cu_budget, int cus, int beside_other_kernels,
+                              int64_t *workers, int64_t *helpers);
+
+/*
  * How the budgeted fused kernel lays a row of H elements over a workgroup (host
  * arithmetic only, no device needed): waves per row (0: the row is narrower
  * than a wave and takes a power-of-two group of lanes), 16-byte vectors per

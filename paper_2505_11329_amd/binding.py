@@ -89,6 +89,9 @@ def lib():
         L.tw_reduce_add_rmsnorm_traced.restype = ctypes.c_int
         L.tw_fused_grid.argtypes = [_i64, _i64, ctypes.c_int, ctypes.c_int]
         L.tw_fused_grid.restype = _i64
+        L.tw_fused_workgroups.argtypes = [_i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                                          ctypes.POINTER(_i64), ctypes.POINTER(_i64)]
+        L.tw_fused_workgroups.restype = ctypes.c_int
         L.tw_reduce_add_rmsnorm_unfused.argtypes = [ctypes.POINTER(FusedArgs), _vp, _vp]
         L.tw_reduce_add_rmsnorm_unfused.restype = ctypes.c_int
         L.tw_reduce_add_rmsnorm_unfused_static.argtypes = [ctypes.POINTER(FusedArgs), _vp]
@@ -189,6 +192,14 @@ def split_point(N, multiple):
 
 def fused_grid(N, H, P, cu_budget=0):
     return int(lib().tw_fused_grid(int(N), int(H), int(P), int(cu_budget)))
+
+
+def fused_workgroups(N, H, P, cu_budget=0, cus=256, beside_other_kernels=False):
+    """tw_fused_workgroups: (workgroups that work on rows, helpers) of a fused step's launch."""
+    w, h = _i64(0), _i64(0)
+    _check(lib().tw_fused_workgroups(int(N), int(H), int(P), int(cu_budget), int(cus), 1 if beside_other_kernels else 0,
+                                     ctypes.byref(w), ctypes.byref(h)), "tw_fused_workgroups")
+    return w.value, h.value
 
 
 # ---- marshalling helpers -------------------------------------------------

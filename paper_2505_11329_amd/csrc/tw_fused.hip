@@ -947,6 +947,11 @@ static bool takes_thin_kernel(int cu_budget, int cus, const FusedGeometry &g, in
 // form of the kernel, 42 rows 6.22 / 6.12, 64 6.0 / 6.7, 128 7.2 / 8.3. P = 16: 16 rows 7.5 / 6.0, 64 rows 8.3 /
 // 7.1 (100 rows, P = 12 7.9 / 8.4); 16384 elements, P = 8: 16 rows 8.6 / 6.9; 512 elements, P = 4, 4 rows, 20 KiB:
 // 1.80 / 1.85. (More than one load to a wave, for fewer helpers: 2 to 20 % slower.)
+// Calls that put another kernel beside the step have none (fused_grid). Beside a GEMM that a caller put on
+// another stream by hand, which no call can know, a launch has to wait until each of its helpers found room: none in
+// small workgroups (16 rows of 8192, P = 8, one step at a time beside 2048 x 8192 x 3584 products 25.0 / 23.8), but the
+// wide kernel's each take a whole compute unit (P = 16: 54 / 81; 22 before the GEMM had helpers on the units it leaves
+// idle). cu_budget, of either call, is for that.
 static int64_t grid_with_helpers(uint32_t n_groups, uint32_t group_bytes, int P, int waves, int cus)
 {
     if (group_bytes * (P + 1ll) <= 20 * 1024) return n_groups;
@@ -955,8 +960,47 @@ static int64_t grid_with_helpers(uint32_t n_groups, uint32_t group_bytes, int P,
     return grid <= cus ? grid : n_groups;
 }
 
+// What one launch for n_rows rows consists of.
+struct FusedGrid {
+    int rows_per_group;
+    uint32_t n_groups;
+    int64_t workers;  // workgroups that work on row groups
+    int64_t all;      // and helpers with them (the same where there are none)
+    bool deep;        // thin_body's DEEP form
+};
+static FusedGrid fused_grid(const tw_fused_args &a, const FusedGeometry &g, bool thin, int64_t n_rows, int cus, FusedPlace place,
+                            bool trace)
+{
+    FusedGrid f = {};
+    const ThinGeometry tg = thin_geometry(g);
+    const int budget = resolve_budget(a.cu_budget, cus);
+    f.rows_per_group = thin ? tg.rows_per_iter : g.rows_per_iter;
+    f.n_groups = static_cast<uint32_t>((n_rows + f.rows_per_group - 1) / f.rows_per_group);
+    f.workers = thin ? thin_grid(n_rows, tg, cus) : fused_grid_size(n_rows, g, budget);
+    // one row group per workgroup, at most one workgroup per compute unit, few bytes: the launch is
+    // latency-bound, everything is requested at once. Not in shared mode, whose workgroups must fit
+    // beside a GEMM's.
+    const bool one_each = f.workers == f.n_groups, shared = a.cu_budget == TW_CU_SHARED;
+    f.deep = thin && !trace && !shared && a.P <= kDeepMaxP && one_each && f.n_groups <= uint32_t(cus) &&
+             n_rows * a.H * 2 * (a.P + 1) <= kDeepInputBytes;
+    f.all = f.workers;
+    // (the helpers' compute units are idle only if nothing else is meant to run on them)
+    if (place == FusedPlace::kAlone && !shared && (f.deep || (!thin && !trace && budget == cus && one_each)))
+        f.all = grid_with_helpers(f.n_groups, static_cast<uint32_t>(f.rows_per_group * a.H * 2), a.P,
+                                  thin ? kThinThreads / 64 : g.block / 64, cus);
+    return f;
+}
+
+// Rows a launch addresses (kMaxLaunchBytes per tensor); more go out as consecutive launches on the
+// same stream.
+static int64_t rows_per_launch(int64_t H, const FusedGeometry &g)
+{
+    const int64_t rows = kMaxLaunchBytes / (H * 2);
+    return rows - rows % g.rows_per_iter;
+}
+
 tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_end, uint32_t *hw_ids,
-                       int64_t hw_ids_len, hipStream_t stream)
+                       int64_t hw_ids_len, hipStream_t stream, FusedPlace place)
 {
     if (row_end <= row_begin) return TW_OK;
     int cus = 0;
@@ -965,36 +1009,19 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
     const int budget = resolve_budget(a.cu_budget, cus);
     const bool trace = hw_ids != nullptr;
 
-    // A launch addresses at most kMaxLaunchBytes per tensor; more rows than that
-    // go out as consecutive launches on the same stream.
-    const int64_t row_bytes = a.H * 2;
-    int64_t rows_per_launch = kMaxLaunchBytes / row_bytes;
-    rows_per_launch -= rows_per_launch % g.rows_per_iter;
-    if (trace && row_end - row_begin > rows_per_launch) return TW_ERR_UNSUPPORTED;
+    const int64_t row_bytes = a.H * 2, most_rows = rows_per_launch(a.H, g);
+    if (trace && row_end - row_begin > most_rows) return TW_ERR_UNSUPPORTED;
     const bool thin = takes_thin_kernel(a.cu_budget, cus, g, row_end - row_begin, a.P);
     // outputs that do not fit the last-level cache are stored with the streaming policy (see st());
     // not under a CU budget, where that is 1 % slower
     const bool streamed = 2 * (row_end - row_begin) * row_bytes >= kLastLevelCacheBytes && (thin || budget == cus);
-    const ThinGeometry tg = thin_geometry(g);
-    const int rows_per_group = thin ? tg.rows_per_iter : g.rows_per_iter;
+    const int q = thin_geometry(g).q;
 
-    for (int64_t r0 = row_begin; r0 < row_end; r0 += rows_per_launch) {
-        const int64_t n_rows = (row_end - r0 < rows_per_launch) ? row_end - r0 : rows_per_launch;
-        int64_t grid = 0;
-        bool deep = false;
-        if (thin) {
-            grid = thin_grid(n_rows, tg, cus);
-            // one row group per workgroup, at most one workgroup per compute unit, few
-            // bytes: the launch is latency-bound, everything is requested at once. Not
-            // in shared mode, whose workgroups must fit beside a GEMM's.
-            const int64_t n_groups = (n_rows + rows_per_group - 1) / rows_per_group;
-            deep = !trace && a.cu_budget != TW_CU_SHARED && a.P <= kDeepMaxP &&
-                   grid == n_groups && n_groups <= cus && n_rows * row_bytes * (a.P + 1) <= kDeepInputBytes;
-        } else {
-            grid = fused_grid_size(n_rows, g, budget);
-            if (grid > 1024) return TW_ERR_UNSUPPORTED;  // (no device has as many compute units)
-        }
-        if (trace && hw_ids_len < grid) return TW_ERR_SHAPE;
+    for (int64_t r0 = row_begin; r0 < row_end; r0 += most_rows) {
+        const int64_t n_rows = (row_end - r0 < most_rows) ? row_end - r0 : most_rows;
+        const FusedGrid f = fused_grid(a, g, thin, n_rows, cus, place, trace);
+        if (!thin && f.workers > 1024) return TW_ERR_UNSUPPORTED;  // (no device has as many compute units)
+        if (trace && hw_ids_len < f.workers) return TW_ERR_SHAPE;
 
         FusedParams prm;
         const int64_t off = r0 * row_bytes;
@@ -1006,8 +1033,8 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
         prm.residual_out = static_cast<char *>(a.residual_out) + off;
         prm.hw_ids = hw_ids;
         prm.n_bytes = static_cast<uint32_t>(n_rows * row_bytes);
-        prm.group_bytes = static_cast<uint32_t>(rows_per_group * row_bytes);
-        prm.n_groups = static_cast<uint32_t>((n_rows + rows_per_group - 1) / rows_per_group);
+        prm.group_bytes = static_cast<uint32_t>(f.rows_per_group * row_bytes);
+        prm.n_groups = f.n_groups;
         prm.hv = g.hv;
         prm.P = a.P;
         prm.tpr_log2 = g.tpr_log2;
@@ -1019,21 +1046,19 @@ tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_en
         const bool traced_p = a.P == 1 || a.P == 2 || a.P == 4 || a.P == 8;
         const bool any_p = (trace && !traced_p) ||
                            (thin ? thin_loops(a.P, g, row_end - row_begin, cus)
-                                 : !wide_fits(a.P, g.vpt) || wide_loops(a.P, g, grid, prm.n_groups, a.N * row_bytes));
-        if (deep || (!thin && !trace && budget == cus && grid == prm.n_groups))
-            grid = grid_with_helpers(prm.n_groups, prm.group_bytes, a.P, thin ? kThinThreads / 64 : g.block / 64, cus);
+                                 : !wide_fits(a.P, g.vpt) || wide_loops(a.P, g, f.workers, f.n_groups, a.N * row_bytes));
         if (thin) {
-            if (any_p) TW_TRY((launch_thin<kAnyPadded>(prm, tg.q, trace, streamed, false, grid, stream)));
+            if (any_p) TW_TRY((launch_thin<kAnyPadded>(prm, q, trace, streamed, false, f.all, stream)));
             else
                 TW_TRY(with_partials(a.P, [&](auto pt) {
-                    return launch_thin<decltype(pt)::value>(prm, tg.q, trace, streamed, deep, grid, stream);
+                    return launch_thin<decltype(pt)::value>(prm, q, trace, streamed, f.deep, f.all, stream);
                 }));
         } else {
-            if (any_p && a.P % kWideBatch == 0) TW_TRY((launch_vpt<kAnyWhole>(prm, g, trace, streamed, grid, stream)));
-            else if (any_p) TW_TRY((launch_vpt<kAnyPadded>(prm, g, trace, streamed, grid, stream)));
+            if (any_p && a.P % kWideBatch == 0) TW_TRY((launch_vpt<kAnyWhole>(prm, g, trace, streamed, f.all, stream)));
+            else if (any_p) TW_TRY((launch_vpt<kAnyPadded>(prm, g, trace, streamed, f.all, stream)));
             else
                 TW_TRY(with_partials(a.P, [&](auto pt) {
-                    return launch_vpt<decltype(pt)::value>(prm, g, trace, streamed, grid, stream);
+                    return launch_vpt<decltype(pt)::value>(prm, g, trace, streamed, f.all, stream);
                 }));
         }
     }
@@ -1091,6 +1116,28 @@ int64_t tw_fused_grid(int64_t N, int64_t H, int P, int cu_budget)
         return thin_grid(N, thin_geometry(g), cus);
     }
     return fused_grid_size(N, g, resolve_budget(cu_budget, cus));
+}
+
+tw_status tw_fused_workgroups(int64_t N, int64_t H, int P, int cu_budget, int cus, int beside_other_kernels, int64_t *workers,
+                              int64_t *helpers)
+{
+    if (N < 0 || H <= 0 || P < 1 || P > TW_MAX_P || cus < 1) return TW_ERR_SHAPE;
+    if (H % 8 != 0 || H > TW_MAX_H) return TW_ERR_UNSUPPORTED;
+    FusedGrid f = {};
+    if (N > 0) {
+        tw_fused_args a = {};
+        a.N = N;
+        a.H = H;
+        a.P = P;
+        a.cu_budget = cu_budget;
+        const FusedGeometry g = fused_geometry(H);
+        const int64_t most_rows = rows_per_launch(H, g);
+        f = fused_grid(a, g, takes_thin_kernel(cu_budget, cus, g, N, P), N < most_rows ? N : most_rows, cus,
+                       beside_other_kernels ? FusedPlace::kBeside : FusedPlace::kAlone, false);
+    }
+    if (workers) *workers = f.workers;
+    if (helpers) *helpers = f.all - f.workers;
+    return TW_OK;
 }
 
 }  // extern "C"

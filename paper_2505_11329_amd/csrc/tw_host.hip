@@ -184,8 +184,9 @@ tw_status tw_split_launch(const tw_fused_args *args, int64_t split_row, void *st
         if (has_a && sa != sp) TW_HIP(hipStreamWaitEvent(sa, fork, 0));
         if (has_b && sb != sp) TW_HIP(hipStreamWaitEvent(sb, fork, 0));
     }
-    if (has_a) TW_TRY(launch_fused(*args, 0, split_row, nullptr, 0, sa));
-    if (has_b) TW_TRY(launch_fused(*args, split_row, args->N, nullptr, 0, sb));
+    const FusedPlace place = has_a && has_b ? FusedPlace::kBeside : FusedPlace::kAlone;
+    if (has_a) TW_TRY(launch_fused(*args, 0, split_row, nullptr, 0, sa, place));
+    if (has_b) TW_TRY(launch_fused(*args, split_row, args->N, nullptr, 0, sb, place));
     if (parent_is_set && join) {
         if (has_a && sa != sp) TW_TRY(stream_wait_stream(sp, sa));
         if (has_b && sb != sp) TW_TRY(stream_wait_stream(sp, sb));
@@ -219,7 +220,8 @@ tw_status tw_overlap_launch(const tw_fused_args *fused, const tw_gemm_args *gemm
     // would pile up five to a compute unit and keep the GEMM out until done).
     const bool gemm_first = fused && gemm && fused->cu_budget == TW_CU_SHARED;
     if (gemm && gemm_first) TW_TRY(launch_gemm(*gemm, sx, fused ? GemmPlace::kBeside : GemmPlace::kAlone));
-    if (fused && fused->N > 0) TW_TRY(launch_fused(*fused, 0, fused->N, nullptr, 0, sc));
+    if (fused && fused->N > 0)
+        TW_TRY(launch_fused(*fused, 0, fused->N, nullptr, 0, sc, gemm ? FusedPlace::kBeside : FusedPlace::kAlone));
     if (gemm && !gemm_first) TW_TRY(launch_gemm(*gemm, sx, fused ? GemmPlace::kBeside : GemmPlace::kAlone));
     if (parent_is_set && join) {
         if (fused && sc != sp) TW_TRY(stream_wait_stream(sp, sc));
@@ -322,7 +324,7 @@ static tw_status weave_pair(const tw_fused_args &f, const tw_gemm_args &g1, cons
 {
     if (mid >= hi) {
         TW_TRY(launch_gemm(rows_of(g1, lo, hi), sx, GemmPlace::kWoven));
-        TW_TRY(launch_fused(f, lo, hi, nullptr, 0, sx));
+        TW_TRY(launch_fused(f, lo, hi, nullptr, 0, sx, FusedPlace::kBeside));
         return launch_gemm(rows_of(g2, lo, hi), sx, GemmPlace::kWoven);
     }
     if (chains) {
@@ -343,10 +345,10 @@ static tw_status weave_pair(const tw_fused_args &f, const tw_gemm_args &g1, cons
             TW_HIP(hipEventRecord(g1a_done, sx));
             TW_HIP(hipStreamWaitEvent(sc, g1a_done, 0));
         }
-        TW_TRY(launch_fused(f, lo, mid, nullptr, 0, sx));
+        TW_TRY(launch_fused(f, lo, mid, nullptr, 0, sx, FusedPlace::kBeside));
         TW_TRY(launch_gemm(rows_of(g2, lo, mid), sx, GemmPlace::kBeside));
         TW_TRY(launch_gemm(rows_of(g1, mid, hi), sc, GemmPlace::kBeside));
-        TW_TRY(launch_fused(f, mid, hi, nullptr, 0, sc));
+        TW_TRY(launch_fused(f, mid, hi, nullptr, 0, sc, FusedPlace::kBeside));
         return launch_gemm(rows_of(g2, mid, hi), sc, GemmPlace::kWoven);
     }
     // compute stream: both G1 first, so the second split's projection is what
@@ -360,7 +362,7 @@ static tw_status weave_pair(const tw_fused_args &f, const tw_gemm_args &g1, cons
     }
     for (int s = 0; s < 2; ++s) {
         TW_HIP(hipStreamWaitEvent(sc, g1_done[s], 0));
-        TW_TRY(launch_fused(f, cuts[s], cuts[s + 1], nullptr, 0, sc));
+        TW_TRY(launch_fused(f, cuts[s], cuts[s + 1], nullptr, 0, sc, FusedPlace::kBeside));
         TW_TRY(borrow_event(&f_done[s]));
         TW_HIP(hipEventRecord(f_done[s], sc));
         TW_HIP(hipStreamWaitEvent(sx, f_done[s], 0));

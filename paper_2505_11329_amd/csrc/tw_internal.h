@@ -84,9 +84,12 @@ struct FusedGeometry {
 };
 FusedGeometry fused_geometry(int64_t H);
 int64_t fused_grid_size(int64_t n_rows, const FusedGeometry &g, int budget_wgs);
+// Where a launch stands. Alone: the compute units that its rows leave idle are its to use. Beside: other
+// kernels of the same call run, or wait to, on another stream (the other half of a split, a GEMM).
+enum class FusedPlace { kAlone, kBeside };
 // Enqueue rows [row_begin, row_end) of a (already validated) fused step.
-tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_end,
-                       uint32_t *hw_ids, int64_t hw_ids_len, hipStream_t stream);
+tw_status launch_fused(const tw_fused_args &a, int64_t row_begin, int64_t row_end, uint32_t *hw_ids, int64_t hw_ids_len,
+                       hipStream_t stream, FusedPlace place = FusedPlace::kAlone);
 
 // ---- GEMM stand-in (tw_gemm.hip) ----
 tw_status validate_gemm(const tw_gemm_args &g);

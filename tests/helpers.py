@@ -1,5 +1,7 @@
 """Shared test plumbing: moving bf16 bit patterns between numpy and the GPU, and
 the parity rule. No arithmetic of the method lives here."""
+import ctypes
+
 import numpy as np
 
 
@@ -37,3 +39,36 @@ def assert_parity(gpu_f64, ref_f64, what):
         i = tuple(bad[0])
         raise AssertionError("%s: %d of %d elements out of tolerance; first at %s: gpu=%r ref=%r"
                              % (what, len(bad), ok.size, i, gpu_f64[i], ref_f64[i]))
+
+
+class _KernelNode(ctypes.Structure):
+    """hipKernelNodeParams"""
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def captured_grids(stream, call):
+    """The workgroups of each kernel that call() launches, found by capturing them (nothing runs). call() works
+    on `stream` and on streams it forks from and joins into it, and allocates nothing."""
+    import paper_2505_11329_amd as tw
+    hip = tw.lib()      # a symbol of a library it was linked against is found through it
+    handle, graph = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p()
+    assert hip.hipStreamBeginCapture(handle, 1) == 0        # hipStreamCaptureModeThreadLocal
+    try:
+        call()
+    finally:
+        ended = hip.hipStreamEndCapture(handle, ctypes.byref(graph))
+    assert ended == 0
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    grids = []
+    for node in nodes:
+        kind, p = ctypes.c_int(-1), _KernelNode()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        if kind.value == 0:     # hipGraphNodeTypeKernel
+            assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+            grids.append(p.grid[0])
+    assert hip.hipGraphDestroy(graph) == 0
+    return grids

@@ -36,7 +36,7 @@ def test_header_declares_the_documented_entry_points():
     # measurement and introspection aids are declared apart from the method's interface
     aids = declared_functions(("tw_measure.h",))
     for must in ("tw_hbm_probe", "tw_hbm_probe_mixed", "tw_hbm_probe_shaped", "tw_hbm_probe_mixed_shaped",
-                 "tw_fused_grid", "tw_fused_layout", "tw_weave_schedule", "tw_gemm_tile_shape", "tw_gemm_tile_choice",
+                 "tw_fused_grid", "tw_fused_workgroups", "tw_fused_layout", "tw_weave_schedule", "tw_gemm_tile_shape", "tw_gemm_tile_choice",
                  "tw_reduce_add_rmsnorm_traced", "tw_streams_overlap", "tw_gemm_bf16_traced",
                  "tw_stream_create_cu_masked", "tw_stream_destroy"):
         assert must in aids and must not in names
@@ -670,3 +670,24 @@ def test_should_split_threshold():
     assert tw.should_split(8192) and tw.should_split(10 ** 6)
     assert tw.should_split(1024, 1024) and not tw.should_split(1023, 1024)
     assert tw.should_split(8192, -5) and not tw.should_split(100, 0)
+
+
+def test_fused_workgroups_and_which_launches_have_helpers():
+    L = tw.lib()
+    for H, P in ((8192, 8), (8192, 16), (16384, 8), (4096, 4), (512, 4)):
+        for N in (1, 16, 41, 63, 64, 300, 5000):
+            for cus in (256, 32):
+                workers, helpers = tw.fused_workgroups(N, H, P, cus=cus)
+                assert workers > 0 and helpers >= 0 and (not helpers or workers + helpers <= cus)
+                # with other kernels beside the step, in the shared mode and under a budget every workgroup has rows
+                assert tw.fused_workgroups(N, H, P, cus=cus, beside_other_kernels=True) == (workers, 0)
+                assert tw.fused_workgroups(N, H, P, cu_budget=tw.CU_SHARED, cus=cus)[1] == 0
+                assert tw.fused_workgroups(N, H, P, cu_budget=cus // 2, cus=cus)[1] == 0
+    assert tw.fused_workgroups(16, 8192, 8)[1] > 0 and tw.fused_workgroups(16, 8192, 16)[1] > 0
+    assert tw.fused_workgroups(64, 8192, 8)[1] == 0 and tw.fused_workgroups(4, 512, 4)[1] == 0
+    assert tw.fused_workgroups(0, 8192, 8) == (0, 0)
+    assert L.tw_fused_workgroups(16, 8192, 8, 0, 256, 0, None, None) == OK
+    for bad in ((-1, 64, 2, 0, 256), (4, 0, 2, 0, 256), (4, 64, 0, 0, 256), (4, 64, 17, 0, 256), (4, 64, 2, 0, 0)):
+        assert L.tw_fused_workgroups(*bad, 0, None, None) == E_SHAPE, bad
+    assert L.tw_fused_workgroups(4, 60, 2, 0, 256, 0, None, None) == E_UNSUP
+    assert L.tw_fused_workgroups(4, 65544, 2, 0, 256, 0, None, None) == E_UNSUP

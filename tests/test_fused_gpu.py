@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import tw_workloads as W
-from helpers import assert_parity, to_bits, to_gpu
+from helpers import assert_parity, captured_grids, to_bits, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -160,6 +160,41 @@ def test_short_launches_with_helper_workgroups(tw, torch_cuda, N, H, P):
     assert np.array_equal(out, out2) and np.array_equal(res, res2)
     out3, res3 = run(tw, torch_cuda, g, out=g["partials"][P - 1], residual_out=g["residual"])
     assert np.array_equal(out, out3) and np.array_equal(res, res3)
+
+
+@pytest.mark.parametrize("N,H,P", [(16, 8192, 8), (16, 8192, 16), (9, 16384, 4)])
+def test_launches_have_helper_workgroups_only_where_they_stand_alone(tw, torch_cuda, N, H, P):
+    """On its own a short launch has helpers beside its N row groups; with a kernel of the same call beside it
+    (the other half of a split, a GEMM, the other chain of a layer) or in the shared mode it has none. Counted in
+    what the calls launch."""
+    torch = torch_cuda
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(N)
+    def draw(*shape):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda:0").normal_(generator=gen)
+    def step(n, **more):
+        return dict(partials=[draw(n, H) for _ in range(P)], residual=draw(n, H), weight=draw(H), eps=1e-5,
+                    out=draw(n, H), residual_out=draw(n, H), **more)
+    parent, a, b = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream()
+    one, two = step(N), step(2 * N)
+    gemm = dict(A=draw(64, 256), B=draw(256, 256), C=draw(64, 256))
+    layer = dict(two, X1=draw(2 * N, 64), W1=draw(H, 64), W2=draw(64, H), Y=draw(2 * N, 64))
+    torch.cuda.synchronize()
+    alone = sum(tw.fused_workgroups(N, H, P, cus=tw.device_cu_count()))
+    assert alone > N
+    assert captured_grids(parent, lambda: tw.reduce_add_rmsnorm(stream=parent, **one)) == [alone]
+    assert captured_grids(parent, lambda: tw.reduce_add_rmsnorm(stream=parent, cu_budget=tw.CU_SHARED, **one)) == [N]
+    assert captured_grids(parent, lambda: tw.split_launch(split_row=N, stream_a=a, stream_b=b, parent=parent, **two)) == [N, N]
+    for rows, want in ((0, [alone]), (N, [alone])):     # one half is empty: nothing beside the other
+        assert captured_grids(parent, lambda: tw.split_launch(split_row=rows, stream_a=a, stream_b=b, parent=parent,
+                                                              **one)) == want
+    grids = captured_grids(parent, lambda: tw.overlap_launch(one, gemm, a, b, parent=parent))
+    assert len(grids) == 2 and N in grids
+    grids = captured_grids(parent, lambda: tw.weave_layer_cuts(cuts=[N], stream_compute=a, stream_comm=b, parent=parent, **layer))
+    assert len(grids) == 6 and grids.count(N) == 2
+    grids = captured_grids(parent, lambda: tw.weave_layer_cuts(cuts=[], stream_compute=a, stream_comm=b, parent=parent,
+                                                               **dict(layer, **one, X1=layer["X1"][:N], Y=layer["Y"][:N])))
+    assert len(grids) == 3 and alone in grids
 
 
 @pytest.mark.parametrize("H", [504, 2056, 4096, 6136, 8192, 8200, 16392, 40000])
