@@ -56,8 +56,9 @@ tw_status tw_reduce_add_rmsnorm_traced(const void *const *partials, const void *
 tw_status tw_gemm_bf16_traced(const void *A, const void *B, void *C, int64_t M, int64_t N, int64_t K,
                               unsigned long long *phase_cycles, int64_t phase_len, void *stream);
 
-/* Number of workgroups the fused kernel is launched with for these sizes on the
- * current device (0 if N == 0; -1 if the arguments are invalid or no device). */
+/* Number of workgroups of the fused kernel that work on rows for these sizes on the
+ * current device (0 if N == 0; -1 if the arguments are invalid or no device): all of
+ * them in a traced launch; tw_fused_workgroups also says how many helpers others have. */
 int64_t tw_fused_grid(int64_t N, int64_t H, int P, int cu_budget);
 
 /*
