@@ -395,7 +395,7 @@ static constexpr int64_t kDeepInputBytes = 6 << 20;
 // (fused_deep_kernel) without the 128-register bound that lets the other one
 // sit beside a GEMM workgroup. Same arithmetic in the same order: same bits.
 static constexpr int kDeepMaxP = 8;   // most partials it has registers for
-static constexpr int kDeepFirst = 6;  // tensors whose addresses arrive in registers (see fused_deep_kernel)
+static constexpr int kDeepFirst = 3;  // tensors whose addresses arrive in registers (see fused_deep_kernel)
 template <int PT, int Q, bool TRACE, bool STREAMED, bool DEEP>
 __device__ __forceinline__ void thin_body(const FusedParams &prm)
 {
@@ -592,22 +592,26 @@ void fused_thin_kernel(const FusedParams prm)
     thin_body<PT, Q, TRACE, STREAMED, false>(prm);
 }
 
-// The arguments of the form for small batches: the first fourteen words arrive in scalar
-// registers with the wave, the rest is a round trip to (host) memory away, over which the loads of
-// the first six tensors are on their way. Tensors in the order of help(): partials, residual, weights.
+// The arguments of the form for small batches: a first one of eight words that arrives in scalar
+// registers with the wave (an argument of more than fourteen does not), and the rest, a round trip to
+// (host) memory away, over which the loads of the first three tensors are on their way. Tensors in the
+// order of help(): partials, residual, weights. Two arguments, for the runtime handles each on its own: with
+// four, six tensors in registers, 16 rows of 8192, P = 8 took 3.81 us where they take 3.75 (from HBM
+// 4.66 / 4.57); a call on the host 2.55 to 2.75 either way, some 0.05 more than with one block that
+// the wave has to fetch (which the same launch then took 5.3 us with).
 struct DeepRest {
     const void *tensor[kDeepMaxP + 2 - kDeepFirst];
     void *out, *residual_out;
     float eps, inv_h;
 };
-typedef uint64_t Words2 __attribute__((ext_vector_type(2)));
-typedef uint64_t Words4 __attribute__((ext_vector_type(4)));  // (few arguments: the runtime handles each on its own)
+typedef uint64_t DeepFirst __attribute__((ext_vector_type(4)));  // kDeepFirst tensors and the sizes
 template <int PT, int Q>
-__global__ __launch_bounds__(kThinThreads) void fused_deep_kernel(Words4 t0123, Words2 t45, uint64_t shape, const DeepRest rest)
+__global__ __launch_bounds__(kThinThreads) void fused_deep_kernel(DeepFirst first, const DeepRest rest)
 {
     auto tensor = [&](int i) -> const void * {
-        return reinterpret_cast<const void *>(i == 0 ? t0123.x : i == 1 ? t0123.y : i == 2 ? t0123.z : i == 3 ? t0123.w : i == 4 ? t45.x : t45.y);
+        return reinterpret_cast<const void *>(i == 0 ? first.x : i == 1 ? first.y : first.z);
     };
+    const uint64_t shape = first.w;
     FusedParams prm;
     prm.n_bytes = static_cast<uint32_t>(shape);
     prm.hv = shape >> 32 & 0xfff;
@@ -752,10 +756,9 @@ static tw_status launch_deep_t(const FusedParams &prm, int64_t grid, hipStream_t
         rest.residual_out = prm.residual_out;
         rest.eps = prm.eps;
         rest.inv_h = prm.inv_h;
+        const uint64_t shape = prm.n_bytes | uint64_t(prm.hv) << 32 | uint64_t(prm.tpr_log2) << 44 | uint64_t(prm.n_groups) << 48;
         TW_HIP(launch_kernel(fused_deep_kernel<PT, Q>, dim3(static_cast<unsigned>(grid)), dim3(kThinThreads), 0u, stream,
-                             Words4{t[0], t[1], t[2], t[3]}, Words2{t[4], t[5]},
-                             prm.n_bytes | uint64_t(prm.hv) << 32 | uint64_t(prm.tpr_log2) << 44 | uint64_t(prm.n_groups) << 48,
-                             rest));
+                             DeepFirst{t[0], t[1], t[2], shape}, rest));
         return TW_OK;
     }
     return TW_ERR_UNSUPPORTED;
