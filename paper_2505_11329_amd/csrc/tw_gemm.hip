@@ -856,8 +856,7 @@ int tile_group_m(int64_t tiles_m, int64_t tiles_per_xcd, int tile_rows, int tile
     return best_gm;
 }
 
-// Helpers (a multiple of the XCDs) for a launch that leaves `idle` compute units without a tile and lasts
-// some `us`: enough to fetch A and B once in that time, and a quarter more; none if there are fewer. They
+// Helpers for a launch that leaves `idle` compute units without a tile and lasts some `us`: enough to fetch A and B once in that time, and a quarter more; none if there are fewer. They
 // fetch for the last-level cache (what an XCD's tiles of this size read is more than its idle units
 // can fetch), as fast as they can. us without / with, operands from HBM and from the cache: 256 x 128
 // tiles, 2048 x 8192 x 3584 108 / 100 and 94.5 / 96, K = 4096 56.7 / 52.1 and 49.4 / 52.5. On the larger tiles, which
@@ -865,18 +864,18 @@ int tile_group_m(int64_t tiles_m, int64_t tiles_per_xcd, int tile_rows, int tile
 // 3000 x 5000 67 / 59.4, but K = 4096 84.6 / 87.2. As operands that are in the cache lose by it, [N x K] weights
 // only if they are large enough to come from HBM; [K x N] weights on single 256 x 128 tiles 0 to 2 % either way, on
 // pairs 3001 x 4096, K = 4104 122 / 104 and 97.2 / 97.9, K = 4096 95.7 / 85.1 and 83.0 / 85.1.
-static int plan_help_all(const tw_gemm_args &g, int64_t idle, double us)
+static HelpPlan plan_help_all(const tw_gemm_args &g, int64_t idle, double us)
 {
     const int64_t max_bytes = int64_t(1) << 31, bytes = (g.M + g.N) * g.K * 2;
-    if (g.b_layout == TW_B_NK && g.N * g.K * 2 < kFromHbmBytes) return 0;
-    if (idle < kXcds || g.K < kHelpFromK || g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return 0;
+    if (g.b_layout == TW_B_NK && g.N * g.K * 2 < kFromHbmBytes) return {};
+    if (idle < kXcds || g.K < kHelpFromK || g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return {};
     const double needed = double(bytes) / (us * kHelperBytesPerUs);
-    if (needed > 0.85 * double(idle)) return 0;
-    return static_cast<int>(std::min<int64_t>(idle, int64_t(1.25 * needed) + kXcds) / kXcds * kXcds);
+    if (needed > 0.85 * double(idle)) return {};
+    return {static_cast<int>(std::min<int64_t>(idle, int64_t(1.25 * needed) + kXcds) / kXcds), pack_help_all(us)};
 }
 
 template <bool B_KN, int WM, int WN, int STAGES, int BK, bool TRACE = false, bool HELPED = false>
-static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t stream, double helped_us = 0.0,
+static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t stream, const HelpPlan &help = {},
                             unsigned long long *phase_cycles = nullptr, int64_t phase_len = 0)
 {
     using Cfg = TileCfg<WM, WN, STAGES, BK>;
@@ -885,10 +884,9 @@ static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t strea
     if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
     const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
     const int64_t slots = int64_t(tiles_per_xcd) * kXcds;
-    const int helpers = helped_us > 0.0 ? plan_help_all(g, budget - slots, helped_us) : 0;
     if constexpr (!HELPED && !TRACE && (!B_KN || WN == 8) && WN > 2)
-        if (helpers > 0) return launch_cfg<B_KN, WM, WN, STAGES, BK, false, true>(g, budget, stream, helped_us);
-    const unsigned grid = static_cast<unsigned>((slots < budget ? slots : budget) + helpers);
+        if (help.helpers > 0) return launch_cfg<B_KN, WM, WN, STAGES, BK, false, true>(g, budget, stream, help);
+    const unsigned grid = static_cast<unsigned>((slots < budget ? slots : budget) + (HELPED ? help.helpers * kXcds : 0));
 
     if (TRACE && phase_len < int64_t(grid) * Cfg::kWaves * kGemmPhases) return TW_ERR_SHAPE;
     auto kern = gemm_bf16_kernel<B_KN, WM, WN, STAGES, BK, TRACE, HELPED>;
@@ -898,8 +896,8 @@ static tw_status launch_cfg(const tw_gemm_args &g, int budget, hipStream_t strea
                          static_cast<const char *>(g.A), static_cast<const char *>(g.B), static_cast<char *>(g.C),
                          static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
                          static_cast<int>(tiles_n), static_cast<int>(g.M - (tiles_m - 1) * BM),
-                         tile_group_m(tiles_m, tiles_per_xcd, BM, BN, budget), tiles_per_xcd, HELPED ? pack_help_all(helped_us) | next_help_word() : 0u,
-                         phase_cycles));
+                         tile_group_m(tiles_m, tiles_per_xcd, BM, BN, budget), tiles_per_xcd,
+                         HELPED ? help.packed | next_help_word() : 0u, phase_cycles));
     return TW_OK;
 }
 
@@ -915,9 +913,8 @@ static double wave_fill(int64_t tiles, int budget)
 struct GemmTiles {
     int rows, cols;
     int small;    // shape of tw_gemm_tile.hip, -1: one of this file's, 256 rows high
-    bool helped;  // with helper workgroups
     bool paired;  // two neighbouring 256 x 128 tiles to a workgroup, as one of 256 x 256 (B stored [K x N])
-    double us;    // estimated time
+    HelpPlan help;
 };
 static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place)
 {
@@ -955,7 +952,7 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place
     // paired, operands from HBM and from the cache: 4096 x 4096, K = 2048 64.4 / 59.4 and 59.7 / 55.0; 4096^3 on 64
     // compute units 384 / 334 and 338 / 302). Not for shorter K, where what a pair pays for its fill and stores
     // counts: 4096 x 4096, K = 1024 38.1 / 36.3 and 33.4 / 33.3, but 2447 x 3584 27.9 / 30.3 and 27.5 / 29.1.
-    GemmTiles take = {BM, kGemmTileN, -1, false, false, 0.0};
+    GemmTiles take = {BM, kGemmTileN, -1, false, {}};
     double us = 1e300;
     const auto consider = [&](int cols, double us_per_step, double us_per_turn, bool pairs = false) {
         const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + cols - 1) / cols);
@@ -965,7 +962,6 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place
             us = t;
             take.cols = pairs ? cols / 2 : cols;
             take.paired = pairs;
-            take.us = t;
         }
     };
     consider(kGemmTileN, g.b_layout == TW_B_KN ? 0.84 : 0.745, 2.7);
@@ -976,12 +972,19 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place
     }
     if (g.b_layout == TW_B_KN && place != GemmPlace::kBeside && g.K >= 2048) consider(2 * kGemmTileN, 1.40, 9.0, true);
     double small_us = 0.0;
-    bool helped = false;
-    const int small = best_small_tile(g, budget, place, &small_us, &helped);
+    HelpPlan help;
+    const int small = best_small_tile(g, budget, place, &small_us, &help);
     if (small >= 0 && small_us < 0.98 * us) {
         take.small = small;
-        take.helped = helped;
+        take.help = help;
         small_tile_size(small, &take.rows, &take.cols);
+        return take;
+    }
+    const bool alone = place == GemmPlace::kAlone || place == GemmPlace::kChain;
+    if (alone && (g.b_layout == TW_B_KN ? take.paired : take.cols == kGemmTileN || (take.cols > 64 && g.K % 64 != 0))) {
+        const int64_t cols = take.paired ? 2 * take.cols : take.cols;
+        const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + cols - 1) / cols);
+        take.help = plan_help_all(g, budget - (tiles + kXcds - 1) / kXcds * kXcds, us);
     }
     return take;
 }
@@ -993,18 +996,15 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, GemmPlace place
     TW_TRY(current_cu_count(&cus));
     const int budget = resolve_budget(g.cu_budget, cus);
     const GemmTiles t = choose_tiles(g, budget, place);
-    if (t.small >= 0) return launch_small_tile(g, t.small, t.helped, budget, cus, place == GemmPlace::kBeside, stream);
-    const bool alone = place == GemmPlace::kAlone || place == GemmPlace::kChain;
-    const bool kn = g.b_layout == TW_B_KN;
-    const double helped_us = alone && (kn || t.cols == kGemmTileN || g.K % 64 != 0) ? t.us : 0.0;
-    if (kn)
-        return t.paired ? launch_cfg<true, 8, 8, 5, 64>(g, budget, stream, helped_us)
+    if (t.small >= 0) return launch_small_tile(g, t.small, t.help, budget, cus, place == GemmPlace::kBeside, stream);
+    if (g.b_layout == TW_B_KN)
+        return t.paired ? launch_cfg<true, 8, 8, 5, 64>(g, budget, stream, t.help)
                         : launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
     switch (t.cols) {
     case 64: return launch_cfg<false, 4, 2, 3, 64>(g, budget, stream);
-    case 256: return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream, helped_us);
-    case 192: return launch_cfg<false, 8, 6, 2, 64>(g, budget, stream, helped_us);
-    default: return launch_cfg<false, 4, 4, 3, 64>(g, budget, stream, helped_us);
+    case 256: return launch_cfg<false, 8, 8, 2, 64>(g, budget, stream, t.help);
+    case 192: return launch_cfg<false, 8, 6, 2, 64>(g, budget, stream, t.help);
+    default: return launch_cfg<false, 4, 4, 3, 64>(g, budget, stream, t.help);
     }
 }
 
@@ -1025,7 +1025,7 @@ extern "C" tw_status tw_gemm_bf16_traced(const void *A, const void *B, void *C, 
     const int64_t tiles_m = (g.M + BM - 1) / BM;
     const int64_t wide_tiles = tiles_m * ((g.N + kGemmTileN - 1) / kGemmTileN), big_tiles = tiles_m * ((g.N + 255) / 256);
     if (2 * wide_tiles <= cus || wave_fill(big_tiles, cus) < wave_fill(wide_tiles, cus) - 0.05) return TW_ERR_UNSUPPORTED;
-    return launch_cfg<false, 8, 8, 2, 64, true>(g, cus, static_cast<hipStream_t>(stream), 0.0, phase_cycles, phase_len);
+    return launch_cfg<false, 8, 8, 2, 64, true>(g, cus, static_cast<hipStream_t>(stream), {}, phase_cycles, phase_len);
 }
 
 extern "C" tw_status tw_gemm_tile_choice(int64_t M, int64_t N, int64_t K, int b_layout, int cus,

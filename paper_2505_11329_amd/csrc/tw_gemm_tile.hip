@@ -417,8 +417,7 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
 struct TileLaunch {
     int budget, cus;
     bool beside;
-    int helpers;    // for each XCD (kXcds * helpers more workgroups than tiles)
-    uint32_t help;  // pack_help(), without the launch's word
+    HelpPlan help;
 };
 // LONG_K: from which K on there are loading waves (kNeverLoaders: not for this shape).
 static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
@@ -430,8 +429,8 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
     // loading waves 14.2, 32 x 3584, K = 8192 15.6 and 16.2; with helpers they are ahead again)
     const bool one_row = STREAM_B && g.M <= kBlk * WM * WVM;
     if constexpr (LONG_K < kNeverLoaders && !LOADERS)
-        if ((LONG_K == kLoadersIfHelped ? l.helpers > 0 : g.K >= LONG_K) && !(l.beside && WVM * WVN == 8) &&
-            !(one_row && l.helpers == 0))
+        if ((LONG_K == kLoadersIfHelped ? l.help.helpers > 0 : g.K >= LONG_K) && !(l.beside && WVM * WVN == 8) &&
+            !(one_row && l.help.helpers == 0))
             return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM_B, true>(g, l, stream);
     using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
     const int64_t tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
@@ -443,8 +442,8 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
     // The whole device: a workgroup per tile, as many to a compute unit as fit. Under a
     // budget, and with helpers, one to a compute unit: more than half of its LDS is asked for.
     constexpr int kAloneBytes = T::kLdsBytes > 81 * 1024 ? T::kLdsBytes : 81 * 1024;
-    const bool whole = l.budget >= l.cus && l.helpers == 0;
-    const unsigned grid = static_cast<unsigned>((whole || slots < l.budget ? slots : l.budget) + l.helpers * kXcds);
+    const bool whole = l.budget >= l.cus && l.help.helpers == 0;
+    const unsigned grid = static_cast<unsigned>((whole || slots < l.budget ? slots : l.budget) + l.help.helpers * kXcds);
     auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, S, LOADERS, STREAM_B>;
     static std::atomic<int> allowed[kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), kAloneBytes, allowed));
@@ -454,7 +453,7 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
                          static_cast<int>(g.N), static_cast<int>(g.K), static_cast<int>(tiles_m),
                          static_cast<int>(tiles_n), static_cast<int>(g.M - (tiles_m - 1) * T::BM),
                          tile_group_m(tiles_m, tiles_per_xcd, T::BM, T::BN, l.budget), tiles_per_xcd,
-                         l.helpers > 0 ? l.help | next_help_word() : 0u));
+                         l.help.helpers > 0 ? l.help.packed | next_help_word() : 0u));
     return TW_OK;
 }
 
@@ -509,7 +508,7 @@ double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_s
 // quarter more; with too few the tiles wait for the helpers (three where eight are needed: 10 to 60 %
 // slower than none). Also false where the estimated time does not come below `limit`, before the rest is worked out
 // (a call for [K x N] weights costs 0.4 us less on the host).
-static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget, double limit, TileLaunch *l, double *us)
+static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget, double limit, HelpPlan *plan, double *us)
 {
     const float per_step = g.b_layout == TW_B_KN ? t.us_help_kn : t.us_help_nk;
     const int64_t max_bytes = int64_t(1) << 31;
@@ -533,16 +532,16 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
     const int windows = static_cast<int>((g.K * 2 + kHelpWindow - 1) / kHelpWindow);
     const double pace = 1.15 * time * 100 / windows;
     const double lead = std::max(2.0, kHelpLeadBytes / (double(lines) * kHelpWindow));
-    l->helpers = static_cast<int>(std::min<int64_t>(idle, int64_t(1.25 * needed) + 1));
-    l->help = pack_help(pace, pace * lead);
+    plan->helpers = static_cast<int>(std::min<int64_t>(idle, int64_t(1.25 * needed) + 1));
+    plan->packed = pack_help(pace, pace * lead);
     return true;
 }
 
 // The shape of the least estimated time, -1: none for the layout.
-int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *us, bool *helped)
+int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *us, HelpPlan *help)
 {
     int best = -1;
-    *helped = false;
+    *help = {};
     for (int i = 0; i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i) {
         const SmallTileShape &t = kSmallTiles[i];
         const float per_step = g.b_layout == TW_B_KN ? t.us_kn : t.us_nk;
@@ -561,13 +560,13 @@ int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *
     const int only = best;
     const double plain = *us;
     for (int i = 0; i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i) {
-        TileLaunch l;
+        HelpPlan plan;
         double est;
         const double limit = i == only ? 1e300 : std::min(0.94 * plain, *us);
-        if ((keep && i != only) || !plan_help(g, kSmallTiles[i], budget, limit, &l, &est)) continue;
+        if ((keep && i != only) || !plan_help(g, kSmallTiles[i], budget, limit, &plan, &est)) continue;
         best = i;
         *us = std::min(est, *us);
-        *helped = true;
+        *help = plan;
     }
     return best;
 }
@@ -578,13 +577,11 @@ void small_tile_size(int shape, int *rows, int *cols)
     *cols = kSmallTiles[shape].cols;
 }
 
-tw_status launch_small_tile(const tw_gemm_args &g, int shape, bool helped, int budget, int cus, bool beside, hipStream_t stream)
+tw_status launch_small_tile(const tw_gemm_args &g, int shape, const HelpPlan &help, int budget, int cus, bool beside,
+                            hipStream_t stream)
 {
     const SmallTileShape &t = kSmallTiles[shape];
-    TileLaunch l = {budget, cus, beside, 0, 0};
-    double us;
-    if (helped && !plan_help(g, t, budget, 1e300, &l, &us)) return TW_ERR_UNSUPPORTED;
-    return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, l, stream);
+    return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, {budget, cus, beside, help}, stream);
 }
 
 }  // namespace tw

@@ -107,9 +107,14 @@ int tile_group_m(int64_t tiles_m, int64_t tiles_per_xcd, int tile_rows, int tile
 // grid of tiles, the shape of the least (-1: none for the layout), its size and its launch.
 double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_step, double us_per_step,
                     double us_per_turn, int budget);
-int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *us, bool *helped);
+struct HelpPlan {
+    int helpers = 0;      // workgroups of each XCD past the tiles'
+    uint32_t packed = 0;  // their argument (tw_help.h), without the launch's word
+};
+int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *us, HelpPlan *help);
 void small_tile_size(int shape, int *rows, int *cols);
-tw_status launch_small_tile(const tw_gemm_args &g, int shape, bool helped, int budget, int cus, bool beside, hipStream_t stream);
+tw_status launch_small_tile(const tw_gemm_args &g, int shape, const HelpPlan &help, int budget, int cus, bool beside,
+                            hipStream_t stream);
 
 // ---- fork/join events (tw_host.hip) ----
 // A small per-device pool of timing-disabled events used to order streams.
