@@ -110,6 +110,27 @@ tw_status tw_gemm_tile_choice(int64_t M, int64_t N, int64_t K, int b_layout, int
                               int *tile_m, int *tile_n);
 
 /*
+ * What tw_gemm_bf16 launches for a product of these sizes on `cus` compute units, and what the calls that launch
+ * it as one of several do: where it stands is `place`. Alone: tw_gemm_bf16, tw_overlap_launch without a fused step.
+ * Beside: next to another kernel. Woven: the first and last product of a split layer boundary, with nothing
+ * beside them for most of the time. Chain: the products of an unsplit layer boundary. Host arithmetic only.
+ * TW_ERR_NULL without a plan, else errors as tw_gemm_tile_choice, and TW_ERR_SHAPE for another place.
+ */
+#define TW_GEMM_ALONE 0
+#define TW_GEMM_BESIDE 1
+#define TW_GEMM_WOVEN 2
+#define TW_GEMM_CHAIN 3
+typedef struct {
+    int tile_m, tile_n;         /* rows and columns of an output tile */
+    int tiles_per_workgroup;    /* that it works on at a time: 1, or 2 neighbouring ones in a row */
+    int64_t workers;            /* workgroups that work on tiles (of the last ones some may find none left) */
+    int64_t helpers;            /* workgroups that only fetch operands ahead of them, on units without a tile */
+    int helpers_for_all;        /* helpers: 0 each for the tiles of its XCD, into that one's L2; 1 all operands once,
+                                   into the last-level cache */
+} tw_gemm_launch;
+tw_status tw_gemm_plan(int64_t M, int64_t N, int64_t K, int b_layout, int cus, int place, tw_gemm_launch *plan);
+
+/*
  * Measurement aid (not part of the method): a streaming kernel with the same
  * persistent, CU-budgeted launch shape as the fused kernel, used to measure
  * what a given number of compute units can pull from / push to HBM, and as the

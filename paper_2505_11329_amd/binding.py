@@ -24,6 +24,7 @@ STATUS = {0: "TW_OK", 1: "TW_ERR_NULL", 2: "TW_ERR_SHAPE", 3: "TW_ERR_ALIGN", 4:
           5: "TW_ERR_UNSUPPORTED", 6: "TW_ERR_SPLIT", 7: "TW_ERR_HIP"}
 PROBE_READ, PROBE_COPY, PROBE_WRITE = 0, 1, 2
 B_NK, B_KN = 0, 1
+GEMM_ALONE, GEMM_BESIDE, GEMM_WOVEN, GEMM_CHAIN = 0, 1, 2, 3
 CU_SHARED = -1
 WEAVE_AUTO, WEAVE_ORDERED, WEAVE_CHAINS = 0, 1, 2
 MAX_P = 16
@@ -50,6 +51,12 @@ class LayerArgs(ctypes.Structure):
     """struct tw_layer_args"""
     _fields_ = [("X1", _vp), ("W1", _vp), ("K1", _i64), ("fused", FusedArgs), ("W2", _vp), ("N2", _i64),
                 ("Y", _vp), ("gemm_cu_budget", ctypes.c_int), ("schedule", ctypes.c_int)]
+
+
+class GemmLaunch(ctypes.Structure):
+    """struct tw_gemm_launch"""
+    _fields_ = [("tile_m", ctypes.c_int), ("tile_n", ctypes.c_int), ("tiles_per_workgroup", ctypes.c_int),
+                ("workers", _i64), ("helpers", _i64), ("helpers_for_all", ctypes.c_int)]
 
 
 class TwError(RuntimeError):
@@ -146,6 +153,8 @@ def lib():
         L.tw_gemm_tile_choice.argtypes = [_i64, _i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                           ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
         L.tw_gemm_tile_choice.restype = ctypes.c_int
+        L.tw_gemm_plan.argtypes = [_i64, _i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.POINTER(GemmLaunch)]
+        L.tw_gemm_plan.restype = ctypes.c_int
         L.tw_hbm_probe_mixed.argtypes = [_vp, _vp, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp]
         L.tw_hbm_probe_mixed.restype = ctypes.c_int
         L.tw_hbm_probe_shaped.argtypes = [_vp, _vp, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp]
@@ -386,6 +395,13 @@ def gemm_tile_choice(M, N, K, b_layout=B_NK, cus=256, beside_other_kernels=False
     _check(lib().tw_gemm_tile_choice(int(M), int(N), int(K), int(b_layout), int(cus), 1 if beside_other_kernels else 0,
                                      ctypes.byref(m), ctypes.byref(n)), "tw_gemm_tile_choice")
     return m.value, n.value
+
+
+def gemm_plan(M, N, K, b_layout=B_NK, cus=256, place=GEMM_ALONE):
+    """tw_gemm_plan: what is launched for a product of these sizes, a GemmLaunch."""
+    plan = GemmLaunch()
+    _check(lib().tw_gemm_plan(int(M), int(N), int(K), int(b_layout), int(cus), int(place), ctypes.byref(plan)), "tw_gemm_plan")
+    return plan
 
 
 def weave_layer(X1, W1, partials, residual, weight, eps, W2, split_row, stream_compute, stream_comm,

@@ -1039,6 +1039,23 @@ extern "C" tw_status tw_gemm_tile_choice(int64_t M, int64_t N, int64_t K, int b_
     return TW_OK;
 }
 
+extern "C" tw_status tw_gemm_plan(int64_t M, int64_t N, int64_t K, int b_layout, int cus, int place, tw_gemm_launch *plan)
+{
+    if (!plan) return TW_ERR_NULL;
+    if (M < 1 || N < 1 || K < 0 || cus < 1 || (b_layout != TW_B_NK && b_layout != TW_B_KN)) return TW_ERR_SHAPE;
+    if (place < TW_GEMM_ALONE || place > TW_GEMM_CHAIN) return TW_ERR_SHAPE;
+    constexpr GemmPlace places[] = {GemmPlace::kAlone, GemmPlace::kBeside, GemmPlace::kWoven, GemmPlace::kChain};
+    const tw_gemm_args g = {nullptr, nullptr, nullptr, M, N, K, b_layout, 0};
+    const GemmTiles t = choose_tiles(g, cus, places[place]);
+    const int64_t cols = t.paired ? 2 * t.cols : t.cols;
+    const int64_t tiles = ((M + t.rows - 1) / t.rows) * ((N + cols - 1) / cols);
+    const int64_t slots = (tiles + kXcds - 1) / kXcds * kXcds;
+    const bool several = t.small >= 0 && t.help.helpers == 0;  // of the small tiles, as many to a unit as fit
+    *plan = {t.rows, t.cols, t.paired ? 2 : 1, several || slots < cus ? slots : cus, int64_t(t.help.helpers) * kXcds,
+             t.small < 0 && t.help.helpers > 0};
+    return TW_OK;
+}
+
 extern "C" tw_status tw_gemm_bf16(const void *A, const void *B, void *C, int64_t M, int64_t N, int64_t K,
                                   int b_layout, int cu_budget, void *stream)
 {

@@ -36,7 +36,7 @@ def test_header_declares_the_documented_entry_points():
     # measurement and introspection aids are declared apart from the method's interface
     aids = declared_functions(("tw_measure.h",))
     for must in ("tw_hbm_probe", "tw_hbm_probe_mixed", "tw_hbm_probe_shaped", "tw_hbm_probe_mixed_shaped",
-                 "tw_fused_grid", "tw_fused_workgroups", "tw_fused_layout", "tw_weave_schedule", "tw_gemm_tile_shape", "tw_gemm_tile_choice",
+                 "tw_fused_grid", "tw_fused_workgroups", "tw_fused_layout", "tw_weave_schedule", "tw_gemm_tile_shape", "tw_gemm_tile_choice", "tw_gemm_plan",
                  "tw_reduce_add_rmsnorm_traced", "tw_streams_overlap", "tw_gemm_bf16_traced",
                  "tw_stream_create_cu_masked", "tw_stream_destroy"):
         assert must in aids and must not in names
@@ -275,6 +275,43 @@ def test_gemm_tile_choice_and_the_shapes_the_gpu_tests_cover():
     assert L.tw_gemm_tile_choice(16, 16, 16, tw.B_NK, 256, 0, None, None) == OK
     for bad in ((0, 16, 16, 0, 256), (16, 0, 16, 0, 256), (16, 16, -8, 0, 256), (16, 16, 16, 2, 256), (16, 16, 16, 0, 0)):
         assert L.tw_gemm_tile_choice(*bad, 0, None, None) == E_SHAPE, bad
+
+
+def test_gemm_plan_and_the_launches_the_gpu_tests_mean_to_have_helpers():
+    import random
+    import test_gemm_gpu as cases
+    layouts = {"nk": tw.B_NK, "kn": tw.B_KN}
+    assert set(cases.NOT_HELPED) < set(cases.HELPED)
+    for case in cases.HELPED:
+        layout, *size = case
+        assert (tw.gemm_plan(*size, layouts[layout]).helpers > 0) == (case not in cases.NOT_HELPED), case
+    for layout, tile, tiles, *size in cases.HELPED_TILES:
+        plan = tw.gemm_plan(*size, layouts[layout])
+        assert ((plan.tile_m, plan.tile_n), plan.tiles_per_workgroup) == (tile, tiles), (layout, size)
+        assert plan.helpers > 0 and plan.helpers_for_all == (tile[0] == 256)
+    for T in (33, 64, 100, 200):
+        assert tw.gemm_plan(T, 3584, 8192, place=tw.GEMM_CHAIN).helpers > 0
+    rng = random.Random(4)
+    for _ in range(4000):
+        M, N, K = int(2 ** rng.uniform(0, 13.5)), 8 * int(2 ** rng.uniform(0, 11)), 8 * int(2 ** rng.uniform(0, 12))
+        code, cus = rng.choice((tw.B_NK, tw.B_KN)), rng.choice((1, 3, 16, 64, 256))
+        for place in (tw.GEMM_ALONE, tw.GEMM_BESIDE, tw.GEMM_WOVEN, tw.GEMM_CHAIN):
+            plan = tw.gemm_plan(M, N, K, code, cus, place)
+            if place in (tw.GEMM_ALONE, tw.GEMM_BESIDE):
+                assert (plan.tile_m, plan.tile_n) == tw.gemm_tile_choice(M, N, K, code, cus, place == tw.GEMM_BESIDE)
+            # helpers: on compute units without a tile, an equal number in each XCD, in calls that leave them idle
+            assert plan.helpers == 0 or (place in (tw.GEMM_ALONE, tw.GEMM_CHAIN) and plan.helpers % 8 == 0
+                                         and plan.workers + plan.helpers <= cus and K >= 2048)
+            columns = plan.tile_n * plan.tiles_per_workgroup
+            tiles = -(-M // plan.tile_m) * -(-N // columns)
+            assert plan.workers <= -(-tiles // 8) * 8 and (plan.workers >= min(tiles, cus))
+            assert plan.tiles_per_workgroup in (1, 2) and (plan.tiles_per_workgroup == 1 or code == tw.B_KN)
+    L = tw.lib()
+    plan = tw.GemmLaunch()
+    assert L.tw_gemm_plan(16, 16, 16, 0, 256, 0, None) == E_NULL
+    for bad in ((0, 16, 16, 0, 256, 0), (16, 16, -8, 0, 256, 0), (16, 16, 16, 2, 256, 0), (16, 16, 16, 0, 0, 0), (16, 16, 16, 0, 256, 4),
+                (16, 16, 16, 0, 256, -1)):
+        assert L.tw_gemm_plan(*bad, ctypes.byref(plan)) == E_SHAPE, bad
 
 
 def test_overlap_launch_argument_checks():

@@ -11,7 +11,7 @@ import pytest
 
 import oracle
 import tw_workloads as W
-from helpers import to_bits, to_gpu
+from helpers import captured_grids, to_bits, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -266,6 +266,52 @@ HELPED = [("nk", 16, 1280, 8192), ("nk", 1, 8, 2048), ("nk", 64, 1280, 4096), ("
           ("nk", 2048, 3584, 4800), ("nk", 1990, 3528, 4904), ("nk", 3001, 4096, 4104), ("nk", 2000, 5000, 3400)]
 
 
+# of these the ones on the other side of the rule: without helpers
+NOT_HELPED = [("nk", 40, 1272, 2056), ("nk", 150, 600, 4104), ("nk", 333, 1280, 4096), ("nk", 700, 1000, 2560),
+              ("kn", 146, 1288, 4104), ("kn", 1000, 1000, 2504), ("kn", 1200, 2000, 2240), ("kn", 16, 8192, 4096),
+              ("nk", 2048, 3584, 2048), ("nk", 1990, 3528, 2056), ("nk", 3001, 4096, 2056), ("nk", 2000, 5000, 2504)]
+# (layout, tile, tiles to a workgroup, M, N, K): every kernel that has helpers, rows and windows of K that are not
+# whole, tiles in one and in several blocks of rows, and the depths of a model's down projections
+HELPED_TILES = [("nk", (16, 16), 1, 24, 24, 4864), ("nk", (16, 16), 1, 1207, 8, 2048), ("nk", (16, 16), 1, 16, 1024, 14336),
+                ("nk", (16, 16), 1, 16, 1024, 28672), ("nk", (32, 16), 1, 483, 144, 2080), ("nk", (32, 32), 1, 160, 984, 2064),
+                ("nk", (64, 32), 1, 250, 1224, 2224), ("nk", (64, 64), 1, 142, 3448, 2152), ("nk", (96, 64), 1, 259, 3520, 2856),
+                ("nk", (96, 96), 1, 356, 4144, 2272), ("nk", (128, 128), 1, 500, 5496, 3232),
+                ("nk", (256, 128), 1, 1046, 5392, 3432), ("nk", (256, 192), 1, 1609, 5456, 3560),
+                ("nk", (256, 256), 1, 2582, 5032, 4000), ("nk", (256, 128), 1, 1989, 3520, 14336),
+                ("kn", (32, 32), 1, 16, 4096, 14336), ("kn", (32, 32), 1, 64, 1024, 28672), ("kn", (32, 32), 1, 128, 1024, 28672),
+                ("kn", (64, 32), 1, 177, 968, 2048), ("kn", (64, 64), 1, 1665, 256, 2056), ("kn", (96, 64), 1, 131, 5472, 2136),
+                ("kn", (96, 128), 1, 810, 1936, 2056), ("kn", (128, 128), 1, 481, 5568, 2888),
+                ("kn", (192, 64), 1, 3981, 392, 3776), ("kn", (256, 128), 2, 1809, 5232, 2160)]
+
+
+@pytest.mark.parametrize("layout,tile,tiles,M,N,K", HELPED_TILES)
+def test_every_gemm_kernel_with_helper_workgroups(tw, torch_cuda, layout, tile, tiles, M, N, K):
+    """The launch has the helpers that the plan says; its bits are those of 8 compute units, which have none to spare;
+    samples against the fp64 product."""
+    torch = torch_cuda
+    code = tw.B_NK if layout == "nk" else tw.B_KN
+    plan = tw.gemm_plan(M, N, K, code, tw.device_cu_count())
+    assert ((plan.tile_m, plan.tile_n), plan.tiles_per_workgroup) == (tile, tiles) and plan.helpers > 0
+    assert plan.helpers_for_all == (tile[0] == 256) and tw.gemm_plan(M, N, K, code, 8).helpers == 0
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(M + N + K)
+    A, Bnk = (torch.empty((n, K), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.5, generator=gen) for n in (M, N))
+    B = Bnk if layout == "nk" else Bnk.t().contiguous()
+    C, D = (torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    assert captured_grids(stream, lambda: tw.gemm_bf16(A, B, C=C, b_layout=code, stream=stream)) == [plan.workers + plan.helpers]
+    tw.gemm_bf16(A, B, C=D, b_layout=code, cu_budget=8)
+    for _ in range(2):
+        C.fill_(float("nan"))
+        tw.gemm_bf16(A, B, C=C, b_layout=code)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_bits(C), to_bits(D))
+    ms, ns = [0, M // 2, M - 1], [0, N // 2 - 1, N - 1]
+    ref = oracle.gemm(to_bits(A[ms]), to_bits(Bnk[ns]), "nk")
+    gemm_check(oracle.bf16_to_f64(to_bits(C[ms][:, ns])), ref, K, 0.5, "%s %dx%dx%d" % (layout, M, N, K))
+
+
 @pytest.mark.parametrize("layout,M,N,K", HELPED)
 def test_gemm_with_helper_workgroups(tw, torch_cuda, layout, M, N, K):
     """Products of few tiles and long K, where compute units without a tile fetch operands ahead: tiles in one and in
@@ -273,6 +319,8 @@ def test_gemm_with_helper_workgroups(tw, torch_cuda, layout, M, N, K):
     compute units, which leave none to spare, and samples against the fp64 product; launch after launch on other weights."""
     torch = torch_cuda
     code = tw.B_NK if layout == "nk" else tw.B_KN
+    helpers = tw.gemm_plan(M, N, K, code, tw.device_cu_count()).helpers
+    assert (helpers > 0) == ((layout, M, N, K) not in NOT_HELPED)
     for seed in (0, 1):
         g = W.make_gemm_inputs(M, K, N, 0.5, seed=M + N + K + seed, b_layout=layout)
         A, B = to_gpu(g["A"]), to_gpu(g["B"])
@@ -298,6 +346,8 @@ def test_gemm_pairs_of_tiles_of_weights_stored_k_by_n(tw, torch_cuda, M, N, K, b
     a = W.make_gemm_inputs(M, K, N, 0.5, seed=M + K, b_layout="nk")
     b = W.make_gemm_inputs(M, K, N, 0.5, seed=M + K, b_layout="kn")
     assert tw.gemm_tile_choice(M, N, K, tw.B_KN, budget or tw.device_cu_count()) == (256, 128)
+    plan = tw.gemm_plan(M, N, K, tw.B_KN, budget or tw.device_cu_count())
+    assert plan.tiles_per_workgroup == 2 and (plan.helpers > 0) == (M == 3001)
     A, B = to_gpu(b["A"]), to_gpu(b["B"])
     want = to_bits(tw.gemm_bf16(A, to_gpu(a["B"])))
     for _ in range(2):
@@ -321,6 +371,14 @@ def test_layer_whose_gemm_has_helper_workgroups_equals_the_three_calls(tw, torch
     gen.manual_seed(T)
     rand = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.5, generator=gen)
     X1, W1, W2, parts, res, w = rand(T, K1), rand(H, K1), rand(N2, H), [rand(T, H) for _ in range(P)], rand(T, H), rand(H)
+    first, second = (tw.gemm_plan(T, n, k, tw.B_NK, tw.device_cu_count(), tw.GEMM_CHAIN) for n, k in ((H, K1), (N2, H)))
+    alone = tw.gemm_plan(T, N2, H, tw.B_NK, tw.device_cu_count())
+    assert second.helpers > 0 and alone.helpers == 0 and second.tile_m * second.tile_n > alone.tile_m * alone.tile_n
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    outputs = dict(out=rand(T, H), residual_out=rand(T, H), Y=rand(T, N2))
+    torch.cuda.synchronize()
+    assert captured_grids(a, lambda: tw.weave_layer_auto(X1, W1, parts, res, w, 1e-5, W2, a, b, parent=a, **outputs)) == [
+        first.workers, sum(tw.fused_workgroups(T, H, P, cus=tw.device_cu_count())), second.workers + second.helpers]
     out, res_out, Y, row = tw.weave_layer_auto(X1, W1, parts, res, w, 1e-5, W2, torch.cuda.current_stream(), torch.cuda.Stream())
     torch.cuda.synchronize()
     assert row == T
@@ -515,7 +573,8 @@ def test_gemms_with_helper_workgroups_on_several_streams(tw, torch_cuda):
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(3)
     rand = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.5, generator=gen)
-    for M, N, K in ((64, 1280, 4096), (2048, 3584, 2056)):
+    for M, N, K in ((64, 1280, 4096), (2048, 3584, 2056), (2048, 3584, 4800)):
+        assert (tw.gemm_plan(M, N, K, tw.B_NK, tw.device_cu_count()).helpers > 0) == (K > 2056)
         A, B = [rand(M, K) for _ in range(3)], [rand(N, K) for _ in range(3)]
         want = [to_bits(tw.gemm_bf16(a, b, cu_budget=8)) for a, b in zip(A, B)]
         C = [torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(3)]
