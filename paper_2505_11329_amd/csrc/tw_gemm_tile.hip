@@ -517,8 +517,15 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
     const int64_t per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds, idle = budget / kXcds - per_xcd;
     if (idle < 1) return false;
     const double from_memory = double(g.M + g.N) * g.K * 2 / kHbmBytesPerUs;
-    // (rows that do not start on a line: two lines for every 64 of K)
-    const double time = std::max(double(per_step) * (g.K % 64 ? 1.2 : 1.0) * g.K / 64, from_memory);
+    // Rows that do not start on a line: two lines for every 64 of K, or, in [K x N] weights, of N: there tiles of 64 rows took
+    // 1.25 to 1.35 times as long as with whole lines (32 x 32, 192 x 64 and 128 x 128 as long, 96 rows 1.1 to 1.2), and were
+    // chosen for an estimate that they did not keep. us before there were helpers / without this / with it, from the
+    // cache and from HBM: [34 x 7040] x [7040 x 6344] 23.5 / 33.0 / 22.3 and 33.1 / 32.4 / 32.9, [388 x 3328] x [3328 x 632]
+    // 11.1 / 13.4 / 11.5 and 17.3 / 14.5 / 12.6. 200 such sizes, times over those before helpers: 0.938 / 0.922 (the slowest
+    // 1.24 / 1.14) and 0.758 / 0.757.
+    const double off_line_a = g.K % 64 ? 1.2 : 1.0;
+    const double off_line_b = g.b_layout == TW_B_KN && g.N % 64 && t.rows == 64 ? 1.3 : 1.0;
+    const double time = std::max(double(per_step) * off_line_a * off_line_b * g.K / 64, from_memory);
     *us = time + 4.0;
     if (*us >= limit) return false;
     const int group_m = tile_group_m(tiles_m, per_xcd, t.rows, t.cols, budget);

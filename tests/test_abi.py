@@ -291,6 +291,10 @@ def test_gemm_plan_and_the_launches_the_gpu_tests_mean_to_have_helpers():
         assert plan.helpers > 0 and plan.helpers_for_all == (tile[0] == 256)
     for T in (33, 64, 100, 200):
         assert tw.gemm_plan(T, 3584, 8192, place=tw.GEMM_CHAIN).helpers > 0
+    # [K x N] weights whose rows are not whole lines: no larger tiles of 64 rows for the helpers' sake
+    for M, N, K in ((34, 6344, 7040), (388, 632, 3328), (111, 3304, 7360)):
+        assert tw.gemm_tile_choice(M, N, K, tw.B_KN) == tw.gemm_tile_choice(M, N, K, tw.B_KN, beside_other_kernels=True)
+    assert tw.gemm_plan(70, 3328, 8192, tw.B_KN).helpers > 0
     rng = random.Random(4)
     for _ in range(4000):
         M, N, K = int(2 ** rng.uniform(0, 13.5)), 8 * int(2 ** rng.uniform(0, 11)), 8 * int(2 ** rng.uniform(0, 12))

@@ -279,7 +279,7 @@ HELPED_TILES = [("nk", (16, 16), 1, 24, 24, 4864), ("nk", (16, 16), 1, 1207, 8, 
                 ("nk", (256, 128), 1, 1046, 5392, 3432), ("nk", (256, 192), 1, 1609, 5456, 3560),
                 ("nk", (256, 256), 1, 2582, 5032, 4000), ("nk", (256, 128), 1, 1989, 3520, 14336),
                 ("kn", (32, 32), 1, 16, 4096, 14336), ("kn", (32, 32), 1, 64, 1024, 28672), ("kn", (32, 32), 1, 128, 1024, 28672),
-                ("kn", (64, 32), 1, 177, 968, 2048), ("kn", (64, 64), 1, 1665, 256, 2056), ("kn", (96, 64), 1, 131, 5472, 2136),
+                ("kn", (64, 32), 1, 34, 4392, 2056), ("kn", (64, 64), 1, 1665, 256, 2056), ("kn", (96, 64), 1, 131, 5472, 2136),
                 ("kn", (96, 128), 1, 810, 1936, 2056), ("kn", (128, 128), 1, 481, 5568, 2888),
                 ("kn", (192, 64), 1, 3981, 392, 3776), ("kn", (256, 128), 2, 1809, 5232, 2160)]
 
