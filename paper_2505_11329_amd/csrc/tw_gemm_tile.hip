@@ -462,8 +462,8 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
 // 0 %, but up to +3 % at 1024, [K x N] -12 to +1 % and up to +6 % at 1024; 64 x 32 and 64 x 64 -10 to +2 %
 // and +1 to +5 % up to 1024; 96 x 64 -6 to 0 % and up to +2 %, [K x N] -13 to +1 %, +2 to +4 % at 176 and 256; 96 x 96 -11 to 0 %, up to
 // +2 % at 136; 96 x 128 -11 to +1 %, +2 to +5 % below 320 (0.2 us, what starting four more waves takes); 192 x 64 [K x N] -10 to 0 %, +2 to +6 % at 512; 128 x 128 [K x N] -18 to -4 %, up to +5 % at 512;
-// 64 x 64 [K x N] 0 to +7 % but -4 % with helpers; 192 x 64 and 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: with
-// helpers only.
+// 64 x 64 [K x N] 0 to +7 % but -4 % with helpers; 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: with
+// helpers only; 192 x 64 [N x K] the same, and no size takes it with helpers.
 // The shapes, smallest first, and what one 64-deep K step of a tile takes when about
 // every compute unit has one (us, measured on MI355X at K = 3584 and 8192). Several
 // tiles to a compute unit take their times in turn, also where two fit at once. [K x N]
@@ -486,7 +486,7 @@ static const SmallTileShape kSmallTiles[] = {
     {96, 64, 64, 0.255f, 0.280f, 0.182f, 0.240f, launch_tile_t<false, 3, 2, 2, 2, 64, 6, 2048>, launch_tile_t<true, 3, 2, 2, 2, 64, 6, 320>},
     {96, 96, 64, 0.338f, 0.0f, 0.245f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6, 320>, nullptr},
     {96, 128, 64, 0.405f, 0.430f, 0.260f, 0.290f, launch_tile_t<false, 3, 4, 2, 2, 64, 5, 512>, launch_tile_t<true, 3, 4, 2, 2, 64, 5, 512>},
-    {192, 64, 64, 0.430f, 0.500f, 0.320f, 0.400f, launch_tile_t<false, 3, 2, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 3, 2, 4, 2, 64, 4, 2048>},
+    {192, 64, 64, 0.430f, 0.500f, 0.0f, 0.400f, launch_tile_t<false, 3, 2, 4, 2, 64, 4, kNeverLoaders>, launch_tile_t<true, 3, 2, 4, 2, 64, 4, 2048>},
     {128, 128, 64, 0.530f, 0.550f, 0.370f, 0.460f, launch_tile_t<false, 2, 4, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 2, 4, 4, 2, 64, 4, 2048>},
     {192, 128, 64, 0.700f, 0.690f, 0.0f, 0.0f, launch_tile_t<false, 3, 4, 4, 2, 64, 3, kNeverLoaders>, launch_tile_t<true, 3, 4, 4, 2, 64, 3, kNeverLoaders>},
 };
@@ -562,19 +562,23 @@ int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *
     if (best < 0 || place == GemmPlace::kBeside || place == GemmPlace::kWoven) return best;
     // Larger tiles that leave compute units to helpers gain nothing where the operands are in the
     // cache, where [N x K] weights of 59 MB and 64 rows take 19 us with them and 15 without (from HBM
-    // 17 and 21): they are taken for [K x N] weights, which gain either way, and for a layer's weights, unless small.
+    // 17 and 21): they are taken for a layer's weights, unless small, and for [K x N] weights, which gain more from HBM
+    // than they lose from the cache: us before helpers / now, cache and HBM, [128 x 8192] x [8192 x 2048] 21.4 / 19.0 and
+    // 34.4 / 19.0, [70 x 8192] x [8192 x 3328] 21.6 / 23.2 and 31.5 / 23.6, [294 x 2560] x [2560 x 1024] 8.3 / 9.7 and 13.4 / 9.9.
     const bool keep = g.b_layout == TW_B_NK && (place != GemmPlace::kChain || g.N * g.K * 2 < kFromHbmBytes);
     const int only = best;
     const double plain = *us;
-    for (int i = 0; i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i) {
+    const auto consider = [&](int shape, double limit) {
         HelpPlan plan;
         double est;
-        const double limit = i == only ? 1e300 : std::min(0.94 * plain, *us);
-        if ((keep && i != only) || !plan_help(g, kSmallTiles[i], budget, limit, &plan, &est)) continue;
-        best = i;
+        if (!plan_help(g, kSmallTiles[shape], budget, limit, &plan, &est)) return;
+        best = shape;
         *us = std::min(est, *us);
         *help = plan;
-    }
+    };
+    consider(only, 1e300);
+    for (int i = 0; !keep && i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i)
+        if (i != only) consider(i, std::min(0.94 * plain, *us));
     return best;
 }
 
