@@ -141,9 +141,6 @@ def test_decode_sized_whole_device_launches_on_both_sides_of_the_all_at_once_lim
             assert np.array_equal(out, out2) and np.array_equal(res, res2), (N, budget)
 
 
-# Each P has kernels of its own, in small workgroups (1 to 4 vectors per thread, one chunk of loads in flight or
-# two) and in the wide geometry (1 to 8 vectors per thread): every launch mode against the confined one, which is
-# checked against the oracle, on one row and on row counts around the edges.
 @pytest.mark.parametrize("N,H,P", [(1, 8192, 8), (8, 8192, 8), (9, 8176, 8), (40, 8192, 8), (41, 8192, 8), (1, 520, 8),
                                    (33, 2056, 5), (64, 8192, 4), (65, 8192, 4), (17, 1024, 8), (18, 1024, 6), (3, 512, 7),
                                    (5, 5120, 1), (16, 8192, 16), (64, 8192, 16), (65, 8192, 9), (10, 16392, 3), (16, 16384, 8),
@@ -197,6 +194,9 @@ def test_launches_have_helper_workgroups_only_where_they_stand_alone(tw, torch_c
     assert len(grids) == 3 and alone in grids
 
 
+# Each P has kernels of its own, in small workgroups (1 to 4 vectors per thread, one chunk of loads in flight or
+# two) and in the wide geometry (1 to 8 vectors per thread): every launch mode against the confined one, which is
+# checked against the oracle, on one row and on row counts around the edges.
 @pytest.mark.parametrize("H", [504, 2056, 4096, 6136, 8192, 8200, 16392, 40000])
 @pytest.mark.parametrize("P", [3, 5, 6, 7, 9, 11, 13, 16])
 def test_kernels_of_every_partial_count(tw, torch_cuda, H, P):

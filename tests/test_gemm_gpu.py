@@ -238,13 +238,23 @@ def test_gemm_every_tile_shape(tw, torch_cuda, tile, layouts, M, N, K, budget):
         gemm_check(oracle.bf16_to_f64(to_bits(C)), ref, K, 0.5, "%s tiles, %s %dx%dx%d" % (tile, layout, M, N, K))
 
 
-@pytest.mark.parametrize("tile,layouts,M,N,budget", [(c[0], c[1], c[2], c[3], c[5]) for c in TILE_CASES if c[0][0] < 256 and c[4] == 1032])
-def test_gemm_tiles_with_loading_waves(tw, torch_cuda, tile, layouts, M, N, budget):
-    """Both sides of the K from which on some shapes have waves that only load, and every number of K steps past a whole
-    round of the LDS stages (three to six of 64 to 256); several tiles to a workgroup."""
+# (tile, layouts, M, N, budget, K): around each K from which on a shape has waves that only load, and every number of K
+# steps from there past a whole round of its LDS stages (three to six steps of 64 to 256)
+LOADING_CASES = [(c[0], c[1], c[2], c[3], c[5], (2040, 2048, 2056, 2120, 2184, 2304, 2440, 2568))
+                 for c in TILE_CASES if c[0][0] < 256 and c[4] == 1032]
+LOADING_CASES += [(tile, layouts, M, N, budget, (312, 320, 328, 384, 392, 448, 512, 576, 584, 640))
+                  for tile, layouts, M, N, budget in (((96, 96), "nk", 97, 136, 4), ((96, 96), "nk", 1, 264, 1),
+                                                      ((96, 64), "kn", 129, 72, 4))]
+LOADING_CASES += [((96, 128), "both", M, N, budget, (504, 512, 520, 576, 584, 640))
+                  for M, N, budget in ((97, 200, 4), (1, 328, 1))]
+
+
+@pytest.mark.parametrize("tile,layouts,M,N,budget,Ks", LOADING_CASES)
+def test_gemm_tiles_with_loading_waves(tw, torch_cuda, tile, layouts, M, N, budget, Ks):
+    """Both sides of the K from which on a shape has waves that only load; a tile to a workgroup and several."""
     for layout in ("nk", "kn") if layouts == "both" else (layouts,):
         code = tw.B_NK if layout == "nk" else tw.B_KN
-        for K in (2040, 2048, 2056, 2120, 2184, 2304, 2440, 2568):
+        for K in Ks:
             assert tw.gemm_tile_choice(M, N, K, code, budget) == tile
             g = W.make_gemm_inputs(M, K, N, 0.5, seed=M + N + K, b_layout=layout)
             C = torch_cuda.full((M, N), float("nan"), dtype=torch_cuda.bfloat16, device="cuda:0")
@@ -567,22 +577,33 @@ def test_traced_gemm_counts_phases_and_gives_the_same_product(tw, torch_cuda):
 
 
 def test_gemms_with_helper_workgroups_on_several_streams(tw, torch_cuda):
-    """Three streams, each with more launches than there are words to tell helpers by: launches whose helpers find no compute
-    unit until the tiles are done end as well, and every product has the bits it has alone."""
+    """Three streams that run side by side, with more launches in all than there are words to tell helpers by (128): launches
+    whose helpers find no compute unit until the tiles are done end as well, and every product has the bits it has
+    alone. Helpers of an XCD, helpers for all beside 256-row tiles, and beside pairs of tiles of [K x N] weights;
+    and none."""
     torch = torch_cuda
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(3)
     rand = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.5, generator=gen)
-    for M, N, K in ((64, 1280, 4096), (2048, 3584, 2056), (2048, 3584, 4800)):
-        assert (tw.gemm_plan(M, N, K, tw.B_NK, tw.device_cu_count()).helpers > 0) == (K > 2056)
-        A, B = [rand(M, K) for _ in range(3)], [rand(N, K) for _ in range(3)]
-        want = [to_bits(tw.gemm_bf16(a, b, cu_budget=8)) for a, b in zip(A, B)]
+    streams = [torch.cuda.Stream()]
+    for _ in range(32):
+        s = torch.cuda.Stream()
+        if len(streams) < 3 and all(tw.streams_overlap(s, t) for t in streams):
+            streams.append(s)
+    assert len(streams) == 3
+    for M, N, K, layout, tiles, for_all in ((64, 1280, 4096, "nk", 1, 0), (2048, 3584, 4800, "nk", 1, 1),
+                                            (3001, 4096, 4104, "kn", 2, 1), (2048, 3584, 2056, "nk", 1, None)):
+        code = tw.B_NK if layout == "nk" else tw.B_KN
+        plan = tw.gemm_plan(M, N, K, code, tw.device_cu_count())
+        assert plan.tiles_per_workgroup == tiles and (plan.helpers_for_all if plan.helpers else None) == for_all
+        A = [rand(M, K) for _ in range(3)]
+        B = [rand(*((N, K) if layout == "nk" else (K, N))) for _ in range(3)]
+        want = [to_bits(tw.gemm_bf16(a, b, b_layout=code, cu_budget=8)) for a, b in zip(A, B)]
         C = [torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(3)]
-        streams = [torch.cuda.Stream() for _ in range(3)]
         torch.cuda.synchronize()
         for _ in range(50):
             for a, b, c, s in zip(A, B, C, streams):
-                tw.gemm_bf16(a, b, C=c, stream=s)
+                tw.gemm_bf16(a, b, C=c, b_layout=code, stream=s)
         torch.cuda.synchronize()
         for c, w in zip(C, want):
             assert np.array_equal(to_bits(c), w)
