@@ -538,7 +538,8 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
     if (needed > 0.85 * idle) return false;
     const int windows = static_cast<int>((g.K * 2 + kHelpWindow - 1) / kHelpWindow);
     const double pace = kHelpPace * time * 100 / windows;
-    const double lead = std::max(1.0, kHelpLeadBytes / (double(lines) * kHelpWindow));
+    const double window_bytes = double(lines) * kHelpWindow;
+    const double lead = std::max(1.0, std::max(kHelpLeadLeast, kHelpLeadMost - kHelpLag * windows * window_bytes) / window_bytes);
     plan->helpers = static_cast<int>(std::min<int64_t>(idle, int64_t(1.25 * needed) + 1));
     plan->packed = pack_help(pace, pace * lead);
     return true;

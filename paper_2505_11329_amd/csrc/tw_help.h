@@ -21,13 +21,13 @@ namespace tw {
 //
 // They keep `lead` windows (kHelpWindow bytes of K) ahead of a window every `pace` ticks of the
 // 100 MHz clock: further ahead they would push out of the 4 MiB what the tiles have yet to read. What the tiles fall
-// behind the clock comes on top and grows with K, so the lead is a small part of the 4 MiB and the clock a little
-// slower than the tiles are expected to be: kHelpLeadBytes, and kHelpPace times the expected time. us with 1.5 MB and
-// 1.15 / with 0.6 MB and 1.05, operands from the cache: [64 x 28672] x [28672 x 4096], stored [K x N], 101 / 60 (78
-// without helpers), [52 x 23680] x [23680 x 3072] 77 / 49 (62), [182 x 17536] x [17536 x 3072], [N x K], 53 / 45 (49).
-// 147 sizes with K from 2048 to 10000 and 139 with up to 32768, times over those without helpers or loading waves, from
-// the cache and from HBM: 0.893 and 0.705 / 0.888 and 0.703; 0.866 and 0.630 / 0.837 and 0.618. (0.3 MB, or a clock
-// of 0.9, for which the tiles are too slow, or of 1.25: level, and 2 to 7 % slower where K is large.)
+// behind the clock comes on top and grows with K: the clock is a little slower than the tiles are expected to be
+// (kHelpPace), and the lead gets smaller by a tenth (kHelpLag) of all that the XCD reads, from kHelpLeadMost to kHelpLeadLeast.
+// us with 1.5 MB and 1.15 throughout / so, operands from the cache: [64 x 28672] x [28672 x 4096], stored [K x N], 103 / 60 (78
+// without helpers), [52 x 23680] x [23680 x 3072] 78 / 55 (62), [182 x 17536] x [17536 x 3072], [N x K], 53 / 48 (49). 131 sizes
+// with K from 2048 to 10000 against 1.5 MB and 1.15, from the cache and from HBM: 0.998 and 0.999, 47 with up to 32768 0.951 and
+// 0.981. (0.6 MB throughout: the same, but 7 % slower for [329 x 4816] x [4816 x 776]; 0.9 MB 0.998 and 0.998, 0.968 and 0.995; a
+// clock of 0.9, for which the tiles are too slow, or of 1.25: level, and 2 to 7 % slower where K is large.)
 //
 // Where the XCD's share is more than its idle units can fetch, the helpers of all XCDs fetch every
 // operand once, for the last-level cache, and keep no pace (ALL).
@@ -61,7 +61,8 @@ __device__ __forceinline__ void say_begun(uint32_t help)
         __hip_atomic_store(&tiles_begun[help % kHelpWords], static_cast<uint32_t>(__builtin_amdgcn_s_memrealtime()),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-static constexpr double kHelpLeadBytes = 0.6e6, kHelpPace = 1.05, kHelperBytesPerUs = 50e3, kHbmBytesPerUs = 5.3e6;
+static constexpr double kHelpLeadMost = 1.5e6, kHelpLeadLeast = 0.6e6, kHelpLag = 0.1, kHelpPace = 1.05;
+static constexpr double kHelperBytesPerUs = 50e3, kHbmBytesPerUs = 5.3e6;
 static constexpr int64_t kHelpFromK = 2048;
 // Weights of at least this many bytes are taken to come from HBM: the last-level cache holds 256 MiB, and
 // a model's other weights pass through it between two uses of one.
