@@ -105,10 +105,11 @@ def main():
                          "kernel is measured against")
     ap.add_argument("--gemm-phases", action="store_true",
                     help="where the clocks of the 256x256 GEMM tile's K loop go (tw_gemm_bf16_traced), as JSON")
-    ap.add_argument("--counters-run", choices=("fused", "gemm", "weave", "probe", "train"), default=None,
+    ap.add_argument("--counters-run", choices=("fused", "few-rows", "gemm", "weave", "probe", "train"), default=None,
                     help="for rocprofv3 --pmc. fused: a few fused launches plus plain copy launches of known "
                          "size (tw_hbm_probe, 192 MiB read + 192 MiB written each) to scale the byte counters "
-                         "by. gemm: a few launches of the bf16 GEMM on products of seven tile shapes. weave (for "
+                         "by. few-rows: 16 rows, with helper workgroups. gemm: a few launches of the bf16 GEMM on "
+                         "products of nine kinds, those with helper workgroups also without. weave (for "
                          "rocprofv3 --kernel-trace): the T=4096 layer boundary unsplit, then woven in the "
                          "ordered schedule, then as one chain per split, five calls each with a device "
                          "synchronisation after every call, so that the trace shows which kernels overlap")
@@ -418,14 +419,18 @@ def main():
                           "order": ["unsplit"] * 3 + ["woven"] * 3}))
         return
     if args.counters_run == "gemm":
-        # from a large square product down to a decode step's, one tile shape each, and one product whose
+        # from a large square product down to a decode step's, one tile shape each, and products whose
         # weights are stored [K x N]; weights rotate so that they come from HBM (where they exceed the cache by
-        # themselves, one set does)
+        # themselves, one set does). Products with helper workgroups a second time on the compute units that have
+        # tiles, where there are none
         gc = W.CONFIGS["c5_overlap_tp8"]["gemm"]
         shapes = [(8192, 8192, 8192, "nk"), (8192, 8192, 1280, "nk"), (gc["M"], gc["K"], gc["N"], "nk"),
-                  (gc["M"], gc["K"], 1280, "nk"), (333, 8192, 3584, "nk"), (16, 8192, 3584, "nk"),
-                  (3001, 4104, 4096, "kn")]
+                  (gc["M"], gc["K"], 1280, "nk"), (333, 8192, 3584, "nk"), (16, 8192, 3584, "nk"), (16, 8192, 1280, "nk"),
+                  (3001, 4104, 4096, "kn"), (16, 4096, 4096, "kn")]
+        runs = []
         for (M, K, N, layout) in shapes:
+            code = tw.B_NK if layout == "nk" else tw.B_KN
+            plan = tw.gemm_plan(M, N, K, code, tw.device_cu_count())
             gen = torch.Generator(device=dev)
             gen.manual_seed(M + N)
             A = torch.empty((M, K), dtype=torch.bfloat16, device=dev).normal_(0.0, gc["std"], generator=gen)
@@ -434,13 +439,15 @@ def main():
                   for _ in range(max(1, min(12, (300 << 20) // (N * K * 2))))]
             C = torch.empty((M, N), dtype=torch.bfloat16, device=dev)
             torch.cuda.synchronize()
-            for i in range(12):
-                tw.gemm_bf16(A, Bs[i % len(Bs)], C=C, b_layout=tw.B_NK if layout == "nk" else tw.B_KN, stream=stream)
-            torch.cuda.synchronize()
-        print(json.dumps({"counters_run": "gemm", "launches_per_shape": 12,
-                          "products": ["%d x %d x %d %s" % s for s in shapes],
-                          "tiles": [tw.gemm_tile_choice(M, N, K, tw.B_NK if layout == "nk" else tw.B_KN)
-                                    for (M, K, N, layout) in shapes]}))
+            for budget in (0, plan.workers) if plan.helpers else (0,):
+                for i in range(12):
+                    tw.gemm_bf16(A, Bs[i % len(Bs)], C=C, b_layout=code, cu_budget=budget, stream=stream)
+                torch.cuda.synchronize()
+                p = tw.gemm_plan(M, N, K, code, budget or tw.device_cu_count())
+                runs.append({"product": "%d x %d x %d %s" % (M, K, N, layout), "cu_budget": budget,
+                             "tile": [p.tile_m, p.tile_n], "tiles_per_workgroup": p.tiles_per_workgroup,
+                             "workgroups": p.workers, "helpers": p.helpers})
+        print(json.dumps({"counters_run": "gemm", "launches_per_product": 12, "products": runs}))
         return
     if args.counters_run == "probe":
         # plain streaming kernels with the fused kernel's budgeted launch shape, for the L1 request counters
@@ -456,6 +463,18 @@ def main():
         torch.cuda.synchronize()
         print(json.dumps({"counters_run": "probe", "read_bytes": pb, "mixed_bytes_read": 9 * sb,
                           "mixed_bytes_written": 2 * sb, "cu_budget": args.budget}))
+        return
+    if args.counters_run == "few-rows":
+        # a decode step's rows (H = 8192, P = 8) from HBM, with helper workgroups; sets that the cache does not hold
+        sets = fused_sets(WORKLOAD, 160, N=16)
+        torch.cuda.synchronize()
+        for s in sets:
+            tw.reduce_add_rmsnorm(s["partials"], s["residual"], s["weight"], s["eps"], out=s["out"],
+                                  residual_out=s["res_out"], stream=stream)
+        torch.cuda.synchronize()
+        workers, helpers = tw.fused_workgroups(16, 8192, 8, cus=tw.device_cu_count())
+        print(json.dumps({"counters_run": "few-rows", "rows": 16, "launches": len(sets), "workgroups": workers,
+                          "helpers": helpers, "fused_algorithmic_bytes": algo_bytes(sets[0])}))
         return
     if args.counters_run == "fused":
         sets = fused_sets(WORKLOAD, 4)

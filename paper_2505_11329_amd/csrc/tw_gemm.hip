@@ -542,7 +542,8 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
             // landed, A(kt) and B(kt - 1) are read by every wave (a wave waits for its last read of a
             // sub-step inside it), and the loads of K step kt + 2 into their slots follow in the second
             // sub-step. Single / paired, us, operands from HBM and from the cache: 4096^3 115 / 105 and 108 / 96,
-            // 8192^3 882 / 756 and 873 / 741, 8192 x 3584, K = 8192 418 / 376 and 394 / 330, 5000^3 307 / 252 and 288 / 232. (For B stored [N x K] the ring schedule is 1 to 20 % ahead of this one.)
+            // 8192^3 882 / 756 and 873 / 741, 8192 x 3584, K = 8192 418 / 376 and 394 / 330, 5000^3 307 / 252 and 288 / 232.
+            // (For B stored [N x K] the ring schedule is 1 to 20 % ahead of this one.)
             auto slot_a = [&](int sl) { return static_cast<uint32_t>(sl * kStageABytes); };
             auto slot_b = [&](int sl) { return static_cast<uint32_t>(Cfg::kRollBOffset + sl * Cfg::kStageBBytes); };
             static_for<2>([&](auto st) {
@@ -856,14 +857,14 @@ int tile_group_m(int64_t tiles_m, int64_t tiles_per_xcd, int tile_rows, int tile
     return best_gm;
 }
 
-// Helpers for a launch that leaves `idle` compute units without a tile and lasts some `us`: enough to fetch A and B once in that time, and a quarter more; none if there are fewer. They
-// fetch for the last-level cache (what an XCD's tiles of this size read is more than its idle units
-// can fetch), as fast as they can. us without / with, operands from HBM and from the cache: 256 x 128
-// tiles, 2048 x 8192 x 3584 108 / 100 and 94.5 / 96, K = 4096 56.7 / 52.1 and 49.4 / 52.5. On the larger tiles, which
-// the matrix cores bound, only where rows are not whole lines: 3001 x 4104 x 4096 110 / 91 and 85.1 / 86.3, 2000 x
-// 3000 x 5000 67 / 59.4, but K = 4096 84.6 / 87.2. As operands that are in the cache lose by it, [N x K] weights
-// only if they are large enough to come from HBM; [K x N] weights on single 256 x 128 tiles 0 to 2 % either way, on
-// pairs 3001 x 4096, K = 4104 122 / 104 and 97.2 / 97.9, K = 4096 95.7 / 85.1 and 83.0 / 85.1.
+// Helpers for a launch that leaves `idle` compute units without a tile and lasts some `us`: enough to fetch A and B
+// once in that time, and a quarter more; none if there are fewer. They fetch for the last-level cache (what an XCD's
+// tiles of this size read is more than its idle units can fetch), as fast as they can. us without / with, operands from
+// HBM and from the cache: 256 x 128 tiles, 2048 x 8192 x 3584 108 / 100 and 94.5 / 96, K = 4096 56.7 / 52.1 and 49.4 /
+// 52.5. On the larger tiles, which the matrix cores bound, only where rows are not whole lines: 3001 x 4104 x 4096 110 /
+// 91 and 85.1 / 86.3, 2000 x 3000 x 5000 67 / 59.4, but K = 4096 84.6 / 87.2. As operands that are in the cache lose by
+// it, [N x K] weights only if they are large enough to come from HBM; [K x N] weights on single 256 x 128 tiles 0 to 2 %
+// either way, on pairs 3001 x 4096, K = 4104 122 / 104 and 97.2 / 97.9, K = 4096 95.7 / 85.1 and 83.0 / 85.1.
 static HelpPlan plan_help_all(const tw_gemm_args &g, int64_t idle, double us)
 {
     const int64_t max_bytes = int64_t(1) << 31, bytes = (g.M + g.N) * g.K * 2;

@@ -457,13 +457,17 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
     return TW_OK;
 }
 
-// The loading waves' K: measured, loading waves against none, for 96 and 256 tiles, K = 512, 1024, 4096 and 8192 and some
-// shorter ones, from the cache and from HBM: tiles of 16 x 16 -7 to -14 % from K = 4096 on and up to +7 % at 512; 32 x 32 -19 to
-// 0 %, but up to +3 % at 1024, [K x N] -12 to +1 % and up to +6 % at 1024; 64 x 32 and 64 x 64 -10 to +2 %
-// and +1 to +5 % up to 1024; 96 x 64 -6 to 0 % and up to +2 %, [K x N] -13 to +1 %, +2 to +4 % at 176 and 256; 96 x 96 -11 to 0 %, up to
-// +2 % at 136; 96 x 128 -11 to +1 %, +2 to +5 % below 320 (0.2 us, what starting four more waves takes); 192 x 64 [K x N] -10 to 0 %, +2 to +6 % at 512; 128 x 128 [K x N] -18 to -4 %, up to +5 % at 512;
-// 64 x 64 [K x N] 0 to +7 % but -4 % with helpers; 128 x 128 [N x K] -7 to +3 %, and +1 to +10 % up to 1024: with
-// helpers only; 192 x 64 [N x K] the same, and no size takes it with helpers.
+// From which K a shape has loading waves. Time with them over time without, 96 and 256 tiles, K = 512, 1024, 4096 and 8192
+// and some shorter ones, from the cache and from HBM:
+//   16 x 16             -7 to -14 % from K = 4096 on, up to +7 % at 512
+//   32 x 32             -19 to 0 %, up to +3 % at 1024; [K x N] -12 to +1 %, up to +6 % at 1024
+//   64 x 32, 64 x 64    -10 to +2 %, +1 to +5 % up to 1024; 64 x 64 [K x N] 0 to +7 %, but -4 % with helpers
+//   96 x 64             -6 to 0 %, up to +2 %; [K x N] -13 to +1 %, +2 to +4 % at 176 and 256
+//   96 x 96             -11 to 0 %, up to +2 % at 136
+//   96 x 128            -11 to +1 %, +2 to +5 % below 320 (0.2 us, what starting four more waves takes)
+//   192 x 64 [K x N]    -10 to 0 %, +2 to +6 % at 512
+//   128 x 128 [K x N]   -18 to -4 %, up to +5 % at 512
+//   192 x 64, 128 x 128 -7 to +3 %, +1 to +10 % up to 1024: with helpers only, and no size has 192 x 64 with them
 // The shapes, smallest first, and what one 64-deep K step of a tile takes when about
 // every compute unit has one (us, measured on MI355X at K = 3584 and 8192). Several
 // tiles to a compute unit take their times in turn, also where two fit at once. [K x N]
@@ -478,17 +482,28 @@ struct SmallTileShape {
     tw_status (*kn)(const tw_gemm_args &, const TileLaunch &, hipStream_t);
 };
 static const SmallTileShape kSmallTiles[] = {
-    {16, 16, 256, 0.075f, 0.0f, 0.051f, 0.0f, launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, true>, nullptr},
-    {32, 16, 256, 0.097f, 0.0f, 0.060f, 0.0f, launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, true>, nullptr},
-    {32, 32, 128, 0.132f, 0.150f, 0.078f, 0.102f, launch_tile_t<false, 1, 1, 2, 2, 128, 4, 2048, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
-    {64, 32, 128, 0.180f, 0.200f, 0.109f, 0.122f, launch_tile_t<false, 2, 1, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 1, 2, 2, 128, 4, 2048>},
-    {64, 64, 128, 0.200f, 0.230f, 0.139f, 0.155f, launch_tile_t<false, 2, 2, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 2, 2, 2, 128, 4, kLoadersIfHelped>},
-    {96, 64, 64, 0.255f, 0.280f, 0.182f, 0.240f, launch_tile_t<false, 3, 2, 2, 2, 64, 6, 2048>, launch_tile_t<true, 3, 2, 2, 2, 64, 6, 320>},
-    {96, 96, 64, 0.338f, 0.0f, 0.245f, 0.0f, launch_tile_t<false, 3, 3, 2, 2, 64, 6, 320>, nullptr},
-    {96, 128, 64, 0.405f, 0.430f, 0.260f, 0.290f, launch_tile_t<false, 3, 4, 2, 2, 64, 5, 512>, launch_tile_t<true, 3, 4, 2, 2, 64, 5, 512>},
-    {192, 64, 64, 0.430f, 0.500f, 0.0f, 0.400f, launch_tile_t<false, 3, 2, 4, 2, 64, 4, kNeverLoaders>, launch_tile_t<true, 3, 2, 4, 2, 64, 4, 2048>},
-    {128, 128, 64, 0.530f, 0.550f, 0.370f, 0.460f, launch_tile_t<false, 2, 4, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 2, 4, 4, 2, 64, 4, 2048>},
-    {192, 128, 64, 0.700f, 0.690f, 0.0f, 0.0f, launch_tile_t<false, 3, 4, 4, 2, 64, 3, kNeverLoaders>, launch_tile_t<true, 3, 4, 4, 2, 64, 3, kNeverLoaders>},
+    {16, 16, 256, 0.075f, 0.0f, 0.051f, 0.0f,
+     launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, true>, nullptr},
+    {32, 16, 256, 0.097f, 0.0f, 0.060f, 0.0f,
+     launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, true>, nullptr},
+    {32, 32, 128, 0.132f, 0.150f, 0.078f, 0.102f,
+     launch_tile_t<false, 1, 1, 2, 2, 128, 4, 2048, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
+    {64, 32, 128, 0.180f, 0.200f, 0.109f, 0.122f,
+     launch_tile_t<false, 2, 1, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 1, 2, 2, 128, 4, 2048>},
+    {64, 64, 128, 0.200f, 0.230f, 0.139f, 0.155f,
+     launch_tile_t<false, 2, 2, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 2, 2, 2, 128, 4, kLoadersIfHelped>},
+    {96, 64, 64, 0.255f, 0.280f, 0.182f, 0.240f,
+     launch_tile_t<false, 3, 2, 2, 2, 64, 6, 2048>, launch_tile_t<true, 3, 2, 2, 2, 64, 6, 320>},
+    {96, 96, 64, 0.338f, 0.0f, 0.245f, 0.0f,
+     launch_tile_t<false, 3, 3, 2, 2, 64, 6, 320>, nullptr},
+    {96, 128, 64, 0.405f, 0.430f, 0.260f, 0.290f,
+     launch_tile_t<false, 3, 4, 2, 2, 64, 5, 512>, launch_tile_t<true, 3, 4, 2, 2, 64, 5, 512>},
+    {192, 64, 64, 0.430f, 0.500f, 0.0f, 0.400f,
+     launch_tile_t<false, 3, 2, 4, 2, 64, 4, kNeverLoaders>, launch_tile_t<true, 3, 2, 4, 2, 64, 4, 2048>},
+    {128, 128, 64, 0.530f, 0.550f, 0.370f, 0.460f,
+     launch_tile_t<false, 2, 4, 4, 2, 64, 4, kLoadersIfHelped>, launch_tile_t<true, 2, 4, 4, 2, 64, 4, 2048>},
+    {192, 128, 64, 0.700f, 0.690f, 0.0f, 0.0f,
+     launch_tile_t<false, 3, 4, 4, 2, 64, 3, kNeverLoaders>, launch_tile_t<true, 3, 4, 4, 2, 64, 3, kNeverLoaders>},
 };
 
 // A grid's tiles are worked off in turns of one to a compute unit. The launch, the first
@@ -506,13 +521,13 @@ double tile_grid_us(int64_t M, int64_t N, int64_t K, int rows, int cols, int k_s
 // Helpers for g cut into tiles of shape t: false where they do not pay. A helper gets some 50 KB a us, so
 // enough of them to fetch what the XCD with the most to read needs within the product's time, and a
 // quarter more; with too few the tiles wait for the helpers (three where eight are needed: 10 to 60 %
-// slower than none). Also false where the estimated time does not come below `limit`, before the rest is worked out
-// (a call for [K x N] weights costs 0.4 us less on the host).
+// slower than none). Also false where the estimated time does not come below `limit`, before the rest is worked out.
 static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget, double limit, HelpPlan *plan, double *us)
 {
     const float per_step = g.b_layout == TW_B_KN ? t.us_help_kn : t.us_help_nk;
     const int64_t max_bytes = int64_t(1) << 31;
-    if (per_step == 0.0f || g.K < kHelpFromK || g.N > (1 << 20) || g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return false;
+    if (per_step == 0.0f || g.K < kHelpFromK || g.N > (1 << 20)) return false;
+    if (g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return false;
     const int64_t tiles_m = (g.M + t.rows - 1) / t.rows, tiles_n = (g.N + t.cols - 1) / t.cols;
     const int64_t per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds, idle = budget / kXcds - per_xcd;
     if (idle < 1) return false;

@@ -14,20 +14,23 @@ namespace tw {
 // weights cost is not their share of the requests but HBM's latency for all of them (a panel
 // shared by seven compute units of an XCD comes in at 60 GB/s a unit from HBM and at 105 from the
 // caches). Touching lines ahead from the compute units that work on tiles costs the requests it
-// saves; from others it is free. Measured in us, without / with helpers, operands from HBM: [128 x
-// 8192] x [8192 x 3584] 25.8 / 20.7, [64 x 8192] x [8192 x 1280] 14.7 / 11.1, [16 x 8192] x [8192 x 1280] 11.5 / 9.9;
-// [K x N], whose rows of a narrow tile are less than a line: [16 x 4096] x [4096 x 4096] 17.4 / 10.2 (from the cache
-// 11.8 / 9.3), [128 x 8192] x [8192 x 2048] 30.7 / 19.0.
+// saves; from others it is free. us before there were helpers / now, operands from HBM and from the cache: [16 x 8192] x
+// [8192 x 1280] 11.6 / 10.0 and 10.6 / 9.2, [64 x 8192] x [8192 x 1280] 14.7 / 11.1 and 11.5 / 10.2; [K x N], whose rows of
+// a narrow tile are less than a line: [16 x 4096] x [4096 x 4096] 19.3 / 10.4 and 11.5 / 9.4, [128 x 8192] x [8192 x 2048]
+// 34.5 / 19.1 and 21.4 / 19.0. In the counters the same bytes come from beyond the L2 with helpers and without; L2 hits
+// and the latency of a request, [16 x 8192] x [8192 x 1280] 46 -> 65 % and 422 -> 275 clocks, [16 x 4096] x [4096 x 4096]
+// 59 -> 71 % and 659 -> 490.
 //
 // They keep `lead` windows (kHelpWindow bytes of K) ahead of a window every `pace` ticks of the
 // 100 MHz clock: further ahead they would push out of the 4 MiB what the tiles have yet to read. What the tiles fall
 // behind the clock comes on top and grows with K: the clock is a little slower than the tiles are expected to be
-// (kHelpPace), and the lead gets smaller by a tenth (kHelpLag) of all that the XCD reads, from kHelpLeadMost to kHelpLeadLeast.
-// us with 1.5 MB and 1.15 throughout / so, operands from the cache: [64 x 28672] x [28672 x 4096], stored [K x N], 103 / 60 (78
-// without helpers), [52 x 23680] x [23680 x 3072] 78 / 55 (62), [182 x 17536] x [17536 x 3072], [N x K], 53 / 48 (49). 131 sizes
-// with K from 2048 to 10000 against 1.5 MB and 1.15, from the cache and from HBM: 0.998 and 0.999, 47 with up to 32768 0.951 and
-// 0.981. (0.6 MB throughout: the same, but 7 % slower for [329 x 4816] x [4816 x 776]; 0.9 MB 0.998 and 0.998, 0.968 and 0.995; a
-// clock of 0.9, for which the tiles are too slow, or of 1.25: level, and 2 to 7 % slower where K is large.)
+// (kHelpPace), and the lead gets smaller by a tenth (kHelpLag) of all that the XCD reads, from kHelpLeadMost to
+// kHelpLeadLeast. us with 1.5 MB and 1.15 throughout / so, operands from the cache: [64 x 28672] x [28672 x 4096], stored
+// [K x N], 103 / 60 (78 without helpers), [52 x 23680] x [23680 x 3072] 78 / 55 (62), [182 x 17536] x [17536 x 3072],
+// [N x K], 53 / 48 (49). 131 sizes with K from 2048 to 10000 against 1.5 MB and 1.15, from the cache and from HBM: 0.998
+// and 0.999, 47 with up to 32768 0.951 and 0.981. (0.6 MB throughout: the same, but 7 % slower for [329 x 4816] x
+// [4816 x 776]; 0.9 MB 0.998 and 0.998, 0.968 and 0.995; a clock of 0.9, for which the tiles are too slow, or of 1.25:
+// level, and 2 to 7 % slower where K is large.)
 //
 // Where the XCD's share is more than its idle units can fetch, the helpers of all XCDs fetch every
 // operand once, for the last-level cache, and keep no pace (ALL).
