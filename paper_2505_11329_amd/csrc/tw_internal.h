@@ -29,7 +29,7 @@ tw_status hip_fail(hipError_t e, const char *where);
 // "last error", which may be somebody else's).
 template <typename... Params, typename... Args>
 inline hipError_t launch_kernel(void (*kern)(Params...), dim3 grid, dim3 block, unsigned lds_bytes,
-                                hipStream_t stream, Args... args)
+                                hipStream_t stream, const Args &...args)
 {
     void *argv[] = {const_cast<void *>(static_cast<const void *>(&args))...};
     return hipLaunchKernel(reinterpret_cast<const void *>(kern), grid, block, argv, lds_bytes, stream);
