@@ -127,6 +127,7 @@ typedef struct {
     int64_t helpers;            /* workgroups that only fetch operands ahead of them, on units without a tile */
     int helpers_for_all;        /* helpers: 0 each for the tiles of its XCD, into that one's L2; 1 all operands once,
                                    into the last-level cache */
+    int loading_waves;          /* of a workgroup, beside those that multiply: waves that only load; 0: all do both */
 } tw_gemm_launch;
 tw_status tw_gemm_plan(int64_t M, int64_t N, int64_t K, int b_layout, int cus, int place, tw_gemm_launch *plan);
 

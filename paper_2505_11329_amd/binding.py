@@ -56,7 +56,7 @@ class LayerArgs(ctypes.Structure):
 class GemmLaunch(ctypes.Structure):
     """struct tw_gemm_launch"""
     _fields_ = [("tile_m", ctypes.c_int), ("tile_n", ctypes.c_int), ("tiles_per_workgroup", ctypes.c_int),
-                ("workers", _i64), ("helpers", _i64), ("helpers_for_all", ctypes.c_int)]
+                ("workers", _i64), ("helpers", _i64), ("helpers_for_all", ctypes.c_int), ("loading_waves", ctypes.c_int)]
 
 
 class TwError(RuntimeError):

@@ -1053,7 +1053,8 @@ extern "C" tw_status tw_gemm_plan(int64_t M, int64_t N, int64_t K, int b_layout,
     const int64_t slots = (tiles + kXcds - 1) / kXcds * kXcds;
     const bool several = t.small >= 0 && t.help.helpers == 0;  // of the small tiles, as many to a unit as fit
     *plan = {t.rows, t.cols, t.paired ? 2 : 1, several || slots < cus ? slots : cus, int64_t(t.help.helpers) * kXcds,
-             t.small < 0 && t.help.helpers > 0};
+             t.small < 0 && t.help.helpers > 0,
+             t.small < 0 ? 0 : small_tile_loading_waves(g, t.small, t.help, places[place] == GemmPlace::kBeside)};
     return TW_OK;
 }
 

@@ -418,6 +418,7 @@ struct TileLaunch {
     int budget, cus;
     bool beside;
     HelpPlan help;
+    int *loading_waves = nullptr;  // not NULL: nothing is launched, but how many waves of a workgroup would only load
 };
 // LONG_K: from which K on there are loading waves (kNeverLoaders: not for this shape).
 static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
@@ -433,6 +434,10 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
             !(one_row && l.help.helpers == 0))
             return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM_B, true>(g, l, stream);
     using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
+    if (l.loading_waves) {
+        *l.loading_waves = LOADERS ? T::kWaves : 0;
+        return TW_OK;
+    }
     const int64_t tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
     if constexpr (STREAM_B)
         if (tiles_m > 1) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, false, LOADERS>(g, l, stream);
@@ -609,6 +614,14 @@ tw_status launch_small_tile(const tw_gemm_args &g, int shape, const HelpPlan &he
 {
     const SmallTileShape &t = kSmallTiles[shape];
     return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, {budget, cus, beside, help}, stream);
+}
+
+int small_tile_loading_waves(const tw_gemm_args &g, int shape, const HelpPlan &help, bool beside)
+{
+    const SmallTileShape &t = kSmallTiles[shape];
+    int waves = 0;
+    (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, {0, 0, beside, help, &waves}, nullptr);
+    return waves;
 }
 
 }  // namespace tw

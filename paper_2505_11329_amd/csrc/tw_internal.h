@@ -115,6 +115,7 @@ int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *
 void small_tile_size(int shape, int *rows, int *cols);
 tw_status launch_small_tile(const tw_gemm_args &g, int shape, const HelpPlan &help, int budget, int cus, bool beside,
                             hipStream_t stream);
+int small_tile_loading_waves(const tw_gemm_args &g, int shape, const HelpPlan &help, bool beside);
 
 // ---- fork/join events (tw_host.hip) ----
 // A small per-device pool of timing-disabled events used to order streams.

@@ -36,7 +36,8 @@ def test_header_declares_the_documented_entry_points():
     # measurement and introspection aids are declared apart from the method's interface
     aids = declared_functions(("tw_measure.h",))
     for must in ("tw_hbm_probe", "tw_hbm_probe_mixed", "tw_hbm_probe_shaped", "tw_hbm_probe_mixed_shaped",
-                 "tw_fused_grid", "tw_fused_workgroups", "tw_fused_layout", "tw_weave_schedule", "tw_gemm_tile_shape", "tw_gemm_tile_choice", "tw_gemm_plan",
+                 "tw_fused_grid", "tw_fused_workgroups", "tw_fused_layout", "tw_weave_schedule", "tw_gemm_tile_shape",
+                 "tw_gemm_tile_choice", "tw_gemm_plan",
                  "tw_reduce_add_rmsnorm_traced", "tw_streams_overlap", "tw_gemm_bf16_traced",
                  "tw_stream_create_cu_masked", "tw_stream_destroy"):
         assert must in aids and must not in names
@@ -289,6 +290,15 @@ def test_gemm_plan_and_the_launches_the_gpu_tests_mean_to_have_helpers():
         plan = tw.gemm_plan(*size, layouts[layout])
         assert ((plan.tile_m, plan.tile_n), plan.tiles_per_workgroup) == (tile, tiles), (layout, size)
         assert plan.helpers > 0 and plan.helpers_for_all == (tile[0] == 256)
+    for tile, layouts_, M, N, budget, Ks in cases.LOADING_CASES:
+        for layout in ("nk", "kn") if layouts_ == "both" else (layouts_,):
+            cases.assert_loading_waves(tw, tile, layout, M, N, budget, Ks)
+    assert {k for k, K in cases.LOADING_FROM.items()} == {
+        (layout, c[0]) for c in cases.LOADING_CASES for layout in (("nk", "kn") if c[1] == "both" else (c[1],))
+        if min(c[5]) < cases.LOADING_FROM.get((layout, c[0]), 0) <= max(c[5])}      # both sides of each
+    # next to another kernel eight waves that multiply have none beside them
+    assert tw.gemm_plan(193, 136, 2048, tw.B_KN, 4).loading_waves == 4
+    assert tw.gemm_plan(193, 136, 2048, tw.B_KN, 4, tw.GEMM_BESIDE).loading_waves == 0
     for T in (33, 64, 100, 200):
         assert tw.gemm_plan(T, 3584, 8192, place=tw.GEMM_CHAIN).helpers > 0
     # [K x N] weights whose rows are not whole lines: no larger tiles of 64 rows for the helpers' sake

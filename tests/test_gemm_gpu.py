@@ -238,6 +238,21 @@ def test_gemm_every_tile_shape(tw, torch_cuda, tile, layouts, M, N, K, budget):
         gemm_check(oracle.bf16_to_f64(to_bits(C)), ref, K, 0.5, "%s tiles, %s %dx%dx%d" % (tile, layout, M, N, K))
 
 
+# From which K on a shape has waves that only load where its launch has no helpers (not there: none without)
+LOADING_FROM = {("nk", (16, 16)): 2048, ("nk", (32, 16)): 2048, ("nk", (32, 32)): 2048, ("nk", (64, 32)): 2048, ("nk", (64, 64)): 2048,
+                ("nk", (96, 64)): 2048, ("nk", (96, 96)): 320, ("nk", (96, 128)): 512, ("kn", (32, 32)): 2048, ("kn", (64, 32)): 2048,
+                ("kn", (96, 64)): 320, ("kn", (96, 128)): 512, ("kn", (192, 64)): 2048, ("kn", (128, 128)): 2048}
+
+
+def assert_loading_waves(tw, tile, layout, M, N, budget, Ks):
+    one_row = layout == "nk" and tile[1] <= 32 and tile[0] <= 32 and M <= tile[0]     # weights that are streamed
+    for K in Ks:
+        plan = tw.gemm_plan(M, N, K, tw.B_NK if layout == "nk" else tw.B_KN, budget)
+        assert (plan.tile_m, plan.tile_n) == tile and plan.helpers == 0
+        has = K >= LOADING_FROM.get((layout, tile), 1 << 30) and not one_row
+        assert plan.loading_waves == (4 if has else 0), (tile, layout, K)
+
+
 # (tile, layouts, M, N, budget, K): around each K from which on a shape has waves that only load, and every number of K
 # steps from there past a whole round of its LDS stages (three to six steps of 64 to 256)
 LOADING_CASES = [(c[0], c[1], c[2], c[3], c[5], (2040, 2048, 2056, 2120, 2184, 2304, 2440, 2568))
@@ -254,8 +269,8 @@ def test_gemm_tiles_with_loading_waves(tw, torch_cuda, tile, layouts, M, N, budg
     """Both sides of the K from which on a shape has waves that only load; a tile to a workgroup and several."""
     for layout in ("nk", "kn") if layouts == "both" else (layouts,):
         code = tw.B_NK if layout == "nk" else tw.B_KN
+        assert_loading_waves(tw, tile, layout, M, N, budget, Ks)
         for K in Ks:
-            assert tw.gemm_tile_choice(M, N, K, code, budget) == tile
             g = W.make_gemm_inputs(M, K, N, 0.5, seed=M + N + K, b_layout=layout)
             C = torch_cuda.full((M, N), float("nan"), dtype=torch_cuda.bfloat16, device="cuda:0")
             tw.gemm_bf16(to_gpu(g["A"]), to_gpu(g["B"]), C=C, b_layout=code, cu_budget=budget)
@@ -302,6 +317,7 @@ def test_every_gemm_kernel_with_helper_workgroups(tw, torch_cuda, layout, tile, 
     code = tw.B_NK if layout == "nk" else tw.B_KN
     plan = tw.gemm_plan(M, N, K, code, tw.device_cu_count())
     assert ((plan.tile_m, plan.tile_n), plan.tiles_per_workgroup) == (tile, tiles) and plan.helpers > 0
+    assert plan.loading_waves == (0 if tile[0] == 256 else 4)
     assert plan.helpers_for_all == (tile[0] == 256) and tw.gemm_plan(M, N, K, code, 8).helpers == 0
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(M + N + K)
