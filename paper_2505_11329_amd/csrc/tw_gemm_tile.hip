@@ -28,8 +28,10 @@
 // stage s are in registers; once every wave has them and stage s + 1 has landed (one
 // vmcnt wait and one barrier), the stage's LDS takes the loads of step s + S, and the
 // reads of stage s + 1's fragments go out between the matrix instructions of stage s
-// (a single wave's chain of dependent matrix instructions leaves 22 clocks between two
-// of them, room for two reads: 15.2 -> 13.7 us at 16 rows against reads first).
+// (15.2 -> 13.7 us at 16 rows against reads first). Waves of a single block, one chain of
+// dependent matrix instructions, have a K loop of their own that never waits for all of its
+// reads (kRolls; what bounded those tiles was that chain: 480 clocks for 256 of K, of which
+// the matrix instructions take 180 and the loads of a 16 x 16 tile 290, now 300).
 // Rows are laid out as in tw_gemm.hip: 16-byte pieces xor-swizzled so that a fragment
 // read touches every bank once.
 #include <algorithm>
@@ -72,6 +74,14 @@ struct SmallTile {
     static constexpr bool kTail = S > 3;
     static_assert(!LOADERS || kTail, "loading waves load nothing past the end of K");
 };
+
+// Which kernels have the rolling K loop (see there): those whose waves have one block each, of [K x N] weights with loading
+// waves only (short K: 5 % slower).
+template <bool B_KN, int WM, int WN, bool LOADERS>
+static constexpr bool rolls()
+{
+    return WM * WN == 1 && (!B_KN || LOADERS);
+}
 
 // Position of the 16-byte piece c of row r, of the 2 BK bytes a row takes: two rows of
 // 128 bytes share a 256-byte line of all 64 banks (see lds_piece in tw_gemm.hip); rows of
@@ -116,6 +126,8 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // as in tw_gemm.hip: the host pass needs the launch stub only
     using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
+    constexpr bool kRolls = rolls<B_KN, WM, WN, LOADERS>();
+    constexpr int kFilled = kRolls ? S - 1 : S;  // stages filled ahead of the first step
     constexpr int SUBS = BK / kSubK, NW = T::kWaves, BM = T::BM, BN = T::BN, kRowBytes = BK * 2;
     static_assert(!B_KN || BN == 32 || BN == 64 || BN == 128, "kn_swizzle");
     // Weights that one row of tiles reads once are not worth keeping in the caches (16 rows,
@@ -287,7 +299,7 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
         // the previous tile's loads have landed and nobody reads LDS any more
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
-        static_for<S>([&](auto s) {
+        static_for<kFilled>([&](auto s) {
             if (loads && (!T::kTail || decltype(s)::value < k_tiles)) fetch(fetch_ctx(decltype(s)::value, decltype(s)::value));
         });
         if (LOADERS && help) say_begun(help);
@@ -311,46 +323,163 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
                 fbkn[i] = T::kABytes + row * (BN * 2) + (((col >> 3) ^ (kn_swizzle<BN>(row) << 1)) << 4) + (col & 7) * 2;
             }
         }
-        wait_vm(T::kTail ? k_tiles - 1 : S, std::integral_constant<int, S - 1>{});
-        F f0, f1;
-        if (computes) {
-            read_all(f0, 0);
-            settle(f0);
-        }
-        int slot = 0, kt = 0;
-        // Step kt, its fragments in cur; those of the next one have arrived in nxt at its end (no read is under way where
-        // the control flow branches or joins). MAIN: stage kt + S is loaded meanwhile.
-        auto step = [&](F &cur, F &nxt, auto main_tag) {
-            constexpr bool MAIN = decltype(main_tag)::value;
-            // stage kt + 1 has landed, stage kt is read
-            wait_vm(MAIN ? S : k_tiles - 2 - kt, std::integral_constant<int, S - 2>{});
-            Fetch c;
-            if (loads) c = fetch_ctx(kt + S, slot);
-            if constexpr (LOADERS || !MAIN)
-                if (loads && kt + S < k_tiles) fetch(c);
-            slot = slot + 1 == S ? 0 : slot + 1;
-            ++kt;
-            __builtin_amdgcn_sched_barrier(0);
+        wait_vm(T::kTail ? k_tiles - 1 : S, std::integral_constant<int, kFilled - 1>{});
+        if constexpr (kRolls) {
+            // A wave's single block is one chain of matrix instructions, each of which waits for the one before (22
+            // clocks), so nothing else may stand in it: fragments are read kAhead sub-steps ahead, from one stage into
+            // the next, and waited for by count, never all of them. Once a stage, ahead of its first read of the next
+            // one, the waves meet: that has landed, and the stage before this is read and takes the loads of step kt +
+            // S - 1 (one stage more in LDS than the other loop, for as many on their way). What bounds a tile now is its
+            // intake at the L1's 64 bytes a clock, and weights from HBM. us before / with this, operands from the cache
+            // and from HBM: [16 x 8192] x [8192 x 16] 8.8 / 6.4 and 9.0 / 6.6, x [8192 x 1280] 9.3 / 7.0 and 10.0 / 8.2, x
+            // [8192 x 3584] 13.5 / 12.2 and 14.5 / 14.2; [64 x 8192] x [8192 x 1280] 10.3 / 8.5 and 11.1 / 10.2; [K x N]
+            // [32 x 8192] x [8192 x 1280] 15.6 / 13.0 and 15.9 / 14.8. 180 sizes of 1 to 64 rows: 0.959 and 0.980; up to 3 %
+            // (0.1 us) slower where K is no more than the stages hold. Reads 3 to 7 sub-steps ahead are level, six and
+            // eight stages 1 to 8 % slower from the cache.
+            constexpr int kAhead = 4, kBases = 4;
+            static_assert(SUBS % kAhead == 0 && (kAhead - 1) * kPerSub < 16, "reads ahead, lgkmcnt field");
+            // What the waves that load do at the meeting of step kt. MAIN: a whole stage is to be loaded, and the offsets
+            // go on by one (with the waits and ranges of the last steps throughout, loading took longer than multiplying).
+            Fetch c = fetch_ctx(S - 2, S - 1);
+            int slot = S - 1;
+            auto meet = [&](int kt, auto main_tag) {
+                if constexpr (decltype(main_tag)::value) {
+                    constexpr int n = (S - 3) * T::kLoads;
+                    if (loads) __builtin_amdgcn_s_waitcnt(((n >> 4) << 14) | 0x0F70 | (n & 15));  // vmcnt(n)
+                    if constexpr (B_KN) {
+                        c = fetch_ctx(kt + S - 1, slot);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < kRepeat; ++q) c.off[q] += kRowBytes;
+                        c.base = (lds_char_ptr_t)(lds + slot * T::kStageBytes + loader * 1024);
+                    }
+                    __builtin_amdgcn_s_barrier();
+                } else {
+                    wait_vm(k_tiles - 2 - kt, std::integral_constant<int, S - 3>{});
+                    c = fetch_ctx(kt + S - 1, slot);
+                }
+                slot = slot + 1 == S ? 0 : slot + 1;
+            };
             if (computes) {
-                multiply(cur, nxt, slot, c, main_tag);
-                settle(nxt);
-            } else if constexpr (MAIN && !LOADERS) {
-                fetch(c);
-            }
-        };
-        while (kt + (T::kTail ? S + 1 : 0) < k_tiles) {  // (without a tail, a step past an odd end works on zeros)
-            step(f0, f1, std::true_type{});
-            step(f1, f0, std::true_type{});
-        }
-        if constexpr (T::kTail) {
-            for (;;) {
-                step(f0, f1, std::false_type{});
-                if (kt == k_tiles) break;
-                step(f1, f0, std::false_type{});
-                if (kt == k_tiles) break;
+                bf16x8 a[SUBS], b[B_KN ? 1 : SUBS];
+                u32x2 blo[B_KN ? SUBS : 1], bhi[B_KN ? SUBS : 1];
+                uint32_t at_a[kBases], at_b[kBases];  // in the stage that is read; sub-step s: those of s % 4, and s / 4 lines on
+                auto stage = [&](int of) {
+                    const uint32_t base = of * T::kStageBytes;
+#pragma unroll
+                    for (int q = 0; q < kBases; ++q) {
+                        at_a[q] = fa[q] + base;
+                        at_b[q] = B_KN ? fbkn[0] + base : fb[q] + base;
+                    }
+                };
+                auto read = [&](auto s_tag) {
+                    constexpr int s = decltype(s_tag)::value, kOff = s / 4 * 256;
+                    a[s] = lds_read16<kOff>(at_a[s % 4]);
+                    if constexpr (B_KN) {
+                        blo[s] = lds_read_tr8<s * kSubK * BN * 2>(at_b[0]);
+                        bhi[s] = lds_read_tr8<s * kSubK * BN * 2 + 4 * BN * 2>(at_b[0]);
+                    } else {
+                        b[s] = lds_read16<kOff>(at_b[s % 4]);
+                    }
+                };
+                int next = 0;
+                auto roll = [&](int kt, auto main_tag) {
+                    constexpr bool MAIN = decltype(main_tag)::value;
+                    static_for<SUBS>([&](auto s_tag) {
+                        constexpr int s = decltype(s_tag)::value, kNewer = (kAhead - 1) * kPerSub;
+                        bf16x8 bs;
+                        if constexpr (B_KN) {
+                            asm volatile("s_waitcnt lgkmcnt(%[n])" : "+v"(a[s]), "+v"(blo[s]), "+v"(bhi[s]) : [n] "n"(kNewer) : "memory");
+                            const u32x4 t = {blo[s].x, blo[s].y, bhi[s].x, bhi[s].y};
+                            bs = __builtin_bit_cast(bf16x8, t);
+                        } else {
+                            asm volatile("s_waitcnt lgkmcnt(%[n])" : "+v"(a[s]), "+v"(b[s]) : [n] "n"(kNewer) : "memory");
+                            bs = b[s];
+                        }
+                        acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bs, a[s], acc[0][0], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if constexpr (s == SUBS - kAhead) {
+                            next = next + 1 == S ? 0 : next + 1;
+                            stage(next);
+                            if constexpr (LOADERS) __builtin_amdgcn_s_barrier();
+                            else meet(kt, main_tag);
+                        }
+                        read(std::integral_constant<int, (s + kAhead) % SUBS>{});
+                        if constexpr (!LOADERS && s >= SUBS - kAhead) {
+                            static_for<T::kLoads>([&](auto i) {
+                                if constexpr (decltype(i)::value * kAhead / T::kLoads == s - (SUBS - kAhead))
+                                    if (MAIN || kt + S - 1 < k_tiles) fetch_one(c, i);
+                            });
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    });
+                };
+                stage(0);
+                static_for<kAhead>([&](auto s) { read(s); });
+                int kt = 0;
+                if constexpr (!LOADERS)
+                    for (; kt + S < k_tiles; ++kt) roll(kt, std::true_type{});
+                for (; kt < k_tiles; ++kt) roll(kt, std::false_type{});
+                // (what the last step asked for past the end of K)
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int s = 0; s < SUBS; ++s) {
+                    asm volatile("" ::"v"(a[s]));
+                    if constexpr (B_KN) asm volatile("" ::"v"(blo[s]), "v"(bhi[s]));
+                    else asm volatile("" ::"v"(b[s]));
+                }
+            } else {
+                int kt = 0;
+                for (; kt + S < k_tiles; ++kt) {
+                    meet(kt, std::true_type{});
+                    fetch(c);
+                }
+                for (; kt < k_tiles; ++kt) {
+                    meet(kt, std::false_type{});
+                    if (kt + S - 1 < k_tiles) fetch(c);
+                }
             }
         } else {
-            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): loads past the end
+            F f0, f1;
+            if (computes) {
+                read_all(f0, 0);
+                settle(f0);
+            }
+            int slot = 0, kt = 0;
+            // Step kt, its fragments in cur; those of the next one have arrived in nxt at its end (no read is under way where
+            // the control flow branches or joins). MAIN: stage kt + S is loaded meanwhile.
+            auto step = [&](F &cur, F &nxt, auto main_tag) {
+                constexpr bool MAIN = decltype(main_tag)::value;
+                // stage kt + 1 has landed, stage kt is read
+                wait_vm(MAIN ? S : k_tiles - 2 - kt, std::integral_constant<int, S - 2>{});
+                Fetch c;
+                if (loads) c = fetch_ctx(kt + S, slot);
+                if constexpr (LOADERS || !MAIN)
+                    if (loads && kt + S < k_tiles) fetch(c);
+                slot = slot + 1 == S ? 0 : slot + 1;
+                ++kt;
+                __builtin_amdgcn_sched_barrier(0);
+                if (computes) {
+                    multiply(cur, nxt, slot, c, main_tag);
+                    settle(nxt);
+                } else if constexpr (MAIN && !LOADERS) {
+                    fetch(c);
+                }
+            };
+            while (kt + (T::kTail ? S + 1 : 0) < k_tiles) {  // (without a tail, a step past an odd end works on zeros)
+                step(f0, f1, std::true_type{});
+                step(f1, f0, std::true_type{});
+            }
+            if constexpr (T::kTail) {
+                for (;;) {
+                    step(f0, f1, std::false_type{});
+                    if (kt == k_tiles) break;
+                    step(f1, f0, std::false_type{});
+                    if (kt == k_tiles) break;
+                }
+            } else {
+                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): loads past the end
+            }
         }
         // A lane holds row l15 and four consecutive columns of each block. Rows past M and
         // columns past N are dropped by the range check.
@@ -426,14 +555,15 @@ template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K
 static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipStream_t stream)
 {
     // (eight waves that multiply and four that load leave no registers for a workgroup beside them; weights that
-    // one row of tiles reads once each come as fast to the waves that multiply: 32 x 8192, K = 4096 13.8 us, with
-    // loading waves 14.2, 32 x 3584, K = 8192 15.6 and 16.2; with helpers they are ahead again)
+    // one row of tiles reads once each come as fast, from HBM, to the waves that multiply: 32 x 3584, K = 8192 16.1 us, with
+    // loading waves 17.2; with helpers they are ahead again)
     const bool one_row = STREAM_B && g.M <= kBlk * WM * WVM;
     if constexpr (LONG_K < kNeverLoaders && !LOADERS)
         if ((LONG_K == kLoadersIfHelped ? l.help.helpers > 0 : g.K >= LONG_K) && !(l.beside && WVM * WVN == 8) &&
             !(one_row && l.help.helpers == 0))
             return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM_B, true>(g, l, stream);
-    using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
+    constexpr int STAGES = S + (rolls<B_KN, WM, WN, LOADERS>() ? 1 : 0);  // (see the K loop)
+    using T = SmallTile<WM, WN, WVM, WVN, BK, STAGES, LOADERS>;
     if (l.loading_waves) {
         *l.loading_waves = LOADERS ? T::kWaves : 0;
         return TW_OK;
@@ -449,7 +579,7 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
     constexpr int kAloneBytes = T::kLdsBytes > 81 * 1024 ? T::kLdsBytes : 81 * 1024;
     const bool whole = l.budget >= l.cus && l.help.helpers == 0;
     const unsigned grid = static_cast<unsigned>((whole || slots < l.budget ? slots : l.budget) + l.help.helpers * kXcds);
-    auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, S, LOADERS, STREAM_B>;
+    auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, STAGES, LOADERS, STREAM_B>;
     static std::atomic<int> allowed[kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), kAloneBytes, allowed));
     TW_HIP(launch_kernel(kern, dim3(grid), dim3(T::kThreads),

@@ -283,6 +283,24 @@ def test_gemm_tiles_with_loading_waves(tw, torch_cuda, tile, layouts, M, N, budg
             gemm_check(got[ms, ns], ref, K, 0.5, "%s tiles, %s K = %d" % (tile, layout, K))
 
 
+@pytest.mark.parametrize("tile,M,N,step", [((16, 16), 17, 24, 256), ((32, 16), 33, 24, 256), ((32, 32), 33, 40, 128)])
+def test_gemm_tiles_of_one_block_to_a_wave_around_every_stage(tw, torch_cuda, tile, M, N, step):
+    """K of one to nine LDS stages, and eight elements more and less, without and with waves that only load (2048): the bits
+    of the same rows of a large product; several tiles to a workgroup."""
+    torch = torch_cuda
+    Ks = sorted({max(8, n * step + d) for n in range(1, 10) for d in (-8, 0, 8)} | {2048 + n * step + d for n in range(3) for d in (0, 8)})
+    for K in Ks:
+        assert tw.gemm_tile_choice(M, N, K, tw.B_NK, 4) == tile
+        g = W.make_gemm_inputs(M, K, N, 0.5, seed=K, b_layout="nk")
+        A, B = to_gpu(g["A"]), to_gpu(g["B"])
+        big = torch.cat([A, torch.ones((4096 - M, K), dtype=torch.bfloat16, device="cuda:0")])
+        want = to_bits(tw.gemm_bf16(big, B)[:M])
+        for budget in (4, 0):
+            C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+            tw.gemm_bf16(A, B, C, cu_budget=budget)
+            assert np.array_equal(to_bits(C), want), (tile, K, budget)
+
+
 HELPED = [("nk", 16, 1280, 8192), ("nk", 1, 8, 2048), ("nk", 64, 1280, 4096), ("nk", 40, 1272, 2056), ("nk", 150, 600, 4104),
           ("nk", 333, 1280, 4096), ("nk", 700, 1000, 2560), ("kn", 16, 4096, 2048), ("kn", 5, 4104, 2056), ("kn", 64, 4096, 2112),
           ("kn", 130, 1280, 4096), ("kn", 146, 1288, 4104), ("kn", 300, 1000, 3000), ("kn", 433, 328, 4104), ("kn", 1000, 1000, 2504),
