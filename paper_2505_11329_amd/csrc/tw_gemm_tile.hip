@@ -621,6 +621,8 @@ static const SmallTileShape kSmallTiles[] = {
      launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, true>, nullptr},
     {32, 16, 256, 0.097f, 0.0f, 0.060f, 0.0f,
      launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, true>, nullptr},
+    {16, 32, 256, 0.115f, 0.149f, 0.050f, 0.080f,
+     launch_tile_t<false, 1, 1, 1, 2, 256, 4, 2048, true>, launch_tile_t<true, 1, 1, 1, 2, 256, 4, 2048>},
     {32, 32, 128, 0.132f, 0.150f, 0.078f, 0.102f,
      launch_tile_t<false, 1, 1, 2, 2, 128, 4, 2048, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
     {64, 32, 128, 0.180f, 0.200f, 0.109f, 0.122f,
@@ -640,6 +642,14 @@ static const SmallTileShape kSmallTiles[] = {
     {192, 128, 64, 0.700f, 0.690f, 0.0f, 0.0f,
      launch_tile_t<false, 3, 4, 4, 2, 64, 3, kNeverLoaders>, launch_tile_t<true, 3, 4, 4, 2, 64, 3, kNeverLoaders>},
 };
+
+// Tiles of 16 x 32 are for one row of them: a second reads the weights again, which those of 32 x 32 read once. What
+// bounds a decode step's tile is its intake, and of that a 16 x 16 tile spends half on the same 16 rows, a 32 x 32 one a
+// quarter on rows that are not there. us before / with them, operands from the cache and from HBM: [16 x 8192] x [8192 x 8192]
+// 25.4 / 21.9 and 26.9 / 23.2, [16 x 4096] x [4096 x 6144] 11.8 / 11.0 and 12.1 / 11.4, [16 x 3584] x [3584 x 8192] 10.9 / 10.4
+// and 11.4 / 11.2; [K x N], with helpers, [16 x 8192] x [8192 x 3584] 15.4 / 13.6 and 16.5 / 14.6. 120 sizes of up to 16 rows,
+// both layouts: 0.95 and 0.98, the slowest 1.03.
+static bool wide_for(const SmallTileShape &t, int64_t M) { return t.rows == 16 && t.cols == 32 && M > 16; }
 
 // A grid's tiles are worked off in turns of one to a compute unit. The launch, the first
 // turn's pipeline fill and the last one's stores cost any grid about the same; each
@@ -661,7 +671,7 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
 {
     const float per_step = g.b_layout == TW_B_KN ? t.us_help_kn : t.us_help_nk;
     const int64_t max_bytes = int64_t(1) << 31;
-    if (per_step == 0.0f || g.K < kHelpFromK || g.N > (1 << 20)) return false;
+    if (per_step == 0.0f || wide_for(t, g.M) || g.K < kHelpFromK || g.N > (1 << 20)) return false;
     if (g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return false;
     const int64_t tiles_m = (g.M + t.rows - 1) / t.rows, tiles_n = (g.N + t.cols - 1) / t.cols;
     const int64_t per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds, idle = budget / kXcds - per_xcd;
@@ -703,7 +713,7 @@ int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *
     for (int i = 0; i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i) {
         const SmallTileShape &t = kSmallTiles[i];
         const float per_step = g.b_layout == TW_B_KN ? t.us_kn : t.us_nk;
-        if (per_step == 0.0f) continue;
+        if (per_step == 0.0f || wide_for(t, g.M)) continue;
         const double est = tile_grid_us(g.M, g.N, g.K, t.rows, t.cols, t.k_step, per_step, 3.0, budget);
         if (best < 0 || est < *us) {
             best = i;

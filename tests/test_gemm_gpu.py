@@ -172,7 +172,7 @@ def _every_tile_shape():
 
 
 # the tile shapes that are built, by layout of B (and, below, sizes and budgets that take each of them)
-KN_TILES = [(32, 32), (64, 32), (64, 64), (96, 64), (96, 128), (192, 64), (128, 128), (192, 128), (256, 128)]
+KN_TILES = [(16, 32), (32, 32), (64, 32), (64, 64), (96, 64), (96, 128), (192, 64), (128, 128), (192, 128), (256, 128)]
 NK_TILES = [(16, 16), (32, 16), (96, 96), (256, 64), (256, 192), (256, 256)] + KN_TILES
 
 
@@ -209,6 +209,7 @@ def test_gemm_full_tile_of_the_largest_k(tw, torch_cuda, rows, cols, layout):
 # shape is ever chosen for that.
 TILE_CASES = [((16, 16), "nk", 17, 24, 1032, 4), ((16, 16), "nk", 1, 8, 200, 1),
               ((32, 16), "nk", 33, 24, 1032, 4), ((32, 16), "nk", 17, 8, 200, 1),
+              ((16, 32), "nk", 9, 72, 1032, 4), ((16, 32), "both", 16, 72, 1000, 4), ((16, 32), "both", 1, 24, 200, 1),
               ((32, 32), "both", 33, 40, 1032, 4), ((32, 32), "both", 1, 8, 72, 1),
               ((64, 32), "both", 65, 40, 1032, 4), ((64, 32), "both", 33, 8, 72, 1),
               ((64, 64), "both", 65, 72, 1032, 4), ((64, 64), "both", 1, 40, 72, 1),
@@ -239,7 +240,7 @@ def test_gemm_every_tile_shape(tw, torch_cuda, tile, layouts, M, N, K, budget):
 
 
 # From which K on a shape has waves that only load where its launch has no helpers (not there: none without)
-LOADING_FROM = {("nk", (16, 16)): 2048, ("nk", (32, 16)): 2048, ("nk", (32, 32)): 2048, ("nk", (64, 32)): 2048, ("nk", (64, 64)): 2048,
+LOADING_FROM = {("nk", (16, 32)): 2048, ("kn", (16, 32)): 2048, ("nk", (16, 16)): 2048, ("nk", (32, 16)): 2048, ("nk", (32, 32)): 2048, ("nk", (64, 32)): 2048, ("nk", (64, 64)): 2048,
                 ("nk", (96, 64)): 2048, ("nk", (96, 96)): 320, ("nk", (96, 128)): 512, ("kn", (32, 32)): 2048, ("kn", (64, 32)): 2048,
                 ("kn", (96, 64)): 320, ("kn", (96, 128)): 512, ("kn", (192, 64)): 2048, ("kn", (128, 128)): 2048}
 
@@ -260,6 +261,7 @@ LOADING_CASES = [(c[0], c[1], c[2], c[3], c[5], (2040, 2048, 2056, 2120, 2184, 2
 LOADING_CASES += [(tile, layouts, M, N, budget, (312, 320, 328, 384, 392, 448, 512, 576, 584, 640))
                   for tile, layouts, M, N, budget in (((96, 96), "nk", 97, 136, 4), ((96, 96), "nk", 1, 264, 1),
                                                       ((96, 64), "kn", 129, 72, 4))]
+LOADING_CASES += [((16, 32), "kn", 9, 72, 4, (1976, 2040, 2048, 2184, 2304, 2440, 2560))]
 LOADING_CASES += [((96, 128), "both", M, N, budget, (504, 512, 520, 576, 584, 640))
                   for M, N, budget in ((97, 200, 4), (1, 328, 1))]
 
@@ -315,7 +317,8 @@ NOT_HELPED = [("nk", 40, 1272, 2056), ("nk", 150, 600, 4104), ("nk", 333, 1280, 
               ("nk", 2048, 3584, 2048), ("nk", 1990, 3528, 2056), ("nk", 3001, 4096, 2056), ("nk", 2000, 5000, 2504)]
 # (layout, tile, tiles to a workgroup, M, N, K): every kernel that has helpers, rows and windows of K that are not
 # whole, tiles in one and in several blocks of rows, and the depths of a model's down projections
-HELPED_TILES = [("nk", (16, 16), 1, 24, 24, 4864), ("nk", (16, 16), 1, 1207, 8, 2048), ("nk", (16, 16), 1, 16, 1024, 14336),
+HELPED_TILES = [("kn", (16, 32), 1, 16, 1280, 8192), ("kn", (16, 32), 1, 9, 1048, 2056), ("kn", (16, 32), 1, 1, 520, 14336),
+                ("nk", (16, 16), 1, 24, 24, 4864), ("nk", (16, 16), 1, 1207, 8, 2048), ("nk", (16, 16), 1, 16, 1024, 14336),
                 ("nk", (16, 16), 1, 16, 1024, 28672), ("nk", (32, 16), 1, 483, 144, 2080), ("nk", (32, 32), 1, 160, 984, 2064),
                 ("nk", (64, 32), 1, 250, 1224, 2224), ("nk", (64, 64), 1, 142, 3448, 2152), ("nk", (96, 64), 1, 259, 3520, 2856),
                 ("nk", (96, 96), 1, 356, 4144, 2272), ("nk", (128, 128), 1, 500, 5496, 3232),
