@@ -46,7 +46,6 @@ static constexpr int kWaves = kThreads / 64;
 // Dynamic LDS each workgroup requests so that only one fits on a compute unit
 // (gfx950 has 160 KiB per CU).
 static constexpr unsigned kOccupancyPadBytes = 96 * 1024;
-static constexpr int64_t kLastLevelCacheBytes = int64_t(256) << 20;
 
 struct FusedParams {
     const void *partials[TW_MAX_P];

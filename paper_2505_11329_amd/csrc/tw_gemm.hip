@@ -865,10 +865,10 @@ int tile_group_m(int64_t tiles_m, int64_t tiles_per_xcd, int tile_rows, int tile
 // 91 and 85.1 / 86.3, 2000 x 3000 x 5000 67 / 59.4, but K = 4096 84.6 / 87.2. As operands that are in the cache lose by
 // it, [N x K] weights only if they are large enough to come from HBM; [K x N] weights on single 256 x 128 tiles 0 to 2 %
 // either way, on pairs 3001 x 4096, K = 4104 122 / 104 and 97.2 / 97.9, K = 4096 95.7 / 85.1 and 83.0 / 85.1.
-static HelpPlan plan_help_all(const tw_gemm_args &g, int64_t idle, double us)
+static HelpPlan plan_help_all(const tw_gemm_args &g, GemmPlace place, int64_t idle, double us)
 {
     const int64_t max_bytes = int64_t(1) << 31, bytes = (g.M + g.N) * g.K * 2;
-    if (g.b_layout == TW_B_NK && g.N * g.K * 2 < kFromHbmBytes) return {};
+    if (g.b_layout == TW_B_NK && place != GemmPlace::kTrain && g.N * g.K * 2 < kFromHbmBytes) return {};
     if (idle < kXcds || g.K < kHelpFromK || g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return {};
     const double needed = double(bytes) / (us * kHelperBytesPerUs);
     if (needed > 0.85 * double(idle)) return {};
@@ -981,11 +981,11 @@ static GemmTiles choose_tiles(const tw_gemm_args &g, int budget, GemmPlace place
         small_tile_size(small, &take.rows, &take.cols);
         return take;
     }
-    const bool alone = place == GemmPlace::kAlone || place == GemmPlace::kChain;
+    const bool alone = place == GemmPlace::kAlone || place == GemmPlace::kChain || place == GemmPlace::kTrain;
     if (alone && (g.b_layout == TW_B_KN ? take.paired : take.cols == kGemmTileN || (take.cols > 64 && g.K % 64 != 0))) {
         const int64_t cols = take.paired ? 2 * take.cols : take.cols;
         const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + cols - 1) / cols);
-        take.help = plan_help_all(g, budget - (tiles + kXcds - 1) / kXcds * kXcds, us);
+        take.help = plan_help_all(g, place, budget - (tiles + kXcds - 1) / kXcds * kXcds, us);
     }
     return take;
 }

@@ -621,7 +621,7 @@ static const SmallTileShape kSmallTiles[] = {
      launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, true>, nullptr},
     {32, 16, 256, 0.097f, 0.0f, 0.060f, 0.0f,
      launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, true>, nullptr},
-    {16, 32, 256, 0.115f, 0.149f, 0.050f, 0.080f,
+    {16, 32, 256, 0.115f, 0.149f, 0.060f, 0.080f,
      launch_tile_t<false, 1, 1, 1, 2, 256, 4, 2048, true>, launch_tile_t<true, 1, 1, 1, 2, 256, 4, 2048>},
     {32, 32, 128, 0.132f, 0.150f, 0.078f, 0.102f,
      launch_tile_t<false, 1, 1, 2, 2, 128, 4, 2048, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
@@ -726,7 +726,11 @@ int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *
     // 17 and 21): they are taken for a layer's weights, unless small, and for [K x N] weights, which gain more from HBM
     // than they lose from the cache: us before helpers / now, cache and HBM, [128 x 8192] x [8192 x 2048] 21.4 / 19.0 and
     // 34.4 / 19.0, [70 x 8192] x [8192 x 3328] 21.6 / 23.2 and 31.5 / 23.6, [294 x 2560] x [2560 x 1024] 8.3 / 9.7 and 13.4 / 9.9.
-    const bool keep = g.b_layout == TW_B_NK && (place != GemmPlace::kChain || g.N * g.K * 2 < kFromHbmBytes);
+    // In a train whose weights together are more than the cache holds, every weight comes from HBM: [333 x 8192] x [8192 x 1280]
+    // takes 26.4 without and 21.2 with them. us of a train of eight 70B-class boundaries as a chain of single ones / so, 150 rows
+    // 357 / 348, 512 648 / 635, 700 756 / 744, 1500 1286 / 1252, level at 16 to 128 and from 1800 on.
+    const bool train = place == GemmPlace::kTrain;
+    const bool keep = g.b_layout == TW_B_NK && !train && (place != GemmPlace::kChain || g.N * g.K * 2 < kFromHbmBytes);
     const int only = best;
     const double plain = *us;
     const auto consider = [&](int shape, double limit) {
@@ -739,7 +743,7 @@ int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *
     };
     consider(only, 1e300);
     for (int i = 0; !keep && i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i)
-        if (i != only) consider(i, std::min(0.94 * plain, *us));
+        if (i != only) consider(i, std::min((train ? 1.0 : 0.94) * plain, *us));
     return best;
 }
 

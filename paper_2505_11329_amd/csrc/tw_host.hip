@@ -272,6 +272,14 @@ int tw_weave_schedule(int64_t T, int64_t K1, int64_t H, int P, int64_t N2, int f
     return takes_chains(layer, cus) ? TW_WEAVE_CHAINS : TW_WEAVE_ORDERED;
 }
 
+// The two GEMMs of a boundary over all its rows.
+static void gemms_of(const tw_layer_args &layer, tw_gemm_args *g1, tw_gemm_args *g2)
+{
+    const tw_fused_args &f = layer.fused;
+    *g1 = {layer.X1, layer.W1, const_cast<void *>(f.partials[0]), f.N, f.H, layer.K1, TW_B_NK, layer.gemm_cu_budget};
+    *g2 = {f.out, layer.W2, layer.Y, f.N, layer.N2, f.H, TW_B_NK, layer.gemm_cu_budget};
+}
+
 // Checks shared by every way of launching a layer boundary; on TW_OK with T > 0
 // *g1 and *g2 are the two GEMMs over all T rows.
 static tw_status validate_layer(const tw_layer_args *layer, void *stream_compute, void *stream_comm, tw_gemm_args *g1,
@@ -287,8 +295,7 @@ static tw_status validate_layer(const tw_layer_args *layer, void *stream_compute
         layer->schedule != TW_WEAVE_CHAINS)
         return TW_ERR_UNSUPPORTED;
     if (T == 0) return TW_OK;
-    *g1 = {layer->X1, layer->W1, const_cast<void *>(f.partials[0]), T, f.H, layer->K1, TW_B_NK, layer->gemm_cu_budget};
-    *g2 = {f.out, layer->W2, layer->Y, T, layer->N2, f.H, TW_B_NK, layer->gemm_cu_budget};
+    gemms_of(*layer, g1, g2);
     TW_TRY(validate_gemm(*g1));
     TW_TRY(validate_gemm(*g2));
     // Y is written while the other split's fused kernel may still be running:
@@ -371,6 +378,18 @@ static tw_status weave_pair(const tw_fused_args &f, const tw_gemm_args &g1, cons
     return TW_OK;
 }
 
+// A boundary (validated) as one chain, its products where `place` says. A fused step that was to share the compute units
+// has them to itself here and takes whichever kernel the whole device runs fastest (same bits).
+static tw_status unsplit_layer(const tw_fused_args &f, const tw_gemm_args &g1, const tw_gemm_args &g2, GemmPlace place,
+                               hipStream_t stream)
+{
+    TW_TRY(launch_gemm(g1, stream, place));
+    tw_fused_args alone = f;
+    if (alone.cu_budget == TW_CU_SHARED) alone.cu_budget = 0;
+    TW_TRY(launch_fused(alone, 0, f.N, nullptr, 0, stream));
+    return launch_gemm(g2, stream, place);
+}
+
 tw_status tw_weave_layer_cuts(const tw_layer_args *layer, const int64_t *cuts, int n_cuts, void *stream_compute,
                               void *stream_comm, void *parent, int parent_is_set, int join)
 {
@@ -387,15 +406,9 @@ tw_status tw_weave_layer_cuts(const tw_layer_args *layer, const int64_t *cuts, i
     hipStream_t sx = static_cast<hipStream_t>(stream_compute), sc = static_cast<hipStream_t>(stream_comm);
     hipStream_t sp = static_cast<hipStream_t>(parent);
     if (n_cuts == 0) {
-        // nothing to weave: the chain runs on the compute stream, with no events. A
-        // fused step that was to share the compute units has them to itself here and
-        // takes whichever kernel the whole device runs fastest (same bits).
+        // nothing to weave: the chain runs on the compute stream, with no events
         if (parent_is_set && sx != sp) TW_TRY(stream_wait_stream(sx, sp));
-        TW_TRY(launch_gemm(g1, sx, GemmPlace::kChain));
-        tw_fused_args alone = f;
-        if (alone.cu_budget == TW_CU_SHARED) alone.cu_budget = 0;
-        TW_TRY(launch_fused(alone, 0, T, nullptr, 0, sx));
-        TW_TRY(launch_gemm(g2, sx, GemmPlace::kChain));
+        TW_TRY(unsplit_layer(f, g1, g2, GemmPlace::kChain, sx));
         if (parent_is_set && join && sx != sp) TW_TRY(stream_wait_stream(sp, sx));
         return TW_OK;
     }
@@ -434,21 +447,35 @@ tw_status tw_weave_train(const tw_layer_args *layers, int n_layers, int64_t spli
     if (!layers) return TW_ERR_NULL;
     // everything is checked before anything is launched
     const int64_t T = layers[0].fused.N;
+    double weight_bytes = 0.0;
     for (int i = 0; i < n_layers; ++i) {
         tw_gemm_args g1, g2;
         TW_TRY(validate_layer(&layers[i], stream_compute, stream_comm, &g1, &g2));
         if (layers[i].fused.N != T) return TW_ERR_SHAPE;
+        weight_bytes += 2.0 * double(layers[i].fused.H) * double(layers[i].K1 + layers[i].N2);
     }
     if (split_row < 0 || split_row > T) return TW_ERR_SPLIT;
+    if (T == 0) return TW_OK;
     const bool whole = split_row == 0 || split_row == T;
+    hipStream_t sx = static_cast<hipStream_t>(stream_compute), sp = static_cast<hipStream_t>(parent);
+    if (whole) {
+        const GemmPlace place = weight_bytes > double(kLastLevelCacheBytes) ? GemmPlace::kTrain : GemmPlace::kChain;
+        if (parent_is_set && sx != sp) TW_TRY(stream_wait_stream(sx, sp));
+        for (int i = 0; i < n_layers; ++i) {
+            tw_gemm_args g1, g2;
+            gemms_of(layers[i], &g1, &g2);
+            TW_TRY(unsplit_layer(layers[i].fused, g1, g2, place, sx));
+        }
+        if (parent_is_set && join && sx != sp) TW_TRY(stream_wait_stream(sp, sx));
+        return TW_OK;
+    }
     for (int i = 0; i < n_layers; ++i)
-        TW_TRY(tw_weave_layer_cuts(&layers[i], &split_row, whole ? 0 : 1, stream_compute, stream_comm, parent,
+        TW_TRY(tw_weave_layer_cuts(&layers[i], &split_row, 1, stream_compute, stream_comm, parent,
                                    (i == 0 && parent_is_set) ? 1 : 0, 0));
-    if (parent_is_set && join && T > 0) {
-        hipStream_t sx = static_cast<hipStream_t>(stream_compute), sc = static_cast<hipStream_t>(stream_comm);
-        hipStream_t sp = static_cast<hipStream_t>(parent);
+    if (parent_is_set && join) {
+        hipStream_t sc = static_cast<hipStream_t>(stream_comm);
         if (sx != sp) TW_TRY(stream_wait_stream(sp, sx));
-        if (!whole && sc != sp) TW_TRY(stream_wait_stream(sp, sc));
+        if (sc != sp) TW_TRY(stream_wait_stream(sp, sc));
     }
     return TW_OK;
 }

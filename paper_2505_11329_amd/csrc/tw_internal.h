@@ -68,6 +68,7 @@ inline bool ranges_overlap(const void *a, uint64_t alen, const void *b, uint64_t
 // One launch addresses its tensors with 32-bit byte offsets; longer batches are
 // cut into several launches on the host (rows are independent).
 static constexpr int64_t kMaxLaunchBytes = int64_t(1) << 31;
+static constexpr int64_t kLastLevelCacheBytes = int64_t(256) << 20;
 
 // ---- fused reduce + residual add + RMSNorm (tw_fused.hip) ----
 // Host-only argument checks; no HIP call.
@@ -97,8 +98,9 @@ tw_status validate_gemm(const tw_gemm_args &g);
 // second GEMM): of the 256-row tiles it then takes the 256 x 128 ones only; smaller tiles where
 // they are estimated faster, as on its own. Woven: nothing beside it for most of the time, tiles
 // as on its own, but the compute units without a tile are not its to use. Chain: on its own, one of a
-// layer's products in a row.
-enum class GemmPlace { kAlone, kBeside, kWoven, kChain };
+// layer's products in a row. Train: a chain whose weights come from HBM whatever their size, being more together than the
+// last-level cache holds.
+enum class GemmPlace { kAlone, kBeside, kWoven, kChain, kTrain };
 tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, GemmPlace place = GemmPlace::kAlone);
 static constexpr int kGemmTileM = 256, kGemmTileN = 128;
 // Tile rows per block of the tile ordering.

@@ -427,3 +427,34 @@ def test_weave_layer_random_shapes_cuts_and_schedules(tw, torch_cuda):
             for name, g_, w_ in zip(("G1", "out", "residual_out", "Y"), got, (C0, out0, res0, Y0)):
                 assert np.array_equal(g_, w_), (what, cuts, schedule, budgets, name)
 
+
+@pytest.mark.parametrize("rows", [16, 150, 700, 1500])
+def test_train_of_more_weights_than_the_cache_holds_gives_the_bits_of_its_layers(tw, torch_cuda, rows):
+    """An unsplit train with 300 MB of weights, whose products take other tiles and helpers than those of a single
+    boundary, against its boundaries one by one."""
+    torch = torch_cuda
+    H_, K1_, N2_, n = 4096, 4096, 5120, 4
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(rows)
+    draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.05, generator=gen)
+    empty = lambda *shape: torch.full(shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    assert n * H_ * (K1_ + N2_) * 2 > 256 << 20
+    W1, W2, X1, other = [draw(H_, K1_) for _ in range(n)], [draw(N2_, H_) for _ in range(n)], draw(rows, K1_), draw(rows, H_)
+    weight, first = draw(H_), draw(rows, H_)
+    sx, sc = torch.cuda.current_stream(), torch.cuda.Stream()
+    results = []
+    for train in (True, False):
+        residual, layers = first, []
+        for i in range(n):
+            layers.append(dict(X1=X1, W1=W1[i], partials=[empty(rows, H_), other], residual=residual, weight=weight, eps=1e-5,
+                               W2=W2[i], out=empty(rows, H_), residual_out=empty(rows, H_), Y=empty(rows, N2_)))
+            residual = layers[-1]["residual_out"]
+        if train:
+            tw.weave_train(layers, rows, sx, sc)
+        else:
+            for l in layers:
+                tw.weave_layer(split_row=rows, stream_compute=sx, stream_comm=sc, **l)
+        torch.cuda.synchronize()
+        results.append([l[k] for l in layers for k in ("out", "residual_out", "Y")])
+    for got, want in zip(*results):
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and not torch.isnan(got).any()
