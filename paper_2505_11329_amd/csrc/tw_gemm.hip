@@ -756,6 +756,10 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
         // are read: with all 256 accumulator registers of the 256 x 256 tile taken the
         // register allocator spills (13, none in the K loop), and a reload in the middle of
         // the stores would wait for all of them.
+        // Written through to memory (kStorePolicy) and not kept dirty in the L2, which the end of the launch would have to
+        // wait for. us before / so: 4096 x 4096, K = 1024 32.2 / 31.1, 1024 x 8192, K = 1024 18.8 / 18.2, 4096^3 96.6 / 95.2,
+        // 8192^3 746 / 747; a train of eight boundaries of 1000 rows 943 / 932. Stored "nt" 8192 x 8192, K = 1024 is faster yet
+        // (124.6 / 123.7 / 117.3), but what reads the result next is slower: a boundary of 4096 rows 365 / 364 / 387.
         constexpr int kRowPitch = kBlk * WN * 2 + 32;
         constexpr int kRegion = kBlk * WM * kRowPitch;
         // A row of the sub-tile goes out as runs of kPieces 16-byte pieces (a row of 96 columns in three runs of 64 bytes).
@@ -793,7 +797,7 @@ __global__ __launch_bounds__(64 * (2 * BM / (kBlk * WM))) void gemm_bf16_kernel(
             for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
                 const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) u32x4 *>(
                     static_cast<uintptr_t>(r_addr + i * kRowsPerStore * kRowPitch));
-                __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, 0);  // (no scalar offset: see st())
+                __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, kStorePolicy);  // (no scalar offset: see st())
             }
         }
         if constexpr (TRACE) phase[kPhaseStores] += now() - t_stores;

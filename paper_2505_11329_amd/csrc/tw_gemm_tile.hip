@@ -487,7 +487,9 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
         const __amdgpu_buffer_rsrc_t rc = make_rsrc(C + m0 * c_row_bytes, static_cast<uint32_t>(rows_a * c_row_bytes));
         if constexpr (T::kStagedStores) {
             // Through LDS, each wave in a region of its own, rows padded by 32 bytes, so that a
-            // store covers whole rows of the wave's outputs (as in tw_gemm.hip).
+            // store covers whole rows of the wave's outputs, written through (as in tw_gemm.hip). The shapes whose stores do
+            // not go through LDS keep the default policy: their few bytes leave within the launch either way (sc1: 16 rows,
+            // K = 8192, N = 3584 level, 64 x 4096, K = 1024 4.13 -> 4.17 us).
             constexpr int kRowPitch = kBlk * WN * 2 + 32, kRegion = kBlk * WM * kRowPitch;
             constexpr int kPieces = kBlk * WN * 2 / 16, kRowsPerStore = 64 / kPieces;
             static_assert(T::kCompute * kRegion <= T::kLdsBytes, "the waves' regions");
@@ -517,7 +519,7 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
                 for (int i = 0; i < kBlk * WM / kRowsPerStore; ++i) {
                     const u32x4 v = *reinterpret_cast<__attribute__((address_space(3))) u32x4 *>(
                         static_cast<uintptr_t>(r_addr + i * kRowsPerStore * kRowPitch));
-                    __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, 0);  // (no scalar offset: see st())
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rc, g_off + store_rows_bytes * i, 0, kStorePolicy);  // (no scalar offset: see st())
                 }
             }
         } else if (computes) {
