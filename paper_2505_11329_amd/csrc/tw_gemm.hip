@@ -1001,7 +1001,7 @@ tw_status launch_gemm(const tw_gemm_args &g, hipStream_t stream, GemmPlace place
     TW_TRY(current_cu_count(&cus));
     const int budget = resolve_budget(g.cu_budget, cus);
     const GemmTiles t = choose_tiles(g, budget, place);
-    if (t.small >= 0) return launch_small_tile(g, t.small, t.help, budget, cus, place == GemmPlace::kBeside, stream);
+    if (t.small >= 0) return launch_small_tile(g, t.small, t.help, budget, cus, place, stream);
     if (g.b_layout == TW_B_KN)
         return t.paired ? launch_cfg<true, 8, 8, 5, 64>(g, budget, stream, t.help)
                         : launch_cfg<true, 4, 4, 3, 64>(g, budget, stream);
@@ -1058,7 +1058,7 @@ extern "C" tw_status tw_gemm_plan(int64_t M, int64_t N, int64_t K, int b_layout,
     const bool several = t.small >= 0 && t.help.helpers == 0;  // of the small tiles, as many to a unit as fit
     *plan = {t.rows, t.cols, t.paired ? 2 : 1, several || slots < cus ? slots : cus, int64_t(t.help.helpers) * kXcds,
              t.small < 0 && t.help.helpers > 0,
-             t.small < 0 ? 0 : small_tile_loading_waves(g, t.small, t.help, places[place] == GemmPlace::kBeside)};
+             t.small < 0 ? 0 : small_tile_loading_waves(g, t.small, t.help, places[place])};
     return TW_OK;
 }
 

@@ -547,23 +547,28 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
 
 struct TileLaunch {
     int budget, cus;
-    bool beside;
+    GemmPlace place;
     HelpPlan help;
     int *loading_waves = nullptr;  // not NULL: nothing is launched, but how many waves of a workgroup would only load
 };
 // LONG_K: from which K on there are loading waves (kNeverLoaders: not for this shape).
 static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
-template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, bool STREAM_B = false, bool LOADERS = false>
+// STREAM: whether weights that one row of tiles reads once go past the caches (kStreamPolicy). Of the shapes for up to
+// 64 rows only in trains, whose weights come from HBM: us kept / past the caches, from HBM, [40 x 3584] x [3584 x 8192] 14.8 /
+// 13.1, 64 rows 17.4 / 15.2, [64 x 1024] x [1024 x 8192] 6.8 / 6.5, but weights that are in the cache do not stay there: 11.2 /
+// 12.7 and 11.7 / 15.0. (Several rows of tiles: -14 to +20 % from HBM, +10 to +57 % from the cache.)
+enum Stream { kKeep, kStream, kStreamInTrains };
+template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, Stream STREAM = kKeep, bool LOADERS = false>
 static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipStream_t stream)
 {
     // (eight waves that multiply and four that load leave no registers for a workgroup beside them; weights that
     // one row of tiles reads once each come as fast, from HBM, to the waves that multiply: 32 x 3584, K = 8192 16.1 us, with
     // loading waves 17.2; with helpers they are ahead again)
-    const bool one_row = STREAM_B && g.M <= kBlk * WM * WVM;
+    const bool one_row = STREAM != kKeep && g.M <= kBlk * WM * WVM && (STREAM == kStream || l.place == GemmPlace::kTrain);
     if constexpr (LONG_K < kNeverLoaders && !LOADERS)
-        if ((LONG_K == kLoadersIfHelped ? l.help.helpers > 0 : g.K >= LONG_K) && !(l.beside && WVM * WVN == 8) &&
+        if ((LONG_K == kLoadersIfHelped ? l.help.helpers > 0 : g.K >= LONG_K) && !(l.place == GemmPlace::kBeside && WVM * WVN == 8) &&
             !(one_row && l.help.helpers == 0))
-            return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM_B, true>(g, l, stream);
+            return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM, true>(g, l, stream);
     constexpr int STAGES = S + (rolls<B_KN, WM, WN, LOADERS>() ? 1 : 0);  // (see the K loop)
     using T = SmallTile<WM, WN, WVM, WVN, BK, STAGES, LOADERS>;
     if (l.loading_waves) {
@@ -571,8 +576,8 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
         return TW_OK;
     }
     const int64_t tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
-    if constexpr (STREAM_B)
-        if (tiles_m > 1) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, false, LOADERS>(g, l, stream);
+    if constexpr (STREAM != kKeep)
+        if (!one_row) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, kKeep, LOADERS>(g, l, stream);
     if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
     const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
     const int64_t slots = int64_t(tiles_per_xcd) * kXcds;
@@ -581,7 +586,7 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
     constexpr int kAloneBytes = T::kLdsBytes > 81 * 1024 ? T::kLdsBytes : 81 * 1024;
     const bool whole = l.budget >= l.cus && l.help.helpers == 0;
     const unsigned grid = static_cast<unsigned>((whole || slots < l.budget ? slots : l.budget) + l.help.helpers * kXcds);
-    auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, STAGES, LOADERS, STREAM_B>;
+    auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, STAGES, LOADERS, STREAM != kKeep>;
     static std::atomic<int> allowed[kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), kAloneBytes, allowed));
     TW_HIP(launch_kernel(kern, dim3(grid), dim3(T::kThreads),
@@ -620,15 +625,17 @@ struct SmallTileShape {
 };
 static const SmallTileShape kSmallTiles[] = {
     {16, 16, 256, 0.075f, 0.0f, 0.051f, 0.0f,
-     launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, true>, nullptr},
+     launch_tile_t<false, 1, 1, 1, 1, 256, 4, 2048, kStream>, nullptr},
     {32, 16, 256, 0.097f, 0.0f, 0.060f, 0.0f,
-     launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, true>, nullptr},
+     launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, kStream>, nullptr},
     {16, 32, 256, 0.115f, 0.149f, 0.060f, 0.080f,
-     launch_tile_t<false, 1, 1, 1, 2, 256, 4, 2048, true>, launch_tile_t<true, 1, 1, 1, 2, 256, 4, 2048>},
+     launch_tile_t<false, 1, 1, 1, 2, 256, 4, 2048, kStream>, launch_tile_t<true, 1, 1, 1, 2, 256, 4, 2048>},
     {32, 32, 128, 0.132f, 0.150f, 0.078f, 0.102f,
-     launch_tile_t<false, 1, 1, 2, 2, 128, 4, 2048, true>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
+     launch_tile_t<false, 1, 1, 2, 2, 128, 4, 2048, kStream>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
+    {48, 32, 128, 0.150f, 0.0f, 0.093f, 0.0f,
+     launch_tile_t<false, 3, 1, 1, 2, 128, 4, 2048, kStreamInTrains>, nullptr},
     {64, 32, 128, 0.180f, 0.200f, 0.109f, 0.122f,
-     launch_tile_t<false, 2, 1, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 1, 2, 2, 128, 4, 2048>},
+     launch_tile_t<false, 2, 1, 2, 2, 128, 4, 2048, kStreamInTrains>, launch_tile_t<true, 2, 1, 2, 2, 128, 4, 2048>},
     {64, 64, 128, 0.200f, 0.230f, 0.139f, 0.155f,
      launch_tile_t<false, 2, 2, 2, 2, 128, 4, 2048>, launch_tile_t<true, 2, 2, 2, 2, 128, 4, kLoadersIfHelped>},
     {96, 64, 64, 0.255f, 0.280f, 0.182f, 0.240f,
@@ -645,13 +652,23 @@ static const SmallTileShape kSmallTiles[] = {
      launch_tile_t<false, 3, 4, 4, 2, 64, 3, kNeverLoaders>, launch_tile_t<true, 3, 4, 4, 2, 64, 3, kNeverLoaders>},
 };
 
+// 48 x 32 takes in 80 rows a step where 64 x 32 takes 96, and as one row of tiles leaves the helpers the compute units that
+// two rows of 32 x 32 would use: trains of eight boundaries, us before / streamed / streamed with this shape, 33 rows 216.6 / 212.8
+// / 205.0, 40 222.6 / 217.1 / 210.2, 48 234.1 / 229.1 / 222.8 (64 248.5 / 244.6 / 244.3); a boundary of 36 rows 25.6 / 24.6.
+// Only where K is enough for helpers, below it is level with 64 x 32; in two rows it gains 6 % from the cache and loses 3 % from
+// HBM ([96 x 8192] x [8192 x 3584]). (48 x 16, 64 x 16, 96 x 32 and 128 x 32, streamed: level to 80 % slower; 4 % faster at 80 rows,
+// N = 8192.)
+//
 // Tiles of 16 x 32 are for one row of them: a second reads the weights again, which those of 32 x 32 read once. What
 // bounds a decode step's tile is its intake, and of that a 16 x 16 tile spends half on the same 16 rows, a 32 x 32 one a
 // quarter on rows that are not there. us before / with them, operands from the cache and from HBM: [16 x 8192] x [8192 x 8192]
 // 25.4 / 21.9 and 26.9 / 23.2, [16 x 4096] x [4096 x 6144] 11.8 / 11.0 and 12.1 / 11.4, [16 x 3584] x [3584 x 8192] 10.9 / 10.4
 // and 11.4 / 11.2; [K x N], with helpers, [16 x 8192] x [8192 x 3584] 15.4 / 13.6 and 16.5 / 14.6. 120 sizes of up to 16 rows,
 // both layouts: 0.95 and 0.98, the slowest 1.03.
-static bool wide_for(const SmallTileShape &t, int64_t M) { return t.rows == 16 && t.cols == 32 && M > 16; }
+static bool left_out(const SmallTileShape &t, int64_t M, int64_t K)
+{
+    return t.cols == 32 && ((t.rows == 16 && M > 16) || (t.rows == 48 && (M > 48 || K < kHelpFromK)));
+}
 
 // A grid's tiles are worked off in turns of one to a compute unit. The launch, the first
 // turn's pipeline fill and the last one's stores cost any grid about the same; each
@@ -673,7 +690,7 @@ static bool plan_help(const tw_gemm_args &g, const SmallTileShape &t, int budget
 {
     const float per_step = g.b_layout == TW_B_KN ? t.us_help_kn : t.us_help_nk;
     const int64_t max_bytes = int64_t(1) << 31;
-    if (per_step == 0.0f || wide_for(t, g.M) || g.K < kHelpFromK || g.N > (1 << 20)) return false;
+    if (per_step == 0.0f || left_out(t, g.M, g.K) || g.K < kHelpFromK || g.N > (1 << 20)) return false;
     if (g.M * g.K * 2 >= max_bytes || g.N * g.K * 2 >= max_bytes) return false;
     const int64_t tiles_m = (g.M + t.rows - 1) / t.rows, tiles_n = (g.N + t.cols - 1) / t.cols;
     const int64_t per_xcd = (tiles_m * tiles_n + kXcds - 1) / kXcds, idle = budget / kXcds - per_xcd;
@@ -715,7 +732,7 @@ int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *
     for (int i = 0; i < int(sizeof(kSmallTiles) / sizeof(kSmallTiles[0])); ++i) {
         const SmallTileShape &t = kSmallTiles[i];
         const float per_step = g.b_layout == TW_B_KN ? t.us_kn : t.us_nk;
-        if (per_step == 0.0f || wide_for(t, g.M)) continue;
+        if (per_step == 0.0f || left_out(t, g.M, g.K)) continue;
         const double est = tile_grid_us(g.M, g.N, g.K, t.rows, t.cols, t.k_step, per_step, 3.0, budget);
         if (best < 0 || est < *us) {
             best = i;
@@ -755,18 +772,18 @@ void small_tile_size(int shape, int *rows, int *cols)
     *cols = kSmallTiles[shape].cols;
 }
 
-tw_status launch_small_tile(const tw_gemm_args &g, int shape, const HelpPlan &help, int budget, int cus, bool beside,
+tw_status launch_small_tile(const tw_gemm_args &g, int shape, const HelpPlan &help, int budget, int cus, GemmPlace place,
                             hipStream_t stream)
 {
     const SmallTileShape &t = kSmallTiles[shape];
-    return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, {budget, cus, beside, help}, stream);
+    return (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, {budget, cus, place, help}, stream);
 }
 
-int small_tile_loading_waves(const tw_gemm_args &g, int shape, const HelpPlan &help, bool beside)
+int small_tile_loading_waves(const tw_gemm_args &g, int shape, const HelpPlan &help, GemmPlace place)
 {
     const SmallTileShape &t = kSmallTiles[shape];
     int waves = 0;
-    (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, {0, 0, beside, help, &waves}, nullptr);
+    (g.b_layout == TW_B_KN ? t.kn : t.nk)(g, {0, 0, place, help, &waves}, nullptr);
     return waves;
 }
 

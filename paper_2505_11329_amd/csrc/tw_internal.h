@@ -115,9 +115,9 @@ struct HelpPlan {
 };
 int best_small_tile(const tw_gemm_args &g, int budget, GemmPlace place, double *us, HelpPlan *help);
 void small_tile_size(int shape, int *rows, int *cols);
-tw_status launch_small_tile(const tw_gemm_args &g, int shape, const HelpPlan &help, int budget, int cus, bool beside,
+tw_status launch_small_tile(const tw_gemm_args &g, int shape, const HelpPlan &help, int budget, int cus, GemmPlace place,
                             hipStream_t stream);
-int small_tile_loading_waves(const tw_gemm_args &g, int shape, const HelpPlan &help, bool beside);
+int small_tile_loading_waves(const tw_gemm_args &g, int shape, const HelpPlan &help, GemmPlace place);
 
 // ---- fork/join events (tw_host.hip) ----
 // A small per-device pool of timing-disabled events used to order streams.

@@ -173,7 +173,7 @@ def _every_tile_shape():
 
 # the tile shapes that are built, by layout of B (and, below, sizes and budgets that take each of them)
 KN_TILES = [(16, 32), (32, 32), (64, 32), (64, 64), (96, 64), (96, 128), (192, 64), (128, 128), (192, 128), (256, 128)]
-NK_TILES = [(16, 16), (32, 16), (96, 96), (256, 64), (256, 192), (256, 256)] + KN_TILES
+NK_TILES = [(16, 16), (32, 16), (48, 32), (96, 96), (256, 64), (256, 192), (256, 256)] + KN_TILES
 
 
 @pytest.mark.parametrize("rows,cols,layout", list(_every_tile_shape()))
@@ -211,6 +211,7 @@ TILE_CASES = [((16, 16), "nk", 17, 24, 1032, 4), ((16, 16), "nk", 1, 8, 200, 1),
               ((32, 16), "nk", 33, 24, 1032, 4), ((32, 16), "nk", 17, 8, 200, 1),
               ((16, 32), "nk", 9, 72, 1032, 4), ((16, 32), "both", 16, 72, 1000, 4), ((16, 32), "both", 1, 24, 200, 1),
               ((32, 32), "both", 33, 40, 1032, 4), ((32, 32), "both", 1, 8, 72, 1),
+              ((48, 32), "nk", 33, 72, 2056, 3), ((48, 32), "nk", 48, 8, 2048, 1),
               ((64, 32), "both", 65, 40, 1032, 4), ((64, 32), "both", 33, 8, 72, 1),
               ((64, 64), "both", 65, 72, 1032, 4), ((64, 64), "both", 1, 40, 72, 1),
               ((96, 64), "both", 129, 72, 1032, 4), ((96, 64), "both", 1, 8, 8, 1),
@@ -283,6 +284,22 @@ def test_gemm_tiles_with_loading_waves(tw, torch_cuda, tile, layouts, M, N, budg
             got = oracle.bf16_to_f64(to_bits(C))
             assert np.isfinite(got).all()
             gemm_check(got[ms, ns], ref, K, 0.5, "%s tiles, %s K = %d" % (tile, layout, K))
+
+
+@pytest.mark.parametrize("M,N,budget", [(47, 40, 2), (33, 104, 4), (48, 24, 1)])
+def test_gemm_tiles_of_48_rows_around_every_stage(tw, torch_cuda, M, N, budget):
+    """Every number of K steps past a whole round of the LDS stages, eight elements more and less: the bits of the same rows of a
+    large product. The shape is taken from K = 2048 on, and always has waves that only load."""
+    torch = torch_cuda
+    for K in sorted({2048 + n * 128 + d for n in range(6) for d in (0, 8, 120)}):
+        plan = tw.gemm_plan(M, N, K, tw.B_NK, budget)
+        assert (plan.tile_m, plan.tile_n, plan.loading_waves) == (48, 32, 4)
+        g = W.make_gemm_inputs(M, K, N, 0.5, seed=K, b_layout="nk")
+        A, B = to_gpu(g["A"]), to_gpu(g["B"])
+        big = torch.cat([A, torch.ones((4096 - M, K), dtype=torch.bfloat16, device="cuda:0")])
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        tw.gemm_bf16(A, B, C, cu_budget=budget)
+        assert np.array_equal(to_bits(C), to_bits(tw.gemm_bf16(big, B)[:M])), K
 
 
 @pytest.mark.parametrize("tile,M,N,step", [((16, 16), 17, 24, 256), ((32, 16), 33, 24, 256), ((32, 32), 33, 40, 128)])

@@ -432,8 +432,18 @@ def test_weave_layer_random_shapes_cuts_and_schedules(tw, torch_cuda):
 def test_train_of_more_weights_than_the_cache_holds_gives_the_bits_of_its_layers(tw, torch_cuda, rows):
     """An unsplit train with 300 MB of weights, whose products take other tiles and helpers than those of a single
     boundary, against its boundaries one by one."""
-    torch = torch_cuda
-    H_, K1_, N2_, n = 4096, 4096, 5120, 4
+    _train_against_its_layers(tw, torch_cuda, rows, 4096, 4096, 5120, 4)
+
+
+@pytest.mark.parametrize("rows,H_,K1_,N2_", [(33, 8192, 1024, 3584), (48, 8192, 3584, 1280), (40, 8192, 2056, 2568), (49, 8192, 1032, 3592),
+                                             (64, 8192, 3584, 1280), (65, 8192, 1024, 3584)])
+def test_train_of_one_row_of_tiles_streams_its_weights_and_gives_the_bits_of_its_layers(tw, torch_cuda, rows, H_, K1_, N2_):
+    """Both sides of the tile heights 48 and 64, of which a single row reads the weights past the caches, with helpers and without;
+    K and N that are no whole stages and tiles."""
+    _train_against_its_layers(tw, torch_cuda, rows, H_, K1_, N2_, -(-(270 << 20) // (H_ * (K1_ + N2_) * 2)))
+
+
+def _train_against_its_layers(tw, torch, rows, H_, K1_, N2_, n):
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(rows)
     draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.05, generator=gen)
