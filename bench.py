@@ -41,13 +41,13 @@ TRAFFIC_FROM_PROFILE = {
         "profile": "profiles/fused_kernel_c3_70b_shard_tp8_budget32.md",
         "kernel": "tw::fused_kernel<8, 1, false, false>",
         "fetched_KiB": 147728, "written_KiB": 32768,
-        "kernel_source_sha256_12": "0e7f071c8b9d",
+        "kernel_source_sha256_12": "e90d9ae1680b",
     },
     (WORKLOAD, 0): {
         "profile": "profiles/fused_kernel_c3_whole_device_and_shared.md",
         "kernel": "tw::fused_thin_kernel<8, 4, false, false>",
-        "fetched_KiB": 147667, "written_KiB": 32750,
-        "kernel_source_sha256_12": "0e7f071c8b9d",
+        "fetched_KiB": 147667, "written_KiB": 32751,
+        "kernel_source_sha256_12": "e90d9ae1680b",
     },
 }
 KERNEL_SOURCES = ("paper_2505_11329_amd/csrc/tw_fused.hip", "paper_2505_11329_amd/csrc/tw_device.h")

@@ -16,11 +16,11 @@
 // XCD reads (3 to 20 % slower); rotating the order in which the workgroups of an XCD
 // ask for a shared panel's rows (nothing at these sizes).
 //
-// Measured on MI355X, weights from HBM, us (the 256-row tiles before / now / the
-// vendor library): [16 x 8192] x [8192 x 3584] 64 / 13.1 / 20 (59 MB of weights: 4.5
-// TB/s), [16 x 8192] x [8192 x 1280] 46 / 11.5 / 20, [64 x 8192] x [8192 x 3584] 64 /
-// 20.6 / 24, [333 x 8192] x [8192 x 3584] 65 / 37 / 45, [512 x 8192] x [8192 x 1280]
-// 73 / 33 / 32.
+// Measured on MI355X, weights from HBM, us (the 256-row tiles before / these tiles
+// without helpers and the rolling K loop / the vendor library): [16 x 8192] x [8192 x
+// 3584] 64 / 13.1 / 20 (59 MB of weights: 4.5 TB/s), [16 x 8192] x [8192 x 1280] 46 /
+// 11.5 / 20 (with both, on another box, 8.2), [64 x 8192] x [8192 x 3584] 64 / 20.6 / 24,
+// [333 x 8192] x [8192 x 3584] 65 / 37 / 45, [512 x 8192] x [8192 x 1280] 73 / 33 / 32.
 //
 // Shape of a workgroup: WVM x WVN waves own WM x WN blocks of 16 x 16 each; tiles of
 // one or two blocks still get four waves, which share the loading. S stages of BK deep
