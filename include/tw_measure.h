@@ -113,13 +113,15 @@ tw_status tw_gemm_tile_choice(int64_t M, int64_t N, int64_t K, int b_layout, int
  * What tw_gemm_bf16 launches for a product of these sizes on `cus` compute units, and what the calls that launch
  * it as one of several do: where it stands is `place`. Alone: tw_gemm_bf16, tw_overlap_launch without a fused step.
  * Beside: next to another kernel. Woven: the first and last product of a split layer boundary, with nothing
- * beside them for most of the time. Chain: the products of an unsplit layer boundary. Host arithmetic only.
- * TW_ERR_NULL without a plan, else errors as tw_gemm_tile_choice, and TW_ERR_SHAPE for another place.
+ * beside them for most of the time. Chain: the products of an unsplit layer boundary, and of an unsplit train whose
+ * weights the last-level cache can hold. Train: those of an unsplit train (tw_weave_train) with more weights than that.
+ * Host arithmetic only. TW_ERR_NULL without a plan, else errors as tw_gemm_tile_choice, and TW_ERR_SHAPE for another place.
  */
 #define TW_GEMM_ALONE 0
 #define TW_GEMM_BESIDE 1
 #define TW_GEMM_WOVEN 2
 #define TW_GEMM_CHAIN 3
+#define TW_GEMM_TRAIN 4
 typedef struct {
     int tile_m, tile_n;         /* rows and columns of an output tile */
     int tiles_per_workgroup;    /* that it works on at a time: 1, or 2 neighbouring ones in a row */

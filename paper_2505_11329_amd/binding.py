@@ -24,7 +24,7 @@ STATUS = {0: "TW_OK", 1: "TW_ERR_NULL", 2: "TW_ERR_SHAPE", 3: "TW_ERR_ALIGN", 4:
           5: "TW_ERR_UNSUPPORTED", 6: "TW_ERR_SPLIT", 7: "TW_ERR_HIP"}
 PROBE_READ, PROBE_COPY, PROBE_WRITE = 0, 1, 2
 B_NK, B_KN = 0, 1
-GEMM_ALONE, GEMM_BESIDE, GEMM_WOVEN, GEMM_CHAIN = 0, 1, 2, 3
+GEMM_ALONE, GEMM_BESIDE, GEMM_WOVEN, GEMM_CHAIN, GEMM_TRAIN = 0, 1, 2, 3, 4
 CU_SHARED = -1
 WEAVE_AUTO, WEAVE_ORDERED, WEAVE_CHAINS = 0, 1, 2
 MAX_P = 16

@@ -1048,8 +1048,8 @@ extern "C" tw_status tw_gemm_plan(int64_t M, int64_t N, int64_t K, int b_layout,
 {
     if (!plan) return TW_ERR_NULL;
     if (M < 1 || N < 1 || K < 0 || cus < 1 || (b_layout != TW_B_NK && b_layout != TW_B_KN)) return TW_ERR_SHAPE;
-    if (place < TW_GEMM_ALONE || place > TW_GEMM_CHAIN) return TW_ERR_SHAPE;
-    constexpr GemmPlace places[] = {GemmPlace::kAlone, GemmPlace::kBeside, GemmPlace::kWoven, GemmPlace::kChain};
+    if (place < TW_GEMM_ALONE || place > TW_GEMM_TRAIN) return TW_ERR_SHAPE;
+    constexpr GemmPlace places[] = {GemmPlace::kAlone, GemmPlace::kBeside, GemmPlace::kWoven, GemmPlace::kChain, GemmPlace::kTrain};
     const tw_gemm_args g = {nullptr, nullptr, nullptr, M, N, K, b_layout, 0};
     const GemmTiles t = choose_tiles(g, cus, places[place]);
     const int64_t cols = t.paired ? 2 * t.cols : t.cols;

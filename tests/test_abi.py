@@ -301,6 +301,12 @@ def test_gemm_plan_and_the_launches_the_gpu_tests_mean_to_have_helpers():
     assert tw.gemm_plan(193, 136, 2048, tw.B_KN, 4, tw.GEMM_BESIDE).loading_waves == 0
     for T in (33, 64, 100, 200):
         assert tw.gemm_plan(T, 3584, 8192, place=tw.GEMM_CHAIN).helpers > 0
+    # in a train of more weights than the cache holds
+    for (M, N, K), chain, train in (((16, 2560, 2048), (16, 16, 0), (16, 32, 144)), ((333, 1280, 8192), (64, 32, 0), (64, 64, 96)),
+                                    ((2000, 3584, 4104), (256, 128, 0), (256, 128, 24))):
+        for place, want in ((tw.GEMM_CHAIN, chain), (tw.GEMM_TRAIN, train)):
+            plan = tw.gemm_plan(M, N, K, place=place)
+            assert (plan.tile_m, plan.tile_n, plan.helpers) == want, (M, N, K, place)
     # [K x N] weights whose rows are not whole lines: no larger tiles of 64 rows for the helpers' sake
     for M, N, K in ((34, 6344, 7040), (388, 632, 3328), (111, 3304, 7360)):
         assert tw.gemm_tile_choice(M, N, K, tw.B_KN) == tw.gemm_tile_choice(M, N, K, tw.B_KN, beside_other_kernels=True)
@@ -309,12 +315,12 @@ def test_gemm_plan_and_the_launches_the_gpu_tests_mean_to_have_helpers():
     for _ in range(4000):
         M, N, K = int(2 ** rng.uniform(0, 13.5)), 8 * int(2 ** rng.uniform(0, 11)), 8 * int(2 ** rng.uniform(0, 12))
         code, cus = rng.choice((tw.B_NK, tw.B_KN)), rng.choice((1, 3, 16, 64, 256))
-        for place in (tw.GEMM_ALONE, tw.GEMM_BESIDE, tw.GEMM_WOVEN, tw.GEMM_CHAIN):
+        for place in (tw.GEMM_ALONE, tw.GEMM_BESIDE, tw.GEMM_WOVEN, tw.GEMM_CHAIN, tw.GEMM_TRAIN):
             plan = tw.gemm_plan(M, N, K, code, cus, place)
             if place in (tw.GEMM_ALONE, tw.GEMM_BESIDE):
                 assert (plan.tile_m, plan.tile_n) == tw.gemm_tile_choice(M, N, K, code, cus, place == tw.GEMM_BESIDE)
             # helpers: on compute units without a tile, an equal number in each XCD, in calls that leave them idle
-            assert plan.helpers == 0 or (place in (tw.GEMM_ALONE, tw.GEMM_CHAIN) and plan.helpers % 8 == 0
+            assert plan.helpers == 0 or (place in (tw.GEMM_ALONE, tw.GEMM_CHAIN, tw.GEMM_TRAIN) and plan.helpers % 8 == 0
                                          and plan.workers + plan.helpers <= cus and K >= 2048)
             columns = plan.tile_n * plan.tiles_per_workgroup
             tiles = -(-M // plan.tile_m) * -(-N // columns)
@@ -323,7 +329,7 @@ def test_gemm_plan_and_the_launches_the_gpu_tests_mean_to_have_helpers():
     L = tw.lib()
     plan = tw.GemmLaunch()
     assert L.tw_gemm_plan(16, 16, 16, 0, 256, 0, None) == E_NULL
-    for bad in ((0, 16, 16, 0, 256, 0), (16, 16, -8, 0, 256, 0), (16, 16, 16, 2, 256, 0), (16, 16, 16, 0, 0, 0), (16, 16, 16, 0, 256, 4),
+    for bad in ((0, 16, 16, 0, 256, 0), (16, 16, -8, 0, 256, 0), (16, 16, 16, 2, 256, 0), (16, 16, 16, 0, 0, 0), (16, 16, 16, 0, 256, 5),
                 (16, 16, 16, 0, 256, -1)):
         assert L.tw_gemm_plan(*bad, ctypes.byref(plan)) == E_SHAPE, bad
 
