@@ -48,8 +48,13 @@ class _KernelNode(ctypes.Structure):
 
 
 def captured_grids(stream, call):
-    """The workgroups of each kernel that call() launches, found by capturing them (nothing runs). call() works
-    on `stream` and on streams it forks from and joins into it, and allocates nothing."""
+    """The workgroups of each kernel that call() launches (see captured_kernels)."""
+    return [grid for _, grid in captured_kernels(stream, call)]
+
+
+def captured_kernels(stream, call):
+    """(function, workgroups) of each kernel that call() launches, found by capturing them (nothing runs). call()
+    works on `stream` and on streams it forks from and joins into it, and allocates nothing."""
     import paper_2505_11329_amd as tw
     hip = tw.lib()      # a symbol of a library it was linked against is found through it
     handle, graph = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p()
@@ -63,12 +68,12 @@ def captured_grids(stream, call):
     assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
     nodes = (ctypes.c_void_p * n.value)()
     assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
-    grids = []
+    kernels = []
     for node in nodes:
         kind, p = ctypes.c_int(-1), _KernelNode()
         assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
         if kind.value == 0:     # hipGraphNodeTypeKernel
             assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
-            grids.append(p.grid[0])
+            kernels.append((p.func, p.grid[0]))
     assert hip.hipGraphDestroy(graph) == 0
-    return grids
+    return kernels

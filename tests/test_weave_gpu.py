@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import tw_workloads as W
-from helpers import assert_parity, to_bits, to_gpu
+from helpers import assert_parity, captured_kernels, to_bits, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -430,20 +430,40 @@ def test_weave_layer_random_shapes_cuts_and_schedules(tw, torch_cuda):
 
 @pytest.mark.parametrize("rows", [16, 150, 700, 1500])
 def test_train_of_more_weights_than_the_cache_holds_gives_the_bits_of_its_layers(tw, torch_cuda, rows):
-    """An unsplit train with 300 MB of weights, whose products take other tiles and helpers than those of a single
-    boundary, against its boundaries one by one."""
-    _train_against_its_layers(tw, torch_cuda, rows, 4096, 4096, 5120, 4)
+    """An unsplit train with 300 MB of weights against its boundaries one by one. At these sizes both launch the same
+    kernels (asserted); those that differ are below."""
+    assert not any(_train_against_its_layers(tw, torch_cuda, rows, 4096, 4096, 5120, 4))
+
+
+# (rows, H, K1, N2, the products that the train launches otherwise): small tiles with helpers in the place of others without,
+# which product of a boundary that is; the 256-row tiles of 2000 and 1900 rows get helpers for every operand
+@pytest.mark.parametrize("rows,H_,K1_,N2_,other", [(16, 2560, 2048, 2048, (True, True)), (9, 2568, 2056, 2056, (True, False)),
+                                                   (150, 8192, 1024, 1280, (False, True)), (333, 8192, 1024, 1280, (False, True)),
+                                                   (700, 8192, 1024, 1280, (False, True)), (1500, 8192, 1024, 1280, (False, True)),
+                                                   (2000, 4104, 1024, 3584, (False, True)), (1900, 3584, 2048, 1024, (True, True))])
+def test_train_whose_weights_come_from_memory_takes_other_tiles_and_helpers_with_the_same_bits(tw, torch_cuda, rows, H_, K1_, N2_, other):
+    cus = tw.device_cu_count()
+    plans = [[tw.gemm_plan(rows, n, k, tw.B_NK, cus, place) for place in (tw.GEMM_CHAIN, tw.GEMM_TRAIN)] for n, k in ((H_, K1_), (N2_, H_))]
+    assert tuple(chain.helpers == 0 and train.helpers > 0 for chain, train in plans) == other
+    n = -(-(270 << 20) // (H_ * (K1_ + N2_) * 2))
+    assert _train_against_its_layers(tw, torch_cuda, rows, H_, K1_, N2_, n) == other
 
 
 @pytest.mark.parametrize("rows,H_,K1_,N2_", [(33, 8192, 1024, 3584), (48, 8192, 3584, 1280), (40, 8192, 2056, 2568), (49, 8192, 1032, 3592),
                                              (64, 8192, 3584, 1280), (65, 8192, 1024, 3584)])
 def test_train_of_one_row_of_tiles_streams_its_weights_and_gives_the_bits_of_its_layers(tw, torch_cuda, rows, H_, K1_, N2_):
-    """Both sides of the tile heights 48 and 64, of which a single row reads the weights past the caches, with helpers and without;
-    K and N that are no whole stages and tiles."""
-    _train_against_its_layers(tw, torch_cuda, rows, H_, K1_, N2_, -(-(270 << 20) // (H_ * (K1_ + N2_) * 2)))
+    """Both sides of the tile heights 48 and 64, of which a single row reads the weights past the caches (other kernels than a
+    boundary's), with helpers and without; K and N that are no whole stages and tiles."""
+    n = -(-(270 << 20) // (H_ * (K1_ + N2_) * 2))
+    other = _train_against_its_layers(tw, torch_cuda, rows, H_, K1_, N2_, n)
+    tall = [tw.gemm_plan(rows, n_, k, tw.B_NK, tw.device_cu_count(), tw.GEMM_TRAIN).tile_m >= 48 for n_, k in ((H_, K1_), (N2_, H_))]
+    for product in range(2):
+        assert other[product] or rows > 64 or not tall[product], product
+    assert rows <= 64 or not any(other)
 
 
 def _train_against_its_layers(tw, torch, rows, H_, K1_, N2_, n):
+    """Bits, and that both launch what the plans say. Returns which of a boundary's two products the train launches otherwise."""
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(rows)
     draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.05, generator=gen)
@@ -451,20 +471,32 @@ def _train_against_its_layers(tw, torch, rows, H_, K1_, N2_, n):
     assert n * H_ * (K1_ + N2_) * 2 > 256 << 20
     W1, W2, X1, other = [draw(H_, K1_) for _ in range(n)], [draw(N2_, H_) for _ in range(n)], draw(rows, K1_), draw(rows, H_)
     weight, first = draw(H_), draw(rows, H_)
-    sx, sc = torch.cuda.current_stream(), torch.cuda.Stream()
-    results = []
+    sx, sc = torch.cuda.Stream(), torch.cuda.Stream()
+    cus = tw.device_cu_count()
+    fused = sum(tw.fused_workgroups(rows, H_, 2, cus=cus))
+    results, kernels = [], []
     for train in (True, False):
         residual, layers = first, []
         for i in range(n):
             layers.append(dict(X1=X1, W1=W1[i], partials=[empty(rows, H_), other], residual=residual, weight=weight, eps=1e-5,
                                W2=W2[i], out=empty(rows, H_), residual_out=empty(rows, H_), Y=empty(rows, N2_)))
             residual = layers[-1]["residual_out"]
-        if train:
-            tw.weave_train(layers, rows, sx, sc)
-        else:
-            for l in layers:
-                tw.weave_layer(split_row=rows, stream_compute=sx, stream_comm=sc, **l)
+
+        def call():
+            if train:
+                tw.weave_train(layers, rows, sx, sc, parent=sx)
+            else:
+                for l in layers:
+                    tw.weave_layer(split_row=rows, stream_compute=sx, stream_comm=sc, parent=sx, fused_cu_budget=tw.CU_SHARED, **l)
+        torch.cuda.synchronize()
+        kernels.append(captured_kernels(sx, call))
+        plans = [tw.gemm_plan(rows, n_, k, tw.B_NK, cus, tw.GEMM_TRAIN if train else tw.GEMM_CHAIN) for n_, k in ((H_, K1_), (N2_, H_))]
+        assert [grid for _, grid in kernels[-1]] == [plans[0].workers + plans[0].helpers, fused, plans[1].workers + plans[1].helpers] * n
+        call()
         torch.cuda.synchronize()
         results.append([l[k] for l in layers for k in ("out", "residual_out", "Y")])
     for got, want in zip(*results):
         assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and not torch.isnan(got).any()
+    differ = [a != b for a, b in zip(*kernels)]
+    assert differ == [differ[0], False, differ[2]] * n
+    return differ[0], differ[2]
