@@ -302,12 +302,14 @@ def test_gemm_tiles_of_48_rows_around_every_stage(tw, torch_cuda, M, N, budget):
         assert np.array_equal(to_bits(C), to_bits(tw.gemm_bf16(big, B)[:M])), K
 
 
-@pytest.mark.parametrize("tile,M,N,step", [((16, 16), 17, 24, 256), ((32, 16), 33, 24, 256), ((32, 32), 33, 40, 128)])
-def test_gemm_tiles_of_one_block_to_a_wave_around_every_stage(tw, torch_cuda, tile, M, N, step):
-    """K of one to nine LDS stages, and eight elements more and less, without and with waves that only load (2048): the bits
-    of the same rows of a large product; several tiles to a workgroup."""
+@pytest.mark.parametrize("tile,M,N,step,first", [((16, 16), 17, 24, 256, 1), ((32, 16), 33, 24, 256, 1), ((16, 32), 15, 104, 256, 3),
+                                                 ((32, 32), 33, 40, 128, 1)])
+def test_gemm_tiles_of_one_block_to_a_wave_around_every_stage(tw, torch_cuda, tile, M, N, step, first):
+    """K of one to nine LDS stages (16 x 32: from three on, below it is not taken for every K), and eight elements more and less,
+    without and with waves that only load (2048; 16 x 32 has them with helpers only, see STREAMED_AND_HELPED): the bits of the
+    same rows of a large product; several tiles to a workgroup."""
     torch = torch_cuda
-    Ks = sorted({max(8, n * step + d) for n in range(1, 10) for d in (-8, 0, 8)} | {2048 + n * step + d for n in range(3) for d in (0, 8)})
+    Ks = sorted({max(8, n * step + d) for n in range(first, 10) for d in (-8, 0, 8)} | {2048 + n * step + d for n in range(3) for d in (0, 8)})
     for K in Ks:
         assert tw.gemm_tile_choice(M, N, K, tw.B_NK, 4) == tile
         g = W.make_gemm_inputs(M, K, N, 0.5, seed=K, b_layout="nk")
@@ -332,11 +334,12 @@ HELPED = [("nk", 16, 1280, 8192), ("nk", 1, 8, 2048), ("nk", 64, 1280, 4096), ("
 NOT_HELPED = [("nk", 40, 1272, 2056), ("nk", 150, 600, 4104), ("nk", 333, 1280, 4096), ("nk", 700, 1000, 2560),
               ("kn", 146, 1288, 4104), ("kn", 1000, 1000, 2504), ("kn", 1200, 2000, 2240), ("kn", 16, 8192, 4096),
               ("nk", 2048, 3584, 2048), ("nk", 1990, 3528, 2056), ("nk", 3001, 4096, 2056), ("nk", 2000, 5000, 2504)]
-# (layout, tile, tiles to a workgroup, M, N, K): every kernel that has helpers, rows and windows of K that are not
+# (layout, tile, tiles to a workgroup, M, N, K): every kernel that has helpers as a call of its own (those that only a boundary
+# or a train launches with them: STREAMED_AND_HELPED, and the trains of test_weave_gpu.py), rows and windows of K that are not
 # whole, tiles in one and in several blocks of rows, and the depths of a model's down projections
 HELPED_TILES = [("kn", (16, 32), 1, 16, 1280, 8192), ("kn", (16, 32), 1, 9, 1048, 2056), ("kn", (16, 32), 1, 1, 520, 14336),
                 ("nk", (16, 16), 1, 24, 24, 4864), ("nk", (16, 16), 1, 1207, 8, 2048), ("nk", (16, 16), 1, 16, 1024, 14336),
-                ("nk", (16, 16), 1, 16, 1024, 28672), ("nk", (32, 16), 1, 483, 144, 2080), ("nk", (32, 32), 1, 160, 984, 2064),
+                ("nk", (16, 16), 1, 16, 1024, 28672), ("nk", (32, 16), 1, 483, 144, 2080), ("nk", (32, 16), 1, 18, 2120, 5832), ("nk", (32, 32), 1, 160, 984, 2064),
                 ("nk", (64, 32), 1, 250, 1224, 2224), ("nk", (64, 64), 1, 142, 3448, 2152), ("nk", (96, 64), 1, 259, 3520, 2856),
                 ("nk", (96, 96), 1, 356, 4144, 2272), ("nk", (128, 128), 1, 500, 5496, 3232),
                 ("nk", (256, 128), 1, 1046, 5392, 3432), ("nk", (256, 192), 1, 1609, 5456, 3560),
@@ -452,6 +455,42 @@ def test_layer_whose_gemm_has_helper_workgroups_equals_the_three_calls(tw, torch
     torch.cuda.synchronize()
     for a, b in ((out, out2), (res_out, res2), (Y, Y2)):
         assert np.array_equal(to_bits(a), to_bits(b))
+
+
+# One row of tiles, waves that only load, and helpers, the weights past the caches: (tile, M, N, K, as a boundary's second
+# product), K of every remainder of the five LDS stages and, where the choice allows it, eight elements more and less
+STREAMED_AND_HELPED = [((16, 16), 16, 1024, sorted(4096 + n * 256 + d for n in range(6) for d in (-8, 0, 8)), False),
+                       ((32, 16), 18, 2120, sorted(5888 + n * 256 + d for n in range(6) for d in (-8, 0, 8)), False),
+                       ((16, 32), 16, 2560, range(8192, 8192 + 6 * 256, 64), True),
+                       ((16, 32), 10, 2728, range(7680, 7680 + 6 * 256, 64), True),
+                       ((32, 32), 19, 2912, range(7744, 7744 + 6 * 128, 64), True)]
+
+
+@pytest.mark.parametrize("tile,M,N,Ks,in_layer", STREAMED_AND_HELPED)
+def test_streamed_weights_with_helper_workgroups_around_every_stage(tw, torch_cuda, tile, M, N, Ks, in_layer):
+    """The bits of 8 compute units, which have no helpers, and for one K samples against the fp64 product. The tiles of 32
+    columns have helpers here only where a boundary's weights are taken to come from memory."""
+    torch = torch_cuda
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(M)
+    rand = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.5, generator=gen)
+    sx, sc = torch.cuda.current_stream(), torch.cuda.Stream()
+    for K in Ks:
+        plan = tw.gemm_plan(M, N, K, tw.B_NK, tw.device_cu_count(), tw.GEMM_CHAIN if in_layer else tw.GEMM_ALONE)
+        assert (plan.tile_m, plan.tile_n, plan.loading_waves) == tile + (4,) and plan.helpers > 0, K
+        A, B = rand(M, K), rand(N, K)
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        if in_layer:
+            A, _, _ = tw.weave_layer(rand(M, 64), rand(K, 64), [rand(M, K) for _ in range(2)], rand(M, K), rand(K), 1e-5, B, M, sx, sc, Y=C)
+        else:
+            tw.gemm_bf16(A, B, C=C)
+        assert tw.gemm_plan(M, N, K, tw.B_NK, 8).helpers == 0
+        assert np.array_equal(to_bits(C), to_bits(tw.gemm_bf16(A, B, cu_budget=8))), K
+        if K == Ks[1]:
+            rng = np.random.default_rng(K)
+            ms, ns = np.append(rng.integers(0, M, 200), [0, M - 1]), np.append(rng.integers(0, N, 200), [0, N - 1])
+            ref = oracle.gemm_samples(to_bits(A), to_bits(B), "nk", ms, ns)
+            gemm_check(oracle.bf16_to_f64(to_bits(C))[ms, ns], ref, K, 0.5, "%s tiles, K = %d" % (tile, K))
 
 
 @pytest.mark.parametrize("layout,K,tile", [("nk", 512, (256, 128)), ("nk", 2048, (256, 256)), ("kn", 512, (256, 128))])
