@@ -134,6 +134,14 @@ typedef struct {
 tw_status tw_gemm_plan(int64_t M, int64_t N, int64_t K, int b_layout, int cus, int place, tw_gemm_launch *plan);
 
 /*
+ * Where the products of these boundaries stand in an unsplit tw_weave_train: TW_GEMM_TRAIN where their weights are more
+ * bytes than the last-level cache holds, else TW_GEMM_CHAIN. Weights that several boundaries point at count once. Of a
+ * boundary only W1, K1, W2, N2 and fused.H are looked at, the weights themselves are not. Host arithmetic only. -1 without
+ * layers, for n_layers outside 1 ... TW_MAX_TRAIN and for sizes below 0 (H: below 1).
+ */
+int tw_train_place(const tw_layer_args *layers, int n_layers);
+
+/*
  * Measurement aid (not part of the method): a streaming kernel with the same
  * persistent, CU-budgeted launch shape as the fused kernel, used to measure
  * what a given number of compute units can pull from / push to HBM, and as the

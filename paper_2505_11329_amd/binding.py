@@ -155,6 +155,8 @@ def lib():
         L.tw_gemm_tile_choice.restype = ctypes.c_int
         L.tw_gemm_plan.argtypes = [_i64, _i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.POINTER(GemmLaunch)]
         L.tw_gemm_plan.restype = ctypes.c_int
+        L.tw_train_place.argtypes = [ctypes.POINTER(LayerArgs), ctypes.c_int]
+        L.tw_train_place.restype = ctypes.c_int
         L.tw_hbm_probe_mixed.argtypes = [_vp, _vp, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp]
         L.tw_hbm_probe_mixed.restype = ctypes.c_int
         L.tw_hbm_probe_shaped.argtypes = [_vp, _vp, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp]

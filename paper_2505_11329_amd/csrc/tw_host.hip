@@ -1,7 +1,9 @@
 // Host side of libtw that is not tied to one kernel: status strings, device
 // queries, the event pool, the token split and the overlap launch.
 #include <algorithm>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "tw_internal.h"
@@ -439,6 +441,48 @@ tw_status tw_weave_layer_cuts(const tw_layer_args *layer, const int64_t *cuts, i
     return TW_OK;
 }
 
+// Where the products of an unsplit train stand: whether its weights come from HBM, being more together than the last-level
+// cache holds. Boundaries that point at the same bytes (a block that is used again, a train that repeats some layers)
+// count them once: weights that stay in the cache are not to be streamed past it. us of a train of eight boundaries over two
+// pairs of weights, 155 MB (70B-class boundaries), every use counted / as it is: 33 rows 206.5 / 196.2, 48 222.2 / 206.4, 64
+// 244.0 / 225.4, 150 321.3 / 310.0, 333 463.5 / 439.2, 700 717.3 / 705.8, 1500 1211 / 1218, level at 1, 16 and 100. Over four pairs, 310
+// MB, as boundaries of their own / as from HBM: 33 rows 216.3 / 207.9, 64 253.3 / 243.7, 700 742.5 / 732.9. (Weights used twice in a row in a train of more than the cache holds count as from HBM.)
+static GemmPlace train_place(const tw_layer_args *layers, int n_layers)
+{
+    struct Weight {
+        uintptr_t at, end;
+    };
+    const auto weight = [&](int i) {  // W1 and W2 of the boundaries in turn
+        const tw_layer_args &l = layers[i / 2];
+        const uintptr_t at = reinterpret_cast<uintptr_t>(i % 2 ? l.W2 : l.W1);
+        return Weight{at, at + static_cast<uintptr_t>(i % 2 ? l.N2 : l.K1) * static_cast<uintptr_t>(l.fused.H) * 2};
+    };
+    double bytes = 0.0;
+    for (int i = 0; i < 2 * n_layers; ++i) bytes += double(weight(i).end - weight(i).at);
+    if (bytes <= double(kLastLevelCacheBytes)) return GemmPlace::kChain;
+    const std::unique_ptr<Weight[]> by_address(new (std::nothrow) Weight[2 * static_cast<size_t>(n_layers)]);
+    if (!by_address) return GemmPlace::kTrain;
+    for (int i = 0; i < 2 * n_layers; ++i) by_address[i] = weight(i);
+    std::sort(&by_address[0], &by_address[0] + 2 * n_layers, [](const Weight &a, const Weight &b) { return a.at < b.at; });
+    bytes = 0.0;
+    uintptr_t counted = 0;  // up to this address
+    for (int i = 0; i < 2 * n_layers; ++i) {
+        const uintptr_t from = std::max(by_address[i].at, counted);
+        if (by_address[i].end <= from) continue;
+        bytes += double(by_address[i].end - from);
+        counted = by_address[i].end;
+    }
+    return bytes > double(kLastLevelCacheBytes) ? GemmPlace::kTrain : GemmPlace::kChain;
+}
+
+int tw_train_place(const tw_layer_args *layers, int n_layers)
+{
+    if (!layers || n_layers < 1 || n_layers > TW_MAX_TRAIN) return -1;
+    for (int i = 0; i < n_layers; ++i)
+        if (layers[i].K1 < 0 || layers[i].N2 < 0 || layers[i].fused.H < 1) return -1;
+    return train_place(layers, n_layers) == GemmPlace::kTrain ? TW_GEMM_TRAIN : TW_GEMM_CHAIN;
+}
+
 tw_status tw_weave_train(const tw_layer_args *layers, int n_layers, int64_t split_row, void *stream_compute,
                          void *stream_comm, void *parent, int parent_is_set, int join)
 {
@@ -447,19 +491,17 @@ tw_status tw_weave_train(const tw_layer_args *layers, int n_layers, int64_t spli
     if (!layers) return TW_ERR_NULL;
     // everything is checked before anything is launched
     const int64_t T = layers[0].fused.N;
-    double weight_bytes = 0.0;
     for (int i = 0; i < n_layers; ++i) {
         tw_gemm_args g1, g2;
         TW_TRY(validate_layer(&layers[i], stream_compute, stream_comm, &g1, &g2));
         if (layers[i].fused.N != T) return TW_ERR_SHAPE;
-        weight_bytes += 2.0 * double(layers[i].fused.H) * double(layers[i].K1 + layers[i].N2);
     }
     if (split_row < 0 || split_row > T) return TW_ERR_SPLIT;
     if (T == 0) return TW_OK;
     const bool whole = split_row == 0 || split_row == T;
     hipStream_t sx = static_cast<hipStream_t>(stream_compute), sp = static_cast<hipStream_t>(parent);
     if (whole) {
-        const GemmPlace place = weight_bytes > double(kLastLevelCacheBytes) ? GemmPlace::kTrain : GemmPlace::kChain;
+        const GemmPlace place = train_place(layers, n_layers);
         if (parent_is_set && sx != sp) TW_TRY(stream_wait_stream(sx, sp));
         for (int i = 0; i < n_layers; ++i) {
             tw_gemm_args g1, g2;

@@ -37,7 +37,7 @@ def test_header_declares_the_documented_entry_points():
     aids = declared_functions(("tw_measure.h",))
     for must in ("tw_hbm_probe", "tw_hbm_probe_mixed", "tw_hbm_probe_shaped", "tw_hbm_probe_mixed_shaped",
                  "tw_fused_grid", "tw_fused_workgroups", "tw_fused_layout", "tw_weave_schedule", "tw_gemm_tile_shape",
-                 "tw_gemm_tile_choice", "tw_gemm_plan",
+                 "tw_gemm_tile_choice", "tw_gemm_plan", "tw_train_place",
                  "tw_reduce_add_rmsnorm_traced", "tw_streams_overlap", "tw_gemm_bf16_traced",
                  "tw_stream_create_cu_masked", "tw_stream_destroy"):
         assert must in aids and must not in names
@@ -332,6 +332,53 @@ def test_gemm_plan_and_the_launches_the_gpu_tests_mean_to_have_helpers():
     for bad in ((0, 16, 16, 0, 256, 0), (16, 16, -8, 0, 256, 0), (16, 16, 16, 2, 256, 0), (16, 16, 16, 0, 0, 0), (16, 16, 16, 0, 256, 5),
                 (16, 16, 16, 0, 256, -1)):
         assert L.tw_gemm_plan(*bad, ctypes.byref(plan)) == E_SHAPE, bad
+
+
+def test_train_place_counts_the_bytes_of_its_weights_once():
+    """An unsplit train's weights are taken to come from memory where they are more than the 256 MiB of the last-level cache:
+    boundaries that point at the same weights, at a part of others', or at overlapping ones, count their bytes once."""
+    from paper_2505_11329_amd.binding import LayerArgs
+    L, MiB = tw.lib(), 1 << 20
+    H, K1, N2 = 8192, 1024, 3072                    # W1 16 MiB, W2 48 MiB
+
+    def place(weights):
+        layers = (LayerArgs * len(weights))()
+        for l, (W1, k1, W2, n2) in zip(layers, weights):
+            l.W1, l.K1, l.W2, l.N2, l.fused.H = W1, k1, W2, n2, H
+        return L.tw_train_place(layers, len(weights))
+
+    def pair(i, at=1 << 40):
+        return (at + i * 64 * MiB, K1, at + i * 64 * MiB + 16 * MiB, N2)
+
+    for n in range(1, 13):
+        assert place([pair(i) for i in range(n)]) == (tw.GEMM_TRAIN if n > 4 else tw.GEMM_CHAIN), n
+        assert place([pair(i % 2) for i in range(n)]) == tw.GEMM_CHAIN, n
+        assert place([pair(i % 5) for i in range(n)]) == (tw.GEMM_TRAIN if n > 4 else tw.GEMM_CHAIN), n
+    # a fifth pair that is the first ones' bytes: whole, a part of one, across two; then eight more of K
+    four = [pair(i) for i in range(4)]
+    base = four[0][0]
+    assert place(four + [(base, K1, base + 16 * MiB, N2)] * 5) == tw.GEMM_CHAIN
+    assert place(four + [(base + 3 * MiB, 64, base + 100 * MiB, 2048)]) == tw.GEMM_CHAIN
+    assert place([(base, 4 * (K1 + N2), base, N2)] + four) == tw.GEMM_CHAIN
+    assert place(four + [(base + 255 * MiB, 128, base, N2)]) == tw.GEMM_TRAIN       # one MiB past the end
+    assert place(four + [(base - MiB, 128, base, N2)]) == tw.GEMM_TRAIN
+    assert place([pair(3), pair(0), (base + 256 * MiB, 8, base, N2), pair(2), pair(1)]) == tw.GEMM_TRAIN
+    # no weights at all, and as many boundaries as a train may have
+    assert place([(base, 0, base, 0)]) == tw.GEMM_CHAIN
+    assert place([pair(i % 4) for i in range(4096)]) == tw.GEMM_CHAIN
+    assert place([pair(i) for i in range(4096)]) == tw.GEMM_TRAIN
+    layers = (LayerArgs * 4097)()
+    assert L.tw_train_place(layers, 1) == -1                                        # H = 0
+    for l in layers:
+        l.fused.H = H
+    assert L.tw_train_place(layers, 4096) == tw.GEMM_CHAIN
+    for n in (-1, 0, 4097):
+        assert L.tw_train_place(layers, n) == -1
+    assert L.tw_train_place(None, 1) == -1
+    for name in ("K1", "N2"):
+        setattr(layers[0], name, -8)
+        assert L.tw_train_place(layers, 1) == -1
+        setattr(layers[0], name, 0)
 
 
 def test_overlap_launch_argument_checks():

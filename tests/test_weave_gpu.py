@@ -462,14 +462,23 @@ def test_train_of_one_row_of_tiles_streams_its_weights_and_gives_the_bits_of_its
     assert rows <= 64 or not any(other)
 
 
-def _train_against_its_layers(tw, torch, rows, H_, K1_, N2_, n):
-    """Bits, and that both launch what the plans say. Returns which of a boundary's two products the train launches otherwise."""
+@pytest.mark.parametrize("rows", [48, 333])
+def test_train_over_few_weights_launches_what_its_layers_do(tw, torch_cuda, rows):
+    """Two pairs of weights, 151 MB, that eight boundaries use in turn: they stay in the cache, however often they are used."""
+    assert not any(_train_against_its_layers(tw, torch_cuda, rows, 8192, 1024, 3584, 8, pairs=2))
+
+
+def _train_against_its_layers(tw, torch, rows, H_, K1_, N2_, n, pairs=None):
+    """Bits, and that both launch what the plans say: a train of n boundaries, each with weights of its own or `pairs` pairs that the
+    cache holds. Returns which of a boundary's two products the train launches otherwise."""
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(rows)
     draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.05, generator=gen)
     empty = lambda *shape: torch.full(shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
     assert n * H_ * (K1_ + N2_) * 2 > 256 << 20
-    W1, W2, X1, other = [draw(H_, K1_) for _ in range(n)], [draw(N2_, H_) for _ in range(n)], draw(rows, K1_), draw(rows, H_)
+    W1, W2 = [draw(H_, K1_) for _ in range(pairs or n)], [draw(N2_, H_) for _ in range(pairs or n)]
+    X1, other = draw(rows, K1_), draw(rows, H_)
+    place = tw.GEMM_CHAIN if pairs else tw.GEMM_TRAIN
     weight, first = draw(H_), draw(rows, H_)
     sx, sc = torch.cuda.Stream(), torch.cuda.Stream()
     cus = tw.device_cu_count()
@@ -478,8 +487,8 @@ def _train_against_its_layers(tw, torch, rows, H_, K1_, N2_, n):
     for train in (True, False):
         residual, layers = first, []
         for i in range(n):
-            layers.append(dict(X1=X1, W1=W1[i], partials=[empty(rows, H_), other], residual=residual, weight=weight, eps=1e-5,
-                               W2=W2[i], out=empty(rows, H_), residual_out=empty(rows, H_), Y=empty(rows, N2_)))
+            layers.append(dict(X1=X1, W1=W1[i % len(W1)], partials=[empty(rows, H_), other], residual=residual, weight=weight, eps=1e-5,
+                               W2=W2[i % len(W2)], out=empty(rows, H_), residual_out=empty(rows, H_), Y=empty(rows, N2_)))
             residual = layers[-1]["residual_out"]
 
         def call():
@@ -490,7 +499,7 @@ def _train_against_its_layers(tw, torch, rows, H_, K1_, N2_, n):
                     tw.weave_layer(split_row=rows, stream_compute=sx, stream_comm=sc, parent=sx, fused_cu_budget=tw.CU_SHARED, **l)
         torch.cuda.synchronize()
         kernels.append(captured_kernels(sx, call))
-        plans = [tw.gemm_plan(rows, n_, k, tw.B_NK, cus, tw.GEMM_TRAIN if train else tw.GEMM_CHAIN) for n_, k in ((H_, K1_), (N2_, H_))]
+        plans = [tw.gemm_plan(rows, n_, k, tw.B_NK, cus, place if train else tw.GEMM_CHAIN) for n_, k in ((H_, K1_), (N2_, H_))]
         assert [grid for _, grid in kernels[-1]] == [plans[0].workers + plans[0].helpers, fused, plans[1].workers + plans[1].helpers] * n
         call()
         torch.cuda.synchronize()
