@@ -327,7 +327,8 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
         if constexpr (kRolls) {
             // A wave's single block is one chain of matrix instructions, each of which waits for the one before (22
             // clocks), so nothing else may stand in it: fragments are read kAhead sub-steps ahead, from one stage into
-            // the next, and waited for by count, never all of them. Once a stage, ahead of its first read of the next
+            // the next, and waited for by count, never all of them. (So reads are under way where the loop ends, of which the
+            // compiler knows nothing: a test follows the built code for uses of their registers.) Once a stage, ahead of its first read of the next
             // one, the waves meet: that has landed, and the stage before this is read and takes the loads of step kt +
             // S - 1 (one stage more in LDS than the other loop, for as many on their way). What bounds a tile now is its
             // intake at the L1's 64 bytes a clock, and weights from HBM. us before / with this, operands from the cache
