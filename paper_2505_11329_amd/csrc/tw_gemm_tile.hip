@@ -30,7 +30,7 @@
 // reads of stage s + 1's fragments go out between the matrix instructions of stage s
 // (15.2 -> 13.7 us at 16 rows against reads first). Waves of a single block, one chain of
 // dependent matrix instructions, have a K loop of their own that never waits for all of its
-// reads (kRolls; what bounded those tiles was that chain: 480 clocks for 256 of K, of which
+// reads (ROLLS; what bounded those tiles was that chain: 480 clocks for 256 of K, of which
 // the matrix instructions take 180 and the loads of a 16 x 16 tile 290, now 300).
 // Rows are laid out as in tw_gemm.hip: 16-byte pieces xor-swizzled so that a fragment
 // read touches every bank once.
@@ -75,8 +75,8 @@ struct SmallTile {
     static_assert(!LOADERS || kTail, "loading waves load nothing past the end of K");
 };
 
-// Which kernels have the rolling K loop (see there): those whose waves have one block each, of [K x N] weights with loading
-// waves only (short K: 5 % slower).
+// Which shapes have the rolling K loop (see there): those whose waves have one block each, of [K x N] weights with loading
+// waves only (short K: 5 % slower). Some short K take the other loop all the same (kShortK).
 template <bool B_KN, int WM, int WN, bool LOADERS>
 static constexpr bool rolls()
 {
@@ -119,15 +119,14 @@ struct StageFrags {
 // no division that tile_at can spare, the fragment addresses later. (16 rows, K = 1024, N =
 // 8192: 5.6 -> 5.1 us; K = 8192, N = 3584: 13.7 -> 13.2; 512 x 4096 x 2048: 15.0 -> 14.7.)
 // last_rows: rows of A in the last row of tiles.
-template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, bool LOADERS, bool STREAM_B>
+template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, bool LOADERS, bool STREAM_B, bool ROLLS>
 __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThreads)) void gemm_tile_kernel(
     const char *A, const char *B, char *C, int N, int K, int tiles_m, int tiles_n, int last_rows, int group_m,
     int tiles_per_xcd, uint32_t help)
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // as in tw_gemm.hip: the host pass needs the launch stub only
     using T = SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>;
-    constexpr bool kRolls = rolls<B_KN, WM, WN, LOADERS>();
-    constexpr int kFilled = kRolls ? S - 1 : S;  // stages filled ahead of the first step
+    constexpr int kFilled = ROLLS ? S - 1 : S;  // stages filled ahead of the first step
     constexpr int SUBS = BK / kSubK, NW = T::kWaves, BM = T::BM, BN = T::BN, kRowBytes = BK * 2;
     static_assert(!B_KN || BN == 32 || BN == 64 || BN == 128, "kn_swizzle");
     // Weights that one row of tiles reads once are not worth keeping in the caches (16 rows,
@@ -324,7 +323,7 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
             }
         }
         wait_vm(T::kTail ? k_tiles - 1 : S, std::integral_constant<int, kFilled - 1>{});
-        if constexpr (kRolls) {
+        if constexpr (ROLLS) {
             // A wave's single block is one chain of matrix instructions, each of which waits for the one before (22
             // clocks), so nothing else may stand in it: fragments are read kAhead sub-steps ahead, from one stage into
             // the next, and waited for by count, never all of them. (So reads are under way where the loop ends, of which the
@@ -334,8 +333,8 @@ __global__ __launch_bounds__((SmallTile<WM, WN, WVM, WVN, BK, S, LOADERS>::kThre
             // intake at the L1's 64 bytes a clock, and weights from HBM. us before / with this, operands from the cache
             // and from HBM: [16 x 8192] x [8192 x 16] 8.8 / 6.4 and 9.0 / 6.6, x [8192 x 1280] 9.3 / 7.0 and 10.0 / 8.2, x
             // [8192 x 3584] 13.5 / 12.2 and 14.5 / 14.2; [64 x 8192] x [8192 x 1280] 10.3 / 8.5 and 11.1 / 10.2; [K x N]
-            // [32 x 8192] x [8192 x 1280] 15.6 / 13.0 and 15.9 / 14.8. 180 sizes of 1 to 64 rows: 0.959 and 0.980; up to 3 %
-            // (0.1 us) slower where K is no more than the stages hold. Reads 3 to 7 sub-steps ahead are level, six and
+            // [32 x 8192] x [8192 x 1280] 15.6 / 13.0 and 15.9 / 14.8. 180 sizes of 1 to 64 rows: 0.959 and 0.980 (K of two stages to 1024: see
+            // kShortK). Reads 3 to 7 sub-steps ahead are level, six and
             // eight stages 1 to 8 % slower from the cache.
             constexpr int kAhead = 4, kBases = 4;
             static_assert(SUBS % kAhead == 0 && (kAhead - 1) * kPerSub < 16, "reads ahead, lgkmcnt field");
@@ -554,12 +553,20 @@ struct TileLaunch {
 };
 // LONG_K: from which K on there are loading waves (kNeverLoaders: not for this shape).
 static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
+// K up to which tiles of 32 rows that could roll and have no loading waves do not, from a second stage on: that loop's one more
+// stage in LDS and its meetings cost more there than its chain gains. Time rolling over time not, from the cache and from HBM:
+//   32 x 32  K to 128 0.993, 0.992; 200 to 512 1.003 to 1.022, 1.004 to 1.012; 640 and 768 1.015 to 1.020, 1.007; 1024 1.003, 1.003;
+//            1152 to 2040 0.985 to 0.96, 1.00
+//   32 x 16  K to 512 1.00; 520 to 1024 1.007 to 1.018, 1.001 to 1.014; 1152 to 2040 0.98 to 1.00, 1.00
+// 16 x 16 tiles, one wave of which multiplies, roll at every K (0.94 to 0.98, 0.98 to 0.99), 16 x 32 are level.
+static constexpr int kShortK = 1024;
 // STREAM: whether weights that one row of tiles reads once go past the caches (kStreamPolicy). Of the shapes for up to
 // 64 rows only in trains, whose weights come from HBM: us kept / past the caches, from HBM, [40 x 3584] x [3584 x 8192] 14.8 /
 // 13.1, 64 rows 17.4 / 15.2, [64 x 1024] x [1024 x 8192] 6.8 / 6.5, but weights that are in the cache do not stay there: 11.2 /
 // 12.7 and 11.7 / 15.0. (Several rows of tiles: -14 to +20 % from HBM, +10 to +57 % from the cache.)
 enum Stream { kKeep, kStream, kStreamInTrains };
-template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, Stream STREAM = kKeep, bool LOADERS = false>
+template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, Stream STREAM = kKeep, bool LOADERS = false,
+          bool ROLLS = rolls<B_KN, WM, WN, LOADERS>()>
 static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipStream_t stream)
 {
     // (eight waves that multiply and four that load leave no registers for a workgroup beside them; weights that
@@ -570,7 +577,10 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
         if ((LONG_K == kLoadersIfHelped ? l.help.helpers > 0 : g.K >= LONG_K) && !(l.place == GemmPlace::kBeside && WVM * WVN == 8) &&
             !(one_row && l.help.helpers == 0))
             return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM, true>(g, l, stream);
-    constexpr int STAGES = S + (rolls<B_KN, WM, WN, LOADERS>() ? 1 : 0);  // (see the K loop)
+    if constexpr (ROLLS && !LOADERS && WVM == 2)
+        if (g.K > BK && g.K <= kShortK)
+            return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, STREAM, LOADERS, false>(g, l, stream);
+    constexpr int STAGES = S + (ROLLS ? 1 : 0);  // (see the K loop)
     using T = SmallTile<WM, WN, WVM, WVN, BK, STAGES, LOADERS>;
     if (l.loading_waves) {
         *l.loading_waves = LOADERS ? T::kWaves : 0;
@@ -578,7 +588,7 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
     }
     const int64_t tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
     if constexpr (STREAM != kKeep)
-        if (!one_row) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, kKeep, LOADERS>(g, l, stream);
+        if (!one_row) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, kKeep, LOADERS, ROLLS>(g, l, stream);
     if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
     const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
     const int64_t slots = int64_t(tiles_per_xcd) * kXcds;
@@ -587,7 +597,7 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
     constexpr int kAloneBytes = T::kLdsBytes > 81 * 1024 ? T::kLdsBytes : 81 * 1024;
     const bool whole = l.budget >= l.cus && l.help.helpers == 0;
     const unsigned grid = static_cast<unsigned>((whole || slots < l.budget ? slots : l.budget) + l.help.helpers * kXcds);
-    auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, STAGES, LOADERS, STREAM != kKeep>;
+    auto kern = gemm_tile_kernel<B_KN, WM, WN, WVM, WVN, BK, STAGES, LOADERS, STREAM != kKeep, ROLLS>;
     static std::atomic<int> allowed[kMaxDevices];
     TW_TRY(allow_dynamic_lds(reinterpret_cast<const void *>(kern), kAloneBytes, allowed));
     TW_HIP(launch_kernel(kern, dim3(grid), dim3(T::kThreads),

@@ -11,7 +11,7 @@ import pytest
 
 import oracle
 import tw_workloads as W
-from helpers import captured_grids, to_bits, to_gpu
+from helpers import captured_grids, captured_kernels, to_bits, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -320,6 +320,26 @@ def test_gemm_tiles_of_one_block_to_a_wave_around_every_stage(tw, torch_cuda, ti
             C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
             tw.gemm_bf16(A, B, C, cu_budget=budget)
             assert np.array_equal(to_bits(C), want), (tile, K, budget)
+
+
+@pytest.mark.parametrize("tile,M,N,step,short", [((16, 16), 15, 1032, 256, False), ((32, 16), 24, 2568, 256, True), ((32, 32), 20, 5128, 128, True)])
+def test_gemm_tiles_of_32_rows_take_another_loop_between_one_stage_and_k_1024(tw, torch_cuda, tile, M, N, step, short):
+    """Which kernel each K takes, on both sides of the lines; the bits of the same rows of a large product."""
+    torch = torch_cuda
+    stream = torch.cuda.Stream()
+    kernel = {}
+    for K in (step, step + 8, 1016, 1024, 1032, 2040):
+        assert tw.gemm_tile_choice(M, N, K, tw.B_NK) == tile, K
+        gen = torch.Generator(device="cuda:0")
+        gen.manual_seed(K)
+        big, B = (torch.empty((n, K), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 0.5, generator=gen) for n in (4096, N))
+        A, C = big[:M].contiguous(), torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        torch.cuda.synchronize()
+        ((kernel[K], _),) = captured_kernels(stream, lambda: tw.gemm_bf16(A, B, C, stream=stream))
+        tw.gemm_bf16(A, B, C)
+        assert np.array_equal(to_bits(C), to_bits(tw.gemm_bf16(big, B)[:M])), K
+    assert kernel[step] == kernel[1032] == kernel[2040] and kernel[step + 8] == kernel[1016] == kernel[1024]
+    assert (kernel[step] != kernel[1024]) == short
 
 
 HELPED = [("nk", 16, 1280, 8192), ("nk", 1, 8, 2048), ("nk", 64, 1280, 4096), ("nk", 40, 1272, 2056), ("nk", 150, 600, 4104),
