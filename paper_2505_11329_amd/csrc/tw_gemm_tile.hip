@@ -551,8 +551,8 @@ struct TileLaunch {
     HelpPlan help;
     int *loading_waves = nullptr;  // not NULL: nothing is launched, but how many waves of a workgroup would only load
 };
-// LONG_K: from which K on there are loading waves (kNeverLoaders: not for this shape).
-static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29;
+// LONG_K: from which K on there are loading waves (kNeverLoaders: not for this shape; kEveryK: at every K that it is taken for).
+static constexpr int kNeverLoaders = 1 << 30, kLoadersIfHelped = 1 << 29, kEveryK = 0;
 // K up to which tiles of 32 rows that could roll and have no loading waves do not, from a second stage on: that loop's one more
 // stage in LDS and its meetings cost more there than its chain gains. Time rolling over time not, from the cache and from HBM:
 //   32 x 32  K to 128 0.993, 0.992; 200 to 512 1.003 to 1.022, 1.004 to 1.012; 640 and 768 1.015 to 1.020, 1.007; 1024 1.003, 1.003;
@@ -563,8 +563,9 @@ static constexpr int kShortK = 1024;
 // STREAM: whether weights that one row of tiles reads once go past the caches (kStreamPolicy). Of the shapes for up to
 // 64 rows only in trains, whose weights come from HBM: us kept / past the caches, from HBM, [40 x 3584] x [3584 x 8192] 14.8 /
 // 13.1, 64 rows 17.4 / 15.2, [64 x 1024] x [1024 x 8192] 6.8 / 6.5, but weights that are in the cache do not stay there: 11.2 /
-// 12.7 and 11.7 / 15.0. (Several rows of tiles: -14 to +20 % from HBM, +10 to +57 % from the cache.)
-enum Stream { kKeep, kStream, kStreamInTrains };
+// 12.7 and 11.7 / 15.0. (Several rows of tiles: -14 to +20 % from HBM, +10 to +57 % from the cache.) kStreamAlways: the shape
+// is taken for one row of tiles only (left_out).
+enum Stream { kKeep, kStream, kStreamInTrains, kStreamAlways };
 template <bool B_KN, int WM, int WN, int WVM, int WVN, int BK, int S, int LONG_K, Stream STREAM = kKeep, bool LOADERS = false,
           bool ROLLS = rolls<B_KN, WM, WN, LOADERS>()>
 static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipStream_t stream)
@@ -572,7 +573,8 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
     // (eight waves that multiply and four that load leave no registers for a workgroup beside them; weights that
     // one row of tiles reads once each come as fast, from HBM, to the waves that multiply: 32 x 3584, K = 8192 16.1 us, with
     // loading waves 17.2; with helpers they are ahead again)
-    const bool one_row = STREAM != kKeep && g.M <= kBlk * WM * WVM && (STREAM == kStream || l.place == GemmPlace::kTrain);
+    const bool one_row = STREAM == kStreamAlways || (STREAM != kKeep && g.M <= kBlk * WM * WVM &&
+                                                     (STREAM == kStream || l.place == GemmPlace::kTrain));
     if constexpr (LONG_K < kNeverLoaders && !LOADERS)
         if ((LONG_K == kLoadersIfHelped ? l.help.helpers > 0 : g.K >= LONG_K) && !(l.place == GemmPlace::kBeside && WVM * WVN == 8) &&
             !(one_row && l.help.helpers == 0))
@@ -587,7 +589,8 @@ static tw_status launch_tile_t(const tw_gemm_args &g, const TileLaunch &l, hipSt
         return TW_OK;
     }
     const int64_t tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
-    if constexpr (STREAM != kKeep)
+    // (at kEveryK, what has no loading waves is one row)
+    if constexpr ((STREAM == kStream || STREAM == kStreamInTrains) && (LOADERS || LONG_K != kEveryK))
         if (!one_row) return launch_tile_t<B_KN, WM, WN, WVM, WVN, BK, S, LONG_K, kKeep, LOADERS, ROLLS>(g, l, stream);
     if (tiles_m * tiles_n > (int64_t(1) << 30)) return TW_ERR_UNSUPPORTED;
     const int tiles_per_xcd = static_cast<int>((tiles_m * tiles_n + kXcds - 1) / kXcds);
@@ -640,11 +643,11 @@ static const SmallTileShape kSmallTiles[] = {
     {32, 16, 256, 0.097f, 0.0f, 0.060f, 0.0f,
      launch_tile_t<false, 1, 1, 2, 1, 256, 4, 2048, kStream>, nullptr},
     {16, 32, 256, 0.115f, 0.149f, 0.060f, 0.080f,
-     launch_tile_t<false, 1, 1, 1, 2, 256, 4, 2048, kStream>, launch_tile_t<true, 1, 1, 1, 2, 256, 4, 2048>},
+     launch_tile_t<false, 1, 1, 1, 2, 256, 4, kLoadersIfHelped, kStreamAlways>, launch_tile_t<true, 1, 1, 1, 2, 256, 4, 2048>},
     {32, 32, 128, 0.132f, 0.150f, 0.078f, 0.102f,
      launch_tile_t<false, 1, 1, 2, 2, 128, 4, 2048, kStream>, launch_tile_t<true, 1, 1, 2, 2, 128, 4, 2048>},
     {48, 32, 128, 0.150f, 0.0f, 0.093f, 0.0f,
-     launch_tile_t<false, 3, 1, 1, 2, 128, 4, 2048, kStreamInTrains>, nullptr},
+     launch_tile_t<false, 3, 1, 1, 2, 128, 4, kEveryK, kStreamInTrains>, nullptr},
     {64, 32, 128, 0.180f, 0.200f, 0.109f, 0.122f,
      launch_tile_t<false, 2, 1, 2, 2, 128, 4, 2048, kStreamInTrains>, launch_tile_t<true, 2, 1, 2, 2, 128, 4, 2048>},
     {64, 64, 128, 0.200f, 0.230f, 0.139f, 0.155f,

@@ -241,7 +241,7 @@ def test_gemm_every_tile_shape(tw, torch_cuda, tile, layouts, M, N, K, budget):
 
 
 # From which K on a shape has waves that only load where its launch has no helpers (not there: none without)
-LOADING_FROM = {("nk", (16, 32)): 2048, ("kn", (16, 32)): 2048, ("nk", (16, 16)): 2048, ("nk", (32, 16)): 2048, ("nk", (32, 32)): 2048, ("nk", (64, 32)): 2048, ("nk", (64, 64)): 2048,
+LOADING_FROM = {("kn", (16, 32)): 2048, ("nk", (16, 16)): 2048, ("nk", (32, 16)): 2048, ("nk", (32, 32)): 2048, ("nk", (64, 32)): 2048, ("nk", (64, 64)): 2048,
                 ("nk", (96, 64)): 2048, ("nk", (96, 96)): 320, ("nk", (96, 128)): 512, ("kn", (32, 32)): 2048, ("kn", (64, 32)): 2048,
                 ("kn", (96, 64)): 320, ("kn", (96, 128)): 512, ("kn", (192, 64)): 2048, ("kn", (128, 128)): 2048}
 
