@@ -677,8 +677,11 @@ static const SmallTileShape kSmallTiles[] = {
 // bounds a decode step's tile is its intake, and of that a 16 x 16 tile spends half on the same 16 rows, a 32 x 32 one a
 // quarter on rows that are not there. us before / with them, operands from the cache and from HBM: [16 x 8192] x [8192 x 8192]
 // 25.4 / 21.9 and 26.9 / 23.2, [16 x 4096] x [4096 x 6144] 11.8 / 11.0 and 12.1 / 11.4, [16 x 3584] x [3584 x 8192] 10.9 / 10.4
-// and 11.4 / 11.2; [K x N], with helpers, [16 x 8192] x [8192 x 3584] 15.4 / 13.6 and 16.5 / 14.6. 120 sizes of up to 16 rows,
-// both layouts: 0.95 and 0.98, the slowest 1.03.
+// and 11.4 / 11.2; [K x N], with helpers, [16 x 8192] x [8192 x 3584] 15.4 / 13.6 and 16.5 / 14.6. Time over that with 32 x 32
+// tiles, from the cache and from HBM, 789 sizes of up to 16 rows: [N x K] 0.92 and 0.94, [K x N] with helpers 0.76 and 0.86, without
+// them K < 2048 0.91 and 1.013, the rest 1.00 and 1.00. Slower are, from HBM, [N x K] at K = 256 (1.01 to 1.03; 1.5 % faster from the
+// cache, and K just below is faster from both) and [K x N] up to K = 2040 (to 1.03, of N = 7680 to 1.05: 0.1 us against the 0.1 to
+// 1.1 that the cache gains elsewhere); from both, [K x N] whose rows are 16 KB apart, N = 8192, from K = 2560 on (1.03 and 1.006).
 static bool left_out(const SmallTileShape &t, int64_t M, int64_t K)
 {
     return t.cols == 32 && ((t.rows == 16 && M > 16) || (t.rows == 48 && (M > 48 || K < kHelpFromK)));

@@ -18,8 +18,8 @@ namespace tw {
 // [8192 x 1280] 11.6 / 10.0 and 10.6 / 9.2, [64 x 8192] x [8192 x 1280] 14.7 / 11.1 and 11.5 / 10.2; [K x N], whose rows of
 // a narrow tile are less than a line: [16 x 4096] x [4096 x 4096] 19.3 / 10.4 and 11.5 / 9.4, [128 x 8192] x [8192 x 2048]
 // 34.5 / 19.1 and 21.4 / 19.0. In the counters the same bytes come from beyond the L2 with helpers and without; L2 hits
-// and the latency of a request, [16 x 8192] x [8192 x 1280] 46 -> 65 % and 422 -> 275 clocks, [16 x 4096] x [4096 x 4096]
-// 59 -> 71 % and 659 -> 490.
+// and the latency of a request, [16 x 8192] x [8192 x 1280] 46 -> 65 % and 446 -> 292 clocks, [16 x 4096] x [4096 x 4096]
+// 59 -> 71 % and 660 -> 509.
 //
 // They keep `lead` windows (kHelpWindow bytes of K) ahead of a window every `pace` ticks of the
 // 100 MHz clock: further ahead they would push out of the 4 MiB what the tiles have yet to read. What the tiles fall
