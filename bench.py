@@ -425,7 +425,8 @@ def main():
         # tiles, where there are none
         gc = W.CONFIGS["c5_overlap_tp8"]["gemm"]
         shapes = [(8192, 8192, 8192, "nk"), (8192, 8192, 1280, "nk"), (gc["M"], gc["K"], gc["N"], "nk"),
-                  (gc["M"], gc["K"], 1280, "nk"), (333, 8192, 3584, "nk"), (16, 8192, 3584, "nk"), (16, 8192, 1280, "nk"),
+                  (gc["M"], gc["K"], 1280, "nk"), (333, 8192, 3584, "nk"), (64, 8192, 1280, "nk"), (40, 3584, 8192, "nk"),
+                  (16, 8192, 8192, "nk"), (16, 8192, 3584, "nk"), (16, 8192, 1280, "nk"),
                   (3001, 4104, 4096, "kn"), (16, 4096, 4096, "kn")]
         runs = []
         for (M, K, N, layout) in shapes:
